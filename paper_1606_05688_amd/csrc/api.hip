@@ -47,36 +47,34 @@ static void make_fft_plan(int N, FftPlan* P)
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // Whether a layer runs without transforming its x axis (mac_xd.hip).  A flag that names a multiply-accumulate form
-// decides; otherwise that route is taken where each kernel-spectrum value would serve too few inputs to be worth
-// generating (the same rule that picks between the two forms of the fully transformed route), provided the y
-// transform has an in-register kernel (only those read the transposed layout).  Measured on 48 -> 48 images of
-// 320^3 with 5^3 kernels: 20.9 ms against 25.0 ms; 40 -> 40 images of 128^3, 3^3 kernels: 0.98 against 1.10 ms.
+// decides; otherwise that route is taken, provided the y transform has an in-register kernel (only those read the
+// transposed layout), except for batches of small images: with fused z+y kernels on both sides the fully transformed
+// route has as many passes, and a kernel-spectrum value generated once per bin serves all inputs.
+// Measured, whole layer, untransformed against fully transformed: 80 -> 80 images of 100^3, 5^3 kernels 1.57 against
+// 2.02 ms; 32 -> 32 of 64^3, 7^3 0.137 against 0.171; 8 x 32 -> 32 of 130^3, 5^3 (no fused kernels) 6.2 against 8.9;
+// 32 x 20 -> 20 of 40 x 128 x 100, 3^3 3.39 against 4.06.  With fused kernels and more than 8 inputs: 64 x 80 -> 80 of
+// 51^3, 5^3 12.2 against 9.8; 16 x 80 -> 80 of 80^3, 5^3 8.5 against 7.2; 13 x 64 -> 23 of 39^3, 2^3 0.44 against 0.37; with
+// at most 8 inputs and k * S >= 32 it is level or ahead above length 64 (8 x 80 -> 80 of 99^3, 5^3 8.5 against 10.2,
+// 8 x 48 -> 48 of 72^3, 4^3 1.67 against 1.66, 8 x 16 -> 16 of 120^3, 5^3 2.05 against 2.04).
 static bool pick_untransformed_x(const LayerPlan& L, unsigned flags)
 {
     if (flags & (ZNNI_MAC_REFERENCE | ZNNI_MAC_SINGLE | ZNNI_MAC_BATCH)) return false;
-    // small images, where one kernel per side does the z and y transforms: the two routes were measured within
-    // a few per cent of each other (lengths 64 and 100), the fully transformed one ahead
-    if (fused_fwd_zy_available(L) && fused_inv_yz_available(L)) return false;
-    return !mac_batch_preferred(L);
+    if (!(fused_fwd_zy_available(L) && fused_inv_yz_available(L))) return true;
+    return L.S <= 8 && (!mac_batch_preferred(L) || L.d.Ny > 64);
 }
 
 // ... and whether it applies the kernel's taps along x through length-8 transforms of overlapping blocks
-// (mac_xb.hip) rather than as shifted reads: wherever that form exists (4 or 5 taps).  Measured, whole layer:
-// 48 -> 48 images of 320^3, 5^3 kernels 18.6 against 20.9 ms; 48 -> 48 of 240^3, 4^3: 7.8 against 8.2 ms;
-// 2 x 32 -> 32 of 128^3, 5^3: 1.49 against 1.55 ms; 80 -> 80 of 200^3, 5^3 (row blocks of three and two tiles):
-// 12.0 against 14.4 ms, with 4^3 kernels 11.2 against 12.4 ms.
+// (mac_xb.hip) rather than as shifted reads: few inputs per batch and 4 or 5 taps, for images small enough for the
+// fused z+y kernels only with five taps and at least 24 blocks along x.  There its sums are a fifth as long and its
+// results the closer ones (48 -> 48 images of 320^3, 5^3 kernels: 2.6e-7 off against 2.9e-7).
 static bool pick_xblock(const LayerPlan& L, unsigned flags)
 {
     if (L.generic_passes || !mac_xb_available(L) || !fast_pass_available(L.d.Ny)) return false;
     if (flags & ZNNI_MAC_XBLOCK) return true;
-    if (flags & ZNNI_MAC_XDIRECT) return false;
-    if (pick_untransformed_x(L, flags)) return true;
-    // small images (one kernel per side for the z and y transforms of the fully transformed route): ahead only with
-    // five taps and at least 24 blocks along x.  Measured, blocks against full length: 80 -> 80 images of 100^3, 5^3
-    // kernels 1.81 against 2.08 ms; 4 x 48 -> 48 of 100^3 2.57 against 2.91; 48 -> 48 of 120^3 1.31 against 1.39;
-    // but 80 -> 80 of 120^3 with 4^3 kernels 2.75 against 2.69, 80 -> 80 of 60^3 with 5^3 0.67 against 0.52.
-    if (flags & (ZNNI_MAC_REFERENCE | ZNNI_MAC_SINGLE | ZNNI_MAC_BATCH)) return false;
-    return L.d.kx == 5 && L.d.nox >= 96 && !mac_batch_preferred(L);
+    if (flags & (ZNNI_MAC_REFERENCE | ZNNI_MAC_SINGLE | ZNNI_MAC_BATCH | ZNNI_MAC_XDIRECT)) return false;
+    if (mac_batch_preferred(L)) return false;
+    const bool fused = fused_fwd_zy_available(L) && fused_inv_yz_available(L);
+    return !fused || (L.d.kx == 5 && L.d.nox >= 96);
 }
 
 static bool pick_xdirect(const LayerPlan& L, unsigned flags)

@@ -49,11 +49,47 @@ __device__ __forceinline__ void kprep_gather(float2* tw2, const float2* __restri
 // from the runs of the neighbouring lanes -- are read once per KPREP_OZ outputs.  (One thread per output re-read w
 // for every oz: 3.2 ms for 80 x 80 kernels of 9^3 at length 100.)
 constexpr int KPREP_OZ = 16;
+
+// Power of two for the kernel transforms of output image j on the route that stores them as split halves (mac_xd.hip):
+// no value of a kernel's transform exceeds the sum of its magnitudes, so the factor that brings the largest such sum
+// over the input images (times the transform's own scale) to 2^14 keeps every value in range.  rs[j], and its inverse
+// at rs[Mp + j].  A wave per input image, lanes along its taps.
+__device__ __forceinline__ void kprep_row_scale(const float* __restrict__ w, float* __restrict__ rs, int j, int f,
+                                                int fo, int Mp, int taps, size_t wj_stride, float scale)
+{
+    __shared__ float best[4];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    float m = 0.f;
+    if (j < fo)
+        for (int i = wave; i < f; i += 4) {
+            const float* wi = w + (size_t)j * wj_stride + (size_t)i * taps;
+            float s = 0.f;
+            for (int t = lane; t < taps; t += 64) s += fabsf(wi[t]);
+#pragma unroll
+            for (int o = 32; o; o >>= 1) s += __shfl_xor(s, o);
+            s *= scale;
+            m = fmaxf(m, s < INFINITY ? s : 0.f);
+        }
+    if (lane == 0) best[wave] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        m = fmaxf(fmaxf(best[0], best[1]), fmaxf(best[2], best[3]));
+        const int e = max(min(14 - ((int)((__float_as_uint(m) >> 23) & 255u) - 127), 120), -120);
+        rs[j] = m > 0.f ? __uint_as_float((unsigned)(127 + e) << 23) : 1.f;
+        rs[Mp + j] = m > 0.f ? __uint_as_float((unsigned)(127 - e) << 23) : 1.f;
+    }
+}
 __global__ __launch_bounds__(256) void k_kprep_z(const float* __restrict__ w, float2* __restrict__ A1,
                                                  const float2* __restrict__ twz, Dims d, int f, int fo, int fp,
-                                                 int Mp, size_t wj_stride)
+                                                 int Mp, size_t wj_stride, int nblk, float* __restrict__ rs,
+                                                 float rs_scale)
 {
     extern __shared__ float2 tw2[];                            // [taps of the chunk][KPREP_OZ]
+    if ((int)blockIdx.x >= nblk) {
+        // the workgroups behind those of the transform: one output image each, its power of two (kprep_row_scale)
+        if (blockIdx.y == 0) kprep_row_scale(w, rs, blockIdx.x - nblk, f, fo, Mp, d.kx * d.ky * d.kz, wj_stride, rs_scale);
+        return;
+    }
     const int N = d.Nz;
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;
     const int oz0 = blockIdx.y * KPREP_OZ;
@@ -328,11 +364,15 @@ znni_status launch_kernel_prep(const LayerPlan& L, const float* w, size_t wj_str
     const Dims& d = L.d;
     const int per = d.kx * L.fp * L.Mp;
     const int per1 = per * d.ky;
-    k_kprep_z<<<dim3((per1 + 255) / 256, (d.zc + KPREP_OZ - 1) / KPREP_OZ), dim3(256),
+    const bool split = L.xdirect && !L.xblock;           // kernel transforms stored as split halves (mac_xd.hip)
+    const int nblk = (per1 + 255) / 256;
+    k_kprep_z<<<dim3(nblk + (split ? L.Mp : 0), (d.zc + KPREP_OZ - 1) / KPREP_OZ), dim3(256),
                 sizeof(float2) * KPREP_OZ * (size_t)std::min(d.kz, KPREP_TAPS), st>>>(
-        w, L.A1, L.twz, d, L.f, L.fo, L.fp, L.Mp, wj_stride);
+        w, L.A1, L.twz, d, L.f, L.fo, L.fp, L.Mp, wj_stride, nblk, mac_xd_row_scales(L),
+        (float)(1.0 / ((double)d.Ny * d.Nz)));
     ZNNI_LAUNCH_CHECK();
     if (L.xblock) return launch_kprep_yb(L, st);
+    if (split) return launch_kprep_xd(L, st);
     // the unnormalised transforms' factor: one per transformed axis
     const float scale = (float)(1.0 / ((L.xdirect ? 1.0 : (double)d.Nx) * d.Ny * d.Nz));
     k_kprep_y<<<dim3((per + 255) / 256, (d.Ny + KPREP_OY - 1) / KPREP_OY, d.zc), dim3(256),

@@ -20,253 +20,579 @@
 // Layouts: X2[img][oz][oy][x < ldx] as the forward y pass leaves it, A[oz][oy][i/4][a][i%4][j<Mp] scaled by
 // 1/(Ny Nz), Yd[imgo][oz][oy][xo < ldxo], which the inverse y pass reads with a transposing load.
 //
-// Work split, operand layout and the three-real-products scheme are those of the kernels in mac_k.hip; the
-// number of taps is a compile-time constant (1 to 9).
+//
+// The products run on the fp16 matrix instructions (v_mfma_f32_16x16x32_f16, sixteen times the rate of the fp32 ones)
+// with every fp32 value carried as two halves, v = hi + lo (two halves together hold 22 bits and a sign, an error of
+// about 1.5 fp32 roundings), and three of the four partial products kept: hi hi, hi lo, lo hi (the fourth is below
+// 2^-22 of the first).  Sums stay fp32.  Halves have a narrow exponent range, so both operands are scaled by powers
+// of two, which costs no accuracy: the image values of a workgroup by their largest magnitude so far (the sums are
+// rescaled when a later chunk is larger), the kernel transforms of an output image by a bound of theirs.  With the
+// largest value at 2^14, every value down to 2^-17 of it keeps all 22 bits, smaller ones an absolute error of 2^-40 of
+// the largest.  Whole layers come out 0.6 to 1.0 times as far from their 64-bit values as with fp32 matrix
+// instructions (80 -> 80 of 128^3, 7^3 kernels: 3.7e-7 against 5.4e-7), and the kernel is (multiply-accumulate alone,
+// before and after): 80 -> 80 of 128^3, 7^3 2.53 -> 1.05 ms; 40 -> 40 of 128^3, 3^3 0.37 -> 0.22; 37 -> 45 of 93 x 110 x
+// 131, 3 x 4 x 5 0.33 -> 0.25; 80 -> 80 of 200^3, 5^3 9.1 -> 3.8.  Up to eight images with one or two taps it is level to a
+// fifth behind (7 -> 38 of 126 x 180 x 119, 1 tap: 0.118 -> 0.142): there nothing but reading and writing spectra is left.
+// What bounds it: matrix instructions about 40 % of the time at two waves per SIMD, the rest their operands (LDS reads,
+// the two forms of an operand), the staging of the image rows between chunks and, for wide kernels, reading A.
+//
+// Complex products as real ones: with the contraction running over (image, real / imaginary part), the kernel
+// operand (Ar, Ai) meets (Xr, -Xi) for the real part of the result and (Xi, Xr) for the imaginary part; both are
+// made from one read of the image operand with one instruction per register.
+//
+// Workgroup = 4 waves = one (oz, oy) pencil of one input x 64*CT outputs along x x 16*RT output images; a wave owns
+// 16*CT outputs and all RT row tiles.  Input images go through in chunks of 16*NG: their rows are read into registers,
+// split, and left in LDS as [image quad][x] units of 16 bytes, the operand layout, so that a tap is a shift by one
+// unit.  One matrix step contracts four (quad, tap) slots: sixteen images of one tap, or, in a last group of fewer
+// images, several taps of fewer quads.  Kernel operands travel global memory -> registers -> LDS, requested two pairs
+// of steps and parked one pair ahead, one quarter per wave (every wave reading all of them for itself asks more of the vector
+// L1 than it delivers: 85 / CT bytes per clock of 64); one barrier per pair of steps.  Nothing is requested for the next chunk
+// while a chunk is multiplied: loads are waited for in order, so kernel operands requested after the image rows would
+// wait for those; the other workgroups of the CU fill the gap instead.
 #include "mac_common.h"
 
 namespace znni {
 
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+
+// Division by a number known at launch: a high product, at most one too large, and a correction.
+struct FastDiv {
+    unsigned d, m;
+    void set(unsigned n) { d = n; m = n > 1 ? (unsigned)((1ull << 32) / n) + 1u : 0u; }
+    __device__ __forceinline__ unsigned div(unsigned n) const
+    {
+        if (d == 1) return n;
+        const unsigned q = __umulhi(n, m);
+        return q * d > n ? q - 1 : q;
+    }
+};
+
 struct XdArgs {
+    FastDiv d_sub, d_ncb, d_S, d_Ny;
     const float2* X2;
-    const float2* A;
+    const half8* A;             // [pencil][slot][row tile][hi, lo][16 output images], 4 complex images each
+    const float* rinv;          // [Mp] inverse of the power of two the kernel transforms of an output image carry
     float2* Yd;
     size_t ximg, yimg;          // elements between the rows of consecutive images in X2 / Yd
     size_t xpen, ypen;          // elements between the rows of pencils (oz, oy) and (oz + 1, oy)
-    int S, f, fo, fp, Mp, nox, ldx, ldxo, Ny;
-    int n2, n1, col1, nmblk, npencils, accumulate;
+    int S, f, fo, Mp, K, nx, nox, ldx, ldxo, Ny;
+    int ncb, nmblk, npencils, accumulate;
 };
 
-// Both operands of an iteration (four input images, all K taps) are requested one iteration ahead.  Where the
-// registers allow, into the other of two register sets, all requests at the top of the iteration (TWO_SETS);
-// otherwise into the registers a tap has just released, tap by tap.  The first form is the faster one where it fits
-// 256 registers: this kernel runs best with two waves per SIMD (a single wave can keep a matrix core busy; with
-// three or four resident waves the same instruction stream was measured up to 1.5 times slower), so registers are
-// not what limits it.
-template <int RTW, int CTW, int K>
-constexpr bool mac_xd_two_sets() { return 12 * RTW * CTW + 4 * K * (RTW + CTW) + 30 <= 250; }
-
-template <int RTW, int CTW, int K>
-__device__ __forceinline__ void mac_xd_body(const XdArgs& g, int col0, int ncolblk, int pencil, int sub)
+constexpr int XD_MAX_K = 9;     // taps along x at most: the halo of a staged row
+// The largest finite magnitude that decides a scale sits at 2^XD_TOP.
+constexpr int XD_TOP = 14;
+// Power-of-two exponent that brings values of magnitude m (finite) to 2^XD_TOP; both it and its negative are exponents
+// of normal numbers.
+__device__ __forceinline__ int xd_scale_exp(float m)
 {
-    const int colblk = sub % ncolblk, mblk = sub / ncolblk;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int e = (int)((__float_as_uint(m) >> 23) & 255u) - 127;
+    return min(XD_TOP - e, 126);
+}
+__device__ __forceinline__ float xd_pow2(int e) { return __uint_as_float((unsigned)(e + 127) << 23); }
+
+__device__ __forceinline__ void xd_split(float v, float s, _Float16& hi, _Float16& lo)
+{
+    hi = (_Float16)(v * s);
+    lo = (_Float16)fmaf(v, s, -(float)hi);
+}
+
+// Largest magnitude of a thread's values so far and two more: one instruction (fmaxf first quiets each operand).
+__device__ __forceinline__ void xd_max3(float& m, float a, float b)
+{
+    asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(m) : "v"(a), "v"(b));
+}
+// Largest value of a wave (non-negative floats, compared as integers: a NaN counts as the largest).
+__device__ __forceinline__ unsigned xd_wave_max(float m)
+{
+    unsigned v = __float_as_uint(m);
+#define ZNNI_XD_DPP(CTRL, ROWS) v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false))
+    ZNNI_XD_DPP(0x111, 0xf);        // row_shr 1, 2, 4, 8: lane 15 of every row of sixteen holds the row's largest
+    ZNNI_XD_DPP(0x112, 0xf);
+    ZNNI_XD_DPP(0x114, 0xf);
+    ZNNI_XD_DPP(0x118, 0xf);
+    ZNNI_XD_DPP(0x142, 0xa);        // row_bcast 15, 31: lane 63 holds the wave's
+    ZNNI_XD_DPP(0x143, 0xc);
+#undef ZNNI_XD_DPP
+    return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+template <int RT, int CT, int NG>
+constexpr size_t xd_lds_bytes() { return (size_t)16 * (2 * 4 * NG * (64 * CT + 16) + 4 * 128 * RT); }
+// Three workgroups per CU where LDS and registers (168 a lane) allow, two otherwise.
+template <int RT, int CT, int NG>
+constexpr int xd_blocks() { return xd_lds_bytes<RT, CT, NG>() <= 53 * 1024 && RT * CT <= 6 ? 3 : 2; }
+
+template <int RT, int CT, int NG>
+__global__ __launch_bounds__(256, (xd_blocks<RT, CT, NG>())) void k_mac_xd(XdArgs g)
+{
+    // staged outputs with their halo, image quads of a chunk (rows of XW units start on the same bank: the sixteen-lane
+    // groups of a 16-byte LDS read then share no bank in any phase)
+    constexpr int XW = 64 * CT + 16, NQ = 4 * NG;
+    static_assert(XD_MAX_K - 1 <= 8 && 8 * NQ <= 256, "the halo is staged one unit per thread");
+    extern __shared__ half8 lds[];
+    half8* const Xs = lds;                                   // [hi, lo][NQ][XW]
+    half8* const As = lds + 2 * NQ * XW;                     // [two pairs of steps][slot kk][row tile][hi, lo][16]
+    __shared__ unsigned wmax[2][4], wfin[4];
+
+    // (as mac_block, without its divisions: the integer divisions of a workgroup's start cost as much as a matrix step)
+    const unsigned xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    const unsigned q8 = g.d_sub.div(slot), sub = slot - q8 * g.d_sub.d;
+    const int pencil = (int)(q8 * 8 + xcd);
+    if (pencil >= g.npencils) return;
+    const unsigned sm = g.d_ncb.div(sub);
+    const int colblk = (int)(sub - sm * g.d_ncb.d);
+    const int mblk = (int)g.d_S.div(sm), sI = (int)sm - mblk * g.S;
+    const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
     const int l16 = lane & 15, kk = lane >> 4;
-    const int Ct = g.S * g.nox;                              // columns of the pencil: (input of the batch, xo)
-    const int m0 = mblk * RTW * 16;
-    const int colw = col0 + colblk * 64 * CTW + wave * CTW * 16;     // first column of this wave
-    const int f = g.f, Mp = g.Mp;
-    const int poz = pencil / g.Ny, poy = pencil - poz * g.Ny;
+    const int K = g.K, f = g.f;
+    const int poz = (int)g.d_Ny.div((unsigned)pencil), poy = pencil - poz * g.Ny;
+    const int col0 = colblk * 64 * CT;
 
-    floatx4 p1[RTW][CTW], p2[RTW][CTW], p3[RTW][CTW];
+    // ---- kernel operands: this thread's share of a step, NU units of 16 bytes (surplus units repeat the last one).
+    // Slots past the last one are read from it.
+    const int nslots = K * ((f + 3) >> 2), nsteps = (nslots + 3) >> 2;
+    const int sstride = 2 * g.Mp, slast = (nslots - 1) * sstride;       // (32 bits: the layer call's shape limits)
+    constexpr int NU = (RT + 1) / 2;
+    const half8* Ab = g.A + (size_t)pencil * nslots * sstride + mblk * RT * 32;
+    int u_off[NU], u_rest[NU], u_e[NU];                      // offset of the unit's slot in the step requested next
 #pragma unroll
-    for (int r = 0; r < RTW; ++r)
-#pragma unroll
-        for (int c = 0; c < CTW; ++c) {
-            p1[r][c] = floatx4{0.f, 0.f, 0.f, 0.f}; p2[r][c] = p1[r][c]; p3[r][c] = p1[r][c];
-        }
-
-    const size_t jstride = (size_t)4 * Mp;              // one step (one tap of one group of four images)
-    const size_t istride = (size_t)K * jstride;         // one iteration
-    const int nI = g.fp >> 2;
-    const float2* Ab = g.A + (size_t)pencil * K * g.fp * Mp + (size_t)kk * Mp + m0 + l16;
-    // Lane (kk, l16) supplies, for column tile c and tap a, X2[4*I4 + kk][xo + K-1 - a]: Xc[c] points at x = xo + K-1
-    // of row 0 of the lane's input, the taps are constant offsets below it.  Columns beyond Ct are clamped (never
-    // stored), rows beyond f are clamped to the last one (their A operands are zero).
-    const float2* Xc[CTW];
-#pragma unroll
-    for (int c = 0; c < CTW; ++c) {
-        const int col = min(colw + c * 16 + l16, Ct - 1);
-        const int sI = g.S == 1 ? 0 : col / g.nox, xo = col - sI * g.nox;
-        Xc[c] = g.X2 + (size_t)sI * f * g.ximg + (size_t)poz * g.xpen + (size_t)poy * g.ldx + xo + (K - 1);
+    for (int i = 0; i < NU; ++i) {
+        u_e[i] = min(wave + 4 * i, 2 * RT - 1) * 64 + lane;
+        const int sl = u_e[i] / (RT * 32);
+        u_off[i] = sl * sstride;
+        u_rest[i] = u_e[i] - sl * (RT * 32);
     }
-    // Row offset of the group of four images being requested; group 0 first.  Only the last group can hold rows
-    // beyond f, so all steps but the one onto the last group are the same for every lane.
-    size_t xrow = (size_t)min(kk, f - 1) * g.ximg;
-    const size_t xstep = (size_t)4 * g.ximg;
-    const size_t xlast = nI >= 2 ? (size_t)(min(4 * (nI - 1) + kk, f - 1) - (4 * (nI - 2) + kk)) * g.ximg : 0;
-
-    // the 3 * RTW * CTW matrix instructions of one tap: three real products per complex one
-#define ZNNI_XD_TAP(GG, XX)                                                                                \
-    {                                                                                                      \
-        float bs_[CTW], as_[RTW];                                                                          \
-        _Pragma("unroll") for (int c = 0; c < CTW; ++c) bs_[c] = XX[c].x + XX[c].y;                        \
-        _Pragma("unroll") for (int r = 0; r < RTW; ++r) as_[r] = GG[r].x + GG[r].y;                        \
-        _Pragma("unroll") for (int r = 0; r < RTW; ++r)                                                    \
-            _Pragma("unroll") for (int c = 0; c < CTW; ++c) {                                              \
-                p1[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(GG[r].x, XX[c].x, p1[r][c], 0, 0, 0);      \
-                p2[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(GG[r].y, XX[c].y, p2[r][c], 0, 0, 0);      \
-                p3[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(as_[r], bs_[c], p3[r][c], 0, 0, 0);        \
-            }                                                                                              \
-    }
-
-    if constexpr (mac_xd_two_sets<RTW, CTW, K>()) {
-        float2 Ga[K][RTW], Gb[K][RTW], Xa[K][CTW], Xb[K][CTW];
+    half8 ring[2][NU];                                       // a pair of steps
+    auto load_a = [&]() {
 #pragma unroll
-        for (int a = 0; a < K; ++a) {
+        for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int r = 0; r < RTW; ++r) Ga[a][r] = Ab[(size_t)a * jstride + r * 16];
-#pragma unroll
-            for (int c = 0; c < CTW; ++c) Xa[a][c] = (Xc[c] + xrow)[-a];
-        }
-        // One iteration on the operands in (CG, CX) while those of the following one travel into (NG, NX); past the
-        // last iteration the A requests read the next pencil or the zeroed padding behind A, the image requests
-        // the last group again, and the values are never used.
-#define ZNNI_XD_ITER(CG, NG, CX, NX, I4)                                                                   \
-    {                                                                                                      \
-        const float2* an_ = Ab + (size_t)((I4) + 1) * istride;                                             \
-        xrow += (I4) + 2 < nI ? xstep : ((I4) + 2 == nI ? xlast : 0);                                      \
-        _Pragma("unroll") for (int a = 0; a < K; ++a) {                                                    \
-            _Pragma("unroll") for (int r = 0; r < RTW; ++r) NG[a][r] = an_[(size_t)a * jstride + r * 16];  \
-            _Pragma("unroll") for (int c = 0; c < CTW; ++c) NX[a][c] = (Xc[c] + xrow)[-a];                 \
-        }                                                                                                  \
-        __builtin_amdgcn_sched_barrier(0);                                                                 \
-        __builtin_amdgcn_iglp_opt(0);       /* interleave the additions with the matrix instructions */    \
-        _Pragma("unroll") for (int a = 0; a < K; ++a) ZNNI_XD_TAP(CG[a], CX[a])                            \
-        __builtin_amdgcn_sched_barrier(0);                                                                 \
-    }
-        int i4 = 0;
-        for (; i4 + 2 <= nI; i4 += 2) {
-            ZNNI_XD_ITER(Ga, Gb, Xa, Xb, i4)
-            ZNNI_XD_ITER(Gb, Ga, Xb, Xa, i4 + 1)
-        }
-        if (i4 < nI) ZNNI_XD_ITER(Ga, Gb, Xa, Xb, i4)
-#undef ZNNI_XD_ITER
-    } else {
-        // One register set: the operands of tap a of the following iteration are requested right after tap a of
-        // this one has been issued, into the registers it has just released.  The requests are issued in the same
-        // order in the prologue as in the loop (tap by tap, A operands then image values), so that the wait for
-        // tap a's operands can leave everything requested after them in flight.
-        float2 G[K][RTW], X[K][CTW];
-#pragma unroll
-        for (int a = 0; a < K; ++a) {
-#pragma unroll
-            for (int r = 0; r < RTW; ++r) G[a][r] = Ab[(size_t)a * jstride + r * 16];
-#pragma unroll
-            for (int c = 0; c < CTW; ++c) X[a][c] = (Xc[c] + xrow)[-a];
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        for (int i4 = 0; i4 < nI; ++i4) {
-            const float2* an = Ab + (size_t)(i4 + 1) * istride;
-            xrow += i4 + 2 < nI ? xstep : (i4 + 2 == nI ? xlast : 0);
-#pragma unroll
-            for (int a = 0; a < K; ++a) {
-                __builtin_amdgcn_iglp_opt(0);
-                ZNNI_XD_TAP(G[a], X[a])
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int r = 0; r < RTW; ++r) G[a][r] = an[(size_t)a * jstride + r * 16];
-#pragma unroll
-                for (int c = 0; c < CTW; ++c) X[a][c] = (Xc[c] + xrow)[-a];
-                __builtin_amdgcn_sched_barrier(0);
+            for (int i = 0; i < NU; ++i) {
+                ring[h][i] = *reinterpret_cast<const half8*>(reinterpret_cast<const char*>(Ab) +
+                                                             (size_t)(unsigned)(min(u_off[i], slast) + u_rest[i]) * 16);
+                u_off[i] = min(u_off[i], slast) + 4 * sstride;
             }
+    };
+    // The pair's operands to LDS; slots past the last one become zeros (only the last pair can hold any).
+    auto park_a = [&](int step, int buf) {
+        half8* d = As + buf * RT * 256;
+        if (4 * step + 7 >= nslots) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int i = 0; i < NU; ++i) {
+                    half8 v = ring[h][i];
+                    if (4 * (step + h) + u_e[i] / (RT * 32) >= nslots)
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) v[e] = (_Float16)0;
+                    d[h * RT * 128 + u_e[i]] = v;
+                }
+        } else {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int i = 0; i < NU; ++i) d[h * RT * 128 + u_e[i]] = ring[h][i];
         }
-    }
-#undef ZNNI_XD_TAP
+    };
 
-    // Combine the three partial products (Re = P1 - P2, Im = P3 - P1 - P2) and store.  Accumulator element e of
-    // lane l is row 4*(l/16)+e, column l%16: 16 neighbouring lanes write 128 contiguous bytes of a row of Yd.
+    floatx4 re[RT][CT], im[RT][CT];
 #pragma unroll
-    for (int c = 0; c < CTW; ++c) {
-        const int col = colw + c * 16 + l16;
-        if (col >= Ct) continue;
-        const int sI = g.S == 1 ? 0 : col / g.nox, xo = col - sI * g.nox;
-        const int row0 = m0 + 4 * kk;
-        float2* y = g.Yd + (size_t)(sI * g.fo + row0) * g.yimg + (size_t)poz * g.ypen + (size_t)poy * g.ldxo + xo;
+    for (int r = 0; r < RT; ++r)
 #pragma unroll
-        for (int r = 0; r < RTW; ++r)
+        for (int c = 0; c < CT; ++c) { re[r][c] = floatx4{0.f, 0.f, 0.f, 0.f}; im[r][c] = re[r][c]; }
+
+    load_a();
+    float rj[RT];                                            // (requested here, used with the results)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                float re = p1[r][c][e] - p2[r][c][e];
-                float im = p3[r][c][e] - p1[r][c][e] - p2[r][c][e];
-                if (row0 + r * 16 + e < g.fo) {
-                    float2* dst = y + (size_t)(r * 16 + e) * g.yimg;
-                    if (g.accumulate) {
-                        const float2 old = *dst;
-                        re += old.x;
-                        im += old.y;
+    for (int r = 0; r < RT; ++r) rj[r] = g.rinv[(mblk * RT + r) * 16 + l16];
+
+    const float2* xrow = g.X2 + (size_t)sI * f * g.ximg + (size_t)poz * g.xpen + (size_t)poy * g.ldx;
+    int sexp = 126;                                          // exponent of the scale the image values carry
+    int chunk = 0;
+    // One chunk of image rows to LDS: wave w takes quads w, w + 4, ..., x along the lanes; the halo behind the outputs, one
+    // (quad, x) unit per thread.  Values beyond a row are read from its end, images beyond the last from the last: neither
+    // reaches a stored output (the images count as zeros).
+    auto stage = [&]() {
+        const int i0 = chunk * 16 * NG;
+        float2 raw[NG][CT][4], halo[4];
+        // (quads beyond the last image are neither read nor staged: no lane group's slot names them)
+#pragma unroll
+        for (int gq = 0; gq < NG; ++gq)
+            if (i0 + 16 * gq + 4 * wave < f)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const char* row = reinterpret_cast<const char*>(xrow + (size_t)min(i0 + 16 * gq + 4 * wave + q, f - 1) * g.ximg);
+#pragma unroll
+                for (int it = 0; it < CT; ++it)
+                    raw[gq][it][q] = *reinterpret_cast<const float2*>(row + 8u * (unsigned)min(col0 + 64 * it + lane, g.nx - 1));
+            }
+            else
+#pragma unroll
+                for (int it = 0; it < CT; ++it)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) raw[gq][it][q] = make_float2(0.f, 0.f);
+        const int hq = min(t >> 3, NQ - 1), hx = min(col0 + 64 * CT + (t & 7), g.nx - 1);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) halo[q] = xrow[(size_t)min(i0 + 4 * hq + q, f - 1) * g.ximg + hx];
+        float m = 0.f;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            xd_max3(m, halo[q].x, halo[q].y);
+#pragma unroll
+            for (int gq = 0; gq < NG; ++gq)
+#pragma unroll
+                for (int it = 0; it < CT; ++it) xd_max3(m, raw[gq][it][q].x, raw[gq][it][q].y);
+        }
+        auto largest = [&](unsigned (&w)[4]) {
+            const unsigned v = xd_wave_max(m);
+            if (lane == 0) w[wave] = v;
+            __syncthreads();
+            return max(max(w[0], w[1]), max(w[2], w[3]));
+        };
+        unsigned mb = largest(wmax[chunk & 1]);
+        if (mb >= 0x7f800000u) {                             // infinities or NaNs: the scale is that of the finite values
+            m = 0.f;
+            auto fin = [&](float2 v) {
+                const float ax = fabsf(v.x), ay = fabsf(v.y);
+                xd_max3(m, ax < INFINITY ? ax : 0.f, ay < INFINITY ? ay : 0.f);
+            };
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                fin(halo[q]);
+#pragma unroll
+                for (int gq = 0; gq < NG; ++gq)
+#pragma unroll
+                    for (int it = 0; it < CT; ++it) fin(raw[gq][it][q]);
+            }
+            mb = largest(wfin);
+            __syncthreads();
+        }
+        const int sn = min(sexp, xd_scale_exp(__uint_as_float(mb)));
+        if (sn < sexp && chunk) {                            // a larger chunk: the sums follow its scale
+#pragma unroll
+            for (int r = 0; r < RT; ++r)
+#pragma unroll
+                for (int c = 0; c < CT; ++c)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        re[r][c][e] = ldexpf(re[r][c][e], sn - sexp);
+                        im[r][c][e] = ldexpf(im[r][c][e], sn - sexp);
                     }
-                    *dst = make_float2(re, im);
+        }
+        sexp = sn;
+        const float sx = xd_pow2(sn);
+        auto put = [&](const float2 (&v)[4], int quad, int x) {
+            half8 h, l;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float s = i0 + 4 * quad + q < f ? sx : 0.f;
+                _Float16 a, b;
+                xd_split(v[q].x, s, a, b);
+                h[2 * q] = a; l[2 * q] = b;
+                xd_split(v[q].y, s, a, b);
+                h[2 * q + 1] = a; l[2 * q + 1] = b;
+            }
+            Xs[quad * XW + x] = h;
+            Xs[(NQ + quad) * XW + x] = l;
+        };
+#pragma unroll
+        for (int gq = 0; gq < NG; ++gq)
+            if (i0 + 16 * gq + 4 * wave < f)
+#pragma unroll
+                for (int it = 0; it < CT; ++it) put(raw[gq][it], 4 * gq + wave, 64 * it + lane);
+        if (t < 8 * NQ) put(halo, hq, 64 * CT + (t & 7));
+        __syncthreads();
+        ++chunk;
+    };
+
+    // position in the contraction: group of four quads inside the chunk, steps left in the group, and this lane group's
+    // slot (quad of the group, tap)
+    int grp = 0, left = 0, quad = 0, a = 0, qx = 0, QC = 4;      // qx = quad * XW
+    int ggrp = 0;
+    auto step = [&](int gs, const half8* as) {               // as: this lane group's kernel operands of the step
+        if (left == 0) {                                     // next group of up to sixteen images
+            if (grp == NG || ggrp == 0) { stage(); grp = 0; }
+            QC = min(4, ((f + 3) >> 2) - 4 * ggrp);
+            left = (K * QC + 3) >> 2;
+            quad = kk % QC; a = kk / QC; qx = quad * XW;
+            ++grp; ++ggrp;
+        }
+        --left;
+        const half8* xs = Xs + (4 * (grp - 1) * XW + wave * 16 * CT) + l16 + qx + max(K - 1 - a, 0);
+        if (QC == 4) ++a;
+        else {
+            quad += 4 % QC; a += 4 / QC;
+            if (quad >= QC) { quad -= QC; ++a; }
+            qx = quad * XW;
+        }
+        uintx4 xh[CT], xl[CT];
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            xh[c] = __builtin_bit_cast(uintx4, xs[16 * c]);
+            xl[c] = __builtin_bit_cast(uintx4, xs[NQ * XW + 16 * c]);
+        }
+        auto neg = [](uintx4 v) { return __builtin_bit_cast(half8, v ^ 0x80000000u); };     // (r, i) -> (r, -i)
+        auto swp = [](uintx4 v) {                                                            // (r, i) -> (i, r)
+            uintx4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = __builtin_amdgcn_alignbit(v[e], v[e], 16);
+            return __builtin_bit_cast(half8, o);
+        };
+#define ZNNI_XD_MFMA(D, X, A) D = __builtin_amdgcn_mfma_f32_16x16x32_f16(X, A, D, 0, 0, 0)
+        if constexpr (CT <= RT) {                            // the two forms of an operand from the side with fewer tiles
+            half8 hr[CT], hi[CT], lr[CT], li[CT];
+#pragma unroll
+            for (int c = 0; c < CT; ++c) { hr[c] = neg(xh[c]); hi[c] = swp(xh[c]); lr[c] = neg(xl[c]); li[c] = swp(xl[c]); }
+#pragma unroll
+            for (int r = 0; r < RT; ++r) {
+                const half8 ah = as[r * 32], al = as[r * 32 + 16];
+#pragma unroll
+                for (int c = 0; c < CT; ++c) { ZNNI_XD_MFMA(re[r][c], lr[c], ah); ZNNI_XD_MFMA(im[r][c], li[c], ah); }
+#pragma unroll
+                for (int c = 0; c < CT; ++c) { ZNNI_XD_MFMA(re[r][c], hr[c], al); ZNNI_XD_MFMA(im[r][c], hi[c], al); }
+#pragma unroll
+                for (int c = 0; c < CT; ++c) { ZNNI_XD_MFMA(re[r][c], hr[c], ah); ZNNI_XD_MFMA(im[r][c], hi[c], ah); }
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < RT; ++r) {
+                const uintx4 ah = __builtin_bit_cast(uintx4, as[r * 32]), al = __builtin_bit_cast(uintx4, as[r * 32 + 16]);
+                const half8 hr = neg(ah), hi = swp(ah), lr = neg(al), li = swp(al);
+#pragma unroll
+                for (int c = 0; c < CT; ++c) {
+                    ZNNI_XD_MFMA(re[r][c], __builtin_bit_cast(half8, xl[c]), hr);
+                    ZNNI_XD_MFMA(im[r][c], __builtin_bit_cast(half8, xl[c]), hi);
+                }
+#pragma unroll
+                for (int c = 0; c < CT; ++c) {
+                    ZNNI_XD_MFMA(re[r][c], __builtin_bit_cast(half8, xh[c]), lr);
+                    ZNNI_XD_MFMA(im[r][c], __builtin_bit_cast(half8, xh[c]), li);
+                }
+#pragma unroll
+                for (int c = 0; c < CT; ++c) {
+                    ZNNI_XD_MFMA(re[r][c], __builtin_bit_cast(half8, xh[c]), hr);
+                    ZNNI_XD_MFMA(im[r][c], __builtin_bit_cast(half8, xh[c]), hi);
                 }
             }
+        }
+#undef ZNNI_XD_MFMA
+    };
+    // The first pair's operands are parked before its first chunk is staged (whose barriers publish them); from then on a
+    // pair's are parked while the pair before it is multiplied, into the half that was read before that.
+    park_a(0, 0);
+    if (nsteps > 2) load_a();
+    const half8* const as0 = As + kk * RT * 32 + l16;
+    for (int gs = 0, buf = 0; gs < nsteps; gs += 2, buf ^= 1) {
+        if (gs) __syncthreads();                             // this pair's operands are in place, the last one's are free
+        step(gs, as0 + buf * RT * 256);
+        if (gs + 2 < nsteps) {
+            park_a(gs + 2, buf ^ 1);
+            if (gs + 4 < nsteps) load_a();
+        }
+        if (gs + 1 < nsteps) step(gs + 1, as0 + buf * RT * 256 + RT * 128);
     }
-}
 
-// Register budget: two waves per SIMD (up to 256 registers) for the tiles that are bound by the matrix cores;
-// the small tiles of narrow layers are bound by memory and keep more waves in flight.
-template <int RTW, int K, bool WIDE>
-constexpr int mac_xd_min_blocks()
-{
-    return (RTW >= 3 || (WIDE && RTW >= 2)) ? 2 : 3;
-}
-
-// One launch for all of a layer's column blocks: pieces [0, n2*nmblk) of a pencil are 128-wide blocks, the rest
-// 64-wide blocks behind them.  WIDE = false leaves the 128-wide path out (row blocks too tall for it).
-template <int RTW, int K, bool WIDE>
-__global__ __launch_bounds__(256, (mac_xd_min_blocks<RTW, K, WIDE>()))
-void k_mac_xd(XdArgs g)
-{
-    int pencil, sub;
-    if (!mac_block((g.n2 + g.n1) * g.nmblk, g.npencils, pencil, sub)) return;
-    if constexpr (WIDE) {
-        if (sub < g.n2 * g.nmblk) {
-            mac_xd_body<RTW, 2, K>(g, 0, g.n2, pencil, sub);
-            return;
+    // ---- accumulator element e of lane (kk, l16): output xo = ... + 4 kk + e of output image ... + l16.  Rows of Yd are
+    // padded to 16 outputs, so a lane always stores its four.
+    const float inv = xd_pow2(-sexp);
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+        const int j = (mblk * RT + r) * 16 + l16;
+        if (j >= g.fo) continue;
+        float2* y = g.Yd + (size_t)(sI * g.fo + j) * g.yimg + (size_t)poz * g.ypen + (size_t)poy * g.ldxo;
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            const int xo = col0 + (wave * CT + c) * 16 + 4 * kk;
+            if (xo >= g.nox) continue;
+            float4* d = reinterpret_cast<float4*>(y + xo);
+            float4 v0 = make_float4(re[r][c][0] * inv * rj[r], im[r][c][0] * inv * rj[r], re[r][c][1] * inv * rj[r], im[r][c][1] * inv * rj[r]);
+            float4 v1 = make_float4(re[r][c][2] * inv * rj[r], im[r][c][2] * inv * rj[r], re[r][c][3] * inv * rj[r], im[r][c][3] * inv * rj[r]);
+            if (g.accumulate) {
+                const float4 o0 = d[0], o1 = d[1];
+                v0.x += o0.x; v0.y += o0.y; v0.z += o0.z; v0.w += o0.w;
+                v1.x += o1.x; v1.y += o1.y; v1.z += o1.z; v1.w += o1.w;
+            }
+            d[0] = v0;
+            d[1] = v1;
         }
     }
-    mac_xd_body<RTW, 1, K>(g, g.col1, g.n1, pencil, sub - g.n2 * g.nmblk);
 }
 
-bool mac_xd_available(const LayerPlan& L)
+// ---------------------------------------------------------------------------------------- kernel transform
+// Second stage (y) of the kernel transform for this route: A1 (after the z stage) -> the split operand layout above,
+//     A[pencil][slot][j / 16][hi, lo][j % 16][image of the quad][re, im] = split( rs[j] * scale *
+//         sum_{b<ky} A1[oz][b][a][i][j] exp(-2 pi i oy b / Ny) ),
+// slots of a pencil in the order the contraction walks them: chunks of four image quads, inside a chunk tap by tap,
+// quads fastest.  One thread: one (slot, j), whose four images' ky values it keeps in registers while it walks KX_OY
+// bins along y; 16 + 16 bytes per bin leave it, 256 contiguous bytes per sixteen threads.  Bound by writing A.
+// (noy = KX_OY bins, or fewer where that leaves the chip short of workgroups)
+constexpr int KX_OY = 32;
+__device__ __forceinline__ void xd_slot(int slot, int K, int fq, int& quad, int& a)
 {
-    const int k = L.d.kx;
-    return k >= 1 && k <= 9 && !(k == 9 && L.mac_RTW == 5);
+    const int c = slot / (4 * K), s = slot - c * 4 * K, QC = min(4, fq - 4 * c);
+    a = s / QC;
+    quad = 4 * c + s - a * QC;
+}
+__device__ __forceinline__ void xd_store(half8* d, const float2 (&v)[4], float s)
+{
+    half8 h, l;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        _Float16 x, y;
+        xd_split(v[q].x, s, x, y);
+        h[2 * q] = x; l[2 * q] = y;
+        xd_split(v[q].y, s, x, y);
+        h[2 * q + 1] = x; l[2 * q + 1] = y;
+    }
+    d[0] = h;
+    d[16] = l;
+}
+template <int KY>          // taps along y; 0: any number, A1 read again for every bin
+__global__ __launch_bounds__(256) void k_kprep_xd(const float2* __restrict__ A1, half8* __restrict__ A,
+                                                  const float2* __restrict__ tw, const float* __restrict__ rs, int N,
+                                                  int ky, int K, int fp, int Mp, float scale, int noy)
+{
+    constexpr int KT = KY ? KY : 1;
+    __shared__ float2 tw2[KX_OY][KT];
+    const int idx = blockIdx.x * 256 + threadIdx.x;
+    const int oy0 = blockIdx.y * noy, oz = blockIdx.z;
+    const int fq = fp >> 2, nslots = K * fq;
+    if constexpr (KY) {
+        for (int e = threadIdx.x; e < noy * KY; e += 256) {
+            const int o = e / KT, b = e - o * KT;
+            tw2[o][b] = tw[(unsigned)((oy0 + o) * b) % (unsigned)N];
+        }
+        __syncthreads();
+    }
+    if (idx >= nslots * Mp) return;
+    const int j = idx % Mp, slot = idx / Mp;
+    int quad, a;
+    xd_slot(slot, K, fq, quad, a);
+    const size_t per = (size_t)K * fp * Mp;
+    const float2* a1 = A1 + (size_t)oz * ky * per + ((size_t)a * fp + 4 * quad) * Mp + j;
+    const float s = rs[j] * scale;                       // scale is no power of two: folded in before the split
+    const int no = min(noy, N - oy0);
+    half8* d = A + ((size_t)(oz * N + oy0) * nslots + slot) * 2 * Mp + (j >> 4) * 32 + (j & 15);
+    const size_t dstep = (size_t)nslots * 2 * Mp;
+    if constexpr (KY) {
+        float2 v[KT][4];
+#pragma unroll
+        for (int b = 0; b < KT; ++b)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float2 x = a1[(size_t)b * per + q * Mp];
+                v[b][q] = make_float2(x.x * s, x.y * s);
+            }
+        for (int o = 0; o < no; ++o, d += dstep) {
+            float2 acc[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                acc[q] = make_float2(0.f, 0.f);
+#pragma unroll
+                for (int b = 0; b < KT; ++b) acc[q] = cfma(acc[q], v[b][q], tw2[o][b]);
+            }
+            xd_store(d, acc, 1.f);
+        }
+    } else {
+        for (int o = 0; o < no; ++o, d += dstep) {
+            float2 acc[4] = {};
+            int t = 0;                                   // (oy * b) mod N
+            for (int b = 0; b < ky; ++b) {
+                const float2 w = tw[t];
+                t += oy0 + o;
+                if (t >= N) t -= N;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) acc[q] = cfma(acc[q], a1[(size_t)b * per + q * Mp], w);
+            }
+            xd_store(d, acc, s);
+        }
+    }
 }
 
-template <int RTW, int K, bool WIDE>
-static znni_status launch_xd(const LayerPlan& L, int accumulate, hipStream_t st)
+float* mac_xd_row_scales(const LayerPlan& L)
+{
+    return reinterpret_cast<float*>(L.A + (size_t)L.d.zc * L.d.Ny * L.d.kx * L.fp * L.Mp);
+}
+
+template <int KY>
+static znni_status launch_kprep_xd_k(const LayerPlan& L, hipStream_t st)
 {
     const Dims& d = L.d;
-    XdArgs g;
-    g.X2 = L.buf1; g.A = L.A; g.Yd = L.Yt;
-    g.ximg = (size_t)d.x2i * d.ldx; g.xpen = (size_t)d.x2o * d.ldx;
-    g.yimg = (size_t)d.ydi * d.ldxo; g.ypen = (size_t)d.ydo * d.ldxo;
-    g.Ny = d.Ny;
-    g.S = L.S; g.f = L.f; g.fo = L.fo; g.fp = L.fp; g.Mp = L.Mp;
-    g.nox = d.nox; g.ldx = d.ldx; g.ldxo = d.ldxo;
-    // columns (input of the batch, xo): blocks of 128 where the row block leaves room, a 64-wide remainder
-    const int Ct = L.S * d.nox;
-    // (a remainder of more than 64 columns goes to one more 128-wide block, ragged, rather than to two 64-wide ones:
-    // the same column slots, half the reads of the kernel transforms)
-    g.n2 = WIDE ? (Ct + 63) / 128 : 0;
-    g.n1 = Ct > g.n2 * 128 ? (Ct - g.n2 * 128 + 63) / 64 : 0;
-    g.col1 = g.n2 * 128;
-    g.nmblk = L.mac_nmblk;
-    g.npencils = d.zc * d.Ny;
-    g.accumulate = accumulate;
-    const int per_pencil = (g.n2 + g.n1) * g.nmblk;
-    const long long blocks = (long long)((g.npencils + 7) / 8) * per_pencil * 8;
-    k_mac_xd<RTW, K, WIDE><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(g);
+    const int items = d.kx * (L.fp >> 2) * L.Mp;
+    const float scale = (float)(1.0 / ((double)d.Ny * d.Nz));
+    const int nb = (items + 255) / 256;
+    int noy = KX_OY;
+    while (noy > 4 && (long long)nb * ((d.Ny + noy - 1) / noy) * d.zc < 1024) noy >>= 1;
+    k_kprep_xd<KY><<<dim3(nb, (d.Ny + noy - 1) / noy, d.zc), dim3(256), 0, st>>>(
+        L.A1, reinterpret_cast<half8*>(L.A), L.twy, mac_xd_row_scales(L), d.Ny, d.ky, d.kx, L.fp, L.Mp, scale, noy);
     if (hipGetLastError() != hipSuccess) return ZNNI_ERR_HIP;
     return ZNNI_OK;
 }
 
-template <int K>
-static znni_status launch_xd_tiles(const LayerPlan& L, int accumulate, hipStream_t st)
+znni_status launch_kprep_xd(const LayerPlan& L, hipStream_t st)
 {
-    const bool wide = L.mac_RTW <= 3 && L.S * L.d.nox > 64;
-    if (wide) {
-        switch (L.mac_RTW) {
-            case 1: return launch_xd<1, K, true>(L, accumulate, st);
-            case 2: return launch_xd<2, K, true>(L, accumulate, st);
-            case 3: return launch_xd<3, K, true>(L, accumulate, st);
-        }
+    switch (L.d.ky) {
+        case 1: return launch_kprep_xd_k<1>(L, st);
+        case 2: return launch_kprep_xd_k<2>(L, st);
+        case 3: return launch_kprep_xd_k<3>(L, st);
+        case 4: return launch_kprep_xd_k<4>(L, st);
+        case 5: return launch_kprep_xd_k<5>(L, st);
+        case 6: return launch_kprep_xd_k<6>(L, st);
+        case 7: return launch_kprep_xd_k<7>(L, st);
+        case 8: return launch_kprep_xd_k<8>(L, st);
+        case 9: return launch_kprep_xd_k<9>(L, st);
     }
-    switch (L.mac_RTW) {
-        case 1: return launch_xd<1, K, false>(L, accumulate, st);
-        case 2: return launch_xd<2, K, false>(L, accumulate, st);
-        case 3: return launch_xd<3, K, false>(L, accumulate, st);
-        case 4: return launch_xd<4, K, false>(L, accumulate, st);
-        case 5: return launch_xd<5, K, false>(L, accumulate, st);
+    return launch_kprep_xd_k<0>(L, st);
+}
+
+// ---------------------------------------------------------------------------------------- host side
+// Widest tile of a row block (its sums, RT * CT * 8 registers a lane, leave room for two waves per SIMD) and images per
+// chunk in groups of sixteen.  Measured, multiply-accumulate alone: one group for up to four row tiles (40 -> 40 of 128^3,
+// 3^3 kernels 0.223 ms, two groups 0.269; 32 -> 32 of 200^3, 5^3 0.667 against 1.04), two for five (80 -> 80 of 128^3, 7^3
+// 1.18 ms, one group 1.25, three 1.55; 80 -> 80 of 200^3, 5^3 3.76, 3.84, 5.07).
+template <int RT> constexpr int xd_max_ct() { return RT >= 5 ? 2 : (RT >= 3 ? 3 : 4); }
+template <int RT> constexpr int xd_groups() { return RT >= 5 ? 2 : 1; }
+bool mac_xd_available(const LayerPlan& L) { return L.d.kx >= 1 && L.d.kx <= XD_MAX_K; }
+
+template <int RT, int CT>
+static znni_status launch_xd(const LayerPlan& L, int ncb, int accumulate, hipStream_t st)
+{
+    const Dims& d = L.d;
+    XdArgs g;
+    g.X2 = L.buf1; g.A = reinterpret_cast<const half8*>(L.A); g.rinv = mac_xd_row_scales(L) + L.Mp; g.Yd = L.Yt;
+    g.ximg = (size_t)d.x2i * d.ldx; g.xpen = (size_t)d.x2o * d.ldx;
+    g.yimg = (size_t)d.ydi * d.ldxo; g.ypen = (size_t)d.ydo * d.ldxo;
+    g.S = L.S; g.f = L.f; g.fo = L.fo; g.Mp = L.Mp; g.K = d.kx;
+    g.nx = d.nx; g.nox = d.nox; g.ldx = d.ldx; g.ldxo = d.ldxo; g.Ny = d.Ny;
+    g.d_sub.set((unsigned)(ncb * L.S * L.mac_nmblk)); g.d_ncb.set((unsigned)ncb); g.d_S.set((unsigned)L.S); g.d_Ny.set((unsigned)d.Ny);
+    g.ncb = ncb; g.nmblk = L.mac_nmblk; g.npencils = d.zc * d.Ny; g.accumulate = accumulate;
+    const long long blocks = (long long)((g.npencils + 7) / 8) * ncb * L.S * g.nmblk * 8;
+    if (blocks > 0x7fffffffll) return ZNNI_ERR_SHAPE;
+    constexpr int NG = xd_groups<RT>();
+    constexpr size_t lds = xd_lds_bytes<RT, CT, NG>();
+    if (lds > 48 * 1024 && hipFuncSetAttribute((const void*)k_mac_xd<RT, CT, NG>,
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+        return ZNNI_ERR_HIP;
+    k_mac_xd<RT, CT, NG><<<dim3((unsigned)blocks), dim3(256), lds, st>>>(g);
+    if (hipGetLastError() != hipSuccess) return ZNNI_ERR_HIP;
+    return ZNNI_OK;
+}
+
+// Columns: as few workgroups per row as the widest tile allows (its sums, RT * CT * 8 registers per lane, leave room for
+// two waves per SIMD), then the narrowest tile that still covers the row with that many.
+template <int RT>
+static znni_status launch_xd_cols(const LayerPlan& L, int accumulate, hipStream_t st)
+{
+    constexpr int MAXCT = xd_max_ct<RT>();
+    const int t64 = (L.d.nox + 63) / 64;                     // 64 outputs: one column tile per wave
+    const int ncb = (t64 + MAXCT - 1) / MAXCT, CT = (t64 + ncb - 1) / ncb;
+    switch (CT) {
+        case 1: return launch_xd<RT, 1>(L, ncb, accumulate, st);
+        case 2: if constexpr (MAXCT >= 2) return launch_xd<RT, 2>(L, ncb, accumulate, st); break;
+        case 3: if constexpr (MAXCT >= 3) return launch_xd<RT, 3>(L, ncb, accumulate, st); break;
+        case 4: if constexpr (MAXCT >= 4) return launch_xd<RT, 4>(L, ncb, accumulate, st); break;
     }
     return ZNNI_ERR_SHAPE;
 }
@@ -274,16 +600,12 @@ static znni_status launch_xd_tiles(const LayerPlan& L, int accumulate, hipStream
 znni_status launch_mac_xd(const LayerPlan& L, int accumulate, hipStream_t st)
 {
     if (!mac_xd_available(L)) return ZNNI_ERR_UNSUPPORTED_SIZE;
-    switch (L.d.kx) {
-        case 1: return launch_xd_tiles<1>(L, accumulate, st);
-        case 2: return launch_xd_tiles<2>(L, accumulate, st);
-        case 3: return launch_xd_tiles<3>(L, accumulate, st);
-        case 4: return launch_xd_tiles<4>(L, accumulate, st);
-        case 5: return launch_xd_tiles<5>(L, accumulate, st);
-        case 6: return launch_xd_tiles<6>(L, accumulate, st);
-        case 7: return launch_xd_tiles<7>(L, accumulate, st);
-        case 8: return launch_xd_tiles<8>(L, accumulate, st);
-        case 9: return launch_xd_tiles<9>(L, accumulate, st);
+    switch (L.mac_RTW) {
+        case 1: return launch_xd_cols<1>(L, accumulate, st);
+        case 2: return launch_xd_cols<2>(L, accumulate, st);
+        case 3: return launch_xd_cols<3>(L, accumulate, st);
+        case 4: return launch_xd_cols<4>(L, accumulate, st);
+        case 5: return launch_xd_cols<5>(L, accumulate, st);
     }
     return ZNNI_ERR_SHAPE;
 }

@@ -270,8 +270,9 @@ znni_status launch_twiddles(const LayerPlan& L, hipStream_t st)
     const Dims& d = L.d;
     // the multiply-accumulate reads a little past A's last pencil (values multiplied by zero at most): that
     // padding is zeroed here
-    // (the block-transform route keeps another array in A and reads nothing behind it)
-    const size_t pad = L.xblock ? 0 : (size_t)(L.fp + 64) * L.Mp;
+    // (the routes that do not transform x at full length read nothing behind their arrays, and one of them keeps its
+    // scales there, mac_xd.hip)
+    const size_t pad = L.xdirect ? 0 : (size_t)(L.fp + 64) * L.Mp;
     const size_t per = (size_t)d.kx * L.fp * L.Mp;
     size_t most = pad > 0 ? pad : 1;
     for (int N : {d.Nx, d.Ny, d.Nz})
