@@ -23,6 +23,7 @@
 // a wave's load is one 256-byte run).
 #include <stdint.h>
 
+#include "direct_split.h"
 #include "znni_internal.h"
 
 namespace znni {
@@ -292,6 +293,8 @@ struct DirectPlan {
     int S, f, fo;
     int taps, T4, RT, RTW, CTW, nmblk, IC;
     bool longz;      // tile shape
+    bool split;      // on fp16 matrix instructions instead (direct_split.hip)
+    SplitPlan sp;
     size_t lds, wp_floats, bytes;
 };
 
@@ -335,6 +338,8 @@ static znni_status direct_plan(int S, int f, int fo, const int n[3], const int k
     P->wp_floats = (size_t)f * P->T4 * P->RT * 16;
     // + one step of padding: the kernel requests its kernel values one step ahead
     P->bytes = ((P->wp_floats + (size_t)P->RT * 64) * 4 + 255) / 256 * 256;
+    P->split = split_plan(S, f, fo, d, &P->sp);
+    if (P->split && P->sp.bytes > P->bytes) P->bytes = (P->sp.bytes + 255) / 256 * 256;
     return ZNNI_OK;
 }
 
@@ -393,6 +398,8 @@ znni_status znni_conv3d_direct_v(int S, int f, int fo, const int n[3], const int
     if ((uintptr_t)workspace & 255u) return ZNNI_ERR_ALIGN;
     if (workspace_bytes < P.bytes) return ZNNI_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
+    if (P.split)
+        return launch_direct_split(P.sp, S, f, fo, P.d, in, w, bias, out, (flags & ZNNI_RELU) ? 1 : 0, workspace, st);
     float* Wp = (float*)workspace;
     const size_t wp_all = P.wp_floats + (size_t)P.RT * 64;        // the look-ahead padding is zeroed too
     k_direct_prep<<<dim3((unsigned)((wp_all + 255) / 256)), dim3(256), 0, st>>>(

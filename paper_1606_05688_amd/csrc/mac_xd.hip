@@ -50,23 +50,9 @@
 // while a chunk is multiplied: loads are waited for in order, so kernel operands requested after the image rows would
 // wait for those; the other workgroups of the CU fill the gap instead.
 #include "mac_common.h"
+#include "split.h"
 
 namespace znni {
-
-typedef _Float16 half8 __attribute__((ext_vector_type(8)));
-typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
-
-// Division by a number known at launch: a high product, at most one too large, and a correction.
-struct FastDiv {
-    unsigned d, m;
-    void set(unsigned n) { d = n; m = n > 1 ? (unsigned)((1ull << 32) / n) + 1u : 0u; }
-    __device__ __forceinline__ unsigned div(unsigned n) const
-    {
-        if (d == 1) return n;
-        const unsigned q = __umulhi(n, m);
-        return q * d > n ? q - 1 : q;
-    }
-};
 
 struct XdArgs {
     FastDiv d_sub, d_ncb, d_S, d_Ny;
@@ -81,43 +67,6 @@ struct XdArgs {
 };
 
 constexpr int XD_MAX_K = 9;     // taps along x at most: the halo of a staged row
-// The largest finite magnitude that decides a scale sits at 2^XD_TOP.
-constexpr int XD_TOP = 14;
-// Power-of-two exponent that brings values of magnitude m (finite) to 2^XD_TOP; both it and its negative are exponents
-// of normal numbers.
-__device__ __forceinline__ int xd_scale_exp(float m)
-{
-    const int e = (int)((__float_as_uint(m) >> 23) & 255u) - 127;
-    return min(XD_TOP - e, 126);
-}
-__device__ __forceinline__ float xd_pow2(int e) { return __uint_as_float((unsigned)(e + 127) << 23); }
-
-__device__ __forceinline__ void xd_split(float v, float s, _Float16& hi, _Float16& lo)
-{
-    hi = (_Float16)(v * s);
-    lo = (_Float16)fmaf(v, s, -(float)hi);
-}
-
-// Largest magnitude of a thread's values so far and two more: one instruction (fmaxf first quiets each operand).
-__device__ __forceinline__ void xd_max3(float& m, float a, float b)
-{
-    asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(m) : "v"(a), "v"(b));
-}
-// Largest value of a wave (non-negative floats, compared as integers: a NaN counts as the largest).
-__device__ __forceinline__ unsigned xd_wave_max(float m)
-{
-    unsigned v = __float_as_uint(m);
-#define ZNNI_XD_DPP(CTRL, ROWS) v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false))
-    ZNNI_XD_DPP(0x111, 0xf);        // row_shr 1, 2, 4, 8: lane 15 of every row of sixteen holds the row's largest
-    ZNNI_XD_DPP(0x112, 0xf);
-    ZNNI_XD_DPP(0x114, 0xf);
-    ZNNI_XD_DPP(0x118, 0xf);
-    ZNNI_XD_DPP(0x142, 0xa);        // row_bcast 15, 31: lane 63 holds the wave's
-    ZNNI_XD_DPP(0x143, 0xc);
-#undef ZNNI_XD_DPP
-    return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
-}
-
 template <int RT, int CT, int NG>
 constexpr size_t xd_lds_bytes() { return (size_t)16 * (2 * 4 * NG * (64 * CT + 16) + 4 * 128 * RT); }
 // Three workgroups per CU where LDS and registers (168 a lane) allow, two otherwise.
@@ -239,14 +188,14 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT, NG>())) void k_mac_xd(XdArg
         float m = 0.f;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            xd_max3(m, halo[q].x, halo[q].y);
+            max3_abs(m, halo[q].x, halo[q].y);
 #pragma unroll
             for (int gq = 0; gq < NG; ++gq)
 #pragma unroll
-                for (int it = 0; it < CT; ++it) xd_max3(m, raw[gq][it][q].x, raw[gq][it][q].y);
+                for (int it = 0; it < CT; ++it) max3_abs(m, raw[gq][it][q].x, raw[gq][it][q].y);
         }
         auto largest = [&](unsigned (&w)[4]) {
-            const unsigned v = xd_wave_max(m);
+            const unsigned v = wave_max(m);
             if (lane == 0) w[wave] = v;
             __syncthreads();
             return max(max(w[0], w[1]), max(w[2], w[3]));
@@ -256,7 +205,7 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT, NG>())) void k_mac_xd(XdArg
             m = 0.f;
             auto fin = [&](float2 v) {
                 const float ax = fabsf(v.x), ay = fabsf(v.y);
-                xd_max3(m, ax < INFINITY ? ax : 0.f, ay < INFINITY ? ay : 0.f);
+                max3_abs(m, ax < INFINITY ? ax : 0.f, ay < INFINITY ? ay : 0.f);
             };
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
@@ -269,7 +218,7 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT, NG>())) void k_mac_xd(XdArg
             mb = largest(wfin);
             __syncthreads();
         }
-        const int sn = min(sexp, xd_scale_exp(__uint_as_float(mb)));
+        const int sn = min(sexp, split_exp(__uint_as_float(mb)));
         if (sn < sexp && chunk) {                            // a larger chunk: the sums follow its scale
 #pragma unroll
             for (int r = 0; r < RT; ++r)
@@ -282,16 +231,16 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT, NG>())) void k_mac_xd(XdArg
                     }
         }
         sexp = sn;
-        const float sx = xd_pow2(sn);
+        const float sx = pow2f(sn);
         auto put = [&](const float2 (&v)[4], int quad, int x) {
             half8 h, l;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const float s = i0 + 4 * quad + q < f ? sx : 0.f;
                 _Float16 a, b;
-                xd_split(v[q].x, s, a, b);
+                split2(v[q].x, s, a, b);
                 h[2 * q] = a; l[2 * q] = b;
-                xd_split(v[q].y, s, a, b);
+                split2(v[q].y, s, a, b);
                 h[2 * q + 1] = a; l[2 * q + 1] = b;
             }
             Xs[quad * XW + x] = h;
@@ -396,7 +345,7 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT, NG>())) void k_mac_xd(XdArg
 
     // ---- accumulator element e of lane (kk, l16): output xo = ... + 4 kk + e of output image ... + l16.  Rows of Yd are
     // padded to 16 outputs, so a lane always stores its four.
-    const float inv = xd_pow2(-sexp);
+    const float inv = pow2f(-sexp);
 #pragma unroll
     for (int r = 0; r < RT; ++r) {
         const int j = (mblk * RT + r) * 16 + l16;
@@ -441,9 +390,9 @@ __device__ __forceinline__ void xd_store(half8* d, const float2 (&v)[4], float s
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         _Float16 x, y;
-        xd_split(v[q].x, s, x, y);
+        split2(v[q].x, s, x, y);
         h[2 * q] = x; l[2 * q] = y;
-        xd_split(v[q].y, s, x, y);
+        split2(v[q].y, s, x, y);
         h[2 * q + 1] = x; l[2 * q + 1] = y;
     }
     d[0] = h;

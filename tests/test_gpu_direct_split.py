@@ -1,0 +1,76 @@
+"""Direct convolution of narrow layers on fp16 matrix instructions (values split in two halves): edges of its tiles and
+slots, scales, values that are not finite."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1606_05688_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+def _rand(seed, S, f, fo, n, k):
+    r = np.random.default_rng(seed)
+    inp = r.uniform(-1, 1, (S, f) + tuple(n)).astype(np.float32)
+    w = (r.standard_normal((fo, f) + tuple(k)) * (f * k[0] * k[1] * k[2]) ** -0.5).astype(np.float32)
+    b = (r.standard_normal(fo) * np.sqrt(0.1)).astype(np.float32)
+    return inp, w, b
+
+
+def _run(inp, w, b=None, relu=False):
+    d = torch.device("cuda:0")
+    out = B.znni_conv3d_direct(torch.from_numpy(inp).to(d), torch.from_numpy(w).to(d),
+                               torch.from_numpy(b).to(d) if b is not None else None, relu=relu)
+    torch.cuda.synchronize()
+    return out
+
+
+# five to twenty images (part of an octet, whole octets, a part of a second and third), one to five row tiles and two row
+# blocks, output rows below, at and above one, two and many column tiles, z remainders of 1, 2 and 3 behind groups of
+# four, one to sixteen steps of slots, several inputs, kernels flat along each axis, more tiles than workgroups
+CASES = [(1, 5, 1, (4, 5, 16), (2, 2, 2)), (1, 8, 80, (13, 9, 50), (2, 2, 2)), (2, 7, 33, (9, 10, 35), (2, 3, 1)),
+         (1, 6, 12, (12, 11, 21), (3, 3, 3)), (1, 8, 44, (5, 17, 130), (1, 4, 1)), (3, 9, 17, (6, 6, 19), (1, 1, 3)),
+         (1, 16, 16, (10, 33, 34), (2, 2, 2)), (1, 20, 64, (7, 8, 36), (1, 2, 2)), (1, 8, 90, (6, 7, 33), (2, 1, 2)),
+         (1, 5, 5, (3, 3, 3), (3, 3, 3)), (1, 8, 16, (40, 70, 90), (1, 2, 1)), (1, 12, 20, (20, 9, 17), (7, 1, 1)),
+         (5, 8, 49, (2, 3, 66), (1, 1, 1))]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "S%d_f%dx%d_n%s_k%s" % (c[0], c[1], c[2], "x".join(map(str, c[3])), "x".join(map(str, c[4]))))
+def test_tile_and_slot_edges_match_oracle(oracle, case):
+    S, f, fo, n, k = case
+    inp, w, b = _rand(sum(n) + fo, S, f, fo, n, k)
+    for relu, bias in ((False, None), (True, b)):
+        got = _run(inp, w, bias, relu).cpu().numpy().astype(np.float64)
+        exp = oracle.conv3d(inp, w, bias, relu=relu)
+        # 32-bit accuracy: sums of at most 448 products, each off by 2^-23 of itself at most, in sums rounded once per
+        # matrix product
+        assert np.linalg.norm(got - exp) <= 5e-7 * np.linalg.norm(exp)
+        assert np.all(np.abs(got - exp) <= oracle.tolerance(inp, w)[None, :, None, None, None])
+
+
+def test_scales_are_powers_of_two():
+    inp, w, _ = _rand(3, 1, 8, 20, (9, 10, 40), (2, 2, 2))
+    base = _run(inp, w)
+    for ei, ew in ((50, 0), (-70, 0), (0, 40), (0, -60)):
+        assert torch.equal(_run(np.ldexp(inp, ei), np.ldexp(w, ew)), torch.ldexp(base, torch.tensor(ei + ew, device=base.device)))
+    assert not _run(np.zeros_like(inp), w).any() and not _run(inp, np.zeros_like(w)).any()
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), -float("inf")])
+def test_values_that_are_not_finite(oracle, bad):
+    """They reach the outputs whose windows hold them, as fp32 arithmetic has it (an infinity times a finite weight is an
+    infinity), and no others."""
+    inp, w, _ = _rand(4, 1, 8, 20, (9, 10, 40), (2, 2, 2))
+    clean = _run(inp, w)
+    inp[0, 3, 4, 5, 20] = bad
+    got = _run(inp, w)
+    win = (slice(None), slice(None), slice(3, 5), slice(4, 6), slice(19, 21))
+    hit = torch.zeros_like(got, dtype=torch.bool)
+    hit[win] = True
+    assert torch.allclose(got[~hit], clean[~hit], rtol=0, atol=1e-6 * float(clean.abs().max()))
+    if np.isnan(bad):
+        assert torch.isnan(got[win]).all()
+    else:
+        assert torch.isinf(got[win]).all()
+        # window corner (3, 4, 19) meets the value with the first tap of the flipped kernel
+        assert torch.equal(torch.sign(got[0, :, 3, 4, 19]), torch.sign(torch.from_numpy(w[:, 3, 0, 0, 0]).to(got.device)) * np.sign(bad))
