@@ -9,9 +9,11 @@
 //                     multiply-accumulate's matrix-core work, plus a fixed cost for its dozen launches;
 //   direct route:     its matrix-core work over the rate the kernel reaches (lower for windows of fewer than 27
 //                     taps, where staging the image tiles weighs more per product) plus the output write, plus
-//                     two launches.
+//                     two launches; layers that run on split halves (direct_split.hip): the larger of tensors moved
+//                     and products over what that kernel reaches.
 //
 // The model only has to rank the two; it is not used for anything else.
+#include "direct_split.h"
 #include "znni_internal.h"
 
 namespace znni {
@@ -21,10 +23,13 @@ constexpr double kPassBytesPerSecFast = 5.3e12;     // in-register pass kernels
 constexpr double kPassBytesPerSecGeneric = 2.0e12;  // generic LDS pass kernels
 constexpr double kPrepBytesPerSec = 4.5e12;         // kernel preparation (write-bound)
 constexpr double kMacFlopsPerSec = 110e12;          // issued matrix-core flops of the multiply-accumulate (S = 1 form)
+constexpr double kMacSplitFlopsPerSec = 0.7e15;     // ... of the form on split halves (no x transform)
 constexpr double kMacBatchSecPerValue = 2.1e-12;    // batch form: per kernel-spectrum value and 16 inputs
 constexpr double kDirectFlopsPerSec = 80e12;        // direct convolution, windows of 27 taps and more
 constexpr double kDirectFlopsPerSecSmall = 60e12;   // ... of fewer taps
 constexpr double kDirectWriteBytesPerSec = 3.6e12;  // direct convolution, output write
+constexpr double kSplitBytesPerSec = 2.6e12;        // direct convolution on split halves: tensors read and written
+constexpr double kSplitFlopsPerSec = 75e12;         // ... and products of whole octets and steps
 constexpr double kLaunchSec = 3.5e-6;
 
 static double fft_seconds(int S, int f, int fo, const int n[3], const int k[3])
@@ -41,9 +46,20 @@ static double fft_seconds(int S, int f, int fo, const int n[3], const int k[3])
         {(double)S * fo * (c * nox * Ny * zc + c * nox * noy * zc), (int)Ny},
         {(double)S * fo * (c * nox * noy * zc + 4.0 * nox * noy * noz), (int)Nz},
     };
+    const double fp = (f + 3) / 4 * 4, Mp = (fo + 15) / 16 * 16;
+    // x axis not transformed (all layers but batches of small images, see pick_untransformed_x): four passes, and a
+    // multiply-accumulate bound by its split products or by the spectra it reads and writes
+    if (k[0] <= 9 && !(k[0] * S >= 32 && Nx <= 120 && S > 8)) {
+        double t = 7 * kLaunchSec;
+        for (int p : {0, 1, 4, 5})
+            t += pass[p].bytes / (fast_pass_available(pass[p].N) ? kPassBytesPerSecFast : kPassBytesPerSecGeneric);
+        t += c * zc * Ny * k[0] * fp * Mp / kPrepBytesPerSec;
+        const double by = c * zc * Ny * ((double)S * f * n[0] + (double)S * fo * nox + k[0] * fp * Mp);
+        const double fl = 24.0 * k[0] * fp * Mp * S * nox * Ny * zc;
+        return t + (by / kPassBytesPerSecFast > fl / kMacSplitFlopsPerSec ? by / kPassBytesPerSecFast : fl / kMacSplitFlopsPerSec);
+    }
     double t = 12 * kLaunchSec;
     for (auto& p : pass) t += p.bytes / (fast_pass_available(p.N) ? kPassBytesPerSecFast : kPassBytesPerSecGeneric);
-    const double fp = (f + 3) / 4 * 4, Mp = (fo + 15) / 16 * 16;
     t += c * zc * Ny * k[0] * fp * Mp / kPrepBytesPerSec;
     // S = 1 form: three real matrix products per complex one, contraction over (input image, x tap), every
     // column; batch form (taken from k*S = 32 on): cost per kernel-spectrum value, once per 16 inputs
@@ -60,8 +76,25 @@ static double direct_seconds(int S, int f, int fo, const int n[3], const int k[3
     const double taps4 = (k[0] * k[1] * k[2] + 3) / 4 * 4, Mp = (fo + 15) / 16 * 16;
     const double flops = 2.0 * S * f * taps4 * Mp * ovox;
     const double wr = 4.0 * S * fo * ovox;
+    Dims d;
+    d.nx = n[0]; d.ny = n[1]; d.nz = n[2];
+    d.kx = k[0]; d.ky = k[1]; d.kz = k[2];
+    d.nox = n[0] - k[0] + 1; d.noy = n[1] - k[1] + 1; d.noz = n[2] - k[2] + 1;
+    SplitPlan P;
+    if (split_plan(S, f, fo, d, &P)) {
+        const double by = wr + 4.0 * S * f * n[0] * n[1] * n[2];
+        const double fl = 2.0 * S * 32 * P.nsteps * 16.0 * P.RT * P.nmblk * ovox;
+        const double tb = by / kSplitBytesPerSec, tf = fl / kSplitFlopsPerSec;
+        return (tb > tf ? tb : tf) + 2 * kLaunchSec;
+    }
     const double rate = k[0] * k[1] * k[2] >= 27 ? kDirectFlopsPerSec : kDirectFlopsPerSecSmall;
-    return flops / rate + wr / kDirectWriteBytesPerSec + 2 * kLaunchSec;
+    // one workgroup's walk over its contraction, however few of them there are: a step's matrix instructions (sixteen to
+    // twenty tiles of 32 cycles per four waves) and about 450 cycles of operand latency.  60 -> 10 images of 27 x 21 x 32,
+    // 7 x 6 x 3 kernels: 0.56 ms, where its products alone would take 0.03
+    const double rows = Mp / 16 < 5 ? Mp / 16 : 5;
+    const double walk = f * taps4 / 4 * (rows * 4 * 32 + 450) / 2.2e9;
+    const double t = flops / rate + wr / kDirectWriteBytesPerSec;
+    return (t > walk ? t : walk) + 2 * kLaunchSec;
 }
 
 }  // namespace znni
