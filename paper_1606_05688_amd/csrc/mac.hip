@@ -359,7 +359,7 @@ void k_mac_mfma(const float2* __restrict__ Xt, const float2* __restrict__ A, flo
         if (hipGetLastError() != hipSuccess) return ZNNI_ERR_HIP; \
     } while (0)
 
-znni_status launch_kernel_prep(const LayerPlan& L, const float* w, size_t wj_stride, hipStream_t st)
+znni_status launch_kernel_prep_z(const LayerPlan& L, const float* w, size_t wj_stride, hipStream_t st)
 {
     const Dims& d = L.d;
     const int per = d.kx * L.fp * L.Mp;
@@ -368,11 +368,18 @@ znni_status launch_kernel_prep(const LayerPlan& L, const float* w, size_t wj_str
     const int nblk = (per1 + 255) / 256;
     k_kprep_z<<<dim3(nblk + (split ? L.Mp : 0), (d.zc + KPREP_OZ - 1) / KPREP_OZ), dim3(256),
                 sizeof(float2) * KPREP_OZ * (size_t)std::min(d.kz, KPREP_TAPS), st>>>(
-        w, L.A1, L.twz, d, L.f, L.fo, L.fp, L.Mp, wj_stride, nblk, mac_xd_row_scales(L),
+        w, L.A1, L.twz, d, L.f, L.fo, L.fp, L.Mp, wj_stride, nblk, L.rs,
         (float)(1.0 / ((double)d.Ny * d.Nz)));
     ZNNI_LAUNCH_CHECK();
+    return ZNNI_OK;
+}
+
+znni_status launch_kernel_prep_y(const LayerPlan& L, hipStream_t st)
+{
+    const Dims& d = L.d;
+    const int per = d.kx * L.fp * L.Mp;
     if (L.xblock) return launch_kprep_yb(L, st);
-    if (split) return launch_kprep_xd(L, st);
+    if (L.xdirect) return launch_kprep_xd(L, st);
     // the unnormalised transforms' factor: one per transformed axis
     const float scale = (float)(1.0 / ((L.xdirect ? 1.0 : (double)d.Nx) * d.Ny * d.Nz));
     k_kprep_y<<<dim3((per + 255) / 256, (d.Ny + KPREP_OY - 1) / KPREP_OY, d.zc), dim3(256),
@@ -380,6 +387,12 @@ znni_status launch_kernel_prep(const LayerPlan& L, const float* w, size_t wj_str
         L.A1, L.A, L.twy, d.Ny, d.kx, d.ky, L.fp, L.Mp, per, scale);
     ZNNI_LAUNCH_CHECK();
     return ZNNI_OK;
+}
+
+znni_status launch_kernel_prep(const LayerPlan& L, const float* w, size_t wj_stride, hipStream_t st)
+{
+    const znni_status rc = launch_kernel_prep_z(L, w, wj_stride, st);
+    return rc ? rc : launch_kernel_prep_y(L, st);
 }
 
 // Tiling of the matrix-core kernel for a layer shape (host only): rows per wave RTW, row padding Mp, and the

@@ -129,10 +129,8 @@ znni_status launch_mac_batch(const LayerPlan& L, int accumulate, hipStream_t st)
 
 // mac_xd.hip: the form for layers whose x axis is not transformed (1 to 9 taps along x).
 bool mac_xd_available(const LayerPlan& L);
-// ... its second stage of the kernel transform, and the powers of two its kernel transforms carry per output image
-// (Mp factors, then their Mp inverses; behind the stored transforms)
+// ... its second stage of the kernel transform
 znni_status launch_kprep_xd(const LayerPlan& L, hipStream_t st);
-float* mac_xd_row_scales(const LayerPlan& L);
 znni_status launch_mac_xd(const LayerPlan& L, int accumulate, hipStream_t st);
 
 // mac_xb.hip: the same route with the x axis transformed in overlapping blocks of eight (up to 5 taps along x):

@@ -387,8 +387,8 @@ static znni_status launch_kprep_yb_r(const LayerPlan& L, hipStream_t st)
     const int nch = (L.f + 7) / 8;
     const int items = nch * 4 * L.Mp;
     const float scale = (float)(1.0 / ((double)d.Ny * d.Nz * XB));
-    k_kprep_yb_r<K, KY><<<dim3((items + 255) / 256, (d.Ny + KR_OY - 1) / KR_OY, d.zc), dim3(256), 0, st>>>(
-        L.A1, L.A, L.twy, d.Ny, L.fp, L.Mp, nch, scale);
+    k_kprep_yb_r<K, KY><<<dim3((items + 255) / 256, (d.Ny + KR_OY - 1) / KR_OY, L.ozn), dim3(256), 0, st>>>(
+        L.A1 + (size_t)L.oz0 * d.ky * d.kx * L.fp * L.Mp, L.A, L.twy, d.Ny, L.fp, L.Mp, nch, scale);
     if (hipGetLastError() != hipSuccess) return ZNNI_ERR_HIP;
     return ZNNI_OK;
 }
@@ -408,8 +408,8 @@ static znni_status launch_kprep_yb_k(const LayerPlan& L, hipStream_t st)
     const int items = nch * 4 * L.Mp;
     const float scale = (float)(1.0 / ((double)d.Ny * d.Nz * XB));
     const int taps = d.ky < KPREP_TAPS_XB ? d.ky : KPREP_TAPS_XB;
-    k_kprep_yb<K><<<dim3((items + 255) / 256, (d.Ny + KB_OY - 1) / KB_OY, d.zc), dim3(256),
-                    sizeof(float2) * KB_OY * (size_t)taps, st>>>(L.A1, L.A, L.twy, d.Ny, d.ky, L.fp, L.Mp, nch, scale);
+    k_kprep_yb<K><<<dim3((items + 255) / 256, (d.Ny + KB_OY - 1) / KB_OY, L.ozn), dim3(256),
+                    sizeof(float2) * KB_OY * (size_t)taps, st>>>(L.A1 + (size_t)L.oz0 * d.ky * d.kx * L.fp * L.Mp, L.A, L.twy, d.Ny, d.ky, L.fp, L.Mp, nch, scale);
     if (hipGetLastError() != hipSuccess) return ZNNI_ERR_HIP;
     return ZNNI_OK;
 }
@@ -429,7 +429,7 @@ static znni_status launch_xb(const LayerPlan& L, int accumulate, int m_base, int
 {
     const Dims& d = L.d;
     XbArgs g;
-    g.X2 = L.buf1; g.Ah = L.A; g.Yd = L.Yt;
+    g.Ah = L.A;
     g.ximg = (size_t)d.x2i * d.ldx; g.xpen = (size_t)d.x2o * d.ldx;
     g.yimg = (size_t)d.ydi * d.ldxo; g.ypen = (size_t)d.ydo * d.ldxo;
     g.S = L.S; g.f = L.f; g.fo = L.fo; g.Mp = L.Mp; g.nx = d.nx; g.nox = d.nox; g.ldx = d.ldx; g.ldxo = d.ldxo;
@@ -443,7 +443,8 @@ static znni_status launch_xb(const LayerPlan& L, int accumulate, int m_base, int
     g.blk1 = g.n2 * 32;
     g.nmblk = nmblk;
     g.m_base = m_base;
-    g.npencils = d.zc * d.Ny;
+    g.npencils = L.ozn * d.Ny;
+    g.X2 = L.buf1 + (size_t)L.oz0 * g.xpen; g.Yd = L.Yt + (size_t)L.oz0 * g.ypen;
     g.accumulate = accumulate;
     const int per_pencil = (g.n2 + g.n1) * g.nmblk;
     const long long blocks = (long long)((g.npencils + 7) / 8) * per_pencil * 8;

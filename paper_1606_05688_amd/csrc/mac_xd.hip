@@ -460,11 +460,6 @@ __global__ __launch_bounds__(256) void k_kprep_xd(const float2* __restrict__ A1,
     }
 }
 
-float* mac_xd_row_scales(const LayerPlan& L)
-{
-    return reinterpret_cast<float*>(L.A + (size_t)L.d.zc * L.d.Ny * L.d.kx * L.fp * L.Mp);
-}
-
 template <int KY>
 static znni_status launch_kprep_xd_k(const LayerPlan& L, hipStream_t st)
 {
@@ -473,9 +468,9 @@ static znni_status launch_kprep_xd_k(const LayerPlan& L, hipStream_t st)
     const float scale = (float)(1.0 / ((double)d.Ny * d.Nz));
     const int nb = (items + 255) / 256;
     int noy = KX_OY;
-    while (noy > 4 && (long long)nb * ((d.Ny + noy - 1) / noy) * d.zc < 1024) noy >>= 1;
-    k_kprep_xd<KY><<<dim3(nb, (d.Ny + noy - 1) / noy, d.zc), dim3(256), 0, st>>>(
-        L.A1, reinterpret_cast<half8*>(L.A), L.twy, mac_xd_row_scales(L), d.Ny, d.ky, d.kx, L.fp, L.Mp, scale, noy);
+    while (noy > 4 && (long long)nb * ((d.Ny + noy - 1) / noy) * L.ozn < 1024) noy >>= 1;
+    k_kprep_xd<KY><<<dim3(nb, (d.Ny + noy - 1) / noy, L.ozn), dim3(256), 0, st>>>(
+        L.A1 + (size_t)L.oz0 * d.ky * d.kx * L.fp * L.Mp, reinterpret_cast<half8*>(L.A), L.twy, L.rs, d.Ny, d.ky, d.kx, L.fp, L.Mp, scale, noy);
     if (hipGetLastError() != hipSuccess) return ZNNI_ERR_HIP;
     return ZNNI_OK;
 }
@@ -510,13 +505,14 @@ static znni_status launch_xd(const LayerPlan& L, int ncb, int accumulate, hipStr
 {
     const Dims& d = L.d;
     XdArgs g;
-    g.X2 = L.buf1; g.A = reinterpret_cast<const half8*>(L.A); g.rinv = mac_xd_row_scales(L) + L.Mp; g.Yd = L.Yt;
+    g.A = reinterpret_cast<const half8*>(L.A); g.rinv = L.rs + L.Mp;
     g.ximg = (size_t)d.x2i * d.ldx; g.xpen = (size_t)d.x2o * d.ldx;
     g.yimg = (size_t)d.ydi * d.ldxo; g.ypen = (size_t)d.ydo * d.ldxo;
     g.S = L.S; g.f = L.f; g.fo = L.fo; g.Mp = L.Mp; g.K = d.kx;
     g.nx = d.nx; g.nox = d.nox; g.ldx = d.ldx; g.ldxo = d.ldxo; g.Ny = d.Ny;
     g.d_sub.set((unsigned)(ncb * L.S * L.mac_nmblk)); g.d_ncb.set((unsigned)ncb); g.d_S.set((unsigned)L.S); g.d_Ny.set((unsigned)d.Ny);
-    g.ncb = ncb; g.nmblk = L.mac_nmblk; g.npencils = d.zc * d.Ny; g.accumulate = accumulate;
+    g.ncb = ncb; g.nmblk = L.mac_nmblk; g.npencils = L.ozn * d.Ny; g.accumulate = accumulate;
+    g.X2 = L.buf1 + (size_t)L.oz0 * g.xpen; g.Yd = L.Yt + (size_t)L.oz0 * g.ypen;
     const long long blocks = (long long)((g.npencils + 7) / 8) * ncb * L.S * g.nmblk * 8;
     if (blocks > 0x7fffffffll) return ZNNI_ERR_SHAPE;
     constexpr int NG = xd_groups<RT>();

@@ -53,6 +53,10 @@ struct LayerPlan {
     float2* twz;  // [Nz]
     float2* A1;   // [zc][ky(b)][kx(a)][fp][Mp]      kernel transform after the z stage
     float2* A;    // [zc][Ny][fp/4][kx][4][Mp]       after the z and y stages, scaled by 1/(Nx Ny Nz)
+    float* rs;    // [2][Mp] scales of the kernel transforms stored as split halves (mac_xd.hip)
+    // Rows oz0 .. oz0 + ozn - 1 of the halved axis that the second stage of the kernel transform and the
+    // multiply-accumulate work on (x axis not transformed; A then holds those rows only).  A whole layer: 0, zc.
+    int oz0, ozn;
     float2* buf0;
     float2* buf1;
     float2* Yt;   // accumulated output spectra: buf1 itself for a whole-layer call (buf0 where the x axis is not
@@ -74,6 +78,8 @@ znni_status launch_twiddles(const LayerPlan& L, hipStream_t st);
 // w points at kernel (j0, i0) of the bank; wj_stride = floats between the kernels of consecutive output images
 // (f_total * kx*ky*kz), so a sub-bank of a larger bank can be transformed in place.
 znni_status launch_kernel_prep(const LayerPlan& L, const float* w, size_t wj_stride, hipStream_t st);
+znni_status launch_kernel_prep_z(const LayerPlan& L, const float* w, size_t wj_stride, hipStream_t st);     // to A1
+znni_status launch_kernel_prep_y(const LayerPlan& L, hipStream_t st);                                       // A1 to A
 znni_status launch_fwd_z(const LayerPlan& L, const float* in, hipStream_t st);
 znni_status launch_fwd_y(const LayerPlan& L, hipStream_t st);
 znni_status launch_fwd_x(const LayerPlan& L, hipStream_t st);
