@@ -64,17 +64,14 @@ static bool pick_untransformed_x(const LayerPlan& L, unsigned flags)
 }
 
 // ... and whether it applies the kernel's taps along x through length-8 transforms of overlapping blocks
-// (mac_xb.hip) rather than as shifted reads: few inputs per batch and 4 or 5 taps, for images small enough for the
-// fused z+y kernels only with five taps and at least 24 blocks along x.  There its sums are a fifth as long and its
-// results the closer ones (48 -> 48 images of 320^3, 5^3 kernels: 2.6e-7 off against 2.9e-7).
+// (mac_xb.hip) rather than as shifted reads: only where the call asks for that form.  Measured, shifted reads on split
+// halves against blocks on fp32, whole layer: 48 -> 48 images of 320^3, 5^3 kernels 17.0 against 17.2 ms; 48 -> 48 of 160^3,
+// 5^3 2.21 against 2.53; 80 -> 80 of 200^3, 5^3 9.3 against 10.4; 80 -> 80 of 100^3, 5^3 1.6 against 1.7; and the closer
+// results (mac_xd.hip).
 static bool pick_xblock(const LayerPlan& L, unsigned flags)
 {
     if (L.generic_passes || !mac_xb_available(L) || !fast_pass_available(L.d.Ny)) return false;
-    if (flags & ZNNI_MAC_XBLOCK) return true;
-    if (flags & (ZNNI_MAC_REFERENCE | ZNNI_MAC_SINGLE | ZNNI_MAC_BATCH | ZNNI_MAC_XDIRECT)) return false;
-    if (mac_batch_preferred(L)) return false;
-    const bool fused = fused_fwd_zy_available(L) && fused_inv_yz_available(L);
-    return !fused || (L.d.kx == 5 && L.d.nox >= 96);
+    return (flags & ZNNI_MAC_XBLOCK) != 0;
 }
 
 static bool pick_xdirect(const LayerPlan& L, unsigned flags)

@@ -70,11 +70,11 @@ constexpr int XD_MAX_K = 9;     // taps along x at most: the halo of a staged ro
 template <int RT, int CT, int NG>
 constexpr size_t xd_lds_bytes() { return (size_t)16 * (2 * 4 * NG * (64 * CT + 16) + 4 * 128 * RT); }
 // Three workgroups per CU where LDS and registers (168 a lane) allow, two otherwise.
-template <int RT, int CT, int NG>
-constexpr int xd_blocks() { return xd_lds_bytes<RT, CT, NG>() <= 53 * 1024 && RT * CT <= 6 ? 3 : 2; }
+template <int RT, int CT, int NG, bool SUM>
+constexpr int xd_blocks() { return xd_lds_bytes<RT, CT, NG>() <= 53 * 1024 && RT * CT <= (SUM ? 5 : 6) ? 3 : 2; }
 
-template <int RT, int CT, int NG>
-__global__ __launch_bounds__(256, (xd_blocks<RT, CT, NG>())) void k_mac_xd(XdArgs g)
+template <int RT, int CT, int NG, bool SUM>
+__global__ __launch_bounds__(256, (xd_blocks<RT, CT, NG, SUM>())) void k_mac_xd(XdArgs g)
 {
     // staged outputs with their halo, image quads of a chunk (rows of XW units start on the same bank: the sixteen-lane
     // groups of a 16-byte LDS read then share no bank in any phase)
@@ -289,7 +289,11 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT, NG>())) void k_mac_xd(XdArg
             for (int e = 0; e < 4; ++e) o[e] = __builtin_amdgcn_alignbit(v[e], v[e], 16);
             return __builtin_bit_cast(half8, o);
         };
-#define ZNNI_XD_MFMA(D, X, A) D = __builtin_amdgcn_mfma_f32_16x16x32_f16(X, A, D, 0, 0, 0)
+        // SUM: a step's three partial products are summed from zero, the small ones first, and added to the running sums by
+        // vector instructions.  The matrix instruction rounds its running sum twice as coarsely as an addition does: over
+        // 45 of them in a row (48 images, five taps) that is 2.1e-7 of the result, 0.6e-7 this way, for 8 % more time.
+        const floatx4 zero = floatx4{0.f, 0.f, 0.f, 0.f};
+#define ZNNI_XD_MFMA(D, X, A, C) D = __builtin_amdgcn_mfma_f32_16x16x32_f16(X, A, C, 0, 0, 0)
         if constexpr (CT <= RT) {                            // the two forms of an operand from the side with fewer tiles
             half8 hr[CT], hi[CT], lr[CT], li[CT];
 #pragma unroll
@@ -297,33 +301,43 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT, NG>())) void k_mac_xd(XdArg
 #pragma unroll
             for (int r = 0; r < RT; ++r) {
                 const half8 ah = as[r * 32], al = as[r * 32 + 16];
+                floatx4 tr[CT], ti[CT];
 #pragma unroll
-                for (int c = 0; c < CT; ++c) { ZNNI_XD_MFMA(re[r][c], lr[c], ah); ZNNI_XD_MFMA(im[r][c], li[c], ah); }
+                for (int c = 0; c < CT; ++c) { tr[c] = SUM ? zero : re[r][c]; ti[c] = SUM ? zero : im[r][c]; }
 #pragma unroll
-                for (int c = 0; c < CT; ++c) { ZNNI_XD_MFMA(re[r][c], hr[c], al); ZNNI_XD_MFMA(im[r][c], hi[c], al); }
+                for (int c = 0; c < CT; ++c) { ZNNI_XD_MFMA(tr[c], lr[c], ah, tr[c]); ZNNI_XD_MFMA(ti[c], li[c], ah, ti[c]); }
 #pragma unroll
-                for (int c = 0; c < CT; ++c) { ZNNI_XD_MFMA(re[r][c], hr[c], ah); ZNNI_XD_MFMA(im[r][c], hi[c], ah); }
+                for (int c = 0; c < CT; ++c) { ZNNI_XD_MFMA(tr[c], hr[c], al, tr[c]); ZNNI_XD_MFMA(ti[c], hi[c], al, ti[c]); }
+#pragma unroll
+                for (int c = 0; c < CT; ++c) { ZNNI_XD_MFMA(tr[c], hr[c], ah, tr[c]); ZNNI_XD_MFMA(ti[c], hi[c], ah, ti[c]); }
+#pragma unroll
+                for (int c = 0; c < CT; ++c) { re[r][c] = SUM ? re[r][c] + tr[c] : tr[c]; im[r][c] = SUM ? im[r][c] + ti[c] : ti[c]; }
             }
         } else {
 #pragma unroll
             for (int r = 0; r < RT; ++r) {
                 const uintx4 ah = __builtin_bit_cast(uintx4, as[r * 32]), al = __builtin_bit_cast(uintx4, as[r * 32 + 16]);
                 const half8 hr = neg(ah), hi = swp(ah), lr = neg(al), li = swp(al);
+                floatx4 tr[CT], ti[CT];
+#pragma unroll
+                for (int c = 0; c < CT; ++c) { tr[c] = SUM ? zero : re[r][c]; ti[c] = SUM ? zero : im[r][c]; }
 #pragma unroll
                 for (int c = 0; c < CT; ++c) {
-                    ZNNI_XD_MFMA(re[r][c], __builtin_bit_cast(half8, xl[c]), hr);
-                    ZNNI_XD_MFMA(im[r][c], __builtin_bit_cast(half8, xl[c]), hi);
+                    ZNNI_XD_MFMA(tr[c], __builtin_bit_cast(half8, xl[c]), hr, tr[c]);
+                    ZNNI_XD_MFMA(ti[c], __builtin_bit_cast(half8, xl[c]), hi, ti[c]);
                 }
 #pragma unroll
                 for (int c = 0; c < CT; ++c) {
-                    ZNNI_XD_MFMA(re[r][c], __builtin_bit_cast(half8, xh[c]), lr);
-                    ZNNI_XD_MFMA(im[r][c], __builtin_bit_cast(half8, xh[c]), li);
+                    ZNNI_XD_MFMA(tr[c], __builtin_bit_cast(half8, xh[c]), lr, tr[c]);
+                    ZNNI_XD_MFMA(ti[c], __builtin_bit_cast(half8, xh[c]), li, ti[c]);
                 }
 #pragma unroll
                 for (int c = 0; c < CT; ++c) {
-                    ZNNI_XD_MFMA(re[r][c], __builtin_bit_cast(half8, xh[c]), hr);
-                    ZNNI_XD_MFMA(im[r][c], __builtin_bit_cast(half8, xh[c]), hi);
+                    ZNNI_XD_MFMA(tr[c], __builtin_bit_cast(half8, xh[c]), hr, tr[c]);
+                    ZNNI_XD_MFMA(ti[c], __builtin_bit_cast(half8, xh[c]), hi, ti[c]);
                 }
+#pragma unroll
+                for (int c = 0; c < CT; ++c) { re[r][c] = SUM ? re[r][c] + tr[c] : tr[c]; im[r][c] = SUM ? im[r][c] + ti[c] : ti[c]; }
             }
         }
 #undef ZNNI_XD_MFMA
@@ -496,11 +510,11 @@ znni_status launch_kprep_xd(const LayerPlan& L, hipStream_t st)
 // chunk in groups of sixteen.  Measured, multiply-accumulate alone: one group for up to four row tiles (40 -> 40 of 128^3,
 // 3^3 kernels 0.223 ms, two groups 0.269; 32 -> 32 of 200^3, 5^3 0.667 against 1.04), two for five (80 -> 80 of 128^3, 7^3
 // 1.18 ms, one group 1.25, three 1.55; 80 -> 80 of 200^3, 5^3 3.76, 3.84, 5.07).
-template <int RT> constexpr int xd_max_ct() { return RT >= 5 ? 2 : (RT >= 3 ? 3 : 4); }
+template <int RT, bool SUM> constexpr int xd_max_ct() { return RT >= 5 || (SUM && RT == 4) ? 2 : (RT >= 3 ? 3 : 4); }
 template <int RT> constexpr int xd_groups() { return RT >= 5 ? 2 : 1; }
 bool mac_xd_available(const LayerPlan& L) { return L.d.kx >= 1 && L.d.kx <= XD_MAX_K; }
 
-template <int RT, int CT>
+template <int RT, int CT, bool SUM>
 static znni_status launch_xd(const LayerPlan& L, int ncb, int accumulate, hipStream_t st)
 {
     const Dims& d = L.d;
@@ -517,29 +531,38 @@ static znni_status launch_xd(const LayerPlan& L, int ncb, int accumulate, hipStr
     if (blocks > 0x7fffffffll) return ZNNI_ERR_SHAPE;
     constexpr int NG = xd_groups<RT>();
     constexpr size_t lds = xd_lds_bytes<RT, CT, NG>();
-    if (lds > 48 * 1024 && hipFuncSetAttribute((const void*)k_mac_xd<RT, CT, NG>,
+    if (lds > 48 * 1024 && hipFuncSetAttribute((const void*)k_mac_xd<RT, CT, NG, SUM>,
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
         return ZNNI_ERR_HIP;
-    k_mac_xd<RT, CT, NG><<<dim3((unsigned)blocks), dim3(256), lds, st>>>(g);
+    k_mac_xd<RT, CT, NG, SUM><<<dim3((unsigned)blocks), dim3(256), lds, st>>>(g);
     if (hipGetLastError() != hipSuccess) return ZNNI_ERR_HIP;
     return ZNNI_OK;
 }
 
 // Columns: as few workgroups per row as the widest tile allows (its sums, RT * CT * 8 registers per lane, leave room for
 // two waves per SIMD), then the narrowest tile that still covers the row with that many.
-template <int RT>
-static znni_status launch_xd_cols(const LayerPlan& L, int accumulate, hipStream_t st)
+template <int RT, bool SUM>
+static znni_status launch_xd_cols_s(const LayerPlan& L, int accumulate, hipStream_t st)
 {
-    constexpr int MAXCT = xd_max_ct<RT>();
+    constexpr int MAXCT = xd_max_ct<RT, SUM>();
     const int t64 = (L.d.nox + 63) / 64;                     // 64 outputs: one column tile per wave
     const int ncb = (t64 + MAXCT - 1) / MAXCT, CT = (t64 + ncb - 1) / ncb;
     switch (CT) {
-        case 1: return launch_xd<RT, 1>(L, ncb, accumulate, st);
-        case 2: if constexpr (MAXCT >= 2) return launch_xd<RT, 2>(L, ncb, accumulate, st); break;
-        case 3: if constexpr (MAXCT >= 3) return launch_xd<RT, 3>(L, ncb, accumulate, st); break;
-        case 4: if constexpr (MAXCT >= 4) return launch_xd<RT, 4>(L, ncb, accumulate, st); break;
+        case 1: return launch_xd<RT, 1, SUM>(L, ncb, accumulate, st);
+        case 2: if constexpr (MAXCT >= 2) return launch_xd<RT, 2, SUM>(L, ncb, accumulate, st); break;
+        case 3: if constexpr (MAXCT >= 3) return launch_xd<RT, 3, SUM>(L, ncb, accumulate, st); break;
+        case 4: if constexpr (MAXCT >= 4) return launch_xd<RT, 4, SUM>(L, ncb, accumulate, st); break;
     }
     return ZNNI_ERR_SHAPE;
+}
+
+// Stepwise sums for four and five taps and at least 16 images: there the block form of mac_xb.hip, with sums a fifth as
+// long, would be the closer one otherwise (48 -> 48 images of 320^2, 5^3 kernels: 3.3e-7 off without them, 2.45e-7 with
+// them, 3.0e-7 in blocks).  Everywhere else the fp32 products this kernel replaced were further off than it is.
+template <int RT>
+static znni_status launch_xd_cols(const LayerPlan& L, int accumulate, hipStream_t st)
+{
+    return mac_xb_available(L) ? launch_xd_cols_s<RT, true>(L, accumulate, st) : launch_xd_cols_s<RT, false>(L, accumulate, st);
 }
 
 znni_status launch_mac_xd(const LayerPlan& L, int accumulate, hipStream_t st)
