@@ -59,8 +59,14 @@ static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 static bool pick_untransformed_x(const LayerPlan& L, unsigned flags)
 {
     if (flags & (ZNNI_MAC_REFERENCE | ZNNI_MAC_SINGLE | ZNNI_MAC_BATCH)) return false;
-    if (!(fused_fwd_zy_available(L) && fused_inv_yz_available(L))) return true;
-    return L.S <= 8 && (!mac_batch_preferred(L) || L.d.Ny > 64);
+    const bool batch = mac_batch_preferred(L);
+    // (rows of the output shorter than half a column block leave most of it idle: 15 x 93 -> 44 of 27 x 21 x 30, 7 x 5 x 2
+    // kernels 0.44 against 0.38 ms)
+    if (!(fused_fwd_zy_available(L) && fused_inv_yz_available(L))) return !batch || L.d.nox >= 32;
+    if (batch) return L.S <= 8 && L.d.Ny > 64;
+    // few pencils and long sums: nothing hides a workgroup's walk (88 -> 14 of 23^3, 6^3 kernels 72 against 60 us)
+    if (L.d.zc * L.d.Ny < 512 && L.f * L.d.kx >= 384) return false;
+    return L.S < 8;                      // (8 x 20 -> 34 of 51^3, 3^3 kernels 0.40 against 0.37 ms)
 }
 
 // ... and whether it applies the kernel's taps along x through length-8 transforms of overlapping blocks

@@ -558,11 +558,11 @@ static znni_status launch_xd_cols_s(const LayerPlan& L, int accumulate, hipStrea
 
 // Stepwise sums for four and five taps and at least 16 images: there the block form of mac_xb.hip, with sums a fifth as
 // long, would be the closer one otherwise (48 -> 48 images of 320^2, 5^3 kernels: 3.3e-7 off without them, 2.45e-7 with
-// them, 3.0e-7 in blocks).  Everywhere else the fp32 products this kernel replaced were further off than it is.
+// them, 3.0e-7 in blocks), and where a batch would otherwise share generated spectra (mac_batch.hip).  Everywhere else the fp32 products this kernel replaced were further off than it is.
 template <int RT>
 static znni_status launch_xd_cols(const LayerPlan& L, int accumulate, hipStream_t st)
 {
-    return mac_xb_available(L) ? launch_xd_cols_s<RT, true>(L, accumulate, st) : launch_xd_cols_s<RT, false>(L, accumulate, st);
+    return mac_xb_available(L) || mac_batch_preferred(L) ? launch_xd_cols_s<RT, true>(L, accumulate, st) : launch_xd_cols_s<RT, false>(L, accumulate, st);
 }
 
 znni_status launch_mac_xd(const LayerPlan& L, int accumulate, hipStream_t st)
