@@ -18,6 +18,7 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0            # MI355X HBM3E, published
 MFMA_FP32_PEAK_TFLOPS = 157.3    # dense fp32 matrix, published
+MFMA_FP16_PEAK_TFLOPS = 2500.0
 # Plain-VALU fp32 without packed instructions (this build switches them off):
 # 256 CUs x 4 SIMDs x 16 lanes x 2 flop (FMA) x 2.4 GHz.
 VALU_FP32_UNPACKED_TFLOPS = 256 * 4 * 16 * 2 * 2.4e9 / 1e12
@@ -227,8 +228,12 @@ def main():
     copy_gbs = 2 * src.numel() * 4 / (copy_ms * 1e-3) / 1e9
     del src, dst
 
-    # the work of the kernels that actually ran (fused kernels and skipped stages priced as such)
+    # the work of the kernels that actually ran (fused kernels and skipped stages priced as such); the form without x
+    # transform runs on fp16 matrix instructions with split values, three partial products per product
     nbytes, nflops = B.znni_conv3d_fft_stage_work(S, f, fo, n, k, relu=layer.relu, mac_reference=route)
+    split = nflops["mac"] == B.znni_conv3d_fft_stage_work(S, f, fo, n, k, mac_reference="xdirect")[1]["mac"] and \
+        nflops["mac"] != B.znni_conv3d_fft_stage_work(S, f, fo, n, k, mac_reference="single")[1]["mac"]
+    mac_peak = MFMA_FP16_PEAK_TFLOPS / 3 if split else MFMA_FP32_PEAK_TFLOPS
     stages = {}
     for s_ in B.STAGES:
         if nbytes[s_] == 0 and nflops[s_] == 0:
@@ -238,12 +243,12 @@ def main():
              "frac_hbm": nbytes[s_] / t / 1e9 / HBM_PEAK_GBS}
         if nflops[s_]:
             e.update({"GFLOP": nflops[s_] / 1e9, "TFLOP/s": nflops[s_] / t / 1e12,
-                      "frac_peak": nflops[s_] / t / 1e12 / MFMA_FP32_PEAK_TFLOPS})
+                      "frac_peak": nflops[s_] / t / 1e12 / mac_peak})
         stages[s_] = e
     dom = max(stages, key=lambda s_: stage_ms[s_])
     t = stage_ms[dom] * 1e-3
     if nflops[dom]:
-        roof = {"kernel": dom, "bound": "mfma", "achieved": nflops[dom] / t / 1e12, "peak": MFMA_FP32_PEAK_TFLOPS,
+        roof = {"kernel": dom, "bound": "mfma", "achieved": nflops[dom] / t / 1e12, "peak": mac_peak,
                 "unit": "TFLOP/s"}
     else:
         roof = {"kernel": dom, "bound": "hbm", "achieved": nbytes[dom] / t / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s"}
@@ -253,11 +258,13 @@ def main():
     roof["avg_launch_ms"] = stage_ms[dom]
     if dom == "mac":
         # `achieved` counts 8 flops per complex multiply-add of the form of the stage that ran (see
-        # znni_conv3d_fft_stage_work_v); each is issued as three real matrix-core products (6 flops), so the matrix
-        # pipes are busy for 3/4 of that rate
-        roof["counting"] = "algorithmic: 8 flops per complex multiply-add; issued_*: the 6 the three-product form issues"
-        roof["issued_TFLOP/s"] = 0.75 * roof["achieved"]
-        roof["issued_frac"] = 0.75 * roof["frac"]
+        # znni_conv3d_fft_stage_work_v).  On fp32 matrix instructions each is issued as three real products (6 flops), so
+        # the matrix pipes are busy for 3/4 of that rate; on split halves as four real products of three partial ones
+        # (24 flops), which the peak above already divides by three
+        issued, form = (3.0, "24 the split form issues (peak: fp16 / 3)") if split else (0.75, "6 the three-product form issues")
+        roof["counting"] = "algorithmic: 8 flops per complex multiply-add; issued_*: the " + form
+        roof["issued_TFLOP/s"] = issued * roof["achieved"]
+        roof["issued_frac"] = roof["frac"] if split else 0.75 * roof["frac"]
         # for comparison, the same stage priced as if the x axis were transformed at full length: the per-bin product
         # plus the kernel-tap sum per bin that stands in for a stored kernel-spectrum bank (the form that ran may
         # do less work than that: these two are rates of an equivalent, not of work done)

@@ -38,7 +38,9 @@
  *   - Work is enqueued on `stream` (a hipStream_t passed as void*; NULL = the default stream) and the call
  *     returns without synchronising, except znni_conv3d_fft_profile, which synchronises the stream.
  *   - Results are deterministic: no floating-point atomics, fixed summation order.
- *   - Tensors are dense, row-major, last index fastest; all arithmetic is fp32.
+ *   - Tensors are dense, row-major, last index fastest.  All values and sums are fp32; two kernels form products
+ *     of fp32 values on fp16 matrix instructions, each value split in two scaled halves (22 bits and a sign), with results
+ *     at least as close to the 64-bit ones as fp32 products give.
  */
 #ifndef ZNNI_H
 #define ZNNI_H
@@ -228,7 +230,9 @@ znni_status znni_conv3d_fft_profile_v(int S, int f, int fo, const int n[3], cons
  * znni_conv3d_fft_sublayers_v: host only.  Writes the division for `budget_bytes` to sub[3] = {S_i, f_i, f'_i}
  *   and the workspace it needs (<= budget_bytes) to *bytes.  ZNNI_ERR_WORKSPACE if even the smallest division
  *   (S_i = f_i = f'_i = 1) does not fit; *bytes then holds what that division needs.
- * znni_conv3d_fft_budget_v: runs the layer with the division chosen for workspace_bytes.  Arguments, ownership,
+ * znni_conv3d_fft_budget_v: runs the layer with the division chosen for workspace_bytes; where the spectra of the whole
+ *   layer fit and only the kernel transforms do not (and x is not transformed), in slabs along the halved axis instead,
+ *   which transforms nothing twice and gives znni_conv3d_fft_v's result bit for bit.  Arguments, ownership,
  *   alignment and status codes as for znni_conv3d_fft_v; ZNNI_ERR_WORKSPACE if no division fits.
  */
 znni_status znni_conv3d_fft_sublayers_v(int S, int f, int fo, const int n[3], const int k[3],
