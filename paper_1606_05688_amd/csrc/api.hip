@@ -80,9 +80,13 @@ static bool pick_xblock(const LayerPlan& L, unsigned flags)
     return (flags & ZNNI_MAC_XBLOCK) != 0;
 }
 
+// Internal flag: the x axis is transformed at full length, the multiply-accumulate form is the library's choice.
+constexpr unsigned ROUTE_FULL_X = 1u << 30;
+
 static bool pick_xdirect(const LayerPlan& L, unsigned flags)
 {
     if (L.xblock) return true;
+    if (flags & ROUTE_FULL_X) return false;
     if (L.generic_passes || !mac_xd_available(L) || !fast_pass_available(L.d.Ny)) return false;
     if (flags & ZNNI_MAC_XDIRECT) return true;
     if (flags & ZNNI_MAC_XBLOCK) return false;
@@ -373,6 +377,21 @@ static znni_status run(const LayerPlan& L, const float* in, const float* w, cons
     return ZNNI_OK;
 }
 
+// Flags that give every block of input images of an output block the same route.  Their products are added up in one
+// set of output spectra, whose layout is the route's; the rules that pick a route look at the number of input images, so
+// the last, smaller block, planned by itself, can come out differently from the others (91 -> 38 images of 18^3, 6^3
+// kernels in blocks of 68).  The full blocks decide; a form of theirs that the last block does not have (blocks of eight
+// along x under 16 images) counts as one that does not exist.
+static unsigned one_route(int S, int f, int fi, int fo, const int n[3], const int k[3], unsigned flags)
+{
+    if (fi >= f || f % fi == 0) return flags;
+    LayerPlan full, rest;
+    if (shape_plan(S, fi, fo, n, k, flags, &full) || shape_plan(S, f % fi, fo, n, k, flags, &rest)) return flags;
+    if (full.xblock != rest.xblock) return (flags & ~(unsigned)ZNNI_MAC_XBLOCK) | ROUTE_FULL_X;
+    if (full.xdirect != rest.xdirect) return flags | (full.xdirect ? (unsigned)ZNNI_MAC_XDIRECT : ROUTE_FULL_X);
+    return flags;
+}
+
 // The layer as the sub-layers of division D, all on one workspace.
 static znni_status run_divided(const Division& D, int S, int f, int fo, const int n[3], const int k[3],
                                const float* in, const float* w, const float* bias, float* out, unsigned flags,
@@ -385,12 +404,13 @@ static znni_status run_divided(const Division& D, int S, int f, int fo, const in
         const int Sc = S - s0 < D.Si ? S - s0 : D.Si;
         for (int j0 = 0; j0 < fo; j0 += D.foi) {
             const int foc = fo - j0 < D.foi ? fo - j0 : D.foi;
+            const unsigned route = one_route(Sc, f, D.fi, foc, n, k, flags);
             LayerPlan L;
             for (int i0 = 0; i0 < f; i0 += D.fi) {
                 const int fc = f - i0 < D.fi ? f - i0 : D.fi;
                 // a block of images is one contiguous tensor only if it spans all images of a tuple or one tuple
                 if (Sc > 1 && (fc != f || foc != fo)) return ZNNI_ERR_SHAPE;
-                ZNNI_DO(shape_plan(Sc, fc, foc, n, k, flags, &L));
+                ZNNI_DO(shape_plan(Sc, fc, foc, n, k, route, &L));
                 for (int q = 0; q < 5; ++q)
                     if (L.sz[q] > D.sz[q]) return ZNNI_ERR_WORKSPACE;
                 place_plan(&L, workspace, D.sz, D.own_yt);
@@ -411,7 +431,7 @@ static znni_status run_divided(const Division& D, int S, int f, int fo, const in
                     ZNNI_DO(launch_fwd_y(L, st));
                     ZNNI_DO(launch_fwd_x(L, st));
                 }
-                ZNNI_DO(launch_mac(L, flags, i0 > 0, st));
+                ZNNI_DO(launch_mac(L, route, i0 > 0, st));
             }
             const float* bsub = bias ? bias + j0 : nullptr;
             float* osub = out + ((size_t)s0 * fo + j0) * ovox;

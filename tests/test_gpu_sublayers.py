@@ -128,3 +128,21 @@ def test_budget_too_small_is_reported_not_run():
     with pytest.raises(B.ZnniError) as e:
         B.znni_conv3d_fft_budget(inp, w, None, workspace=ws)
     assert e.value.status == -4
+
+
+# full blocks of input images on one side of a rule on their number, the last block on the other
+@pytest.mark.parametrize("case", [(91, 38, (18, 18, 18), (6, 6, 6), 0.8, None), (88, 14, (23, 23, 23), (6, 6, 6), 0.8, None),
+                                  (24, 8, (24, 20, 16), (5, 5, 2), 0.8, "xblock")], ids=lambda c: "f%dx%d" % c[:2])
+def test_last_block_takes_the_route_of_the_others(oracle, case):
+    f, fo, n, k, share, form = case
+    budget = int(share * B.znni_conv3d_fft_workspace(1, f, fo, n, k))
+    sub, _ = B.znni_conv3d_fft_sublayers(1, f, fo, n, k, budget)
+    assert sub[1] < f and f % sub[1] > 0
+    inp, w, b = _rand(f, 1, f, fo, n, k)
+    d = torch.device("cuda:0")
+    ti, tw, tb = (torch.from_numpy(t).to(d) for t in (inp, w, b))
+    ws = torch.full((budget,), 0xFF, dtype=torch.uint8, device=d)
+    got = B.znni_conv3d_fft_budget(ti, tw, tb, relu=True, workspace=ws, mac_reference=form or False)
+    torch.cuda.synchronize()
+    tol = oracle.tolerance(inp, w)[None, :, None, None, None]
+    assert np.all(np.abs(got.cpu().numpy().astype(np.float64) - oracle.conv3d(inp, w, b, relu=True)) <= tol)

@@ -1,0 +1,27 @@
+"""Host side of the routes a call takes, by the kernels it would launch (a preloaded recorder stands in for the launches)."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+from paper_1606_05688_amd import binding as B
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def recorder(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("rec") / "launch_recorder.so")
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", so, os.path.join(HERE, "launch_recorder.c")], check=True)
+    return so
+
+
+def test_blocks_of_one_output_block_take_one_route(recorder):
+    """Products of several blocks of input images are added up in one set of spectra: all of them in the same layout."""
+    env = dict(os.environ)
+    env["LD_PRELOAD"] = recorder + (":" + env["LD_PRELOAD"] if env.get("LD_PRELOAD") else "")
+    r = subprocess.run([sys.executable, os.path.join(HERE, "routes_driver.py"), B.lib()._name, recorder, "1500"], env=env,
+                       capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, r.stdout[-1000:] + r.stderr[-3000:]
+    assert "one route each" in r.stdout
