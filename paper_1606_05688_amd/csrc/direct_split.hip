@@ -125,8 +125,8 @@ __global__ __launch_bounds__(SPLIT_NT, 2) void k_direct_split(SplitArgs a)
     for (int c = 0; c < CT; ++c) {
         const unsigned ct = (unsigned)(wave * CT + c), xy = a.d_TZ16.div(ct), x = a.d_TY.div(xy);
         vz[c] = (int)(ct - xy * a.d_TZ16.d) * 16; vx[c] = (int)x; vy[c] = (int)(xy - x * a.d_TY.d);
-        if (vx[c] >= a.TX) { vx[c] = 1 << 20; vy[c] = vz[c] = 0; }            // beyond the tile: nothing to store
-        vox[c] = ((vx[c] < a.TX ? vx[c] : 0) * a.TYI + vy[c]) * a.TZI + vz[c] + l16;
+        if (vx[c] >= a.TX) { vx[c] = -1; vy[c] = vz[c] = 0; }                 // beyond the tile: nothing to store
+        vox[c] = (max(vx[c], 0) * a.TYI + vy[c]) * a.TZI + vz[c] + l16;
     }
     float rj[RT], bj[RT];
 #pragma unroll
@@ -245,7 +245,7 @@ __global__ __launch_bounds__(SPLIT_NT, 2) void k_direct_split(SplitArgs a)
 #pragma unroll
             for (int c = 0; c < CT; ++c) {
                 const int X = x0 + vx[c], Y = y0 + vy[c], Z = z0 + vz[c] + 4 * kk;
-                if (X >= d.nox || Y >= d.noy || Z >= d.noz) continue;
+                if (vx[c] < 0 || X >= d.nox || Y >= d.noy || Z >= d.noz) continue;
                 float v[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) v[e] = acc[r][c][e] * inv * rj[r];

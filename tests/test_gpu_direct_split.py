@@ -74,3 +74,12 @@ def test_values_that_are_not_finite(oracle, bad):
         assert torch.isinf(got[win]).all()
         # window corner (3, 4, 19) meets the value with the first tap of the flipped kernel
         assert torch.equal(torch.sign(got[0, :, 3, 4, 19]), torch.sign(torch.from_numpy(w[:, 3, 0, 0, 0]).to(got.device)) * np.sign(bad))
+
+
+def test_axis_of_more_than_a_million(oracle):
+    """Column tiles beyond a tile's edge store nothing, however long the axis they would land on."""
+    inp, w, b = _rand(8, 1, 8, 8, (1200000, 1, 1), (2, 1, 1))
+    got = _run(inp, w, b).cpu().numpy().astype(np.float64)
+    exp = oracle.conv3d(inp, w, b)
+    assert np.linalg.norm(got - exp) <= 5e-7 * np.linalg.norm(exp)
+    assert np.all(np.abs(got - exp) <= oracle.tolerance(inp, w)[None, :, None, None, None])
