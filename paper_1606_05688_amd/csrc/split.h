@@ -36,24 +36,43 @@ __device__ __forceinline__ void split2(float v, float s, _Float16& hi, _Float16&
     lo = (_Float16)fmaf(v, s, -(float)hi);
 }
 
-// Largest magnitude of a thread's values so far and two more: one instruction (fmaxf first quiets each operand).
+// A value of 2^-17 of the largest still has all its 22 bits; below that a bit goes with every power of two.  Where a value
+// (that is not zero) lies more than 2^-SPLIT_SPAN below the largest of its group, the group is multiplied in fp32.
+constexpr int SPLIT_SPAN = 19;
+
+// Largest magnitude of a thread's values so far and two more: one instruction (fmaxf first quiets each operand; NaNs are
+// passed over).
 __device__ __forceinline__ void max3_abs(float& m, float a, float b)
 {
     asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(m) : "v"(a), "v"(b));
 }
-// Largest value of a wave (non-negative floats, compared as integers: a NaN counts as the largest).
+// Largest (smallest) value of a wave, as unsigned integers (non-negative floats keep their order).
+#define ZNNI_DPP(F, OLD, CTRL, ROWS) v = F(v, (unsigned)__builtin_amdgcn_update_dpp((int)(OLD), (int)v, CTRL, ROWS, 0xf, false))
+// row_shr 1, 2, 4, 8: lane 15 of every row of sixteen holds the row's; row_bcast 15, 31: lane 63 holds the wave's
+#define ZNNI_DPP_ALL(F, OLD)                                                                             \
+    ZNNI_DPP(F, OLD, 0x111, 0xf); ZNNI_DPP(F, OLD, 0x112, 0xf); ZNNI_DPP(F, OLD, 0x114, 0xf);             \
+    ZNNI_DPP(F, OLD, 0x118, 0xf); ZNNI_DPP(F, OLD, 0x142, 0xa); ZNNI_DPP(F, OLD, 0x143, 0xc)
 __device__ __forceinline__ unsigned wave_max(float m)
 {
     unsigned v = __float_as_uint(m);
-#define ZNNI_DPP(CTRL, ROWS) v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false))
-    ZNNI_DPP(0x111, 0xf);        // row_shr 1, 2, 4, 8: lane 15 of every row of sixteen holds the row's largest
-    ZNNI_DPP(0x112, 0xf);
-    ZNNI_DPP(0x114, 0xf);
-    ZNNI_DPP(0x118, 0xf);
-    ZNNI_DPP(0x142, 0xa);        // row_bcast 15, 31: lane 63 holds the wave's
-    ZNNI_DPP(0x143, 0xc);
-#undef ZNNI_DPP
+    ZNNI_DPP_ALL(max, 0u);
     return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+}
+__device__ __forceinline__ unsigned wave_min(unsigned v)
+{
+    ZNNI_DPP_ALL(min, ~0u);
+    return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+}
+#undef ZNNI_DPP_ALL
+#undef ZNNI_DPP
+
+// A magnitude as an integer that orders like it, except that zero is the largest: twice the bits without the sign, less one.
+__device__ __forceinline__ unsigned small_code(float v) { return (__float_as_uint(v) << 1) - 1u; }
+// Whether the smallest such code of a group is out of the range that halves hold next to its largest magnitude (its bits).
+__device__ __forceinline__ bool split_too_wide(unsigned largest, unsigned code)
+{
+    const int e = (int)(largest >> 23) - SPLIT_SPAN;
+    return e > 0 && code < ((unsigned)e << 24) - 1u;
 }
 
 }  // namespace znni

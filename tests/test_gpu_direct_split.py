@@ -83,3 +83,55 @@ def test_axis_of_more_than_a_million(oracle):
     exp = oracle.conv3d(inp, w, b)
     assert np.linalg.norm(got - exp) <= 5e-7 * np.linalg.norm(exp)
     assert np.all(np.abs(got - exp) <= oracle.tolerance(inp, w)[None, :, None, None, None])
+
+
+def _close(oracle, inp, w, rel=2e-6):
+    """Every output to `rel` of the sum of the magnitudes it adds up: what fp32 sums of up to 448 products give (the
+    square root of their number times 2^-24, three standard deviations), however far apart the magnitudes in the layer lie."""
+    got = _run(inp, w).cpu().numpy().astype(np.float64)
+    bad = np.abs(got - oracle.conv3d(inp, w)) > rel * oracle.conv3d(np.abs(inp), np.abs(w)) + 1e-44
+    assert not bad.any(), (int(bad.sum()), bad.size, np.argwhere(bad)[:4].tolist())
+
+
+@pytest.mark.parametrize("big", [1e6, 1e9, 1e12, -float(np.finfo(np.float32).max)])
+def test_a_large_value_leaves_its_neighbours_alone(oracle, big):
+    inp, w, _ = _rand(9, 1, 8, 20, (9, 10, 40), (2, 2, 2))
+    inp[0, 3, 4, 5, 20] = big
+    _close(oracle, inp, w)
+
+
+@pytest.mark.parametrize("shape", [(8, 20, (9, 10, 40), (2, 2, 2)), (11, 70, (8, 9, 35), (2, 1, 3)), (6, 17, (7, 9, 40), (1, 1, 1))])
+def test_magnitudes_far_apart(oracle, shape):
+    """Voxels over 2^80; input images up to 2^36 apart whose kernels make up for it; kernels with far smaller outer taps
+    on images of single points; sparse images."""
+    f, fo, n, k = shape
+    r = np.random.default_rng(10)
+    inp, w, _ = _rand(10, 1, f, fo, n, k)
+    _close(oracle, np.ldexp(inp, r.integers(-40, 40, inp.shape)), w)
+    e = r.integers(-18, 18, f)
+    _close(oracle, np.ldexp(inp, e[:, None, None, None]), np.ldexp(w, -e[:, None, None, None]))
+    points = np.where(r.random(inp.shape) < 0.01, inp, 0).astype(np.float32)
+    _close(oracle, points, w)
+    taps = np.indices(k).sum(0)
+    _close(oracle, points, np.ldexp(w, -15 * taps))
+    _close(oracle, np.maximum(inp, 0), w)
+
+
+def test_scales_whose_product_is_in_range(oracle):
+    """Images and kernels near either end of the exponent range whose products are ordinary numbers."""
+    inp, w, _ = _rand(11, 1, 8, 20, (9, 10, 40), (2, 2, 2))
+    for ei, ew in ((125, -100), (118, -66), (-110, 100), (-100, 60)):
+        _close(oracle, np.ldexp(inp, ei), np.ldexp(w, ew))
+
+
+def test_infinite_kernel_values(oracle):
+    """An infinite kernel value gives an infinity of its product's sign, in its output image only."""
+    inp, w, _ = _rand(12, 1, 8, 20, (9, 10, 40), (2, 2, 2))
+    clean = _run(inp, w)
+    w[7, 2, 0, 1, 1] = float("inf")
+    got = _run(inp, w)
+    assert torch.isinf(got[0, 7]).all()
+    met = torch.from_numpy(inp[0, 2, 1:, :-1, :-1]).to(got.device)           # the voxel that tap meets (kernel flipped)
+    assert torch.equal(torch.sign(got[0, 7]), torch.sign(met))
+    keep = [j for j in range(20) if j != 7]
+    assert torch.allclose(got[:, keep], clean[:, keep], rtol=0, atol=1e-6 * float(clean.abs().max()))
