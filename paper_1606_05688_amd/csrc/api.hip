@@ -332,10 +332,11 @@ static znni_status run(const LayerPlan& L, const float* in, const float* w, cons
     do {                                                                      \
         if (ev && hipEventRecord(ev[s], st) != hipSuccess) return ZNNI_ERR_HIP; \
     } while (0)
-    ZNNI_DO(launch_twiddles(L, st));
+    const size_t bank = (size_t)L.f * L.d.kx * L.d.ky * L.d.kz;
+    ZNNI_DO(launch_twiddles(L, flags & ZNNI_KEEP_KERNELS ? nullptr : w, bank, st));
     ZNNI_MARK(ZNNI_STAGE_KERNEL_PREP);
     // the stored kernel transforms of an earlier call on this workspace may be kept (same w, shape and form)
-    if (!(flags & ZNNI_KEEP_KERNELS)) ZNNI_DO(launch_kernel_prep(L, w, (size_t)L.f * L.d.kx * L.d.ky * L.d.kz, st));
+    if (!(flags & ZNNI_KEEP_KERNELS)) ZNNI_DO(launch_kernel_prep(L, w, bank, st));
     if (L.xdirect) {
         // x axis not transformed: the x stages do nothing and read about zero
         ZNNI_MARK(ZNNI_STAGE_FWD_Z);
@@ -414,8 +415,9 @@ static znni_status run_divided(const Division& D, int S, int f, int fo, const in
                 for (int q = 0; q < 5; ++q)
                     if (L.sz[q] > D.sz[q]) return ZNNI_ERR_WORKSPACE;
                 place_plan(&L, workspace, D.sz, D.own_yt);
-                ZNNI_DO(launch_twiddles(L, st));      // also zeroes the padding behind this chunk's A
-                ZNNI_DO(launch_kernel_prep(L, w + ((size_t)j0 * f + i0) * kvol, (size_t)f * kvol, st));
+                const float* wsub = w + ((size_t)j0 * f + i0) * kvol;
+                ZNNI_DO(launch_twiddles(L, wsub, (size_t)f * kvol, st));      // also zeroes the padding behind this chunk's A
+                ZNNI_DO(launch_kernel_prep(L, wsub, (size_t)f * kvol, st));
                 const float* isub = in + ((size_t)s0 * f + i0) * nvox;
                 if (L.xdirect) {
                     ZNNI_DO(launch_fwd_z(L, isub, st));
@@ -468,7 +470,7 @@ static bool plan_slabs(int S, int f, int fo, const int n[3], const int k[3], uns
                                  : (size_t)d.Ny * d.kx * L->fp * L->Mp * sizeof(float2);
     size_t sz[5] = {L->sz[0], 0, L->sz[2], L->sz[3], 0};       // no Yt of its own: Yd takes turns with X1 in buf0
     place_plan(L, workspace, sz, false);
-    const size_t scales = align_up((size_t)2 * L->Mp * sizeof(float), 256);
+    const size_t scales = align_up(split_scale_floats(*L) * sizeof(float), 256);
     if (budget < L->bytes + scales + 256) return false;
     *rows = (int)((budget - L->bytes - scales - 256) / row < (size_t)d.zc ? (budget - L->bytes - scales - 256) / row : d.zc);
     if ((long long)*rows * d.Ny < SLAB_PENCILS) return false;
@@ -484,8 +486,9 @@ static znni_status run_slabs(LayerPlan L, int rows, const float* in, const float
                              unsigned flags, hipStream_t st)
 {
     znni_status rc;
-    ZNNI_DO(launch_twiddles(L, st));
-    ZNNI_DO(launch_kernel_prep_z(L, w, (size_t)L.f * L.d.kx * L.d.ky * L.d.kz, st));
+    const size_t bank = (size_t)L.f * L.d.kx * L.d.ky * L.d.kz;
+    ZNNI_DO(launch_twiddles(L, w, bank, st));
+    ZNNI_DO(launch_kernel_prep_z(L, w, bank, st));
     ZNNI_DO(launch_fwd_z(L, in, st));
     ZNNI_DO(launch_fwd_y(L, st));
     for (L.oz0 = 0; L.oz0 < L.d.zc; L.oz0 += rows) {

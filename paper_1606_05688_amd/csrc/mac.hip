@@ -50,16 +50,50 @@ __device__ __forceinline__ void kprep_gather(float2* tw2, const float2* __restri
 // for every oz: 3.2 ms for 80 x 80 kernels of 9^3 at length 100.)
 constexpr int KPREP_OZ = 16;
 
-// Power of two for the kernel transforms of output image j on the route that stores them as split halves (mac_xd.hip):
-// no value of a kernel's transform exceeds the sum of its magnitudes, so the factor that brings the largest such sum
-// over the input images (times the transform's own scale) to 2^14 keeps every value in range.  rs[j], and its inverse
-// at rs[Mp + j].  A wave per input image, lanes along its taps.
-__device__ __forceinline__ void kprep_row_scale(const float* __restrict__ w, float* __restrict__ rs, int j, int f,
-                                                int fo, int Mp, int taps, size_t wj_stride, float scale)
+// Powers of two for the kernel transforms on the route that stores them as split halves (mac_xd.hip).
+//
+// Of an input image: where its kernels are far smaller than those of others, its values are likely to be larger (a network
+// that is not normalised), or they would not matter.  Half of the distance, as a power of two, is moved from its kernels to
+// its values; beyond 2^24 all but 2^12, well inside what halves cover by themselves.  (Up to 2^8, nothing: most layers.)
+//
+// Of an output image: no value of a kernel's transform exceeds the sum of its magnitudes, so the factor that brings the
+// largest such sum over the input images (times the transform's own scale) to 2^14 keeps every value in range.  A wave per
+// input image, lanes along its taps.
+__device__ __forceinline__ int kprep_col_exp(float cmax, float most)
+{
+    const int t = (int)(__float_as_uint(cmax) >> 23) - (int)(__float_as_uint(most) >> 23);
+    return cmax == 0.f || t >= -8 ? 0 : (t >= -24 ? t / 2 : max(t + 12, -60));
+}
+__device__ __forceinline__ void kprep_row_scale(const float* __restrict__ w, const SplitScales& S, int parts, int j, int f,
+                                                int fo, int fp, int taps, size_t wj_stride, float scale)
 {
     __shared__ float best[4];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    auto cmax = [&](int i) {
+        float c = S.cmax[i];
+        for (int p = 1; p < parts; ++p) c = fmaxf(c, S.cmax[p * fp + i]);
+        return c;
+    };
     float m = 0.f;
+    for (int i = threadIdx.x; i < f; i += 256) m = fmaxf(m, cmax(i));
+#pragma unroll
+    for (int o = 32; o; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+    if (lane == 0) best[wave] = m;
+    __syncthreads();
+    const float most = fmaxf(fmaxf(best[0], best[1]), fmaxf(best[2], best[3]));
+    __syncthreads();
+    if (j == 0) {
+        int any = 0;
+        for (int i = threadIdx.x; i < fp; i += 256) {
+            const int e = i < f ? kprep_col_exp(cmax(i), most) : 0;
+            S.col[i] = __uint_as_float((unsigned)(127 + e) << 23);
+            S.cinv[i] = __uint_as_float((unsigned)(127 - e) << 23);
+            any |= e;
+        }
+        any = __syncthreads_or(any);
+        if (threadIdx.x == 0) *S.scaled = any;
+    }
+    m = 0.f;
     if (j < fo)
         for (int i = wave; i < f; i += 4) {
             const float* wi = w + (size_t)j * wj_stride + (size_t)i * taps;
@@ -67,7 +101,7 @@ __device__ __forceinline__ void kprep_row_scale(const float* __restrict__ w, flo
             for (int t = lane; t < taps; t += 64) s += fabsf(wi[t]);
 #pragma unroll
             for (int o = 32; o; o >>= 1) s += __shfl_xor(s, o);
-            s *= scale;
+            s = ldexpf(s * scale, -kprep_col_exp(cmax(i), most));
             m = fmaxf(m, s < INFINITY ? s : 0.f);
         }
     if (lane == 0) best[wave] = m;
@@ -75,19 +109,19 @@ __device__ __forceinline__ void kprep_row_scale(const float* __restrict__ w, flo
     if (threadIdx.x == 0) {
         m = fmaxf(fmaxf(best[0], best[1]), fmaxf(best[2], best[3]));
         const int e = max(min(14 - ((int)((__float_as_uint(m) >> 23) & 255u) - 127), 120), -120);
-        rs[j] = m > 0.f ? __uint_as_float((unsigned)(127 + e) << 23) : 1.f;
-        rs[Mp + j] = m > 0.f ? __uint_as_float((unsigned)(127 - e) << 23) : 1.f;
+        S.row[j] = m > 0.f ? __uint_as_float((unsigned)(127 + e) << 23) : 1.f;
+        S.rinv[j] = m > 0.f ? __uint_as_float((unsigned)(127 - e) << 23) : 1.f;
     }
 }
 __global__ __launch_bounds__(256) void k_kprep_z(const float* __restrict__ w, float2* __restrict__ A1,
                                                  const float2* __restrict__ twz, Dims d, int f, int fo, int fp,
-                                                 int Mp, size_t wj_stride, int nblk, float* __restrict__ rs,
+                                                 int Mp, size_t wj_stride, int nblk, SplitScales S, int parts,
                                                  float rs_scale)
 {
     extern __shared__ float2 tw2[];                            // [taps of the chunk][KPREP_OZ]
     if ((int)blockIdx.x >= nblk) {
         // the workgroups behind those of the transform: one output image each, its power of two (kprep_row_scale)
-        if (blockIdx.y == 0) kprep_row_scale(w, rs, blockIdx.x - nblk, f, fo, Mp, d.kx * d.ky * d.kz, wj_stride, rs_scale);
+        if (blockIdx.y == 0) kprep_row_scale(w, S, parts, blockIdx.x - nblk, f, fo, fp, d.kx * d.ky * d.kz, wj_stride, rs_scale);
         return;
     }
     const int N = d.Nz;
@@ -368,7 +402,7 @@ znni_status launch_kernel_prep_z(const LayerPlan& L, const float* w, size_t wj_s
     const int nblk = (per1 + 255) / 256;
     k_kprep_z<<<dim3(nblk + (split ? L.Mp : 0), (d.zc + KPREP_OZ - 1) / KPREP_OZ), dim3(256),
                 sizeof(float2) * KPREP_OZ * (size_t)std::min(d.kz, KPREP_TAPS), st>>>(
-        w, L.A1, L.twz, d, L.f, L.fo, L.fp, L.Mp, wj_stride, nblk, L.rs,
+        w, L.A1, L.twz, d, L.f, L.fo, L.fp, L.Mp, wj_stride, nblk, split_scales(L), (std::max({d.Nx, d.Ny, d.Nz}) + 255) / 256,
         (float)(1.0 / ((double)d.Ny * d.Nz)));
     ZNNI_LAUNCH_CHECK();
     return ZNNI_OK;
@@ -381,7 +415,7 @@ znni_status launch_kernel_prep_y(const LayerPlan& L, hipStream_t st)
     if (L.xblock) return launch_kprep_yb(L, st);
     if (L.xdirect) return launch_kprep_xd(L, st);
     // the unnormalised transforms' factor: one per transformed axis
-    const float scale = (float)(1.0 / ((L.xdirect ? 1.0 : (double)d.Nx) * d.Ny * d.Nz));
+    const float scale = (float)(1.0 / ((double)d.Nx * d.Ny * d.Nz));
     k_kprep_y<<<dim3((per + 255) / 256, (d.Ny + KPREP_OY - 1) / KPREP_OY, d.zc), dim3(256),
                 sizeof(float2) * KPREP_OY * (size_t)std::min(d.ky, KPREP_TAPS), st>>>(
         L.A1, L.A, L.twy, d.Ny, d.kx, d.ky, L.fp, L.Mp, per, scale);

@@ -59,6 +59,8 @@ struct XdArgs {
     const float2* X2;
     const half8* A;             // [pencil][slot][row tile][hi, lo][16 output images], 4 complex images each
     const float* rinv;          // [Mp] inverse of the power of two the kernel transforms of an output image carry
+    const float* col;           // [fp] power of two of an input image's values
+    const int* scaled;          // whether any of those is not one
     float2* Yd;
     size_t ximg, yimg;          // elements between the rows of consecutive images in X2 / Yd
     size_t xpen, ypen;          // elements between the rows of pencils (oz, oy) and (oz + 1, oy)
@@ -73,6 +75,15 @@ constexpr size_t xd_lds_bytes() { return (size_t)16 * (2 * 4 * NG * (64 * CT + 1
 template <int RT, int CT, int NG, bool SUM>
 constexpr int xd_blocks() { return xd_lds_bytes<RT, CT, NG>() <= 53 * 1024 && RT * CT <= (SUM ? 5 : 6) ? 3 : 2; }
 
+// Slot of a pencil's stored kernel transforms -> image quad and tap: the order the contraction walks them in, chunks of four
+// quads, inside a chunk tap by tap, quads fastest.
+__device__ __forceinline__ void xd_slot(int slot, int K, int fq, int& quad, int& a)
+{
+    const int c = slot / (4 * K), s = slot - c * 4 * K, QC = min(4, fq - 4 * c);
+    a = s / QC;
+    quad = 4 * c + s - a * QC;
+}
+
 template <int RT, int CT, int NG, bool SUM>
 __global__ __launch_bounds__(256, (xd_blocks<RT, CT, NG, SUM>())) void k_mac_xd(XdArgs g)
 {
@@ -83,7 +94,7 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT, NG, SUM>())) void k_mac_xd(
     extern __shared__ half8 lds[];
     half8* const Xs = lds;                                   // [hi, lo][NQ][XW]
     half8* const As = lds + 2 * NQ * XW;                     // [two pairs of steps][slot kk][row tile][hi, lo][16]
-    __shared__ unsigned wmax[2][4], wfin[4];
+    __shared__ unsigned wred[2][2][4], wfin[4];              // [turn][largest, smallest][wave]
 
     // (as mac_block, without its divisions: the integer divisions of a workgroup's start cost as much as a matrix step)
     const unsigned xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
@@ -160,6 +171,8 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT, NG, SUM>())) void k_mac_xd(
     const float2* xrow = g.X2 + (size_t)sI * f * g.ximg + (size_t)poz * g.xpen + (size_t)poy * g.ldx;
     int sexp = 126;                                          // exponent of the scale the image values carry
     int chunk = 0;
+    const bool scaled = *g.scaled != 0;
+    bool apart = false;                                      // magnitudes along x too far apart for halves
     // One chunk of image rows to LDS: wave w takes quads w, w + 4, ..., x along the lanes; the halo behind the outputs, one
     // (quad, x) unit per thread.  Values beyond a row are read from its end, images beyond the last from the last: neither
     // reaches a stored output (the images count as zeros).
@@ -185,22 +198,48 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT, NG, SUM>())) void k_mac_xd(
         const int hq = min(t >> 3, NQ - 1), hx = min(col0 + 64 * CT + (t & 7), g.nx - 1);
 #pragma unroll
         for (int q = 0; q < 4; ++q) halo[q] = xrow[(size_t)min(i0 + 4 * hq + q, f - 1) * g.ximg + hx];
+        if (scaled)                                          // the images' powers of two
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+#pragma unroll
+                for (int gq = 0; gq < NG; ++gq) {
+                    const float c = g.col[min(i0 + 16 * gq + 4 * wave + q, f - 1)];
+#pragma unroll
+                    for (int it = 0; it < CT; ++it) { raw[gq][it][q].x *= c; raw[gq][it][q].y *= c; }
+                }
+                const float c = g.col[min(i0 + 4 * hq + q, f - 1)];
+                halo[q].x *= c;
+                halo[q].y *= c;
+            }
+        // largest magnitude, and the code of the smallest: of the images of a thread at one x together, since their products
+        // are added up (an image far below the others, say of rounding errors only, is no reason to leave halves)
         float m = 0.f;
+        unsigned mn;
+        {
+            float u = 0.f;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            max3_abs(m, halo[q].x, halo[q].y);
+            for (int q = 0; q < 4; ++q) max3_abs(u, halo[q].x, halo[q].y);
+            m = u;
+            mn = small_code(u);
 #pragma unroll
-            for (int gq = 0; gq < NG; ++gq)
+            for (int it = 0; it < CT; ++it) {
+                u = 0.f;
 #pragma unroll
-                for (int it = 0; it < CT; ++it) max3_abs(m, raw[gq][it][q].x, raw[gq][it][q].y);
+                for (int gq = 0; gq < NG; ++gq)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) max3_abs(u, raw[gq][it][q].x, raw[gq][it][q].y);
+                m = fmaxf(m, u);
+                mn = min(mn, small_code(u));
+            }
         }
-        auto largest = [&](unsigned (&w)[4]) {
-            const unsigned v = wave_max(m);
-            if (lane == 0) w[wave] = v;
-            __syncthreads();
-            return max(max(w[0], w[1]), max(w[2], w[3]));
-        };
-        unsigned mb = largest(wmax[chunk & 1]);
+        unsigned (&red)[2][4] = wred[chunk & 1];
+        {
+            const unsigned vx = wave_max(m), vn = wave_min(mn);
+            if (lane == 0) { red[0][wave] = vx; red[1][wave] = vn; }
+        }
+        __syncthreads();
+        unsigned mb = max(max(red[0][0], red[0][1]), max(red[0][2], red[0][3]));
+        const unsigned sm = min(min(red[1][0], red[1][1]), min(red[1][2], red[1][3]));
         if (mb >= 0x7f800000u) {                             // infinities or NaNs: the scale is that of the finite values
             m = 0.f;
             auto fin = [&](float2 v) {
@@ -215,9 +254,13 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT, NG, SUM>())) void k_mac_xd(
 #pragma unroll
                     for (int it = 0; it < CT; ++it) fin(raw[gq][it][q]);
             }
-            mb = largest(wfin);
+            const unsigned v = wave_max(m);
+            if (lane == 0) wfin[wave] = v;
+            __syncthreads();
+            mb = max(max(wfin[0], wfin[1]), max(wfin[2], wfin[3]));
             __syncthreads();
         }
+        apart |= split_too_wide(mb, sm);
         const int sn = min(sexp, split_exp(__uint_as_float(mb)));
         if (sn < sexp && chunk) {                            // a larger chunk: the sums follow its scale
 #pragma unroll
@@ -357,6 +400,46 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT, NG, SUM>())) void k_mac_xd(
         if (gs + 1 < nsteps) step(gs + 1, as0 + buf * RT * 256 + RT * 128);
     }
 
+    if (__builtin_amdgcn_readfirstlane(apart)) {
+        // All over again in fp32, from global memory, four slots of one complex image each per pair of matrix instructions
+        // (kernels: their two halves added up).
+        const float sx = pow2f(sexp);
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+#pragma unroll
+            for (int c = 0; c < CT; ++c) { re[r][c] = floatx4{0.f, 0.f, 0.f, 0.f}; im[r][c] = re[r][c]; }
+        for (int gs = 0; gs < nsteps; ++gs) {
+            const int sl = min(4 * gs + kk, nslots - 1);
+            int qd, tap;
+            xd_slot(sl, K, (f + 3) >> 2, qd, tap);
+            const half8* ap = Ab + (size_t)sl * sstride + l16;
+            const float live = 4 * gs + kk < nslots ? sx : 0.f;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float cs = 4 * qd + q < f ? (scaled ? g.col[4 * qd + q] : 1.f) : 0.f;
+                const float2* row = xrow + (size_t)min(4 * qd + q, f - 1) * g.ximg;
+                float2 x[CT];
+#pragma unroll
+                for (int c = 0; c < CT; ++c) {
+                    const float2 v = row[min(col0 + (wave * CT + c) * 16 + l16 + K - 1 - tap, g.nx - 1)];
+                    x[c] = make_float2(v.x * cs * live, v.y * cs * live);
+                }
+#pragma unroll
+                for (int r = 0; r < RT; ++r) {
+                    const half2 ah = reinterpret_cast<const half2*>(ap + r * 32)[q], al = reinterpret_cast<const half2*>(ap + r * 32 + 16)[q];
+                    const float ar = (float)ah[0] + (float)al[0], ai = (float)ah[1] + (float)al[1];
+#pragma unroll
+                    for (int c = 0; c < CT; ++c) {
+                        re[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[c].x, ar, re[r][c], 0, 0, 0);
+                        im[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[c].y, ar, im[r][c], 0, 0, 0);
+                        re[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(-x[c].y, ai, re[r][c], 0, 0, 0);
+                        im[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[c].x, ai, im[r][c], 0, 0, 0);
+                    }
+                }
+            }
+        }
+    }
+
     // ---- accumulator element e of lane (kk, l16): output xo = ... + 4 kk + e of output image ... + l16.  Rows of Yd are
     // padded to 16 outputs, so a lane always stores its four.
     const float inv = pow2f(-sexp);
@@ -364,14 +447,16 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT, NG, SUM>())) void k_mac_xd(
     for (int r = 0; r < RT; ++r) {
         const int j = (mblk * RT + r) * 16 + l16;
         if (j >= g.fo) continue;
+        // the smaller factor first: either alone may be out of range where the result is not
+        const float f0 = fminf(inv, rj[r]), f1 = fmaxf(inv, rj[r]);
         float2* y = g.Yd + (size_t)(sI * g.fo + j) * g.yimg + (size_t)poz * g.ypen + (size_t)poy * g.ldxo;
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
             const int xo = col0 + (wave * CT + c) * 16 + 4 * kk;
             if (xo >= g.nox) continue;
             float4* d = reinterpret_cast<float4*>(y + xo);
-            float4 v0 = make_float4(re[r][c][0] * inv * rj[r], im[r][c][0] * inv * rj[r], re[r][c][1] * inv * rj[r], im[r][c][1] * inv * rj[r]);
-            float4 v1 = make_float4(re[r][c][2] * inv * rj[r], im[r][c][2] * inv * rj[r], re[r][c][3] * inv * rj[r], im[r][c][3] * inv * rj[r]);
+            float4 v0 = make_float4(re[r][c][0] * f0 * f1, im[r][c][0] * f0 * f1, re[r][c][1] * f0 * f1, im[r][c][1] * f0 * f1);
+            float4 v1 = make_float4(re[r][c][2] * f0 * f1, im[r][c][2] * f0 * f1, re[r][c][3] * f0 * f1, im[r][c][3] * f0 * f1);
             if (g.accumulate) {
                 const float4 o0 = d[0], o1 = d[1];
                 v0.x += o0.x; v0.y += o0.y; v0.z += o0.z; v0.w += o0.w;
@@ -392,21 +477,15 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT, NG, SUM>())) void k_mac_xd(
 // bins along y; 16 + 16 bytes per bin leave it, 256 contiguous bytes per sixteen threads.  Bound by writing A.
 // (noy = KX_OY bins, or fewer where that leaves the chip short of workgroups)
 constexpr int KX_OY = 32;
-__device__ __forceinline__ void xd_slot(int slot, int K, int fq, int& quad, int& a)
-{
-    const int c = slot / (4 * K), s = slot - c * 4 * K, QC = min(4, fq - 4 * c);
-    a = s / QC;
-    quad = 4 * c + s - a * QC;
-}
-__device__ __forceinline__ void xd_store(half8* d, const float2 (&v)[4], float s)
+__device__ __forceinline__ void xd_store(half8* d, const float2 (&v)[4])
 {
     half8 h, l;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         _Float16 x, y;
-        split2(v[q].x, s, x, y);
+        split2(v[q].x, 1.f, x, y);
         h[2 * q] = x; l[2 * q] = y;
-        split2(v[q].y, s, x, y);
+        split2(v[q].y, 1.f, x, y);
         h[2 * q + 1] = x; l[2 * q + 1] = y;
     }
     d[0] = h;
@@ -414,8 +493,8 @@ __device__ __forceinline__ void xd_store(half8* d, const float2 (&v)[4], float s
 }
 template <int KY>          // taps along y; 0: any number, A1 read again for every bin
 __global__ __launch_bounds__(256) void k_kprep_xd(const float2* __restrict__ A1, half8* __restrict__ A,
-                                                  const float2* __restrict__ tw, const float* __restrict__ rs, int N,
-                                                  int ky, int K, int fp, int Mp, float scale, int noy)
+                                                  const float2* __restrict__ tw, const float* __restrict__ rs,
+                                                  const float* __restrict__ cinv, int N, int ky, int K, int fp, int Mp, float scale, int noy)
 {
     constexpr int KT = KY ? KY : 1;
     __shared__ float2 tw2[KX_OY][KT];
@@ -436,6 +515,9 @@ __global__ __launch_bounds__(256) void k_kprep_xd(const float2* __restrict__ A1,
     const size_t per = (size_t)K * fp * Mp;
     const float2* a1 = A1 + (size_t)oz * ky * per + ((size_t)a * fp + 4 * quad) * Mp + j;
     const float s = rs[j] * scale;                       // scale is no power of two: folded in before the split
+    float ci[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) ci[q] = cinv[4 * quad + q];
     const int no = min(noy, N - oy0);
     half8* d = A + ((size_t)(oz * N + oy0) * nslots + slot) * 2 * Mp + (j >> 4) * 32 + (j & 15);
     const size_t dstep = (size_t)nslots * 2 * Mp;
@@ -446,7 +528,7 @@ __global__ __launch_bounds__(256) void k_kprep_xd(const float2* __restrict__ A1,
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const float2 x = a1[(size_t)b * per + q * Mp];
-                v[b][q] = make_float2(x.x * s, x.y * s);
+                v[b][q] = make_float2(x.x * s * ci[q], x.y * s * ci[q]);
             }
         for (int o = 0; o < no; ++o, d += dstep) {
             float2 acc[4];
@@ -456,7 +538,7 @@ __global__ __launch_bounds__(256) void k_kprep_xd(const float2* __restrict__ A1,
 #pragma unroll
                 for (int b = 0; b < KT; ++b) acc[q] = cfma(acc[q], v[b][q], tw2[o][b]);
             }
-            xd_store(d, acc, 1.f);
+            xd_store(d, acc);
         }
     } else {
         for (int o = 0; o < no; ++o, d += dstep) {
@@ -469,7 +551,9 @@ __global__ __launch_bounds__(256) void k_kprep_xd(const float2* __restrict__ A1,
 #pragma unroll
                 for (int q = 0; q < 4; ++q) acc[q] = cfma(acc[q], a1[(size_t)b * per + q * Mp], w);
             }
-            xd_store(d, acc, s);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc[q] = make_float2(acc[q].x * s * ci[q], acc[q].y * s * ci[q]);
+            xd_store(d, acc);
         }
     }
 }
@@ -484,7 +568,7 @@ static znni_status launch_kprep_xd_k(const LayerPlan& L, hipStream_t st)
     int noy = KX_OY;
     while (noy > 4 && (long long)nb * ((d.Ny + noy - 1) / noy) * L.ozn < 1024) noy >>= 1;
     k_kprep_xd<KY><<<dim3(nb, (d.Ny + noy - 1) / noy, L.ozn), dim3(256), 0, st>>>(
-        L.A1 + (size_t)L.oz0 * d.ky * d.kx * L.fp * L.Mp, reinterpret_cast<half8*>(L.A), L.twy, L.rs, d.Ny, d.ky, d.kx, L.fp, L.Mp, scale, noy);
+        L.A1 + (size_t)L.oz0 * d.ky * d.kx * L.fp * L.Mp, reinterpret_cast<half8*>(L.A), L.twy, split_scales(L).row, split_scales(L).cinv, d.Ny, d.ky, d.kx, L.fp, L.Mp, scale, noy);
     if (hipGetLastError() != hipSuccess) return ZNNI_ERR_HIP;
     return ZNNI_OK;
 }
@@ -519,7 +603,7 @@ static znni_status launch_xd(const LayerPlan& L, int ncb, int accumulate, hipStr
 {
     const Dims& d = L.d;
     XdArgs g;
-    g.A = reinterpret_cast<const half8*>(L.A); g.rinv = L.rs + L.Mp;
+    g.A = reinterpret_cast<const half8*>(L.A); g.rinv = split_scales(L).rinv; g.col = split_scales(L).col; g.scaled = split_scales(L).scaled;
     g.ximg = (size_t)d.x2i * d.ldx; g.xpen = (size_t)d.x2o * d.ldx;
     g.yimg = (size_t)d.ydi * d.ldxo; g.ypen = (size_t)d.ydo * d.ldxo;
     g.S = L.S; g.f = L.f; g.fo = L.fo; g.Mp = L.Mp; g.K = d.kx;

@@ -26,9 +26,34 @@
 namespace znni {
 
 // The three twiddle tables exp(-2 pi i q / N) of a layer (x, y, z axis) in one launch; blockIdx.y picks the axis.
-// A's zeroed padding behind the last pencil (pad elements at `padp`) is written by the same launch.
-__global__ void k_twiddles(float2* twx, int Nx, float2* twy, int Ny, float2* twz, int Nz, float2* padp, size_t pad)
+// A's zeroed padding behind the last pencil (pad elements at `padp`) is written by the same launch.  So are, from
+// blockIdx.y = 4 on, the largest kernel magnitudes of every input image for the route that splits values in halves
+// (mac_xd.hip): cmax[part][fp], each part over every gridDim.x-th run of 256 values.
+__global__ void k_twiddles(float2* twx, int Nx, float2* twy, int Ny, float2* twz, int Nz, float2* padp, size_t pad,
+                           const float* __restrict__ w, float* cmax, int f, int fo, int fp, int taps, size_t wj_stride)
 {
+    if (blockIdx.y >= 4) {
+        __shared__ float best[4];
+        for (int i = blockIdx.y - 4; i < f; i += gridDim.y - 4) {
+            const float* wi = w + (size_t)i * taps;
+            const unsigned n = (unsigned)fo * taps;          // (below 2^30: the layer call's shape limits)
+            float m = 0.f;
+            for (unsigned e0 = blockIdx.x * 256 + threadIdx.x; e0 < n; e0 += gridDim.x * 1024)
+#pragma unroll
+                for (unsigned u = 0; u < 4; ++u) {           // four loads in flight
+                    const unsigned e = min(e0 + u * gridDim.x * 256, n - 1), j = e / (unsigned)taps;
+                    const float v = fabsf(wi[(size_t)j * wj_stride + (e - j * taps)]);
+                    m = fmaxf(m, v < INFINITY ? v : 0.f);
+                }
+#pragma unroll
+            for (int o = 32; o; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+            if ((threadIdx.x & 63) == 0) best[threadIdx.x >> 6] = m;
+            __syncthreads();
+            if (threadIdx.x == 0) cmax[blockIdx.x * fp + i] = fmaxf(fmaxf(best[0], best[1]), fmaxf(best[2], best[3]));
+            __syncthreads();
+        }
+        return;
+    }
     const size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (blockIdx.y == 3) {
         if (q < pad) padp[q] = make_float2(0.f, 0.f);
@@ -265,7 +290,7 @@ static znni_status allow_lds(const void* fn, size_t bytes)
     return ZNNI_OK;
 }
 
-znni_status launch_twiddles(const LayerPlan& L, hipStream_t st)
+znni_status launch_twiddles(const LayerPlan& L, const float* w, size_t wj_stride, hipStream_t st)
 {
     const Dims& d = L.d;
     // the multiply-accumulate reads a little past A's last pencil (values multiplied by zero at most): that
@@ -277,8 +302,10 @@ znni_status launch_twiddles(const LayerPlan& L, hipStream_t st)
     size_t most = pad > 0 ? pad : 1;
     for (int N : {d.Nx, d.Ny, d.Nz})
         if ((size_t)N > most) most = N;
-    k_twiddles<<<dim3((unsigned)((most + 255) / 256), 4), dim3(256), 0, st>>>(
-        L.twx, d.Nx, L.twy, d.Ny, L.twz, d.Nz, L.A + (size_t)d.zc * d.Ny * per, pad);
+    const unsigned images = w && L.xdirect && !L.xblock ? (unsigned)(L.f < 65531 ? L.f : 65531) : 0;
+    k_twiddles<<<dim3((unsigned)((most + 255) / 256), 4 + images), dim3(256), 0, st>>>(
+        L.twx, d.Nx, L.twy, d.Ny, L.twz, d.Nz, L.A + (size_t)d.zc * d.Ny * per, pad, w, split_scales(L).cmax, L.f, L.fo, L.fp,
+        d.kx * d.ky * d.kz, wj_stride);
     ZNNI_LAUNCH_CHECK();
     return ZNNI_OK;
 }

@@ -53,7 +53,7 @@ struct LayerPlan {
     float2* twz;  // [Nz]
     float2* A1;   // [zc][ky(b)][kx(a)][fp][Mp]      kernel transform after the z stage
     float2* A;    // [zc][Ny][fp/4][kx][4][Mp]       after the z and y stages, scaled by 1/(Nx Ny Nz)
-    float* rs;    // [2][Mp] scales of the kernel transforms stored as split halves (mac_xd.hip)
+    float* rs;    // scales of the kernel transforms stored as split halves (split_scales below, mac_xd.hip)
     // Rows oz0 .. oz0 + ozn - 1 of the halved axis that the second stage of the kernel transform and the
     // multiply-accumulate work on (x axis not transformed; A then holds those rows only).  A whole layer: 0, zc.
     int oz0, ozn;
@@ -74,7 +74,24 @@ znni_status make_plan(int S, int f, int fo, const int n[3], const int k[3], unsi
 
 int lines_per_tile(int N);
 
-znni_status launch_twiddles(const LayerPlan& L, hipStream_t st);
+// The scales behind LayerPlan::rs, powers of two: of the kernel transforms of an output image, with its inverse; of an
+// input image's values, with the inverse that its kernel transforms carry; and, in up to four parts, the largest kernel
+// magnitudes of the input images that the latter come from.
+struct SplitScales {
+    float *row, *rinv;      // [Mp]
+    float *col, *cinv;      // [fp]
+    float* cmax;            // [4][fp]
+    int* scaled;            // [1] whether any of col is not one
+};
+inline SplitScales split_scales(const LayerPlan& L)
+{
+    float* p = L.rs + 2 * (size_t)L.Mp;
+    return SplitScales{L.rs, L.rs + L.Mp, p, p + L.fp, p + 2 * (size_t)L.fp, (int*)(p + 6 * (size_t)L.fp)};
+}
+inline size_t split_scale_floats(const LayerPlan& L) { return 2 * (size_t)L.Mp + 6 * (size_t)L.fp + 1; }
+
+// w: the kernels about to be transformed (as for launch_kernel_prep), NULL where kept transforms are used.
+znni_status launch_twiddles(const LayerPlan& L, const float* w, size_t wj_stride, hipStream_t st);
 // w points at kernel (j0, i0) of the bank; wj_stride = floats between the kernels of consecutive output images
 // (f_total * kx*ky*kz), so a sub-bank of a larger bank can be transformed in place.
 znni_status launch_kernel_prep(const LayerPlan& L, const float* w, size_t wj_stride, hipStream_t st);

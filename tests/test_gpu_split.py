@@ -87,3 +87,58 @@ def test_values_that_are_not_finite_stay_in_their_windows(bad):
     assert not torch.isfinite(got[:, :, hit]).any()
     keep = [x for x in range(67) if not 27 <= x <= 30]
     assert torch.allclose(got[:, :, keep], clean[:, :, keep], rtol=0, atol=1e-6 * float(clean.abs().max()))
+
+
+@pytest.mark.parametrize("shape", [(40, 24, (75, 10, 8), (3, 2, 3)), (18, 80, (70, 12, 8), (7, 3, 2)), (5, 33, (140, 12, 8), (4, 10, 2))])
+@pytest.mark.parametrize("far", [10, 17, 24, 30, 40])
+def test_input_images_of_unequal_magnitude(oracle, shape, far):
+    """Input images up to 2^far apart whose kernels make up for it, as in a network that is not normalised, and images
+    whose kernels are that much smaller without it: every output image to 32-bit accuracy."""
+    f, fo, n, k = shape
+    inp, w = _rand(20, 1, f, fo, n, k)
+    e = np.random.default_rng(21).integers(0, far + 1, f)
+    e[:2] = 0, far
+    for images in (True, False):
+        x = np.ldexp(inp, e[:, None, None, None]) if images else inp
+        v = np.ldexp(w, -e[:, None, None, None])
+        got = _run(x, v).cpu().numpy().astype(np.float64)
+        exp = oracle.conv3d(x, v, None, relu=False)
+        for j in range(fo):
+            assert np.linalg.norm(got[:, j] - exp[:, j]) <= 1e-6 * np.linalg.norm(exp[:, j]), (images, j)
+
+
+@pytest.mark.parametrize("shape", [(18, 20, (70, 10, 8), (4, 2, 3)), (40, 80, (150, 12, 8), (7, 3, 2)), (3, 5, (300, 9, 8), (1, 2, 2)),
+                                   (35, 64, (40, 10, 8), (5, 3, 2))])
+@pytest.mark.parametrize("big", [1e6, 1e9, 1e13])
+def test_a_large_value_stays_near_its_x(oracle, shape, big):
+    """The x axis is not transformed: outputs whose taps do not meet the x of a large value keep 32-bit accuracy."""
+    f, fo, n, k = shape
+    inp, w = _rand(22, 1, f, fo, n, k)
+    inp[0, f // 2, 25, 4, 5] = big
+    got = _run(inp, w).cpu().numpy().astype(np.float64)
+    exp = oracle.conv3d(inp, w, None, relu=False)
+    for x in range(n[0] - k[0] + 1):
+        assert np.linalg.norm(got[:, :, x] - exp[:, :, x]) <= 1e-6 * np.linalg.norm(exp[:, :, x]), x
+
+
+def test_scales_whose_product_is_in_range(oracle):
+    """Images and kernels near either end of the exponent range whose products are ordinary numbers."""
+    inp, w = _rand(23, 1, 20, 20, (70, 10, 8), (3, 2, 3))
+    for ei, ew in ((118, -100), (110, -60), (-100, 100), (-90, 60)):
+        x, v = np.ldexp(inp, ei), np.ldexp(w, ew)
+        got = _run(x, v).cpu().numpy().astype(np.float64)
+        exp = oracle.conv3d(x, v, None, relu=False)
+        assert np.linalg.norm(got - exp) <= 1e-6 * np.linalg.norm(exp), (ei, ew)
+
+
+def test_kept_kernels_keep_the_scales_of_their_input_images(oracle):
+    S, f, fo, n, k = 1, 18, 20, (70, 10, 8), (3, 2, 3)
+    inp, w = _rand(24, S, f, fo, n, k)
+    e = np.arange(f) * 2
+    w = np.ldexp(w, -e[:, None, None, None])
+    d = torch.device("cuda:0")
+    tw, ws = torch.from_numpy(w).to(d), B.alloc_workspace(S, f, fo, n, k)
+    B.znni_conv3d_fft(torch.from_numpy(inp).to(d), tw, None, workspace=ws, mac_reference="xdirect")
+    x = np.ldexp(_rand(25, S, f, fo, n, k)[0], e[:, None, None, None])
+    got = B.znni_conv3d_fft(torch.from_numpy(x).to(d), tw, None, workspace=ws, mac_reference="xdirect", keep_kernels=True)
+    assert torch.equal(got, _run(x, w))
