@@ -48,8 +48,8 @@ static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // Whether a layer runs without transforming its x axis (mac_xd.hip).  A flag that names a multiply-accumulate form
 // decides; otherwise that route is taken, provided the y transform has an in-register kernel (only those read the
-// transposed layout), except for batches of small images: with fused z+y kernels on both sides the fully transformed
-// route has as many passes, and a kernel-spectrum value generated once per bin serves all inputs.
+// transposed layout), except for small images with many inputs or many images: with fused z+y kernels on both sides the
+// fully transformed route has as many passes, and a kernel-spectrum value generated once per bin serves all inputs.
 // Measured, whole layer, untransformed against fully transformed: 80 -> 80 images of 100^3, 5^3 kernels 1.57 against
 // 2.02 ms; 32 -> 32 of 64^3, 7^3 0.137 against 0.171; 8 x 32 -> 32 of 130^3, 5^3 (no fused kernels) 6.2 against 8.9;
 // 32 x 20 -> 20 of 40 x 128 x 100, 3^3 3.39 against 4.06.  With fused kernels and more than 8 inputs: 64 x 80 -> 80 of
@@ -64,9 +64,16 @@ static bool pick_untransformed_x(const LayerPlan& L, unsigned flags)
     // kernels 0.44 against 0.38 ms)
     if (!(fused_fwd_zy_available(L) && fused_inv_yz_available(L))) return !batch || L.d.nox >= 32;
     if (batch) return L.S <= 8 && L.d.Ny > 64;
-    // few pencils and long sums: nothing hides a workgroup's walk (88 -> 14 of 23^3, 6^3 kernels 72 against 60 us)
-    if (L.d.zc * L.d.Ny < 512 && L.f * L.d.kx >= 384) return false;
-    return L.S < 8;                      // (8 x 20 -> 34 of 51^3, 3^3 kernels 0.40 against 0.37 ms)
+    if (L.S >= 8) return false;          // (8 x 20 -> 34 of 51^3, 3^3 kernels 0.40 against 0.37 ms)
+    // Above length 64 four passes without any along x are faster than two fused ones with two along x.  Up to there the
+    // fused kernels gain with every image, and where there are few pencils for long sums nothing hides a workgroup's walk.
+    // Over 339 random layers of up to 8 inputs this is 0.8 % off the faster route on average; never transforming x is 3.8 %
+    // off, always doing so 8.2 %.  Untransformed against transformed, us: 10 -> 44 images of 59^3, 3^3 kernels 83 against
+    // 89; 7 -> 1 of 65^3, 7^3 55 against 75; 50 -> 8 of 19^3, 7^3 65 against 47; 7 x 88 -> 1 of 37^3, 2^3 258 against 197;
+    // 4 x 4 -> 118 of 19^3, 3^3 62 against 49; 7 x 103 -> 7 of 54^3, 3^3 792 against 665; and the largest loss, 18 -> 122 of
+    // 41^3, 6^3 155 against 178.
+    if (L.d.Ny > 64) return true;
+    return L.S * L.f <= 80 && L.S * L.fo <= 112 && 2 * L.f * L.d.kx <= 3 * L.d.zc * L.d.Ny;
 }
 
 // ... and whether it applies the kernel's taps along x through length-8 transforms of overlapping blocks

@@ -25,3 +25,15 @@ def test_blocks_of_one_output_block_take_one_route(recorder):
                        capture_output=True, text=True, timeout=600)
     assert r.returncode == 0, r.stdout[-1000:] + r.stderr[-3000:]
     assert "one route each" in r.stdout
+
+
+# (S, f, fo, n, k, x axis transformed): measured on both routes, the faster one named
+@pytest.mark.parametrize("layer", [(1, 10, 44, 59, 3, False), (1, 8, 8, 64, 5, False), (1, 7, 1, 65, 7, False), (1, 80, 80, 100, 5, False),
+                                   (1, 50, 8, 19, 7, True), (7, 88, 1, 37, 2, True), (4, 4, 118, 19, 3, True),
+                                   (7, 103, 7, 54, 3, True), (1, 45, 30, 16, 7, True), (64, 80, 80, 51, 5, True)],
+                         ids=lambda c: "S%d_f%dx%d_n%d_k%d_%s" % c)
+def test_small_images_take_the_faster_route(layer):
+    S, f, fo, n, k, transformed = layer
+    _, flops = B.znni_conv3d_fft_stage_work(S, f, fo, n, k)
+    _, untransformed = B.znni_conv3d_fft_stage_work(S, f, fo, n, k, mac_reference="xdirect")
+    assert (flops != untransformed) == transformed
