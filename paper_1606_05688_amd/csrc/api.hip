@@ -66,14 +66,18 @@ static bool pick_untransformed_x(const LayerPlan& L, unsigned flags)
     if (batch) return L.S <= 8 && L.d.Ny > 64;
     if (L.S >= 8) return false;          // (8 x 20 -> 34 of 51^3, 3^3 kernels 0.40 against 0.37 ms)
     // Above length 64 four passes without any along x are faster than two fused ones with two along x.  Up to there the
-    // fused kernels gain with every image, and where there are few pencils for long sums nothing hides a workgroup's walk.
-    // Over 339 random layers of up to 8 inputs this is 0.8 % off the faster route on average; never transforming x is 3.8 %
-    // off, always doing so 8.2 %.  Untransformed against transformed, us: 10 -> 44 images of 59^3, 3^3 kernels 83 against
-    // 89; 7 -> 1 of 65^3, 7^3 55 against 75; 50 -> 8 of 19^3, 7^3 65 against 47; 7 x 88 -> 1 of 37^3, 2^3 258 against 197;
-    // 4 x 4 -> 118 of 19^3, 3^3 62 against 49; 7 x 103 -> 7 of 54^3, 3^3 792 against 665; and the largest loss, 18 -> 122 of
-    // 41^3, 6^3 155 against 178.
+    // fused kernels gain with every image, the untransformed route with every product per image (its multiply-accumulate
+    // is the faster one), and where there are few pencils for long sums nothing hides a workgroup's walk.  Over 537
+    // random layers of up to 7 inputs this is 1.1 % off the faster route on average; never transforming x is 5.0 % off,
+    // always doing so 6.9 %.  Untransformed against transformed, us: 10 -> 44 images of 59^3, 3^3 kernels 83 against 89;
+    // 18 -> 122 of 41^3, 6^3 155 against 178; 3 x 83 -> 6 of 41^3, 5^3 189 against 232; 7 -> 1 of 65^3, 7^3 55 against 75;
+    // 50 -> 8 of 19^3, 7^3 65 against 47; 7 x 88 -> 1 of 37^3, 2^3 258 against 197; 4 x 4 -> 118 of 19^3, 3^3 62 against 49;
+    // 7 x 103 -> 7 of 54^3, 3^3 792 against 665.  The largest losses: 9 -> 121 of 14^3, 7^3 64 against 46; 3 x 27 -> 9 of
+    // 49^3, 5^3 110 against 137.
+    const int pencils = L.d.zc * L.d.Ny;
     if (L.d.Ny > 64) return true;
-    return L.S * L.f <= 80 && L.S * L.fo <= 112 && 2 * L.f * L.d.kx <= 3 * L.d.zc * L.d.Ny;
+    if (L.S * L.f <= 80) return L.S * L.fo <= 300 && 2 * L.f * L.d.kx <= 3 * pencils;
+    return pencils >= 512 && (long long)L.f * L.fo * L.d.kx >= 8ll * L.S * (L.f + L.fo);
 }
 
 // ... and whether it applies the kernel's taps along x through length-8 transforms of overlapping blocks

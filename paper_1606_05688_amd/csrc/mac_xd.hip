@@ -171,7 +171,7 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT, NG, SUM>())) void k_mac_xd(
     const float2* xrow = g.X2 + (size_t)sI * f * g.ximg + (size_t)poz * g.xpen + (size_t)poy * g.ldx;
     int sexp = 126;                                          // exponent of the scale the image values carry
     int chunk = 0;
-    const bool scaled = *g.scaled != 0;
+    const int scaled = *g.scaled;                            // (compared where it is used: nothing waits for it before)
     bool apart = false;                                      // magnitudes along x too far apart for halves
     // One chunk of image rows to LDS: wave w takes quads w, w + 4, ..., x along the lanes; the halo behind the outputs, one
     // (quad, x) unit per thread.  Values beyond a row are read from its end, images beyond the last from the last: neither
@@ -238,8 +238,8 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT, NG, SUM>())) void k_mac_xd(
             if (lane == 0) { red[0][wave] = vx; red[1][wave] = vn; }
         }
         __syncthreads();
-        unsigned mb = max(max(red[0][0], red[0][1]), max(red[0][2], red[0][3]));
-        const unsigned sm = min(min(red[1][0], red[1][1]), min(red[1][2], red[1][3]));
+        unsigned mb = (unsigned)__builtin_amdgcn_readfirstlane((int)max(max(red[0][0], red[0][1]), max(red[0][2], red[0][3])));
+        const unsigned sm = (unsigned)__builtin_amdgcn_readfirstlane((int)min(min(red[1][0], red[1][1]), min(red[1][2], red[1][3])));
         if (mb >= 0x7f800000u) {                             // infinities or NaNs: the scale is that of the finite values
             m = 0.f;
             auto fin = [&](float2 v) {
@@ -257,7 +257,7 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT, NG, SUM>())) void k_mac_xd(
             const unsigned v = wave_max(m);
             if (lane == 0) wfin[wave] = v;
             __syncthreads();
-            mb = max(max(wfin[0], wfin[1]), max(wfin[2], wfin[3]));
+            mb = (unsigned)__builtin_amdgcn_readfirstlane((int)max(max(wfin[0], wfin[1]), max(wfin[2], wfin[3])));
             __syncthreads();
         }
         apart |= split_too_wide(mb, sm);
@@ -400,7 +400,7 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT, NG, SUM>())) void k_mac_xd(
         if (gs + 1 < nsteps) step(gs + 1, as0 + buf * RT * 256 + RT * 128);
     }
 
-    if (__builtin_amdgcn_readfirstlane(apart)) {
+    if (apart) {
         // All over again in fp32, from global memory, four slots of one complex image each per pair of matrix instructions
         // (kernels: their two halves added up).
         const float sx = pow2f(sexp);

@@ -30,7 +30,8 @@ def test_blocks_of_one_output_block_take_one_route(recorder):
 # (S, f, fo, n, k, x axis transformed): measured on both routes, the faster one named
 @pytest.mark.parametrize("layer", [(1, 10, 44, 59, 3, False), (1, 8, 8, 64, 5, False), (1, 7, 1, 65, 7, False), (1, 80, 80, 100, 5, False),
                                    (1, 50, 8, 19, 7, True), (7, 88, 1, 37, 2, True), (4, 4, 118, 19, 3, True),
-                                   (7, 103, 7, 54, 3, True), (1, 45, 30, 16, 7, True), (64, 80, 80, 51, 5, True)],
+                                   (7, 103, 7, 54, 3, True), (1, 45, 30, 16, 7, True), (1, 18, 122, 41, 6, False),
+                                   (3, 83, 6, 41, 5, False), (64, 80, 80, 51, 5, True)],
                          ids=lambda c: "S%d_f%dx%d_n%d_k%d_%s" % c)
 def test_small_images_take_the_faster_route(layer):
     S, f, fo, n, k, transformed = layer
