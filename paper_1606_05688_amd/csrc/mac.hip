@@ -68,24 +68,31 @@ __device__ __forceinline__ void kprep_row_scale(const float* __restrict__ w, con
                                                 int fo, int fp, int taps, size_t wj_stride, float scale)
 {
     __shared__ float best[4];
+    __shared__ signed char exps[2048];                       // of the first images; beyond, they are worked out again
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     auto cmax = [&](int i) {
         float c = S.cmax[i];
         for (int p = 1; p < parts; ++p) c = fmaxf(c, S.cmax[p * fp + i]);
         return c;
     };
-    float m = 0.f;
-    for (int i = threadIdx.x; i < f; i += 256) m = fmaxf(m, cmax(i));
+    // (the first kernels are requested before the waits below)
+    const float* wj = w + (size_t)j * wj_stride;
+    const float first = j < fo && wave < f && lane < taps ? fabsf(wj[(size_t)wave * taps + lane]) : 0.f;
+    const float own = (int)threadIdx.x < f ? cmax(threadIdx.x) : 0.f;
+    float m = own;
+    for (int i = threadIdx.x + 256; i < f; i += 256) m = fmaxf(m, cmax(i));
 #pragma unroll
     for (int o = 32; o; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
     if (lane == 0) best[wave] = m;
     __syncthreads();
     const float most = fmaxf(fmaxf(best[0], best[1]), fmaxf(best[2], best[3]));
+    for (int i = threadIdx.x; i < min(f, 2048); i += 256) exps[i] = (signed char)kprep_col_exp(i < 256 ? own : cmax(i), most);
     __syncthreads();
+    auto col_exp = [&](int i) { return i < 2048 ? exps[i] : kprep_col_exp(cmax(i), most); };
     if (j == 0) {
         int any = 0;
         for (int i = threadIdx.x; i < fp; i += 256) {
-            const int e = i < f ? kprep_col_exp(cmax(i), most) : 0;
+            const int e = i < f ? col_exp(i) : 0;
             S.col[i] = __uint_as_float((unsigned)(127 + e) << 23);
             S.cinv[i] = __uint_as_float((unsigned)(127 - e) << 23);
             any |= e;
@@ -96,12 +103,12 @@ __device__ __forceinline__ void kprep_row_scale(const float* __restrict__ w, con
     m = 0.f;
     if (j < fo)
         for (int i = wave; i < f; i += 4) {
-            const float* wi = w + (size_t)j * wj_stride + (size_t)i * taps;
-            float s = 0.f;
-            for (int t = lane; t < taps; t += 64) s += fabsf(wi[t]);
+            const float* wi = wj + (size_t)i * taps;
+            float s = i == wave ? first : 0.f;
+            for (int t = i == wave ? lane + 64 : lane; t < taps; t += 64) s += fabsf(wi[t]);
 #pragma unroll
             for (int o = 32; o; o >>= 1) s += __shfl_xor(s, o);
-            s = ldexpf(s * scale, -kprep_col_exp(cmax(i), most));
+            s = ldexpf(s * scale, -col_exp(i));
             m = fmaxf(m, s < INFINITY ? s : 0.f);
         }
     if (lane == 0) best[wave] = m;
@@ -402,7 +409,7 @@ znni_status launch_kernel_prep_z(const LayerPlan& L, const float* w, size_t wj_s
     const int nblk = (per1 + 255) / 256;
     k_kprep_z<<<dim3(nblk + (split ? L.Mp : 0), (d.zc + KPREP_OZ - 1) / KPREP_OZ), dim3(256),
                 sizeof(float2) * KPREP_OZ * (size_t)std::min(d.kz, KPREP_TAPS), st>>>(
-        w, L.A1, L.twz, d, L.f, L.fo, L.fp, L.Mp, wj_stride, nblk, split_scales(L), (std::max({d.Nx, d.Ny, d.Nz}) + 255) / 256,
+        w, L.A1, L.twz, d, L.f, L.fo, L.fp, L.Mp, wj_stride, nblk, split_scales(L), (int)(split_parts(L).x * split_parts(L).z),
         (float)(1.0 / ((double)d.Ny * d.Nz)));
     ZNNI_LAUNCH_CHECK();
     return ZNNI_OK;

@@ -28,7 +28,7 @@ namespace znni {
 // The three twiddle tables exp(-2 pi i q / N) of a layer (x, y, z axis) in one launch; blockIdx.y picks the axis.
 // A's zeroed padding behind the last pencil (pad elements at `padp`) is written by the same launch.  So are, from
 // blockIdx.y = 4 on, the largest kernel magnitudes of every input image for the route that splits values in halves
-// (mac_xd.hip): cmax[part][fp], each part over every gridDim.x-th run of 256 values.
+// (mac_xd.hip): cmax[part][fp], parts over blockIdx.x and .z, each over its runs of 256 values.
 __global__ void k_twiddles(float2* twx, int Nx, float2* twy, int Ny, float2* twz, int Nz, float2* padp, size_t pad,
                            const float* __restrict__ w, float* cmax, int f, int fo, int fp, int taps, size_t wj_stride)
 {
@@ -38,10 +38,11 @@ __global__ void k_twiddles(float2* twx, int Nx, float2* twy, int Ny, float2* twz
             const float* wi = w + (size_t)i * taps;
             const unsigned n = (unsigned)fo * taps;          // (below 2^30: the layer call's shape limits)
             float m = 0.f;
-            for (unsigned e0 = blockIdx.x * 256 + threadIdx.x; e0 < n; e0 += gridDim.x * 1024)
+            const unsigned part = blockIdx.z * gridDim.x + blockIdx.x, step = gridDim.x * gridDim.z * 256;
+            for (unsigned e0 = part * 256 + threadIdx.x; e0 < n; e0 += 8 * step)
 #pragma unroll
-                for (unsigned u = 0; u < 4; ++u) {           // four loads in flight
-                    const unsigned e = min(e0 + u * gridDim.x * 256, n - 1), j = e / (unsigned)taps;
+                for (unsigned u = 0; u < 8; ++u) {           // eight loads in flight
+                    const unsigned e = min(e0 + u * step, n - 1), j = e / (unsigned)taps;
                     const float v = fabsf(wi[(size_t)j * wj_stride + (e - j * taps)]);
                     m = fmaxf(m, v < INFINITY ? v : 0.f);
                 }
@@ -49,11 +50,12 @@ __global__ void k_twiddles(float2* twx, int Nx, float2* twy, int Ny, float2* twz
             for (int o = 32; o; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
             if ((threadIdx.x & 63) == 0) best[threadIdx.x >> 6] = m;
             __syncthreads();
-            if (threadIdx.x == 0) cmax[blockIdx.x * fp + i] = fmaxf(fmaxf(best[0], best[1]), fmaxf(best[2], best[3]));
+            if (threadIdx.x == 0) cmax[part * fp + i] = fmaxf(fmaxf(best[0], best[1]), fmaxf(best[2], best[3]));
             __syncthreads();
         }
         return;
     }
+    if (blockIdx.z) return;
     const size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (blockIdx.y == 3) {
         if (q < pad) padp[q] = make_float2(0.f, 0.f);
@@ -303,7 +305,7 @@ znni_status launch_twiddles(const LayerPlan& L, const float* w, size_t wj_stride
     for (int N : {d.Nx, d.Ny, d.Nz})
         if ((size_t)N > most) most = N;
     const unsigned images = w && L.xdirect && !L.xblock ? (unsigned)(L.f < 65531 ? L.f : 65531) : 0;
-    k_twiddles<<<dim3((unsigned)((most + 255) / 256), 4 + images), dim3(256), 0, st>>>(
+    k_twiddles<<<dim3((unsigned)((most + 255) / 256), 4 + images, images ? split_parts(L).z : 1), dim3(256), 0, st>>>(
         L.twx, d.Nx, L.twy, d.Ny, L.twz, d.Nz, L.A + (size_t)d.zc * d.Ny * per, pad, w, split_scales(L).cmax, L.f, L.fo, L.fp,
         d.kx * d.ky * d.kz, wj_stride);
     ZNNI_LAUNCH_CHECK();

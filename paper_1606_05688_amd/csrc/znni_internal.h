@@ -75,20 +75,29 @@ znni_status make_plan(int S, int f, int fo, const int n[3], const int k[3], unsi
 int lines_per_tile(int N);
 
 // The scales behind LayerPlan::rs, powers of two: of the kernel transforms of an output image, with its inverse; of an
-// input image's values, with the inverse that its kernel transforms carry; and, in up to four parts, the largest kernel
+// input image's values, with the inverse that its kernel transforms carry; and, in up to sixteen parts, the largest kernel
 // magnitudes of the input images that the latter come from.
 struct SplitScales {
     float *row, *rinv;      // [Mp]
     float *col, *cinv;      // [fp]
-    float* cmax;            // [4][fp]
+    float* cmax;            // [16][fp]
     int* scaled;            // [1] whether any of col is not one
 };
 inline SplitScales split_scales(const LayerPlan& L)
 {
     float* p = L.rs + 2 * (size_t)L.Mp;
-    return SplitScales{L.rs, L.rs + L.Mp, p, p + L.fp, p + 2 * (size_t)L.fp, (int*)(p + 6 * (size_t)L.fp)};
+    return SplitScales{L.rs, L.rs + L.Mp, p, p + L.fp, p + 2 * (size_t)L.fp, (int*)(p + 18 * (size_t)L.fp)};
 }
-inline size_t split_scale_floats(const LayerPlan& L) { return 2 * (size_t)L.Mp + 6 * (size_t)L.fp + 1; }
+inline size_t split_scale_floats(const LayerPlan& L) { return 2 * (size_t)L.Mp + 18 * (size_t)L.fp + 1; }
+// Parts of cmax, over the launch's x and z: eight values a thread each where sixteen parts are enough for that.
+struct SplitParts { unsigned x, z; };
+inline SplitParts split_parts(const LayerPlan& L)
+{
+    const int N = L.d.Nx > L.d.Ny ? (L.d.Nx > L.d.Nz ? L.d.Nx : L.d.Nz) : (L.d.Ny > L.d.Nz ? L.d.Ny : L.d.Nz);
+    const unsigned x = (unsigned)(N + 255) / 256;
+    const size_t n = (size_t)L.fo * L.d.kx * L.d.ky * L.d.kz, z = (n + 2048 * x - 1) / (2048 * x);
+    return SplitParts{x, z < 16 / x ? (unsigned)z : 16 / x};
+}
 
 // w: the kernels about to be transformed (as for launch_kernel_prep), NULL where kept transforms are used.
 znni_status launch_twiddles(const LayerPlan& L, const float* w, size_t wj_stride, hipStream_t st);
