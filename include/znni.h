@@ -24,10 +24,10 @@
  *   - direct primitive: kernels whose staged image tile fits the 160 KB of LDS, about 6^3 taps and below
  *     (ZNNI_ERR_UNSUPPORTED_SIZE); pooling: window at most 4 and image edge at most 4096 per axis;
  *   - znni_conv3d_fft_static_v: layers whose workspace fits ZNNI_STATIC_SCRATCH_BYTES (ZNNI_ERR_WORKSPACE);
- *   - the workspace size reported by the *_workspace calls includes (f~ + 64) * f'~ zeroed complex elements
- *     (f~ = f rounded up to 4, f'~ = f' to 16) after the stored kernel transforms, which two multiply-accumulate kernels
- *     read (and discard) one iteration past the last frequency bin; nothing is read or written outside the
- *     workspace and the tensors for any shape within these limits.
+ *   - the workspace size reported by the *_workspace calls includes (f~ + 64) * f'~ complex elements
+ *     (f~ = f rounded up to 4, f'~ = f' to 16) after the stored kernel transforms: zeroed where x is transformed, for a
+ *     multiply-accumulate kernel that reads (and discards) one iteration past the last frequency bin; otherwise the place
+ *     of the scales; nothing is read or written outside the workspace and the tensors for any shape within these limits.
  *
  * Conventions for every function below
  *   - Returns a znni_status; never throws, aborts or prints.
@@ -40,7 +40,14 @@
  *   - Results are deterministic: no floating-point atomics, fixed summation order.
  *   - Tensors are dense, row-major, last index fastest.  All values and sums are fp32; two kernels form products
  *     of fp32 values on fp16 matrix instructions, each value split in two scaled halves (22 bits and a sign), with results
- *     at least as close to the 64-bit ones as fp32 products give.
+ *     as close to the 64-bit ones as fp32 products give for values of ordinary spread: a value down to 2^-17 of the
+ *     largest that shares its scale keeps 22 bits, one below it has an absolute error of 2^-40 of that largest value.
+ *     Direct primitive: image values more than 2^19 below the largest of their tile (a few hundred voxels of all input
+ *     images) are multiplied in fp32 with it, and so are kernels where all taps of an input image, or one tap of all of
+ *     them, are that far below the largest of the output image; the bound stands for single kernel values.
+ *     Transform route without x transform: likewise in fp32 where magnitudes lie that far apart along x, and input images
+ *     whose kernels are far smaller than those of others have scales of their own; the bound stands for the spectra of
+ *     the input images at one frequency, and for the kernels of an output image after those scales.
  */
 #ifndef ZNNI_H
 #define ZNNI_H
@@ -228,7 +235,8 @@ znni_status znni_conv3d_fft_profile_v(int S, int f, int fo, const int n[3], cons
  * input images is taken in a different order).
  *
  * znni_conv3d_fft_sublayers_v: host only.  Writes the division for `budget_bytes` to sub[3] = {S_i, f_i, f'_i}
- *   and the workspace it needs (<= budget_bytes) to *bytes.  ZNNI_ERR_WORKSPACE if even the smallest division
+ *   and the workspace it needs (<= budget_bytes) to *bytes: what decides whether a budget is enough.  (A layer that
+ *   znni_conv3d_fft_budget_v can run in slabs, see there, has a division too, which is then not used.)  ZNNI_ERR_WORKSPACE if even the smallest division
  *   (S_i = f_i = f'_i = 1) does not fit; *bytes then holds what that division needs.
  * znni_conv3d_fft_budget_v: runs the layer with the division chosen for workspace_bytes; where the spectra of the whole
  *   layer fit and only the kernel transforms do not (and x is not transformed), in slabs along the halved axis instead,

@@ -28,7 +28,20 @@
 // of two, which costs no accuracy: the image values of a workgroup by their largest magnitude so far (the sums are
 // rescaled when a later chunk is larger), the kernel transforms of an output image by a bound of theirs.  With the
 // largest value at 2^14, every value down to 2^-17 of it keeps all 22 bits, smaller ones an absolute error of 2^-40 of
-// the largest.  Whole layers come out 0.6 to 1.0 times as far from their 64-bit values as with fp32 matrix
+// the largest.
+//
+// Values that lie further apart than that:
+//  * Input images whose kernels make up for another magnitude (a network that is not normalised): half of the distance
+//    between the kernels of the images moves to their values, so that both sides stay in range (kprep_row_scale in mac.hip;
+//    images up to 2^40 apart come out to 32-bit accuracy).
+//  * Values along x: the x axis is not transformed, so a row next to one large value has outputs that never meet it.  A
+//    workgroup whose largest values at one x and another are more than 2^SPLIT_SPAN apart sums all over again in fp32, from
+//    global memory.  (A voxel of 1e9 in every 100 000: 40 -> 40 of 128^3, 3^3 kernels 0.84 -> 1.34 ms for the layer, 80 -> 80
+//    with 7^3 2.9 -> 6.8; on fp32 products alone 0.95 and 4.2.)
+//  * What is left: input images far apart whose kernels do not make up for it, each the only one that some output image is
+//    made of, and kernels of an output image far apart both ways: an absolute error of 2^-40 of the largest.
+//
+// Whole layers come out 0.6 to 1.0 times as far from their 64-bit values as with fp32 matrix
 // instructions (80 -> 80 of 128^3, 7^3 kernels: 3.7e-7 against 5.4e-7), and the kernel is (multiply-accumulate alone,
 // before and after): 80 -> 80 of 128^3, 7^3 2.53 -> 1.05 ms; 40 -> 40 of 128^3, 3^3 0.37 -> 0.22; 37 -> 45 of 93 x 110 x
 // 131, 3 x 4 x 5 0.33 -> 0.25; 80 -> 80 of 200^3, 5^3 9.1 -> 3.8.  Up to eight images with one or two taps it is level to a
@@ -71,9 +84,10 @@ struct XdArgs {
 constexpr int XD_MAX_K = 9;     // taps along x at most: the halo of a staged row
 template <int RT, int CT, int NG>
 constexpr size_t xd_lds_bytes() { return (size_t)16 * (2 * 4 * NG * (64 * CT + 16) + 4 * 128 * RT); }
-// Three workgroups per CU where LDS and registers (168 a lane) allow, two otherwise.
+// Three workgroups per CU where LDS and registers (168 a lane) allow, two otherwise; the smallest tile is held to 72 registers
+// for seven (8 -> 8 of 64^3, 5^3 kernels: 57.4 -> 56.3 us for the layer).
 template <int RT, int CT, int NG, bool SUM>
-constexpr int xd_blocks() { return xd_lds_bytes<RT, CT, NG>() <= 53 * 1024 && RT * CT <= (SUM ? 5 : 6) ? 3 : 2; }
+constexpr int xd_blocks() { return RT * CT == 1 ? 7 : xd_lds_bytes<RT, CT, NG>() <= 53 * 1024 && RT * CT <= (SUM ? 5 : 6) ? 3 : 2; }
 
 // Slot of a pencil's stored kernel transforms -> image quad and tap: the order the contraction walks them in, chunks of four
 // quads, inside a chunk tap by tap, quads fastest.
@@ -640,9 +654,11 @@ static znni_status launch_xd_cols_s(const LayerPlan& L, int accumulate, hipStrea
     return ZNNI_ERR_SHAPE;
 }
 
-// Stepwise sums for four and five taps and at least 16 images: there the block form of mac_xb.hip, with sums a fifth as
-// long, would be the closer one otherwise (48 -> 48 images of 320^2, 5^3 kernels: 3.3e-7 off without them, 2.45e-7 with
-// them, 3.0e-7 in blocks), and where a batch would otherwise share generated spectra (mac_batch.hip).  Everywhere else the fp32 products this kernel replaced were further off than it is.
+// Stepwise sums wherever another form of the multiply-accumulate, which the call could have taken, would be closer to
+// the 64-bit result without them: the block form (four and five taps, at least 16 images: sums a fifth as long; 48 -> 48
+// images of 320^2, 5^3 kernels: 3.3e-7 off without stepwise sums, 2.45e-7 with them, 3.0e-7 in blocks) and the batch form.
+// It is no rule on the length of the sums: with seven taps and 80 images they are longer, but the fp32 products this
+// kernel replaced there were at 5.4e-7 against its 3.7e-7, and stepwise sums cost 8 % of the kernel.
 template <int RT>
 static znni_status launch_xd_cols(const LayerPlan& L, int accumulate, hipStream_t st)
 {
