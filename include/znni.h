@@ -12,9 +12,9 @@
  * pruned as in Section III-A (k^2, then k*n~, then n~^2 one-dimensional transforms) and their last stage is
  * evaluated inside the multiply-accumulate kernel, so no full-size kernel spectrum is ever stored.  Along x
  * (the slowest axis, transformed last) the common transform size of images and kernels is the library's choice
- * per layer shape: the full n~ for batches; blocks of eight or no transform at all (the kx-tap sum written out)
- * where a full-length kernel spectrum value would serve one input only.  The valid outputs are the same numbers
- * up to fp32 rounding whichever is taken.  Bias and transfer function are applied where the inverse transform
+ * per layer shape: the full n~ for batches of small images; elsewhere no transform at all (the kx-tap sum written
+ * out; or, where a call asks for it, blocks of eight).  The valid outputs are the same numbers up to fp32 rounding
+ * whichever is taken.  Bias and transfer function are applied where the inverse transform
  * finishes an output image (Section IV-A-3).
  *
  * Limits (every call validates them on the host and returns the status named)
@@ -25,8 +25,8 @@
  *     (ZNNI_ERR_UNSUPPORTED_SIZE); pooling: window at most 4 and image edge at most 4096 per axis;
  *   - znni_conv3d_fft_static_v: layers whose workspace fits ZNNI_STATIC_SCRATCH_BYTES (ZNNI_ERR_WORKSPACE);
  *   - the workspace size reported by the *_workspace calls includes (f~ + 64) * f'~ complex elements
- *     (f~ = f rounded up to 4, f'~ = f' to 16) after the stored kernel transforms: zeroed where x is transformed, for a
- *     multiply-accumulate kernel that reads (and discards) one iteration past the last frequency bin; otherwise the place
+ *     (f~ = f rounded up to 4, f'~ = f' to 16) after the stored kernel transforms: zeroed where x is transformed, for two
+ *     multiply-accumulate kernels that read (and discard) one iteration past the last frequency bin; otherwise the place
  *     of the scales; nothing is read or written outside the workspace and the tensors for any shape within these limits.
  *
  * Conventions for every function below
@@ -42,10 +42,10 @@
  *     of fp32 values on fp16 matrix instructions, each value split in two scaled halves (22 bits and a sign), with results
  *     as close to the 64-bit ones as fp32 products give for values of ordinary spread: a value down to 2^-17 of the
  *     largest that shares its scale keeps 22 bits, one below it has an absolute error of 2^-40 of that largest value.
- *     Direct primitive: image values more than 2^19 below the largest of their tile (a few hundred voxels of all input
- *     images) are multiplied in fp32 with it, and so are kernels where all taps of an input image, or one tap of all of
- *     them, are that far below the largest of the output image; the bound stands for single kernel values.
- *     Transform route without x transform: likewise in fp32 where magnitudes lie that far apart along x, and input images
+ *     Direct primitive: a tile (a few hundred voxels of all input images) that holds image values more than 2^19 apart is
+ *     multiplied in fp32, and so are kernels where all taps of an input image, or one tap of all of them, are that far
+ *     below the largest of their output image; the bound stands for single kernel values.
+ *     Transform route without x transform: fp32 as well where magnitudes lie that far apart along x, and input images
  *     whose kernels are far smaller than those of others have scales of their own; the bound stands for the spectra of
  *     the input images at one frequency, and for the kernels of an output image after those scales.
  */
