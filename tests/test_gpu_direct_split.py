@@ -135,3 +135,24 @@ def test_infinite_kernel_values(oracle):
     assert torch.equal(torch.sign(got[0, 7]), torch.sign(met))
     keep = [j for j in range(20) if j != 7]
     assert torch.allclose(got[:, keep], clean[:, keep], rtol=0, atol=1e-6 * float(clean.abs().max()))
+
+
+def test_replays_of_a_captured_call():
+    """Tiles handed out from a counter that every call clears: replays of a graph, with eager calls between them."""
+    inp, w, b = _rand(13, 1, 8, 80, (40, 30, 90), (2, 2, 2))
+    d = torch.device("cuda:0")
+    ti, tw, tb = (torch.from_numpy(t).to(d) for t in (inp, w, b))
+    ws = torch.empty(B.znni_conv3d_direct_workspace(1, 8, 80, (40, 30, 90), (2, 2, 2)), dtype=torch.uint8, device=d)
+    out = torch.empty((1, 80, 39, 29, 89), device=d)
+    eager = _run(inp, w, b)
+    B.znni_conv3d_direct(ti, tw, tb, out=out, workspace=ws)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        B.znni_conv3d_direct(ti, tw, tb, out=out, workspace=ws)
+    for _ in range(4):
+        out.fill_(float("nan"))
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, eager)
+        assert torch.equal(_run(inp, w, b), eager)

@@ -142,3 +142,20 @@ def test_kept_kernels_keep_the_scales_of_their_input_images(oracle):
     x = np.ldexp(_rand(25, S, f, fo, n, k)[0], e[:, None, None, None])
     got = B.znni_conv3d_fft(torch.from_numpy(x).to(d), tw, None, workspace=ws, mac_reference="xdirect", keep_kernels=True)
     assert torch.equal(got, _run(x, w))
+
+
+@pytest.mark.parametrize("share,shape", [(0.55, (2, 24, 90, (70, 24, 20), (3, 2, 3))), (0.9, (1, 24, 33, (40, 128, 64), (4, 2, 3))),
+                                         (0.2, (1, 40, 90, (70, 24, 20), (3, 2, 3)))])
+def test_a_large_value_under_a_budget(oracle, share, shape):
+    """Sub-batches, slabs along the halved axis and blocks of images whose products are added up, two row blocks of output
+    images: workgroups that sum again in fp32 write where the others do."""
+    S, f, fo, n, k = shape
+    inp, w = _rand(26, S, f, fo, n, k)
+    inp[S - 1, f // 2, 20, 4, 5] = 1e10
+    d = torch.device("cuda:0")
+    ti, tw = torch.from_numpy(inp).to(d), torch.from_numpy(w).to(d)
+    ws = torch.full((int(share * B.znni_conv3d_fft_workspace(S, f, fo, n, k)),), 0xFF, dtype=torch.uint8, device=d)
+    got = B.znni_conv3d_fft_budget(ti, tw, None, workspace=ws, mac_reference="xdirect").cpu().numpy().astype(np.float64)
+    exp = oracle.conv3d(inp, w, None, relu=False)
+    for x in range(n[0] - k[0] + 1):
+        assert np.linalg.norm(got[:, :, x] - exp[:, :, x]) <= 1e-6 * np.linalg.norm(exp[:, :, x]), x
