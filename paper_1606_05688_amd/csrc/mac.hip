@@ -89,17 +89,12 @@ __device__ __forceinline__ void kprep_row_scale(const float* __restrict__ w, con
     for (int i = threadIdx.x; i < min(f, 2048); i += 256) exps[i] = (signed char)kprep_col_exp(i < 256 ? own : cmax(i), most);
     __syncthreads();
     auto col_exp = [&](int i) { return i < 2048 ? exps[i] : kprep_col_exp(cmax(i), most); };
-    if (j == 0) {
-        int any = 0;
+    if (j == 0)
         for (int i = threadIdx.x; i < fp; i += 256) {
             const int e = i < f ? col_exp(i) : 0;
             S.col[i] = __uint_as_float((unsigned)(127 + e) << 23);
             S.cinv[i] = __uint_as_float((unsigned)(127 - e) << 23);
-            any |= e;
         }
-        any = __syncthreads_or(any);
-        if (threadIdx.x == 0) *S.scaled = any;
-    }
     m = 0.f;
     if (j < fo)
         for (int i = wave; i < f; i += 4) {

@@ -33,7 +33,10 @@
 // Values that lie further apart than that:
 //  * Input images whose kernels make up for another magnitude (a network that is not normalised): half of the distance
 //    between the kernels of the images moves to their values, so that both sides stay in range (kprep_row_scale in mac.hip;
-//    images up to 2^40 apart come out to 32-bit accuracy).
+//    images up to 2^40 apart come out to 32-bit accuracy).  The forward y pass does that to the values on its way out:
+//    done here as they are staged, it cost the small layers 1 us more (12 -> 5 of 49 x 38 x 41, 3 x 2 x 5 kernels 40.2
+//    against 39.5 us for the layer, 3 x 5 -> 13 of 56 x 50 x 68, 5 x 5 x 1 86.3 against 84.1; 8 -> 8 of 64^3, 5^3 55.9
+//    against 57.0).
 //  * Values along x: the x axis is not transformed, so a row next to one large value has outputs that never meet it.  A
 //    workgroup whose largest values at one x and another are more than 2^SPLIT_SPAN apart sums all over again in fp32, from
 //    global memory.  (A voxel of 1e9 in every 100 000: 40 -> 40 of 128^3, 3^3 kernels 0.84 -> 1.34 ms for the layer, 80 -> 80
@@ -72,8 +75,6 @@ struct XdArgs {
     const float2* X2;
     const half8* A;             // [pencil][slot][row tile][hi, lo][16 output images], 4 complex images each
     const float* rinv;          // [Mp] inverse of the power of two the kernel transforms of an output image carry
-    const float* col;           // [fp] power of two of an input image's values
-    const int* scaled;          // whether any of those is not one
     float2* Yd;
     size_t ximg, yimg;          // elements between the rows of consecutive images in X2 / Yd
     size_t xpen, ypen;          // elements between the rows of pencils (oz, oy) and (oz + 1, oy)
@@ -84,10 +85,9 @@ struct XdArgs {
 constexpr int XD_MAX_K = 9;     // taps along x at most: the halo of a staged row
 template <int RT, int CT, int NG>
 constexpr size_t xd_lds_bytes() { return (size_t)16 * (2 * 4 * NG * (64 * CT + 16) + 4 * 128 * RT); }
-// Three workgroups per CU where LDS and registers (168 a lane) allow, two otherwise; the smallest tile is held to 72 registers
-// for seven (8 -> 8 of 64^3, 5^3 kernels: 57.4 -> 56.3 us for the layer).
+// Three workgroups per CU where LDS and registers (168 a lane) allow, two otherwise.
 template <int RT, int CT, int NG, bool SUM>
-constexpr int xd_blocks() { return RT * CT == 1 ? 7 : xd_lds_bytes<RT, CT, NG>() <= 53 * 1024 && RT * CT <= (SUM ? 5 : 6) ? 3 : 2; }
+constexpr int xd_blocks() { return xd_lds_bytes<RT, CT, NG>() <= 53 * 1024 && RT * CT <= (SUM ? 5 : 6) ? 3 : 2; }
 
 // Slot of a pencil's stored kernel transforms -> image quad and tap: the order the contraction walks them in, chunks of four
 // quads, inside a chunk tap by tap, quads fastest.
@@ -185,7 +185,6 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT, NG, SUM>())) void k_mac_xd(
     const float2* xrow = g.X2 + (size_t)sI * f * g.ximg + (size_t)poz * g.xpen + (size_t)poy * g.ldx;
     int sexp = 126;                                          // exponent of the scale the image values carry
     int chunk = 0;
-    const int scaled = *g.scaled;                            // (compared where it is used: nothing waits for it before)
     bool apart = false;                                      // magnitudes along x too far apart for halves
     // One chunk of image rows to LDS: wave w takes quads w, w + 4, ..., x along the lanes; the halo behind the outputs, one
     // (quad, x) unit per thread.  Values beyond a row are read from its end, images beyond the last from the last: neither
@@ -212,19 +211,6 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT, NG, SUM>())) void k_mac_xd(
         const int hq = min(t >> 3, NQ - 1), hx = min(col0 + 64 * CT + (t & 7), g.nx - 1);
 #pragma unroll
         for (int q = 0; q < 4; ++q) halo[q] = xrow[(size_t)min(i0 + 4 * hq + q, f - 1) * g.ximg + hx];
-        if (scaled)                                          // the images' powers of two
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-#pragma unroll
-                for (int gq = 0; gq < NG; ++gq) {
-                    const float c = g.col[min(i0 + 16 * gq + 4 * wave + q, f - 1)];
-#pragma unroll
-                    for (int it = 0; it < CT; ++it) { raw[gq][it][q].x *= c; raw[gq][it][q].y *= c; }
-                }
-                const float c = g.col[min(i0 + 4 * hq + q, f - 1)];
-                halo[q].x *= c;
-                halo[q].y *= c;
-            }
         // largest magnitude, and the code of the smallest: of the images of a thread at one x together, since their products
         // are added up (an image far below the others, say of rounding errors only, is no reason to leave halves)
         float m = 0.f;
@@ -430,13 +416,13 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT, NG, SUM>())) void k_mac_xd(
             const float live = 4 * gs + kk < nslots ? sx : 0.f;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const float cs = 4 * qd + q < f ? (scaled ? g.col[4 * qd + q] : 1.f) : 0.f;
+                const float cs = 4 * qd + q < f ? live : 0.f;
                 const float2* row = xrow + (size_t)min(4 * qd + q, f - 1) * g.ximg;
                 float2 x[CT];
 #pragma unroll
                 for (int c = 0; c < CT; ++c) {
                     const float2 v = row[min(col0 + (wave * CT + c) * 16 + l16 + K - 1 - tap, g.nx - 1)];
-                    x[c] = make_float2(v.x * cs * live, v.y * cs * live);
+                    x[c] = make_float2(v.x * cs, v.y * cs);
                 }
 #pragma unroll
                 for (int r = 0; r < RT; ++r) {
@@ -617,7 +603,7 @@ static znni_status launch_xd(const LayerPlan& L, int ncb, int accumulate, hipStr
 {
     const Dims& d = L.d;
     XdArgs g;
-    g.A = reinterpret_cast<const half8*>(L.A); g.rinv = split_scales(L).rinv; g.col = split_scales(L).col; g.scaled = split_scales(L).scaled;
+    g.A = reinterpret_cast<const half8*>(L.A); g.rinv = split_scales(L).rinv;
     g.ximg = (size_t)d.x2i * d.ldx; g.xpen = (size_t)d.x2o * d.ldx;
     g.yimg = (size_t)d.ydi * d.ldxo; g.ypen = (size_t)d.ydo * d.ldxo;
     g.S = L.S; g.f = L.f; g.fo = L.fo; g.Mp = L.Mp; g.K = d.kx;

@@ -31,6 +31,8 @@ struct PassArgs {
     const float* bias;     // inv_z only
     Dims d;
     int nimg, fo, relu;
+    const float* col;      // fwd_y before the multiply-accumulate on split halves: a power of two for each of the f input
+    int f;                 // images of a tuple (mac_xd.hip), NULL otherwise
 };
 
 // Inverse x pass: tiles counted over (oz, oy) together?  Measured 9-11 % faster at lengths 56 and 120 (fewer, full
@@ -93,6 +95,12 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, float2* lds)
         src = (const float2*)a.src + ((size_t)img * d.ydi + (size_t)oz * d.ydo) * d.ldxo + xo0;
         lpitch = 1; epitch = d.ldxo; nvalid = min(16, d.nox - xo0);
     }
+
+    // the image's power of two, requested here and used on the results: before the arithmetic, the loads below would wait
+    // for it
+    float ps = 1.f;
+    if constexpr (KIND == P_FWD_Y)
+        if (a.col) ps = a.col[img < a.f ? img : img % a.f];
 
     // ---- step A: loads first (they do not need the twiddle table), then the barrier, then the arithmetic
     // step A thread = (line la, sample offset ja); samples fastest across lanes, except for the transposing load
@@ -186,7 +194,8 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, float2* lds)
         if (q < R1 && lb < nvalid) {
             float2* o = (float2*)a.dst + ((size_t)img * d.x2i + (size_t)mid * d.x2o) * d.ldx + tile * 16 + lb;
 #pragma unroll
-            for (int r = 0; r < R2; ++r) stg<STREAM>(o + (size_t)(q + R1 * r) * d.ldx, u[r]);
+            for (int r = 0; r < R2; ++r)
+                stg<STREAM>(o + (size_t)(q + R1 * r) * d.ldx, make_float2(u[r].x * ps, u[r].y * ps));
         }
     } else if constexpr (KIND == P_INV_X) {
         // Y2[imgo][oz][xo][oy], xo = element - (kx-1) in [0, nox); with (oz, oy) counted together the tile's
@@ -416,6 +425,7 @@ static PassArgs base_args(const LayerPlan& L, const void* src, void* dst, const 
     PassArgs a;
     a.src = src; a.dst = dst; a.tw = tw; a.bias = nullptr;
     a.d = L.d; a.nimg = nimg; a.fo = L.fo; a.relu = 0;
+    a.col = nullptr; a.f = 1;
     return a;
 }
 
@@ -428,7 +438,9 @@ znni_status launch_fast_fwd_z(const LayerPlan& L, const float* in, hipStream_t s
 znni_status launch_fast_fwd_y(const LayerPlan& L, hipStream_t st)
 {
     const Dims& d = L.d;
-    return launch_kind<P_FWD_Y>(d.Ny, base_args(L, L.buf0, L.buf1, L.twy, L.nimg),
+    PassArgs a = base_args(L, L.buf0, L.buf1, L.twy, L.nimg);
+    if (L.xdirect && !L.xblock) { a.col = split_scales(L).col; a.f = L.f; }
+    return launch_kind<P_FWD_Y>(d.Ny, a,
                                 dim3((d.nx + 15) / 16, d.zc, L.nimg), st);
 }
 znni_status launch_fast_fwd_x(const LayerPlan& L, hipStream_t st)

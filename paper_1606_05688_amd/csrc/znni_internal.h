@@ -81,14 +81,13 @@ struct SplitScales {
     float *row, *rinv;      // [Mp]
     float *col, *cinv;      // [fp]
     float* cmax;            // [16][fp]
-    int* scaled;            // [1] whether any of col is not one
 };
 inline SplitScales split_scales(const LayerPlan& L)
 {
     float* p = L.rs + 2 * (size_t)L.Mp;
-    return SplitScales{L.rs, L.rs + L.Mp, p, p + L.fp, p + 2 * (size_t)L.fp, (int*)(p + 18 * (size_t)L.fp)};
+    return SplitScales{L.rs, L.rs + L.Mp, p, p + L.fp, p + 2 * (size_t)L.fp};
 }
-inline size_t split_scale_floats(const LayerPlan& L) { return 2 * (size_t)L.Mp + 18 * (size_t)L.fp + 1; }
+inline size_t split_scale_floats(const LayerPlan& L) { return 2 * (size_t)L.Mp + 18 * (size_t)L.fp; }
 // Parts of cmax, over the launch's x and z: eight values a thread each where sixteen parts are enough for that.
 struct SplitParts { unsigned x, z; };
 inline SplitParts split_parts(const LayerPlan& L)

@@ -159,3 +159,28 @@ def test_a_large_value_under_a_budget(oracle, share, shape):
     exp = oracle.conv3d(inp, w, None, relu=False)
     for x in range(n[0] - k[0] + 1):
         assert np.linalg.norm(got[:, :, x] - exp[:, :, x]) <= 1e-6 * np.linalg.norm(exp[:, :, x]), x
+
+
+@pytest.mark.parametrize("share,shape", [(None, (3, 5, 20, (70, 10, 8), (3, 2, 3))), (0.55, (2, 24, 90, (70, 24, 20), (3, 2, 3))),
+                                         (0.9, (1, 24, 33, (40, 128, 64), (4, 2, 3))),
+                                         (0.2, (1, 40, 90, (70, 24, 20), (3, 2, 3)))])
+def test_input_images_of_unequal_magnitude_in_batches_and_blocks(oracle, share, shape):
+    """The forward y pass scales the image an input's own number names: several inputs, sub-batches, slabs, blocks of
+    input images (each with scales of its own)."""
+    S, f, fo, n, k = shape
+    inp, w = _rand(27, S, f, fo, n, k)
+    e = np.random.default_rng(28).integers(0, 31, f)
+    e[:2] = 0, 30
+    x, v = np.ldexp(inp, e[:, None, None, None]), np.ldexp(w, -e[:, None, None, None])
+    if share is None:
+        got = _run(x, v)
+    else:
+        d = torch.device("cuda:0")
+        size = int(share * B.znni_conv3d_fft_workspace(S, f, fo, n, k))
+        got = B.znni_conv3d_fft_budget(torch.from_numpy(x).to(d), torch.from_numpy(v).to(d), None, mac_reference="xdirect",
+                                       workspace=torch.full((size,), 0xFF, dtype=torch.uint8, device=d))
+    got = got.cpu().numpy().astype(np.float64)
+    exp = oracle.conv3d(x, v, None, relu=False)
+    for s in range(S):
+        for j in range(fo):
+            assert np.linalg.norm(got[s, j] - exp[s, j]) <= 1e-6 * np.linalg.norm(exp[s, j]), (s, j)
