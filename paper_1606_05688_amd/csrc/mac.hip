@@ -75,9 +75,20 @@ __device__ __forceinline__ void kprep_row_scale(const float* __restrict__ w, con
         for (int p = 1; p < parts; ++p) c = fmaxf(c, S.cmax[p * fp + i]);
         return c;
     };
-    // (the first kernels are requested before the waits below)
+    // Four input images of a wave at a time, all requested at once (eight would take the kernel from 62 registers to 82); the
+    // first ones before the waits below.  One at a time, this walk was what the first kernel stage of small layers waited
+    // for: 77 -> 5 of 18 x 15 x 17, 4 x 1 x 6 kernels 48.3 -> 44.0 us for the layer, 38 -> 15 of 56 x 30 x 40, 7 x 6 x 1 58.2
+    // -> 56.1.  Addresses are clamped instead of loads left out: an image again adds nothing to a maximum, a tap again counts
+    // times zero (where it is not finite, neither is the sum, which then does not count).
+    constexpr int U = 4;
     const float* wj = w + (size_t)j * wj_stride;
-    const float first = j < fo && wave < f && lane < taps ? fabsf(wj[(size_t)wave * taps + lane]) : 0.f;
+    auto request = [&](float (&v)[U], int i0, int t0) {
+        const int t = min(t0 + lane, taps - 1);
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = wj[(size_t)min(i0 + 4 * u, f - 1) * taps + t];
+    };
+    float v[U];
+    if (j < fo) request(v, wave, 0);
     const float own = (int)threadIdx.x < f ? cmax(threadIdx.x) : 0.f;
     float m = own;
     for (int i = threadIdx.x + 256; i < f; i += 256) m = fmaxf(m, cmax(i));
@@ -97,14 +108,23 @@ __device__ __forceinline__ void kprep_row_scale(const float* __restrict__ w, con
         }
     m = 0.f;
     if (j < fo)
-        for (int i = wave; i < f; i += 4) {
-            const float* wi = wj + (size_t)i * taps;
-            float s = i == wave ? first : 0.f;
-            for (int t = i == wave ? lane + 64 : lane; t < taps; t += 64) s += fabsf(wi[t]);
+        for (int i0 = wave; i0 < f; i0 += 4 * U) {
+            float s[U] = {};
+            for (int t0 = 0; t0 < taps; t0 += 64) {
+                if (i0 != wave || t0) request(v, i0, t0);
+                const float live = t0 + lane < taps ? 1.f : 0.f;
 #pragma unroll
-            for (int o = 32; o; o >>= 1) s += __shfl_xor(s, o);
-            s = ldexpf(s * scale, -col_exp(i));
-            m = fmaxf(m, s < INFINITY ? s : 0.f);
+                for (int u = 0; u < U; ++u) s[u] += fabsf(v[u]) * live;
+            }
+#pragma unroll
+            for (int o = 32; o; o >>= 1)
+#pragma unroll
+                for (int u = 0; u < U; ++u) s[u] += __shfl_xor(s[u], o);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float e = ldexpf(s[u] * scale, -col_exp(min(i0 + 4 * u, f - 1)));
+                m = fmaxf(m, e < INFINITY ? e : 0.f);
+            }
         }
     if (lane == 0) best[wave] = m;
     __syncthreads();
