@@ -25,7 +25,7 @@
 // with every fp32 value carried as two halves, v = hi + lo (two halves together hold 22 bits and a sign, an error of
 // about 1.5 fp32 roundings), and three of the four partial products kept: hi hi, hi lo, lo hi (the fourth is below
 // 2^-22 of the first).  Sums stay fp32.  Halves have a narrow exponent range, so both operands are scaled by powers
-// of two, which costs no accuracy: the image values of a workgroup by their largest magnitude so far (the sums are
+// of two, which costs no accuracy: the image values of a wave's strip by their largest magnitude so far (the sums are
 // rescaled when a later chunk is larger), the kernel transforms of an output image by a bound of theirs.  With the
 // largest value at 2^14, every value down to 2^-17 of it keeps all 22 bits, smaller ones an absolute error of 2^-40 of
 // the largest.
@@ -38,7 +38,7 @@
 //    against 39.5 us for the layer, 3 x 5 -> 13 of 56 x 50 x 68, 5 x 5 x 1 86.3 against 84.1; 8 -> 8 of 64^3, 5^3 55.9
 //    against 57.0).
 //  * Values along x: the x axis is not transformed, so a row next to one large value has outputs that never meet it.  A
-//    workgroup whose largest values at one x and another are more than 2^SPLIT_SPAN apart sums all over again in fp32, from
+//    wave whose largest values at one x and another are more than 2^SPLIT_SPAN apart sums all over again in fp32, from
 //    global memory.  (A voxel of 1e9 in every 100 000: 40 -> 40 of 128^3, 3^3 kernels 0.84 -> 1.34 ms for the layer, 80 -> 80
 //    with 7^3 2.9 -> 6.8; on fp32 products alone 0.95 and 4.2.)
 //  * What is left: input images far apart whose kernels do not make up for it, each the only one that some output image is
@@ -49,45 +49,52 @@
 // before and after): 80 -> 80 of 128^3, 7^3 2.53 -> 1.05 ms; 40 -> 40 of 128^3, 3^3 0.37 -> 0.22; 37 -> 45 of 93 x 110 x
 // 131, 3 x 4 x 5 0.33 -> 0.25; 80 -> 80 of 200^3, 5^3 9.1 -> 3.8.  Up to eight images with one or two taps it is level to a
 // fifth behind (7 -> 38 of 126 x 180 x 119, 1 tap: 0.118 -> 0.142): there nothing but reading and writing spectra is left.
-// What bounds it: matrix instructions about 40 % of the time at two waves per SIMD, the rest their operands (LDS reads,
-// the two forms of an operand), the staging of the image rows between chunks and, for wide kernels, reading A.
+// What bounds it: at 48 -> 48 of 320^3, 5^3 (5.0 ms, 6.3 with workgroup-wide staging and 64-column tiles of four waves) the
+// matrix pipes are busy half of the time at 1.75 GHz, where the passes next to it run at 2.1 to 2.2: power, of which the
+// products take most.  Without image reads it took 4.3 ms, without stores 4.4, without any memory access 3.7, with a third
+// of the products 3.7; requesting the next chunk's cache lines ahead, other wave priorities and fewer vector
+// instructions while staging changed nothing.  At 40 -> 40 of 128^3, 3^3 (0.22 ms, 4.8 TB/s) and at 80 -> 80 of 128^3, 7^3
+// (1.05 ms, 4.3 GB of which 3 are kernel transforms) it is memory.
 //
 // Complex products as real ones: with the contraction running over (image, real / imaginary part), the kernel
-// operand (Ar, Ai) meets (Xr, -Xi) for the real part of the result and (Xi, Xr) for the imaginary part; both are
-// made from one read of the image operand with one instruction per register.
+// operand (Ar, Ai) meets (Xr, -Xi) for the real part of the result and (Xi, Xr) for the imaginary part.  The first is what
+// is staged, the second is made of it with one packed instruction per register.
 //
-// Workgroup = 4 waves = one (oz, oy) pencil of one input x 64*CT outputs along x x 16*RT output images; a wave owns
-// 16*CT outputs and all RT row tiles.  Input images go through in chunks of 16*NG: their rows are read into registers,
-// split, and left in LDS as [image quad][x] units of 16 bytes, the operand layout, so that a tap is a shift by one
-// unit.  One matrix step contracts four (quad, tap) slots: sixteen images of one tap, or, in a last group of fewer
-// images, several taps of fewer quads.  Kernel operands travel global memory -> registers -> LDS, requested two pairs
-// of steps and parked one pair ahead, one quarter per wave (every wave reading all of them for itself asks more of the vector
-// L1 than it delivers: 85 / CT bytes per clock of 64); one barrier per pair of steps.  Nothing is requested for the next chunk
-// while a chunk is multiplied: loads are waited for in order, so kernel operands requested after the image rows would
-// wait for those; the other workgroups of the CU fill the gap instead.
+// A wave owns a strip of 16*CT outputs along x of one pencil (oz, oy) of one input and RT row tiles of 16 output images; the
+// four waves of a workgroup own four strips of a pencil, of one input or of several, and share its kernel operands.  Strips
+// are as wide as the row divides best into (launch_xd_cols_s): rows of 316 outputs are four strips of 80 where four waves
+// of one 192-wide tile and the next left a sixth of the products to padding.  Input images go through in chunks of sixteen.  A wave
+// reads its own rows into registers, splits them and leaves them in its own part of LDS as [image quad][x] units of 16
+// bytes, the operand layout, so that a tap is a shift by one unit; no wave waits for another's rows (a workgroup that
+// staged together met at two barriers a chunk).  One matrix step contracts four (quad, tap) slots: sixteen images of one tap,
+// or, in a last chunk of fewer images, several taps of fewer quads.  Kernel operands travel global memory -> registers -> LDS,
+// requested two pairs of steps and parked one pair ahead, one quarter per wave (every wave reading all of them for itself
+// asks more of the vector L1 than it delivers: 85 / CT bytes per clock of 64); one barrier per pair of steps.
 #include "mac_common.h"
 #include "split.h"
 
 namespace znni {
 
 struct XdArgs {
-    FastDiv d_sub, d_ncb, d_S, d_Ny;
+    FastDiv d_sub, d_pg, d_spr, d_nwg, d_Ny;
     const float2* X2;
     const half8* A;             // [pencil][slot][row tile][hi, lo][16 output images], 4 complex images each
     const float* rinv;          // [Mp] inverse of the power of two the kernel transforms of an output image carry
     float2* Yd;
-    size_t ximg, yimg;          // elements between the rows of consecutive images in X2 / Yd
+    unsigned ximg, yimg;        // elements between the rows of consecutive images in X2 / Yd
     size_t xpen, ypen;          // elements between the rows of pencils (oz, oy) and (oz + 1, oy)
-    int S, f, fo, Mp, K, nx, nox, ldx, ldxo, Ny;
-    int ncb, nmblk, npencils, accumulate;
+    int xrow, yrow;             // ... of pencils (oz, oy) and (oz, oy + 1)
+    int xblk, yblk;             // ... of four neighbouring x (xo) and the next four
+    int f, fo, Mp, K, nx, nox, Ny;
+    int nstrips, npencils, accumulate;
 };
 
 constexpr int XD_MAX_K = 9;     // taps along x at most: the halo of a staged row
-template <int RT, int CT, int NG>
-constexpr size_t xd_lds_bytes() { return (size_t)16 * (2 * 4 * NG * (64 * CT + 16) + 4 * 128 * RT); }
+template <int RT, int CT>
+constexpr size_t xd_lds_bytes() { return (size_t)16 * (4 * 8 * (16 * CT + 16) + 4 * 128 * RT); }
 // Three workgroups per CU where LDS and registers (168 a lane) allow, two otherwise.
-template <int RT, int CT, int NG, bool SUM>
-constexpr int xd_blocks() { return xd_lds_bytes<RT, CT, NG>() <= 53 * 1024 && RT * CT <= (SUM ? 5 : 6) ? 3 : 2; }
+template <int RT, int CT>
+constexpr int xd_blocks() { return xd_lds_bytes<RT, CT>() <= 53 * 1024 && RT * CT <= 6 ? 3 : 2; }
 
 // Slot of a pencil's stored kernel transforms -> image quad and tap: the order the contraction walks them in, chunks of four
 // quads, inside a chunk tap by tap, quads fastest.
@@ -98,31 +105,35 @@ __device__ __forceinline__ void xd_slot(int slot, int K, int fq, int& quad, int&
     quad = 4 * c + s - a * QC;
 }
 
-template <int RT, int CT, int NG, bool SUM>
-__global__ __launch_bounds__(256, (xd_blocks<RT, CT, NG, SUM>())) void k_mac_xd(XdArgs g)
+template <int RT, int CT, bool SUM>
+__global__ __launch_bounds__(256, (xd_blocks<RT, CT>())) void k_mac_xd(XdArgs g)
 {
-    // staged outputs with their halo, image quads of a chunk (rows of XW units start on the same bank: the sixteen-lane
-    // groups of a 16-byte LDS read then share no bank in any phase)
-    constexpr int XW = 64 * CT + 16, NQ = 4 * NG;
-    static_assert(XD_MAX_K - 1 <= 8 && 8 * NQ <= 256, "the halo is staged one unit per thread");
+    // staged columns of a strip (its outputs and their halo) and the pitch of an image quad (rows start on the same bank:
+    // the sixteen-lane groups of a 16-byte LDS read then share no bank in any phase)
+    constexpr int XN = 16 * CT + 8, XW = 16 * CT + 16;
+    // Rounds of a wave over a strip's units: strips of three column tiles and more take a quad per round (its image rows are
+    // then scalar addresses) and the columns beyond 64 of all quads in further ones.
+    constexpr int XH = CT >= 3 ? (XN > 64 ? XN - 64 : 0) : XN, NQ = CT >= 3 ? 4 : 0, NR = NQ + (4 * XH + 63) / 64;
+    static_assert(XD_MAX_K - 1 <= 8, "the halo is eight columns");
     extern __shared__ half8 lds[];
-    half8* const Xs = lds;                                   // [hi, lo][NQ][XW]
-    half8* const As = lds + 2 * NQ * XW;                     // [two pairs of steps][slot kk][row tile][hi, lo][16]
-    __shared__ unsigned wred[2][2][4], wfin[4];              // [turn][largest, smallest][wave]
+    half8* const As = lds;                                   // [two pairs of steps][slot kk][row tile][hi, lo][16]
 
-    // (as mac_block, without its divisions: the integer divisions of a workgroup's start cost as much as a matrix step)
+    // (the integer divisions of a workgroup's start cost as much as a matrix step: high products instead)
     const unsigned xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const unsigned q8 = g.d_sub.div(slot), sub = slot - q8 * g.d_sub.d;
-    const int pencil = (int)(q8 * 8 + xcd);
+    const unsigned qg = g.d_sub.div(slot), rem = slot - qg * g.d_sub.d;
+    const unsigned sub = g.d_pg.div(rem);
+    const int pencil = (int)((qg * 8 + xcd) * g.d_pg.d + (rem - sub * g.d_pg.d));
     if (pencil >= g.npencils) return;
-    const unsigned sm = g.d_ncb.div(sub);
-    const int colblk = (int)(sub - sm * g.d_ncb.d);
-    const int mblk = (int)g.d_S.div(sm), sI = (int)sm - mblk * g.S;
+    const int mblk = (int)g.d_nwg.div(sub);
     const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
     const int l16 = lane & 15, kk = lane >> 4;
+    const int strip = ((int)sub - mblk * (int)g.d_nwg.d) * 4 + wave;
+    const bool live = strip < g.nstrips;                     // (waves without a strip only carry kernel operands)
+    const int sI = (int)g.d_spr.div((unsigned)min(strip, g.nstrips - 1));
+    const int col0 = (min(strip, g.nstrips - 1) - sI * (int)g.d_spr.d) * 16 * CT;
     const int K = g.K, f = g.f;
     const int poz = (int)g.d_Ny.div((unsigned)pencil), poy = pencil - poz * g.Ny;
-    const int col0 = colblk * 64 * CT;
+    half8* const Xs = lds + 4 * RT * 128 + wave * 8 * XW;    // this wave's own: [hi, lo][quad][XW]
 
     // ---- kernel operands: this thread's share of a step, NU units of 16 bytes (surplus units repeat the last one).
     // Slots past the last one are read from it.
@@ -178,87 +189,54 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT, NG, SUM>())) void k_mac_xd(
         for (int c = 0; c < CT; ++c) { re[r][c] = floatx4{0.f, 0.f, 0.f, 0.f}; im[r][c] = re[r][c]; }
 
     load_a();
-    float rj[RT];                                            // (requested here, used with the results)
-#pragma unroll
-    for (int r = 0; r < RT; ++r) rj[r] = g.rinv[(mblk * RT + r) * 16 + l16];
 
-    const float2* xrow = g.X2 + (size_t)sI * f * g.ximg + (size_t)poz * g.xpen + (size_t)poy * g.ldx;
+    const float2* xrow = g.X2 + (size_t)(unsigned)(sI * f) * g.ximg + (size_t)poz * g.xpen + (size_t)poy * g.xrow;
+    auto xoff = [&](int x) { x = min(x, g.nx - 1); return (x >> 2) * g.xblk + (x & 3); };
+    auto unit_q = [&](int n) { return n < NQ ? n : min(lane + 64 * (n - NQ), 4 * XH - 1) / max(XH, 1); };
+    auto unit_x = [&](int n) { return n < NQ ? min(lane, XN - 1) : (NQ ? 64 : 0) + min(lane + 64 * (n - NQ), 4 * XH - 1) % max(XH, 1); };
     int sexp = 126;                                          // exponent of the scale the image values carry
     int chunk = 0;
     bool apart = false;                                      // magnitudes along x too far apart for halves
-    // One chunk of image rows to LDS: wave w takes quads w, w + 4, ..., x along the lanes; the halo behind the outputs, one
-    // (quad, x) unit per thread.  Values beyond a row are read from its end, images beyond the last from the last: neither
-    // reaches a stored output (the images count as zeros).
+    // One chunk of sixteen images of the strip to LDS, a (quad, x) unit per lane and round.  Values beyond a row are read
+    // from its end, images beyond the last from the last: neither reaches a stored output (the images count as zeros).
     auto stage = [&]() {
-        const int i0 = chunk * 16 * NG;
-        float2 raw[NG][CT][4], halo[4];
-        // (quads beyond the last image are neither read nor staged: no lane group's slot names them)
+        const int i0 = chunk * 16;
+        float2 raw[NR][4];
 #pragma unroll
-        for (int gq = 0; gq < NG; ++gq)
-            if (i0 + 16 * gq + 4 * wave < f)
+        for (int n = 0; n < NR; ++n) {
+            const int uq = unit_q(n);
+            const unsigned off = 8u * (unsigned)xoff(col0 + unit_x(n));
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const char* row = reinterpret_cast<const char*>(xrow + (size_t)min(i0 + 16 * gq + 4 * wave + q, f - 1) * g.ximg);
-#pragma unroll
-                for (int it = 0; it < CT; ++it)
-                    raw[gq][it][q] = *reinterpret_cast<const float2*>(row + 8u * (unsigned)min(col0 + 64 * it + lane, g.nx - 1));
-            }
-            else
-#pragma unroll
-                for (int it = 0; it < CT; ++it)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) raw[gq][it][q] = make_float2(0.f, 0.f);
-        const int hq = min(t >> 3, NQ - 1), hx = min(col0 + 64 * CT + (t & 7), g.nx - 1);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) halo[q] = xrow[(size_t)min(i0 + 4 * hq + q, f - 1) * g.ximg + hx];
-        // largest magnitude, and the code of the smallest: of the images of a thread at one x together, since their products
+            for (int q = 0; q < 4; ++q)
+                raw[n][q] = *reinterpret_cast<const float2*>(
+                    reinterpret_cast<const char*>(xrow + (size_t)(unsigned)min(i0 + 4 * uq + q, f - 1) * g.ximg) + off);
+        }
+        // largest magnitude, and the code of the smallest: of the images of a unit together, since their products
         // are added up (an image far below the others, say of rounding errors only, is no reason to leave halves)
         float m = 0.f;
-        unsigned mn;
-        {
+        unsigned mn = ~0u;
+#pragma unroll
+        for (int n = 0; n < NR; ++n) {
             float u = 0.f;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) max3_abs(u, halo[q].x, halo[q].y);
-            m = u;
-            mn = small_code(u);
-#pragma unroll
-            for (int it = 0; it < CT; ++it) {
-                u = 0.f;
-#pragma unroll
-                for (int gq = 0; gq < NG; ++gq)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) max3_abs(u, raw[gq][it][q].x, raw[gq][it][q].y);
-                m = fmaxf(m, u);
-                mn = min(mn, small_code(u));
-            }
+            for (int q = 0; q < 4; ++q) max3_abs(u, raw[n][q].x, raw[n][q].y);
+            m = fmaxf(m, u);
+            mn = min(mn, small_code(u));
         }
-        unsigned (&red)[2][4] = wred[chunk & 1];
-        {
-            const unsigned vx = wave_max(m), vn = wave_min(mn);
-            if (lane == 0) { red[0][wave] = vx; red[1][wave] = vn; }
-        }
-        __syncthreads();
-        unsigned mb = (unsigned)__builtin_amdgcn_readfirstlane((int)max(max(red[0][0], red[0][1]), max(red[0][2], red[0][3])));
-        const unsigned sm = (unsigned)__builtin_amdgcn_readfirstlane((int)min(min(red[1][0], red[1][1]), min(red[1][2], red[1][3])));
+        unsigned mb = wave_max(m);
+        const unsigned sm = wave_min(mn);
         if (mb >= 0x7f800000u) {                             // infinities or NaNs: the scale is that of the finite values
             m = 0.f;
-            auto fin = [&](float2 v) {
-                const float ax = fabsf(v.x), ay = fabsf(v.y);
-                max3_abs(m, ax < INFINITY ? ax : 0.f, ay < INFINITY ? ay : 0.f);
-            };
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                fin(halo[q]);
+            for (int n = 0; n < NR; ++n)
 #pragma unroll
-                for (int gq = 0; gq < NG; ++gq)
-#pragma unroll
-                    for (int it = 0; it < CT; ++it) fin(raw[gq][it][q]);
-            }
-            const unsigned v = wave_max(m);
-            if (lane == 0) wfin[wave] = v;
-            __syncthreads();
-            mb = (unsigned)__builtin_amdgcn_readfirstlane((int)max(max(wfin[0], wfin[1]), max(wfin[2], wfin[3])));
-            __syncthreads();
+                for (int q = 0; q < 4; ++q) {
+                    // (hidden from the compiler, which would otherwise look at every value of every chunk before it branches)
+                    asm volatile("" : "+v"(raw[n][q].x), "+v"(raw[n][q].y));
+                    const float ax = fabsf(raw[n][q].x), ay = fabsf(raw[n][q].y);
+                    max3_abs(m, ax < INFINITY ? ax : 0.f, ay < INFINITY ? ay : 0.f);
+                }
+            mb = wave_max(m);
         }
         apart |= split_too_wide(mb, sm);
         const int sn = min(sexp, split_exp(__uint_as_float(mb)));
@@ -275,130 +253,100 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT, NG, SUM>())) void k_mac_xd(
         }
         sexp = sn;
         const float sx = pow2f(sn);
-        auto put = [&](const float2 (&v)[4], int quad, int x) {
-            half8 h, l;
+#pragma unroll
+        for (int n = 0; n < NR; ++n) {
+            const int uq = unit_q(n);
+            uintx4 h, l;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const float s = i0 + 4 * quad + q < f ? sx : 0.f;
-                _Float16 a, b;
-                split2(v[q].x, s, a, b);
-                h[2 * q] = a; l[2 * q] = b;
-                split2(v[q].y, s, a, b);
-                h[2 * q + 1] = a; l[2 * q + 1] = b;
+                unsigned a, b;
+                split_conj(raw[n][q].x, raw[n][q].y, i0 + 4 * uq + q < f ? sx : 0.f, a, b);
+                h[q] = a; l[q] = b;
             }
-            Xs[quad * XW + x] = h;
-            Xs[(NQ + quad) * XW + x] = l;
-        };
-#pragma unroll
-        for (int gq = 0; gq < NG; ++gq)
-            if (i0 + 16 * gq + 4 * wave < f)
-#pragma unroll
-                for (int it = 0; it < CT; ++it) put(raw[gq][it], 4 * gq + wave, 64 * it + lane);
-        if (t < 8 * NQ) put(halo, hq, 64 * CT + (t & 7));
-        __syncthreads();
+            half8* d = Xs + uq * XW + unit_x(n);
+            d[0] = __builtin_bit_cast(half8, h);
+            d[4 * XW] = __builtin_bit_cast(half8, l);
+        }
+        __builtin_amdgcn_wave_barrier();
         ++chunk;
     };
 
-    // position in the contraction: group of four quads inside the chunk, steps left in the group, and this lane group's
-    // slot (quad of the group, tap)
-    int grp = 0, left = 0, quad = 0, a = 0, qx = 0, QC = 4;      // qx = quad * XW
-    int ggrp = 0;
-    auto step = [&](int gs, const half8* as) {               // as: this lane group's kernel operands of the step
-        if (left == 0) {                                     // next group of up to sixteen images
-            if (grp == NG || ggrp == 0) { stage(); grp = 0; }
-            QC = min(4, ((f + 3) >> 2) - 4 * ggrp);
+    // position in the contraction: steps left in the chunk, and this lane group's slot (quad of the chunk, tap)
+    int left = 0, quad = 0, a = 0, qx = 0, QC = 4;           // qx = quad * XW
+    auto step = [&](const half8* as) {                       // as: this lane group's kernel operands of the step
+        if (left == 0) {                                     // next chunk of up to sixteen images
+            QC = min(4, ((f + 3) >> 2) - 4 * chunk);
             left = (K * QC + 3) >> 2;
-            quad = kk % QC; a = kk / QC; qx = quad * XW;
-            ++grp; ++ggrp;
+            quad = QC == 4 ? kk : QC == 3 ? (kk == 3 ? 0 : kk) : kk & (QC - 1);
+            a = QC == 4 ? 0 : QC == 3 ? (kk == 3) : kk >> (QC - 1);
+            qx = quad * XW;
+            stage();
         }
         --left;
-        const half8* xs = Xs + (4 * (grp - 1) * XW + wave * 16 * CT) + l16 + qx + max(K - 1 - a, 0);
+        const half8* xs = Xs + l16 + qx + max(K - 1 - a, 0);
         if (QC == 4) ++a;
         else {
-            quad += 4 % QC; a += 4 / QC;
+            quad += QC == 3; a += QC == 3 ? 1 : QC == 2 ? 2 : 4;
             if (quad >= QC) { quad -= QC; ++a; }
             qx = quad * XW;
         }
-        uintx4 xh[CT], xl[CT];
+        half8 ah[RT], al[RT];
 #pragma unroll
-        for (int c = 0; c < CT; ++c) {
-            xh[c] = __builtin_bit_cast(uintx4, xs[16 * c]);
-            xl[c] = __builtin_bit_cast(uintx4, xs[NQ * XW + 16 * c]);
-        }
-        auto neg = [](uintx4 v) { return __builtin_bit_cast(half8, v ^ 0x80000000u); };     // (r, i) -> (r, -i)
-        auto swp = [](uintx4 v) {                                                            // (r, i) -> (i, r)
-            uintx4 o;
+        for (int r = 0; r < RT; ++r) { ah[r] = as[r * 32]; al[r] = as[r * 32 + 16]; }
+        // (r, -i) -> (i, r), one packed instruction per register
+        auto swp = [](half8 v) {
+            half8 o;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = __builtin_amdgcn_alignbit(v[e], v[e], 16);
-            return __builtin_bit_cast(half8, o);
+            for (int e = 0; e < 4; ++e) {
+                const half2 p = half2{v[2 * e + 1], v[2 * e]} * half2{(_Float16)-1.f, (_Float16)1.f};
+                o[2 * e] = p[0]; o[2 * e + 1] = p[1];
+            }
+            return o;
         };
         // SUM: a step's three partial products are summed from zero, the small ones first, and added to the running sums by
         // vector instructions.  The matrix instruction rounds its running sum twice as coarsely as an addition does: over
         // 45 of them in a row (48 images, five taps) that is 2.1e-7 of the result, 0.6e-7 this way, for 8 % more time.
         const floatx4 zero = floatx4{0.f, 0.f, 0.f, 0.f};
 #define ZNNI_XD_MFMA(D, X, A, C) D = __builtin_amdgcn_mfma_f32_16x16x32_f16(X, A, C, 0, 0, 0)
-        if constexpr (CT <= RT) {                            // the two forms of an operand from the side with fewer tiles
-            half8 hr[CT], hi[CT], lr[CT], li[CT];
 #pragma unroll
-            for (int c = 0; c < CT; ++c) { hr[c] = neg(xh[c]); hi[c] = swp(xh[c]); lr[c] = neg(xl[c]); li[c] = swp(xl[c]); }
+        for (int c = 0; c < CT; ++c) {
+            const half8 hr = xs[16 * c], lr = xs[4 * XW + 16 * c];
+            const half8 hi = swp(hr), li = swp(lr);
+            constexpr int RG = RT == 4 ? 2 : 3;              // row tiles at a time: enough products that do not wait for each other
 #pragma unroll
-            for (int r = 0; r < RT; ++r) {
-                const half8 ah = as[r * 32], al = as[r * 32 + 16];
-                floatx4 tr[CT], ti[CT];
+            for (int r0 = 0; r0 < RT; r0 += RG) {
+                floatx4 tr[RG], ti[RG];
 #pragma unroll
-                for (int c = 0; c < CT; ++c) { tr[c] = SUM ? zero : re[r][c]; ti[c] = SUM ? zero : im[r][c]; }
+                for (int r = r0; r < RT && r < r0 + RG; ++r) { tr[r - r0] = SUM ? zero : re[r][c]; ti[r - r0] = SUM ? zero : im[r][c]; }
 #pragma unroll
-                for (int c = 0; c < CT; ++c) { ZNNI_XD_MFMA(tr[c], lr[c], ah, tr[c]); ZNNI_XD_MFMA(ti[c], li[c], ah, ti[c]); }
+                for (int r = r0; r < RT && r < r0 + RG; ++r) { ZNNI_XD_MFMA(tr[r - r0], ah[r], lr, tr[r - r0]); ZNNI_XD_MFMA(ti[r - r0], ah[r], li, ti[r - r0]); }
 #pragma unroll
-                for (int c = 0; c < CT; ++c) { ZNNI_XD_MFMA(tr[c], hr[c], al, tr[c]); ZNNI_XD_MFMA(ti[c], hi[c], al, ti[c]); }
+                for (int r = r0; r < RT && r < r0 + RG; ++r) { ZNNI_XD_MFMA(tr[r - r0], al[r], hr, tr[r - r0]); ZNNI_XD_MFMA(ti[r - r0], al[r], hi, ti[r - r0]); }
 #pragma unroll
-                for (int c = 0; c < CT; ++c) { ZNNI_XD_MFMA(tr[c], hr[c], ah, tr[c]); ZNNI_XD_MFMA(ti[c], hi[c], ah, ti[c]); }
+                for (int r = r0; r < RT && r < r0 + RG; ++r) { ZNNI_XD_MFMA(tr[r - r0], ah[r], hr, tr[r - r0]); ZNNI_XD_MFMA(ti[r - r0], ah[r], hi, ti[r - r0]); }
 #pragma unroll
-                for (int c = 0; c < CT; ++c) { re[r][c] = SUM ? re[r][c] + tr[c] : tr[c]; im[r][c] = SUM ? im[r][c] + ti[c] : ti[c]; }
-            }
-        } else {
-#pragma unroll
-            for (int r = 0; r < RT; ++r) {
-                const uintx4 ah = __builtin_bit_cast(uintx4, as[r * 32]), al = __builtin_bit_cast(uintx4, as[r * 32 + 16]);
-                const half8 hr = neg(ah), hi = swp(ah), lr = neg(al), li = swp(al);
-                floatx4 tr[CT], ti[CT];
-#pragma unroll
-                for (int c = 0; c < CT; ++c) { tr[c] = SUM ? zero : re[r][c]; ti[c] = SUM ? zero : im[r][c]; }
-#pragma unroll
-                for (int c = 0; c < CT; ++c) {
-                    ZNNI_XD_MFMA(tr[c], __builtin_bit_cast(half8, xl[c]), hr, tr[c]);
-                    ZNNI_XD_MFMA(ti[c], __builtin_bit_cast(half8, xl[c]), hi, ti[c]);
+                for (int r = r0; r < RT && r < r0 + RG; ++r) {
+                    re[r][c] = SUM ? re[r][c] + tr[r - r0] : tr[r - r0];
+                    im[r][c] = SUM ? im[r][c] + ti[r - r0] : ti[r - r0];
                 }
-#pragma unroll
-                for (int c = 0; c < CT; ++c) {
-                    ZNNI_XD_MFMA(tr[c], __builtin_bit_cast(half8, xh[c]), lr, tr[c]);
-                    ZNNI_XD_MFMA(ti[c], __builtin_bit_cast(half8, xh[c]), li, ti[c]);
-                }
-#pragma unroll
-                for (int c = 0; c < CT; ++c) {
-                    ZNNI_XD_MFMA(tr[c], __builtin_bit_cast(half8, xh[c]), hr, tr[c]);
-                    ZNNI_XD_MFMA(ti[c], __builtin_bit_cast(half8, xh[c]), hi, ti[c]);
-                }
-#pragma unroll
-                for (int c = 0; c < CT; ++c) { re[r][c] = SUM ? re[r][c] + tr[c] : tr[c]; im[r][c] = SUM ? im[r][c] + ti[c] : ti[c]; }
             }
         }
 #undef ZNNI_XD_MFMA
     };
-    // The first pair's operands are parked before its first chunk is staged (whose barriers publish them); from then on a
-    // pair's are parked while the pair before it is multiplied, into the half that was read before that.
+    // A pair's kernel operands are parked while the pair before it is multiplied, into the half that was read before that.
     park_a(0, 0);
     if (nsteps > 2) load_a();
     const half8* const as0 = As + kk * RT * 32 + l16;
     for (int gs = 0, buf = 0; gs < nsteps; gs += 2, buf ^= 1) {
-        if (gs) __syncthreads();                             // this pair's operands are in place, the last one's are free
-        step(gs, as0 + buf * RT * 256);
+        __syncthreads();                                     // this pair's operands are in place, the last one's are free
+        if (live) step(as0 + buf * RT * 256);
         if (gs + 2 < nsteps) {
             park_a(gs + 2, buf ^ 1);
             if (gs + 4 < nsteps) load_a();
         }
-        if (gs + 1 < nsteps) step(gs + 1, as0 + buf * RT * 256 + RT * 128);
+        if (live && gs + 1 < nsteps) step(as0 + buf * RT * 256 + RT * 128);
     }
+    if (!live) return;
 
     if (apart) {
         // All over again in fp32, from global memory, four slots of one complex image each per pair of matrix instructions
@@ -413,15 +361,15 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT, NG, SUM>())) void k_mac_xd(
             int qd, tap;
             xd_slot(sl, K, (f + 3) >> 2, qd, tap);
             const half8* ap = Ab + (size_t)sl * sstride + l16;
-            const float live = 4 * gs + kk < nslots ? sx : 0.f;
+            const float on = 4 * gs + kk < nslots ? sx : 0.f;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const float cs = 4 * qd + q < f ? live : 0.f;
-                const float2* row = xrow + (size_t)min(4 * qd + q, f - 1) * g.ximg;
+                const float cs = 4 * qd + q < f ? on : 0.f;
+                const float2* row = xrow + (size_t)(unsigned)min(4 * qd + q, f - 1) * g.ximg;
                 float2 x[CT];
 #pragma unroll
                 for (int c = 0; c < CT; ++c) {
-                    const float2 v = row[min(col0 + (wave * CT + c) * 16 + l16 + K - 1 - tap, g.nx - 1)];
+                    const float2 v = row[xoff(col0 + c * 16 + l16 + K - 1 - tap)];
                     x[c] = make_float2(v.x * cs, v.y * cs);
                 }
 #pragma unroll
@@ -430,40 +378,38 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT, NG, SUM>())) void k_mac_xd(
                     const float ar = (float)ah[0] + (float)al[0], ai = (float)ah[1] + (float)al[1];
 #pragma unroll
                     for (int c = 0; c < CT; ++c) {
-                        re[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[c].x, ar, re[r][c], 0, 0, 0);
-                        im[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[c].y, ar, im[r][c], 0, 0, 0);
-                        re[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(-x[c].y, ai, re[r][c], 0, 0, 0);
-                        im[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[c].x, ai, im[r][c], 0, 0, 0);
+                        re[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar, x[c].x, re[r][c], 0, 0, 0);
+                        im[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar, x[c].y, im[r][c], 0, 0, 0);
+                        re[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(ai, -x[c].y, re[r][c], 0, 0, 0);
+                        im[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(ai, x[c].x, im[r][c], 0, 0, 0);
                     }
                 }
             }
         }
     }
 
-    // ---- accumulator element e of lane (kk, l16): output xo = ... + 4 kk + e of output image ... + l16.  Rows of Yd are
-    // padded to 16 outputs, so a lane always stores its four.
+    // ---- accumulator element e of lane (kk, l16): output image ... + 4 kk + e, output xo = ... + l16: sixteen lanes store a
+    // run of 128 bytes.
     const float inv = pow2f(-sexp);
 #pragma unroll
     for (int r = 0; r < RT; ++r) {
-        const int j = (mblk * RT + r) * 16 + l16;
-        if (j >= g.fo) continue;
-        // the smaller factor first: either alone may be out of range where the result is not
-        const float f0 = fminf(inv, rj[r]), f1 = fmaxf(inv, rj[r]);
-        float2* y = g.Yd + (size_t)(sI * g.fo + j) * g.yimg + (size_t)poz * g.ypen + (size_t)poy * g.ldxo;
+        const int j0 = (mblk * RT + r) * 16 + 4 * kk;
+        const float4 rj = *reinterpret_cast<const float4*>(g.rinv + j0);
 #pragma unroll
-        for (int c = 0; c < CT; ++c) {
-            const int xo = col0 + (wave * CT + c) * 16 + 4 * kk;
-            if (xo >= g.nox) continue;
-            float4* d = reinterpret_cast<float4*>(y + xo);
-            float4 v0 = make_float4(re[r][c][0] * f0 * f1, im[r][c][0] * f0 * f1, re[r][c][1] * f0 * f1, im[r][c][1] * f0 * f1);
-            float4 v1 = make_float4(re[r][c][2] * f0 * f1, im[r][c][2] * f0 * f1, re[r][c][3] * f0 * f1, im[r][c][3] * f0 * f1);
-            if (g.accumulate) {
-                const float4 o0 = d[0], o1 = d[1];
-                v0.x += o0.x; v0.y += o0.y; v0.z += o0.z; v0.w += o0.w;
-                v1.x += o1.x; v1.y += o1.y; v1.z += o1.z; v1.w += o1.w;
+        for (int e = 0; e < 4; ++e) {
+            if (j0 + e >= g.fo) break;
+            // the smaller factor first: either alone may be out of range where the result is not
+            const float s = e == 0 ? rj.x : e == 1 ? rj.y : e == 2 ? rj.z : rj.w, f0 = fminf(inv, s), f1 = fmaxf(inv, s);
+            float2* y = g.Yd + (size_t)(unsigned)(sI * g.fo + j0 + e) * g.yimg + (size_t)poz * g.ypen + (size_t)poy * g.yrow;
+#pragma unroll
+            for (int c = 0; c < CT; ++c) {
+                const int xo = col0 + c * 16 + l16;
+                if (xo >= g.nox) continue;
+                float2* d = y + ((xo >> 2) * g.yblk + (xo & 3));
+                float2 v = make_float2(re[r][c][e] * f0 * f1, im[r][c][e] * f0 * f1);
+                if (g.accumulate) { const float2 o = *d; v.x += o.x; v.y += o.y; }
+                *d = v;
             }
-            d[0] = v0;
-            d[1] = v1;
         }
     }
 }
@@ -590,52 +536,57 @@ znni_status launch_kprep_xd(const LayerPlan& L, hipStream_t st)
 }
 
 // ---------------------------------------------------------------------------------------- host side
-// Widest tile of a row block (its sums, RT * CT * 8 registers a lane, leave room for two waves per SIMD) and images per
-// chunk in groups of sixteen.  Measured, multiply-accumulate alone: one group for up to four row tiles (40 -> 40 of 128^3,
-// 3^3 kernels 0.223 ms, two groups 0.269; 32 -> 32 of 200^3, 5^3 0.667 against 1.04), two for five (80 -> 80 of 128^3, 7^3
-// 1.18 ms, one group 1.25, three 1.55; 80 -> 80 of 200^3, 5^3 3.76, 3.84, 5.07).
-template <int RT, bool SUM> constexpr int xd_max_ct() { return RT >= 5 || (SUM && RT == 4) ? 2 : (RT >= 3 ? 3 : 4); }
-template <int RT> constexpr int xd_groups() { return RT >= 5 ? 2 : 1; }
+// Widest strip of a wave for a row block (its sums take RT * CT * 8 registers a lane and have to leave room for two waves
+// per SIMD).
+template <int RT> constexpr int xd_max_ct() { return RT >= 4 ? 3 : 5; }
 bool mac_xd_available(const LayerPlan& L) { return L.d.kx >= 1 && L.d.kx <= XD_MAX_K; }
 
 template <int RT, int CT, bool SUM>
-static znni_status launch_xd(const LayerPlan& L, int ncb, int accumulate, hipStream_t st)
+static znni_status launch_xd(const LayerPlan& L, int accumulate, hipStream_t st)
 {
     const Dims& d = L.d;
     XdArgs g;
     g.A = reinterpret_cast<const half8*>(L.A); g.rinv = split_scales(L).rinv;
-    g.ximg = (size_t)d.x2i * d.ldx; g.xpen = (size_t)d.x2o * d.ldx;
-    g.yimg = (size_t)d.ydi * d.ldxo; g.ypen = (size_t)d.ydo * d.ldxo;
-    g.S = L.S; g.f = L.f; g.fo = L.fo; g.Mp = L.Mp; g.K = d.kx;
-    g.nx = d.nx; g.nox = d.nox; g.ldx = d.ldx; g.ldxo = d.ldxo; g.Ny = d.Ny;
-    g.d_sub.set((unsigned)(ncb * L.S * L.mac_nmblk)); g.d_ncb.set((unsigned)ncb); g.d_S.set((unsigned)L.S); g.d_Ny.set((unsigned)d.Ny);
-    g.ncb = ncb; g.nmblk = L.mac_nmblk; g.npencils = L.ozn * d.Ny; g.accumulate = accumulate;
+    g.ximg = (unsigned)d.x2i * (unsigned)d.ldx; g.xpen = (size_t)d.x2o * d.ldx; g.xrow = d.ldx; g.xblk = 4;
+    g.yimg = (unsigned)d.ydi * (unsigned)d.ldxo; g.ypen = (size_t)d.ydo * d.ldxo; g.yrow = d.ldxo; g.yblk = 4;
+    g.f = L.f; g.fo = L.fo; g.Mp = L.Mp; g.K = d.kx;
+    g.nx = d.nx; g.nox = d.nox; g.Ny = d.Ny;
+    const int spr = ((d.nox + 15) / 16 + CT - 1) / CT, pg = 1;
+    g.nstrips = L.S * spr; g.npencils = L.ozn * d.Ny; g.accumulate = accumulate;
+    const int nwg = (g.nstrips + 3) / 4, nsub = nwg * L.mac_nmblk;
+    g.d_sub.set((unsigned)(nsub * pg)); g.d_pg.set((unsigned)pg); g.d_spr.set((unsigned)spr); g.d_nwg.set((unsigned)nwg);
+    g.d_Ny.set((unsigned)d.Ny);
     g.X2 = L.buf1 + (size_t)L.oz0 * g.xpen; g.Yd = L.Yt + (size_t)L.oz0 * g.ypen;
-    const long long blocks = (long long)((g.npencils + 7) / 8) * ncb * L.S * g.nmblk * 8;
+    const long long blocks = (long long)((g.npencils + 8 * pg - 1) / (8 * pg)) * nsub * pg * 8;
     if (blocks > 0x7fffffffll) return ZNNI_ERR_SHAPE;
-    constexpr int NG = xd_groups<RT>();
-    constexpr size_t lds = xd_lds_bytes<RT, CT, NG>();
-    if (lds > 48 * 1024 && hipFuncSetAttribute((const void*)k_mac_xd<RT, CT, NG, SUM>,
+    constexpr size_t lds = xd_lds_bytes<RT, CT>();
+    if (lds > 48 * 1024 && hipFuncSetAttribute((const void*)k_mac_xd<RT, CT, SUM>,
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
         return ZNNI_ERR_HIP;
-    k_mac_xd<RT, CT, NG, SUM><<<dim3((unsigned)blocks), dim3(256), lds, st>>>(g);
+    k_mac_xd<RT, CT, SUM><<<dim3((unsigned)blocks), dim3(256), lds, st>>>(g);
     if (hipGetLastError() != hipSuccess) return ZNNI_ERR_HIP;
     return ZNNI_OK;
 }
 
-// Columns: as few workgroups per row as the widest tile allows (its sums, RT * CT * 8 registers per lane, leave room for
-// two waves per SIMD), then the narrowest tile that still covers the row with that many.
+// Columns: the strip width that computes the fewest column tiles (strips are dealt four to a workgroup), the wider one of
+// two that tie.
 template <int RT, bool SUM>
 static znni_status launch_xd_cols_s(const LayerPlan& L, int accumulate, hipStream_t st)
 {
-    constexpr int MAXCT = xd_max_ct<RT, SUM>();
-    const int t64 = (L.d.nox + 63) / 64;                     // 64 outputs: one column tile per wave
-    const int ncb = (t64 + MAXCT - 1) / MAXCT, CT = (t64 + ncb - 1) / ncb;
+    constexpr int MAXCT = xd_max_ct<RT>();
+    const int tiles = (L.d.nox + 15) / 16;
+    int CT = 1;
+    long long best = -1;
+    for (int c = 1; c <= MAXCT; ++c) {
+        const long long n = ((long long)L.S * ((tiles + c - 1) / c) + 3) / 4 * 4 * c;
+        if (best < 0 || n <= best) { best = n; CT = c; }
+    }
     switch (CT) {
-        case 1: return launch_xd<RT, 1, SUM>(L, ncb, accumulate, st);
-        case 2: if constexpr (MAXCT >= 2) return launch_xd<RT, 2, SUM>(L, ncb, accumulate, st); break;
-        case 3: if constexpr (MAXCT >= 3) return launch_xd<RT, 3, SUM>(L, ncb, accumulate, st); break;
-        case 4: if constexpr (MAXCT >= 4) return launch_xd<RT, 4, SUM>(L, ncb, accumulate, st); break;
+        case 1: return launch_xd<RT, 1, SUM>(L, accumulate, st);
+        case 2: return launch_xd<RT, 2, SUM>(L, accumulate, st);
+        case 3: return launch_xd<RT, 3, SUM>(L, accumulate, st);
+        case 4: if constexpr (MAXCT >= 4) return launch_xd<RT, 4, SUM>(L, accumulate, st); break;
+        case 5: if constexpr (MAXCT >= 5) return launch_xd<RT, 5, SUM>(L, accumulate, st); break;
     }
     return ZNNI_ERR_SHAPE;
 }

@@ -37,6 +37,16 @@ __device__ __forceinline__ void split2(float v, float s, _Float16& hi, _Float16&
     lo = (_Float16)fmaf(v, s, -(float)hi);
 }
 
+// (x, -y) as two pairs of halves, the same values as split2 gives: every half leaves one mixed-precision instruction where
+// it belongs (a product, its conversion, the difference and the packing of pairs took three a value).
+__device__ __forceinline__ void split_conj(float x, float y, float s, unsigned& hi, unsigned& lo)
+{
+    asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(hi) : "v"(x), "v"(s));
+    asm("v_fma_mixhi_f16 %0, -%1, %2, 0" : "+v"(hi) : "v"(y), "v"(s));
+    asm("v_fma_mixlo_f16 %0, %1, %2, -%3 op_sel_hi:[0,0,1]" : "=v"(lo) : "v"(x), "v"(s), "v"(hi));
+    asm("v_fma_mixhi_f16 %0, -%1, %2, -%3 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "+v"(lo) : "v"(y), "v"(s), "v"(hi));
+}
+
 // A value of 2^-17 of the largest still has all its 22 bits; below that a bit goes with every power of two.  Where a value
 // (that is not zero) lies more than 2^-SPLIT_SPAN below the largest of its group, the group is multiplied in fp32.
 constexpr int SPLIT_SPAN = 19;
