@@ -231,8 +231,7 @@ def main():
     # the work of the kernels that actually ran (fused kernels and skipped stages priced as such); the form without x
     # transform runs on fp16 matrix instructions with split values, three partial products per product
     nbytes, nflops = B.znni_conv3d_fft_stage_work(S, f, fo, n, k, relu=layer.relu, mac_reference=route)
-    split = nflops["mac"] == B.znni_conv3d_fft_stage_work(S, f, fo, n, k, mac_reference="xdirect")[1]["mac"] and \
-        nflops["mac"] != B.znni_conv3d_fft_stage_work(S, f, fo, n, k, mac_reference="single")[1]["mac"]
+    split = nbytes["fwd_x"] == 0 and route != "xblock"
     mac_peak = MFMA_FP16_PEAK_TFLOPS / 3 if split else MFMA_FP32_PEAK_TFLOPS
     stages = {}
     for s_ in B.STAGES:

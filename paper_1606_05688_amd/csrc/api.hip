@@ -94,9 +94,29 @@ static bool pick_xblock(const LayerPlan& L, unsigned flags)
 // Internal flag: the x axis is transformed at full length, the multiply-accumulate form is the library's choice.
 constexpr unsigned ROUTE_FULL_X = 1u << 30;
 
+// Whether a batch of small images goes untransformed along x with its z and y transforms done four planes at a time: two
+// kernels around the multiply-accumulate where the fully transformed route has four, products on split halves instead of
+// fp32.  Against that stand kx products per output column (of whole column tiles) instead of about one per bin.  So its
+// products, at the rate its multiply-accumulate reaches, are held against the other form's spectrum values and the two x
+// passes.  Over 140 random batches of 8 to 64 inputs (lengths up to 64, 2 to 96 images, 1 to 9 taps) that go
+// here 1.3 times as fast as on the fully transformed route on average, the worst 4 % behind (25 x 84 -> 8 of 29^3, 8 x 4 x 5
+// kernels); 64 x 80 -> 80 of 51^3, 5^3 7.1 against 9.7 ms; 8 x 32 -> 32 of 64^3, 7^3
+// 0.51 against 0.67.  From eight inputs on; for fewer the two routes of before are as they were.
+static bool pick_planes(const LayerPlan& L, unsigned flags)
+{
+    if (flags & (ROUTE_FULL_X | ZNNI_MAC_REFERENCE | ZNNI_MAC_SINGLE | ZNNI_MAC_BATCH | ZNNI_MAC_XDIRECT | ZNNI_MAC_XBLOCK)) return false;
+    if (L.S < 8 || !mac_xd_available(L) || !fused_planes_available(L)) return false;
+    const Dims& d = L.d;
+    const double pairs = (double)L.fp * L.Mp;
+    const double products = 24.0 * d.kx * ((d.nox + 15) & ~15) * pairs * L.S / 0.7e15;
+    const double batch = 1.7e-12 * pairs * d.Nx * ((L.S + 15) / 16);
+    const double passes = 8.0 * ((double)L.nimg * (d.nx + d.Nx) + (double)L.nimgo * (d.Nx + d.nox)) / 5e12;
+    return products < batch + passes;
+}
+
 static bool pick_xdirect(const LayerPlan& L, unsigned flags)
 {
-    if (L.xblock) return true;
+    if (L.xblock || L.planes) return true;
     if (flags & ROUTE_FULL_X) return false;
     if (L.generic_passes || !mac_xd_available(L) || !fast_pass_available(L.d.Ny)) return false;
     if (flags & ZNNI_MAC_XDIRECT) return true;
@@ -139,6 +159,7 @@ static znni_status shape_plan(int S, int f, int fo, const int n[3], const int k[
     plan_mac(L);        // also sets Mp
     L->generic_passes = (flags & ZNNI_PASSES_REFERENCE) != 0;
     L->xblock = pick_xblock(*L, flags);
+    L->planes = pick_planes(*L, flags);
     L->xdirect = pick_xdirect(*L, flags);
     // X2 and Yd are ordered [image][oz][oy]; the order [oz][image][oy] was measured too: 2 % faster for the
     // multiply-accumulate that reads X2 and writes Yd, 6 % slower for the y passes on the other side of them
@@ -334,6 +355,20 @@ static znni_status validate(int S, int f, int fo, const int n[3], const int k[3]
         if (rc) return rc;     \
     } while (0)
 
+// The transforms before and after the multiply-accumulate of a layer whose x axis is not transformed.
+static znni_status fwd_untransformed_x(const LayerPlan& L, const float* in, hipStream_t st)
+{
+    if (L.planes) return launch_fwd_zy_planes(L, in, st);
+    const znni_status rc = launch_fwd_z(L, in, st);
+    return rc ? rc : launch_fwd_y(L, st);
+}
+static znni_status inv_untransformed_x(const LayerPlan& L, const float* bias, float* out, unsigned flags, hipStream_t st)
+{
+    if (L.planes) return launch_inv_yz_planes(L, bias, out, flags, st);
+    const znni_status rc = launch_fast_inv_yt(L, st);
+    return rc ? rc : launch_inv_z(L, bias, out, flags, st);
+}
+
 // Runs the stages in order; if ev != NULL records ev[s] before stage s and ev[ZNNI_NUM_STAGES] at the end.
 static znni_status run(const LayerPlan& L, const float* in, const float* w, const float* bias, float* out,
                        unsigned flags, hipStream_t st, hipEvent_t* ev)
@@ -351,17 +386,17 @@ static znni_status run(const LayerPlan& L, const float* in, const float* w, cons
     if (L.xdirect) {
         // x axis not transformed: the x stages do nothing and read about zero
         ZNNI_MARK(ZNNI_STAGE_FWD_Z);
-        ZNNI_DO(launch_fwd_z(L, in, st));
+        ZNNI_DO(L.planes ? launch_fwd_zy_planes(L, in, st) : launch_fwd_z(L, in, st));
         ZNNI_MARK(ZNNI_STAGE_FWD_Y);
-        ZNNI_DO(launch_fwd_y(L, st));
+        if (!L.planes) ZNNI_DO(launch_fwd_y(L, st));
         ZNNI_MARK(ZNNI_STAGE_FWD_X);
         ZNNI_MARK(ZNNI_STAGE_MAC);
         ZNNI_DO(L.xblock ? launch_mac_xb(L, 0, st) : launch_mac_xd(L, 0, st));
         ZNNI_MARK(ZNNI_STAGE_INV_X);
         ZNNI_MARK(ZNNI_STAGE_INV_Y);
-        ZNNI_DO(launch_fast_inv_yt(L, st));
+        ZNNI_DO(L.planes ? launch_inv_yz_planes(L, bias, out, flags, st) : launch_fast_inv_yt(L, st));
         ZNNI_MARK(ZNNI_STAGE_INV_Z);
-        ZNNI_DO(launch_inv_z(L, bias, out, flags, st));
+        if (!L.planes) ZNNI_DO(launch_inv_z(L, bias, out, flags, st));
         ZNNI_MARK(ZNNI_NUM_STAGES);
         return ZNNI_OK;
     }
@@ -431,8 +466,7 @@ static znni_status run_divided(const Division& D, int S, int f, int fo, const in
                 ZNNI_DO(launch_kernel_prep(L, wsub, (size_t)f * kvol, st));
                 const float* isub = in + ((size_t)s0 * f + i0) * nvox;
                 if (L.xdirect) {
-                    ZNNI_DO(launch_fwd_z(L, isub, st));
-                    ZNNI_DO(launch_fwd_y(L, st));
+                    ZNNI_DO(fwd_untransformed_x(L, isub, st));
                     ZNNI_DO(L.xblock ? launch_mac_xb(L, i0 > 0, st) : launch_mac_xd(L, i0 > 0, st));
                     continue;
                 }
@@ -449,8 +483,7 @@ static znni_status run_divided(const Division& D, int S, int f, int fo, const in
             const float* bsub = bias ? bias + j0 : nullptr;
             float* osub = out + ((size_t)s0 * fo + j0) * ovox;
             if (L.xdirect) {
-                ZNNI_DO(launch_fast_inv_yt(L, st));
-                ZNNI_DO(launch_inv_z(L, bsub, osub, flags, st));
+                ZNNI_DO(inv_untransformed_x(L, bsub, osub, flags, st));
                 continue;
             }
             ZNNI_DO(launch_inv_x(L, st));
@@ -500,15 +533,13 @@ static znni_status run_slabs(LayerPlan L, int rows, const float* in, const float
     const size_t bank = (size_t)L.f * L.d.kx * L.d.ky * L.d.kz;
     ZNNI_DO(launch_twiddles(L, w, bank, st));
     ZNNI_DO(launch_kernel_prep_z(L, w, bank, st));
-    ZNNI_DO(launch_fwd_z(L, in, st));
-    ZNNI_DO(launch_fwd_y(L, st));
+    ZNNI_DO(fwd_untransformed_x(L, in, st));
     for (L.oz0 = 0; L.oz0 < L.d.zc; L.oz0 += rows) {
         L.ozn = L.d.zc - L.oz0 < rows ? L.d.zc - L.oz0 : rows;
         ZNNI_DO(launch_kernel_prep_y(L, st));
         ZNNI_DO(L.xblock ? launch_mac_xb(L, 0, st) : launch_mac_xd(L, 0, st));
     }
-    ZNNI_DO(launch_fast_inv_yt(L, st));
-    return launch_inv_z(L, bias, out, flags, st);
+    return inv_untransformed_x(L, bias, out, flags, st);
 }
 #undef ZNNI_DO
 
@@ -603,7 +634,7 @@ znni_status znni_conv3d_fft_stage_work_v(int S, int f, int fo, const int n[3], c
     const double a = c * zc * d.Ny * (double)f * fo * (L.xblock ? 8 : d.kx);
     for (int q = 0; q < ZNNI_NUM_STAGES; ++q) hbm_bytes[q] = flops[q] = 0.0;
     if (!(flags & ZNNI_KEEP_KERNELS)) hbm_bytes[ZNNI_STAGE_KERNEL_PREP] = 4.0 * f * fo * d.kx * d.ky * d.kz + a;
-    const bool fused_zy = !L.xdirect && fused_fwd_zy_available(L), fused_yz = !L.xdirect && fused_inv_yz_available(L);
+    const bool fused_zy = L.planes || (!L.xdirect && fused_fwd_zy_available(L)), fused_yz = L.planes || (!L.xdirect && fused_inv_yz_available(L));
     if (fused_zy) hbm_bytes[ZNNI_STAGE_FWD_Z] = ni * (4.0 * vox + x2);
     else {
         hbm_bytes[ZNNI_STAGE_FWD_Z] = ni * (4.0 * vox + x1);
@@ -619,6 +650,8 @@ znni_status znni_conv3d_fft_stage_work_v(int S, int f, int fo, const int n[3], c
         const double bins = zc * d.Ny * d.nox;
         hbm_bytes[ZNNI_STAGE_MAC] = ni * x2 + a + no * y2;
         flops[ZNNI_STAGE_MAC] = 8.0 * d.kx * S * (double)f * fo * bins;
+        // rows in blocks of four: the products of whole blocks
+        if (L.planes) flops[ZNNI_STAGE_MAC] = 8.0 * d.kx * S * (double)f * fo * zc * d.Ny * ((d.nox + 3) / 4 * 4);
         if (L.xblock) {
             // one length-8 product per block of V = 9 - kx outputs
             const int V = 9 - d.kx;

@@ -91,7 +91,7 @@ struct XdArgs {
 
 constexpr int XD_MAX_K = 9;     // taps along x at most: the halo of a staged row
 template <int RT, int CT>
-constexpr size_t xd_lds_bytes() { return (size_t)16 * (4 * 8 * (16 * CT + 16) + 4 * 128 * RT); }
+constexpr size_t xd_lds_bytes() { return (size_t)16 * (4 * 8 * (16 * CT + 16) + 4 * 128 * RT + 4 * RT); }
 // Three workgroups per CU where LDS and registers (168 a lane) allow, two otherwise.
 template <int RT, int CT>
 constexpr int xd_blocks() { return xd_lds_bytes<RT, CT>() <= 53 * 1024 && RT * CT <= 6 ? 3 : 2; }
@@ -105,8 +105,8 @@ __device__ __forceinline__ void xd_slot(int slot, int K, int fq, int& quad, int&
     quad = 4 * c + s - a * QC;
 }
 
-template <int RT, int CT, bool SUM>
-__global__ __launch_bounds__(256, (xd_blocks<RT, CT>())) void k_mac_xd(XdArgs g)
+template <int RT, int CT, bool SUM, bool PLANES>
+__device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
 {
     // staged columns of a strip (its outputs and their halo) and the pitch of an image quad (rows start on the same bank:
     // the sixteen-lane groups of a 16-byte LDS read then share no bank in any phase)
@@ -114,8 +114,14 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT>())) void k_mac_xd(XdArgs g)
     // Rounds of a wave over a strip's units: strips of three column tiles and more take a quad per round (its image rows are
     // then scalar addresses) and the columns beyond 64 of all quads in further ones.
     constexpr int XH = CT >= 3 ? (XN > 64 ? XN - 64 : 0) : XN, NQ = CT >= 3 ? 4 : 0, NR = NQ + (4 * XH + 63) / 64;
+    // Whether the four sums of an accumulator are neighbouring outputs of one image, stored as 32 bytes a lane, or outputs
+    // of four images, stored as 128 bytes of an image by sixteen lanes.  The latter takes 2 to 3 % less from three row tiles
+    // on and in planes (8 x 32 -> 32 of 64^3, 7^3 0.26 against 0.30 ms), the former below (7 -> 9 of 150 x 142 x 95 57 against 60 us).
+    constexpr bool XROWS = RT <= 2 && !PLANES;
+    // Where registers allow, the first chunk's rows are requested before anything is waited for, and the rows of the next
+    // chunk while one is multiplied.
+    constexpr bool EARLY = RT * CT <= 10, AHEAD = RT <= 2 && RT * CT <= 8;
     static_assert(XD_MAX_K - 1 <= 8, "the halo is eight columns");
-    extern __shared__ half8 lds[];
     half8* const As = lds;                                   // [two pairs of steps][slot kk][row tile][hi, lo][16]
 
     // (the integer divisions of a workgroup's start cost as much as a matrix step: high products instead)
@@ -134,6 +140,7 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT>())) void k_mac_xd(XdArgs g)
     const int K = g.K, f = g.f;
     const int poz = (int)g.d_Ny.div((unsigned)pencil), poy = pencil - poz * g.Ny;
     half8* const Xs = lds + 4 * RT * 128 + wave * 8 * XW;    // this wave's own: [hi, lo][quad][XW]
+    float* const rjs = reinterpret_cast<float*>(lds + 4 * RT * 128 + 32 * XW);          // [RT * 16]
 
     // ---- kernel operands: this thread's share of a step, NU units of 16 bytes (surplus units repeat the last one).
     // Slots past the last one are read from it.
@@ -191,7 +198,9 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT>())) void k_mac_xd(XdArgs g)
     load_a();
 
     const float2* xrow = g.X2 + (size_t)(unsigned)(sI * f) * g.ximg + (size_t)poz * g.xpen + (size_t)poy * g.xrow;
-    auto xoff = [&](int x) { x = min(x, g.nx - 1); return (x >> 2) * g.xblk + (x & 3); };
+    const int xlast = min(g.nx, col0 + 16 * CT + K - 1) - 1;     // last column any of the strip's outputs needs
+    auto xoff = [&](int x) { x = min(x, xlast); return (x >> 2) * g.xblk + (x & 3); };
+    int QC = 4;                                              // image quads of the chunk
     auto unit_q = [&](int n) { return n < NQ ? n : min(lane + 64 * (n - NQ), 4 * XH - 1) / max(XH, 1); };
     auto unit_x = [&](int n) { return n < NQ ? min(lane, XN - 1) : (NQ ? 64 : 0) + min(lane + 64 * (n - NQ), 4 * XH - 1) % max(XH, 1); };
     int sexp = 126;                                          // exponent of the scale the image values carry
@@ -199,11 +208,18 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT>())) void k_mac_xd(XdArgs g)
     bool apart = false;                                      // magnitudes along x too far apart for halves
     // One chunk of sixteen images of the strip to LDS, a (quad, x) unit per lane and round.  Values beyond a row are read
     // from its end, images beyond the last from the last: neither reaches a stored output (the images count as zeros).
-    auto stage = [&]() {
-        const int i0 = chunk * 16;
-        float2 raw[NR][4];
+    auto round = [&](int n, int qc) { return n < NQ ? n < qc : 64 * (n - NQ) < qc * XH; };
+    float2 raw[NR][4];
+    auto request = [&]() {
+        const int i0 = chunk * 16, qc = min(4, ((f + 3) >> 2) - 4 * chunk);
+        // (rounds of quads beyond the last image are neither read nor staged: no lane group's slot names them)
 #pragma unroll
         for (int n = 0; n < NR; ++n) {
+            if (!round(n, qc)) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) raw[n][q] = make_float2(0.f, 0.f);
+                continue;
+            }
             const int uq = unit_q(n);
             const unsigned off = 8u * (unsigned)xoff(col0 + unit_x(n));
 #pragma unroll
@@ -211,6 +227,9 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT>())) void k_mac_xd(XdArgs g)
                 raw[n][q] = *reinterpret_cast<const float2*>(
                     reinterpret_cast<const char*>(xrow + (size_t)(unsigned)min(i0 + 4 * uq + q, f - 1) * g.ximg) + off);
         }
+    };
+    auto stage = [&]() {
+        const int i0 = chunk * 16;
         // largest magnitude, and the code of the smallest: of the images of a unit together, since their products
         // are added up (an image far below the others, say of rounding errors only, is no reason to leave halves)
         float m = 0.f;
@@ -255,6 +274,7 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT>())) void k_mac_xd(XdArgs g)
         const float sx = pow2f(sn);
 #pragma unroll
         for (int n = 0; n < NR; ++n) {
+            if (!round(n, QC)) continue;
             const int uq = unit_q(n);
             uintx4 h, l;
 #pragma unroll
@@ -272,7 +292,7 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT>())) void k_mac_xd(XdArgs g)
     };
 
     // position in the contraction: steps left in the chunk, and this lane group's slot (quad of the chunk, tap)
-    int left = 0, quad = 0, a = 0, qx = 0, QC = 4;           // qx = quad * XW
+    int left = 0, quad = 0, a = 0, qx = 0;                   // qx = quad * XW
     auto step = [&](const half8* as) {                       // as: this lane group's kernel operands of the step
         if (left == 0) {                                     // next chunk of up to sixteen images
             QC = min(4, ((f + 3) >> 2) - 4 * chunk);
@@ -280,7 +300,9 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT>())) void k_mac_xd(XdArgs g)
             quad = QC == 4 ? kk : QC == 3 ? (kk == 3 ? 0 : kk) : kk & (QC - 1);
             a = QC == 4 ? 0 : QC == 3 ? (kk == 3) : kk >> (QC - 1);
             qx = quad * XW;
+            if (!(chunk ? AHEAD : EARLY)) request();
             stage();
+            if (AHEAD && 16 * chunk < f) request();
         }
         --left;
         const half8* xs = Xs + l16 + qx + max(K - 1 - a, 0);
@@ -307,7 +329,7 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT>())) void k_mac_xd(XdArgs g)
         // vector instructions.  The matrix instruction rounds its running sum twice as coarsely as an addition does: over
         // 45 of them in a row (48 images, five taps) that is 2.1e-7 of the result, 0.6e-7 this way, for 8 % more time.
         const floatx4 zero = floatx4{0.f, 0.f, 0.f, 0.f};
-#define ZNNI_XD_MFMA(D, X, A, C) D = __builtin_amdgcn_mfma_f32_16x16x32_f16(X, A, C, 0, 0, 0)
+#define ZNNI_XD_MFMA(D, A, X, C) D = XROWS ? __builtin_amdgcn_mfma_f32_16x16x32_f16(X, A, C, 0, 0, 0) : __builtin_amdgcn_mfma_f32_16x16x32_f16(A, X, C, 0, 0, 0)
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
             const half8 hr = xs[16 * c], lr = xs[4 * XW + 16 * c];
@@ -334,6 +356,8 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT>())) void k_mac_xd(XdArgs g)
 #undef ZNNI_XD_MFMA
     };
     // A pair's kernel operands are parked while the pair before it is multiplied, into the half that was read before that.
+    if (EARLY && live) request();                            // (the first chunk's rows and kernel operands travel together)
+    if (t < RT * 16) rjs[t] = g.rinv[mblk * RT * 16 + t];
     park_a(0, 0);
     if (nsteps > 2) load_a();
     const half8* const as0 = As + kk * RT * 32 + l16;
@@ -378,40 +402,80 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT>())) void k_mac_xd(XdArgs g)
                     const float ar = (float)ah[0] + (float)al[0], ai = (float)ah[1] + (float)al[1];
 #pragma unroll
                     for (int c = 0; c < CT; ++c) {
-                        re[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar, x[c].x, re[r][c], 0, 0, 0);
-                        im[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar, x[c].y, im[r][c], 0, 0, 0);
-                        re[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(ai, -x[c].y, re[r][c], 0, 0, 0);
-                        im[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(ai, x[c].x, im[r][c], 0, 0, 0);
+                        auto mm = [](float p, float v, floatx4& d) {
+                            d = XROWS ? __builtin_amdgcn_mfma_f32_16x16x4f32(v, p, d, 0, 0, 0) : __builtin_amdgcn_mfma_f32_16x16x4f32(p, v, d, 0, 0, 0);
+                        };
+                        mm(ar, x[c].x, re[r][c]);
+                        mm(ar, x[c].y, im[r][c]);
+                        mm(ai, -x[c].y, re[r][c]);
+                        mm(ai, x[c].x, im[r][c]);
                     }
                 }
             }
         }
     }
 
-    // ---- accumulator element e of lane (kk, l16): output image ... + 4 kk + e, output xo = ... + l16: sixteen lanes store a
-    // run of 128 bytes.
+    // ---- results.  The smaller factor first: either alone may be out of range where the result is not.  Rows of Yd are
+    // padded to whole fours.
     const float inv = pow2f(-sexp);
+    float2* const ypen = g.Yd + (size_t)poz * g.ypen + (size_t)poy * g.yrow;
 #pragma unroll
     for (int r = 0; r < RT; ++r) {
-        const int j0 = (mblk * RT + r) * 16 + 4 * kk;
-        const float4 rj = *reinterpret_cast<const float4*>(g.rinv + j0);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            if (j0 + e >= g.fo) break;
-            // the smaller factor first: either alone may be out of range where the result is not
-            const float s = e == 0 ? rj.x : e == 1 ? rj.y : e == 2 ? rj.z : rj.w, f0 = fminf(inv, s), f1 = fmaxf(inv, s);
-            float2* y = g.Yd + (size_t)(unsigned)(sI * g.fo + j0 + e) * g.yimg + (size_t)poz * g.ypen + (size_t)poy * g.yrow;
+        const int j0 = (mblk * RT + r) * 16;
+        if constexpr (XROWS) {                               // element e of lane (kk, l16): image l16, output 4 kk + e
+            if (j0 + l16 >= g.fo) continue;
+            const float s = rjs[r * 16 + l16], f0 = fminf(inv, s), f1 = fmaxf(inv, s);
+            float2* y = ypen + (size_t)(unsigned)(sI * g.fo + j0 + l16) * g.yimg;
 #pragma unroll
             for (int c = 0; c < CT; ++c) {
-                const int xo = col0 + c * 16 + l16;
+                const int xo = col0 + c * 16 + 4 * kk;
                 if (xo >= g.nox) continue;
-                float2* d = y + ((xo >> 2) * g.yblk + (xo & 3));
-                float2 v = make_float2(re[r][c][e] * f0 * f1, im[r][c][e] * f0 * f1);
-                if (g.accumulate) { const float2 o = *d; v.x += o.x; v.y += o.y; }
-                *d = v;
+                float4* d = reinterpret_cast<float4*>(y + xo);
+                float4 v0 = make_float4(re[r][c][0] * f0 * f1, im[r][c][0] * f0 * f1, re[r][c][1] * f0 * f1, im[r][c][1] * f0 * f1);
+                float4 v1 = make_float4(re[r][c][2] * f0 * f1, im[r][c][2] * f0 * f1, re[r][c][3] * f0 * f1, im[r][c][3] * f0 * f1);
+                if (g.accumulate) {
+                    const float4 o0 = d[0], o1 = d[1];
+                    v0.x += o0.x; v0.y += o0.y; v0.z += o0.z; v0.w += o0.w;
+                    v1.x += o1.x; v1.y += o1.y; v1.z += o1.z; v1.w += o1.w;
+                }
+                d[0] = v0;
+                d[1] = v1;
+            }
+        } else {                                             // ... image 4 kk + e, output l16
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int j = j0 + 4 * kk + e;
+                if (j >= g.fo) break;
+                const float s = rjs[r * 16 + 4 * kk + e], f0 = fminf(inv, s), f1 = fmaxf(inv, s);
+                float2* y = ypen + (size_t)(unsigned)(sI * g.fo + j) * g.yimg;
+#pragma unroll
+                for (int c = 0; c < CT; ++c) {
+                    const int xo = col0 + c * 16 + l16;
+                    if (xo >= g.nox) continue;
+                    float2* d = y + ((xo >> 2) * g.yblk + (xo & 3));
+                    float2 v = make_float2(re[r][c][e] * f0 * f1, im[r][c][e] * f0 * f1);
+                    if (g.accumulate) { const float2 o = *d; v.x += o.x; v.y += o.y; }
+                    *d = v;
+                }
             }
         }
     }
+}
+
+// Rows of X2 and Yd along x.
+template <int RT, int CT, bool SUM>
+__global__ __launch_bounds__(256, (xd_blocks<RT, CT>())) void k_mac_xd(XdArgs g)
+{
+    extern __shared__ half8 lds[];
+    xd_body<RT, CT, SUM, false>(g, lds);
+}
+// Rows in blocks of four x, a block of every oy after the other, as the kernels of passes_fused.hip that take four planes
+// leave and read them.  Four neighbouring pencils share every cache line: they are neighbours on one XCD.
+template <int RT, int CT>
+__global__ __launch_bounds__(256, (xd_blocks<RT, CT>())) void k_mac_planes(XdArgs g)
+{
+    extern __shared__ half8 lds[];
+    xd_body<RT, CT, true, true>(g, lds);
 }
 
 // ---------------------------------------------------------------------------------------- kernel transform
@@ -541,17 +605,23 @@ znni_status launch_kprep_xd(const LayerPlan& L, hipStream_t st)
 template <int RT> constexpr int xd_max_ct() { return RT >= 4 ? 3 : 5; }
 bool mac_xd_available(const LayerPlan& L) { return L.d.kx >= 1 && L.d.kx <= XD_MAX_K; }
 
-template <int RT, int CT, bool SUM>
+template <int RT, int CT, bool SUM, bool PLANES>
 static znni_status launch_xd(const LayerPlan& L, int accumulate, hipStream_t st)
 {
     const Dims& d = L.d;
     XdArgs g;
     g.A = reinterpret_cast<const half8*>(L.A); g.rinv = split_scales(L).rinv;
-    g.ximg = (unsigned)d.x2i * (unsigned)d.ldx; g.xpen = (size_t)d.x2o * d.ldx; g.xrow = d.ldx; g.xblk = 4;
-    g.yimg = (unsigned)d.ydi * (unsigned)d.ldxo; g.ypen = (size_t)d.ydo * d.ldxo; g.yrow = d.ldxo; g.yblk = 4;
+    if (PLANES) {
+        const unsigned nb = (unsigned)(d.nx + 3) / 4, nbo = (unsigned)(d.nox + 3) / 4;
+        g.xpen = (size_t)nb * d.Ny * 4; g.ximg = d.zc * (unsigned)g.xpen; g.xrow = 4; g.xblk = d.Ny * 4;
+        g.ypen = (size_t)nbo * d.Ny * 4; g.yimg = d.zc * (unsigned)g.ypen; g.yrow = 4; g.yblk = d.Ny * 4;
+    } else {
+        g.ximg = (unsigned)d.x2i * (unsigned)d.ldx; g.xpen = (size_t)d.x2o * d.ldx; g.xrow = d.ldx; g.xblk = 4;
+        g.yimg = (unsigned)d.ydi * (unsigned)d.ldxo; g.ypen = (size_t)d.ydo * d.ldxo; g.yrow = d.ldxo; g.yblk = 4;
+    }
     g.f = L.f; g.fo = L.fo; g.Mp = L.Mp; g.K = d.kx;
     g.nx = d.nx; g.nox = d.nox; g.Ny = d.Ny;
-    const int spr = ((d.nox + 15) / 16 + CT - 1) / CT, pg = 1;
+    const int spr = ((d.nox + 15) / 16 + CT - 1) / CT, pg = PLANES ? 4 : 1;
     g.nstrips = L.S * spr; g.npencils = L.ozn * d.Ny; g.accumulate = accumulate;
     const int nwg = (g.nstrips + 3) / 4, nsub = nwg * L.mac_nmblk;
     g.d_sub.set((unsigned)(nsub * pg)); g.d_pg.set((unsigned)pg); g.d_spr.set((unsigned)spr); g.d_nwg.set((unsigned)nwg);
@@ -560,17 +630,20 @@ static znni_status launch_xd(const LayerPlan& L, int accumulate, hipStream_t st)
     const long long blocks = (long long)((g.npencils + 8 * pg - 1) / (8 * pg)) * nsub * pg * 8;
     if (blocks > 0x7fffffffll) return ZNNI_ERR_SHAPE;
     constexpr size_t lds = xd_lds_bytes<RT, CT>();
-    if (lds > 48 * 1024 && hipFuncSetAttribute((const void*)k_mac_xd<RT, CT, SUM>,
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+    void (*kernel)(XdArgs);
+    if constexpr (PLANES) kernel = k_mac_planes<RT, CT>;
+    else kernel = k_mac_xd<RT, CT, SUM>;
+    if (lds > 48 * 1024 && hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
         return ZNNI_ERR_HIP;
-    k_mac_xd<RT, CT, SUM><<<dim3((unsigned)blocks), dim3(256), lds, st>>>(g);
+    kernel<<<dim3((unsigned)blocks), dim3(256), lds, st>>>(g);
     if (hipGetLastError() != hipSuccess) return ZNNI_ERR_HIP;
     return ZNNI_OK;
 }
 
-// Columns: the strip width that computes the fewest column tiles (strips are dealt four to a workgroup), the wider one of
-// two that tie.
-template <int RT, bool SUM>
+// Columns: the strip width whose waves, dealt four to a workgroup, are through a chunk first: its products, its rounds of
+// staging and what a wave waits for in any case (in cycles of a SIMD; products 16 per matrix instruction, 200 per round, 800).
+// Of two that tie the wider one.
+template <int RT, bool SUM, bool PLANES>
 static znni_status launch_xd_cols_s(const LayerPlan& L, int accumulate, hipStream_t st)
 {
     constexpr int MAXCT = xd_max_ct<RT>();
@@ -578,15 +651,17 @@ static znni_status launch_xd_cols_s(const LayerPlan& L, int accumulate, hipStrea
     int CT = 1;
     long long best = -1;
     for (int c = 1; c <= MAXCT; ++c) {
-        const long long n = ((long long)L.S * ((tiles + c - 1) / c) + 3) / 4 * 4 * c;
+        const long long waves = ((long long)L.S * ((tiles + c - 1) / c) + 3) / 4 * 4;
+        const int rounds = (4 * (16 * c + 8) + 63) / 64;
+        const long long n = waves * (96 * L.d.kx * RT * c + 200 * rounds + 800);
         if (best < 0 || n <= best) { best = n; CT = c; }
     }
     switch (CT) {
-        case 1: return launch_xd<RT, 1, SUM>(L, accumulate, st);
-        case 2: return launch_xd<RT, 2, SUM>(L, accumulate, st);
-        case 3: return launch_xd<RT, 3, SUM>(L, accumulate, st);
-        case 4: if constexpr (MAXCT >= 4) return launch_xd<RT, 4, SUM>(L, accumulate, st); break;
-        case 5: if constexpr (MAXCT >= 5) return launch_xd<RT, 5, SUM>(L, accumulate, st); break;
+        case 1: return launch_xd<RT, 1, SUM, PLANES>(L, accumulate, st);
+        case 2: return launch_xd<RT, 2, SUM, PLANES>(L, accumulate, st);
+        case 3: return launch_xd<RT, 3, SUM, PLANES>(L, accumulate, st);
+        case 4: if constexpr (MAXCT >= 4) return launch_xd<RT, 4, SUM, PLANES>(L, accumulate, st); break;
+        case 5: if constexpr (MAXCT >= 5) return launch_xd<RT, 5, SUM, PLANES>(L, accumulate, st); break;
     }
     return ZNNI_ERR_SHAPE;
 }
@@ -599,7 +674,9 @@ static znni_status launch_xd_cols_s(const LayerPlan& L, int accumulate, hipStrea
 template <int RT>
 static znni_status launch_xd_cols(const LayerPlan& L, int accumulate, hipStream_t st)
 {
-    return mac_xb_available(L) || mac_batch_preferred(L) ? launch_xd_cols_s<RT, true>(L, accumulate, st) : launch_xd_cols_s<RT, false>(L, accumulate, st);
+    if (L.planes) return launch_xd_cols_s<RT, true, true>(L, accumulate, st);
+    return mac_xb_available(L) || mac_batch_preferred(L) ? launch_xd_cols_s<RT, true, false>(L, accumulate, st)
+                                                         : launch_xd_cols_s<RT, false, false>(L, accumulate, st);
 }
 
 znni_status launch_mac_xd(const LayerPlan& L, int accumulate, hipStream_t st)

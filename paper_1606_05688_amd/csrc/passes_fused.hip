@@ -80,50 +80,28 @@ constexpr int fused_nth_inv()
     return ((R1 * R2 / 2 + (fused_inv_packs(R1 * R2) ? 0 : 1)) * (R1 > R2 ? R1 : R2) + 63) / 64 * 64;
 }
 
-template <int R1, int R2>
-__global__ __launch_bounds__((fused_nth_inv<R1, R2>())) __attribute__((amdgpu_waves_per_eu((fused_waves<R1, R2, false>()))))
-void k_inv_yz(FusedArgs a)
+constexpr int PLANES = 4, PLANES_MAX = 64;    // (above length 64 four planes at once would be over 1024 threads)
+
+// NP planes from the samples v of their y lines (conjugated, as the loads leave them) to the rows of the output images,
+// plane p at dst + p * pitch.  Of NP neighbouring threads each works on another plane.  R: per plane, RS elements apart,
+// [ZC][P] exchange buffer; between the transforms the plane Q[ZC][QP].  nplanes: planes of a
+// block of four that exist from the first of these on.
+template <int R1, int R2, int NP>
+__device__ __forceinline__ void inv_plane(float2 (&v)[R1], const float2* tws, float2* const R0, int RS, int QP, const Dims& d,
+                                          float* dst0, size_t pitch, int nplanes, float bj, int relu)
 {
     using TS = TwoStep<R1, R2>;
     constexpr int N = TS::N, P = TS::P, ZC = N / 2 + 1;
     constexpr bool PACK = fused_inv_packs(N);
     constexpr int NL = PACK ? N / 2 : ZC;     // lines per transform
-    extern __shared__ float2 lds[];
-    const int QP = a.QP;
-    float2* tws = lds;                 // [N]
-    float2* R = lds + N;               // [ZC][P] exchange buffer; between the transforms the plane Q[ZC][QP]
-    const int t = threadIdx.x, NTH = blockDim.x;
-    const int xo = blockIdx.x, img = blockIdx.y;
-    const Dims& d = a.d;
-    const int nox = d.nox, noy = d.noy, noz = d.noz;
-
-    for (int q = t; q < N; q += NTH) tws[q] = a.tw[q];
-
+    const int t = threadIdx.x / NP, NTH = blockDim.x / NP;
+    float2* const R = R0 + threadIdx.x % NP * RS;
+    const int noy = d.noy, noz = d.noz;
     const int ja = t % R2, la = t / R2;       // step A: (line la, sample offset ja)
     const bool in_a = la < NL;
     const int lb = t % NL, q = t / NL;        // step B: (line lb, output offset q); work only for q < R1
-    float2 v[R1];
     float2 u[R2];
 
-    // ---- inverse along y: the rows oz of the plane, conj . forward . conj
-    if (in_a) {
-        const float2* row = a.src + (((size_t)img * ZC + la) * nox + xo) * d.ldn;
-        if (!PACK || la) {
-#pragma unroll
-            for (int m = 0; m < R1; ++m) {
-                const float2 x = row[ja + R2 * m];
-                v[m] = make_float2(x.x, -x.y);
-            }
-        } else {                              // line 0 = row 0 + i row N/2, conjugated
-            const float2* rown = row + (size_t)(N / 2) * nox * d.ldn;
-#pragma unroll
-            for (int m = 0; m < R1; ++m) {
-                const float2 x = row[ja + R2 * m], y = rown[ja + R2 * m];
-                v[m] = make_float2(x.x - y.y, -(x.y + y.x));
-            }
-        }
-    }
-    __syncthreads();                          // twiddles are in LDS
     if (in_a) TS::step_a(v, la, ja, tws, R);
     __syncthreads();
     if (q < R1) TS::step_b(u, lb, q, R);
@@ -175,22 +153,141 @@ void k_inv_yz(FusedArgs a)
     }
     __syncthreads();
     // rows yo of out[imgo][xo]: real part of line l -> row 2l, minus imaginary part -> row 2l+1
-    const float bj = a.bias ? a.bias[img % a.fo] : 0.f;
-    float* dst = a.out + (((size_t)img * nox + xo) * noy) * noz;
     // a wave per line = pair of rows (one LDS read serves both), or per two or four lines where rows are at most 32
     // or 16 long
     constexpr int LW = N <= 16 ? 16 : N <= 32 ? 32 : 64, RPI = 64 / LW;
-    for (int l = (t / 64) * RPI + (t % 64) / LW; l < np; l += (NTH / 64) * RPI) {
-        const float2* row = R + l * P + (d.kz - 1);
-        float* d0 = dst + (size_t)(2 * l) * noz;
+    const int w = threadIdx.x / 64, lane = threadIdx.x % 64, nw = blockDim.x / 64;
+    for (int i = w * RPI + lane / LW; i < np * NP; i += nw * RPI) {
+        const int l = i / NP, p = i % NP;
+        if (NP > 1 && p * (PLANES / NP) >= nplanes) continue;
+        const float2* row = R0 + p * RS + l * P + (d.kz - 1);
+        float* d0 = dst0 + p * pitch + (size_t)(2 * l) * noz;
         const bool two = 2 * l + 1 < noy;
-        for (int zo = t % LW; zo < noz; zo += LW) {
+        for (int zo = lane % LW; zo < noz; zo += LW) {
             const float2 c = row[zo];
             float v0 = c.x + bj, v1 = bj - c.y;
-            if (a.relu) { v0 = fmaxf(v0, 0.f); v1 = fmaxf(v1, 0.f); }
+            if (relu) { v0 = fmaxf(v0, 0.f); v1 = fmaxf(v1, 0.f); }
             d0[zo] = v0;
             if (two) d0[noz + zo] = v1;
         }
+    }
+}
+
+template <int R1, int R2>
+__global__ __launch_bounds__((fused_nth_inv<R1, R2>())) __attribute__((amdgpu_waves_per_eu((fused_waves<R1, R2, false>()))))
+void k_inv_yz(FusedArgs a)
+{
+    using TS = TwoStep<R1, R2>;
+    constexpr int N = TS::N, ZC = N / 2 + 1;
+    constexpr bool PACK = fused_inv_packs(N);
+    constexpr int NL = PACK ? N / 2 : ZC;     // lines per transform
+    extern __shared__ float2 lds[];
+    float2* tws = lds;                 // [N]
+    const int t = threadIdx.x, NTH = blockDim.x;
+    const int xo = blockIdx.x, img = blockIdx.y;
+    const Dims& d = a.d;
+    const int nox = d.nox;
+
+    for (int q = t; q < N; q += NTH) tws[q] = a.tw[q];
+
+    const int ja = t % R2, la = t / R2;       // step A: (line la, sample offset ja)
+    const bool in_a = la < NL;
+    float2 v[R1];
+
+    // ---- inverse along y: the rows oz of the plane, conj . forward . conj
+    if (in_a) {
+        const float2* row = a.src + (((size_t)img * ZC + la) * nox + xo) * d.ldn;
+        if (!PACK || la) {
+#pragma unroll
+            for (int m = 0; m < R1; ++m) {
+                const float2 x = row[ja + R2 * m];
+                v[m] = make_float2(x.x, -x.y);
+            }
+        } else {                              // line 0 = row 0 + i row N/2, conjugated
+            const float2* rown = row + (size_t)(N / 2) * nox * d.ldn;
+#pragma unroll
+            for (int m = 0; m < R1; ++m) {
+                const float2 x = row[ja + R2 * m], y = rown[ja + R2 * m];
+                v[m] = make_float2(x.x - y.y, -(x.y + y.x));
+            }
+        }
+    }
+    __syncthreads();                          // twiddles are in LDS
+    inv_plane<R1, R2, 1>(v, tws, lds + N, 0, a.QP, d, a.out + (((size_t)img * nox + xo) * d.noy) * d.noz, 0, 1,
+                         a.bias ? a.bias[img % a.fo] : 0.f, a.relu);
+}
+
+// Four neighbouring x at a time, for layers whose x axis is not transformed (mac_xd.hip): their spectra lie as
+// [img][oz][x / 4][oy][x % 4], so that the multiply-accumulate, which reads rows along x, finds 32 bytes together, and a row
+// of a workgroup's blocks is one run.  A workgroup either takes all four planes at once, of four neighbouring threads each
+// works on another one, or one plane after the other, a thread's values of all four in registers.  (Two at a time is slower
+// than either, and so is storing or loading fewer than the 32 bytes: 8 at a time three times, 16 at a time 1.5 times.)
+// Together where the lines of a plane fill whole waves (or a fraction of one), one by one elsewhere: workgroups of 11 to 15
+// waves leave a CU to two of them that wait at the same barriers.  Measured, together against one by one, us: forward at
+// 64 (8 x 32 images) 108, 141; 56 (64 x 80 of 51^3) 1851, 1521; 48 238, 258; 40 103, 90; 32 58, 65; 20 60, 55; 14 49, 67.
+// Inverse at 64 107, 122; 56 1795, 1564; 48 311, 250; 40 115, 88; 32 239, 224; 20 49, 48; 14 33, 40.
+constexpr int planes_together(int N, bool packs) { return packs || N <= 14 ? 4 : 1; }
+constexpr int planes_nth(int lines, int T, int par) { return (par * lines * T + 63) / 64 * 64; }
+// elements from one plane's region to the next: whole rows of the 64 banks and a quarter
+constexpr int planes_pitch(int region) { return (region + 31) / 32 * 32 + 8; }
+template <int R1, int R2, bool FWD>
+struct Planes {
+    static constexpr int N = R1 * R2;
+    static constexpr bool PACK = FWD ? fused_fwd_packs(N) : fused_inv_packs(N);
+    static constexpr int NL = N / 2 + (PACK ? 0 : 1);                   // lines per transform
+    static constexpr int PAR = planes_together(N, PACK), ROUNDS = PLANES / PAR;
+    static constexpr int NTH = planes_nth(NL, R1 > R2 ? R1 : R2, PAR);
+    static constexpr int RS = planes_pitch((FWD ? NL : N / 2 + 1) * (N + 2));
+    // registers: one by one, three (forward) or four waves per SIMD
+    static constexpr int WAVES = PAR > 1 ? 4 : FWD ? 3 : 4;
+};
+
+template <int R1, int R2>
+__global__ __launch_bounds__((Planes<R1, R2, false>::NTH)) __attribute__((amdgpu_waves_per_eu((Planes<R1, R2, false>::WAVES))))
+void k_inv_yz_planes(FusedArgs a)
+{
+    using PL = Planes<R1, R2, false>;
+    constexpr int N = PL::N, ZC = N / 2 + 1, PAR = PL::PAR, ROUNDS = PL::ROUNDS;
+    extern __shared__ float2 lds[];
+    float2* tws = lds;
+    const int t = threadIdx.x / PAR, p = threadIdx.x % PAR;
+    const int xb = blockIdx.x, img = blockIdx.y, nxb = gridDim.x;
+    const Dims& d = a.d;
+
+    for (int q = threadIdx.x; q < N; q += blockDim.x) tws[q] = a.tw[q];
+
+    const int ja = t % R2, la = t / R2;
+    // this thread's values of the ROUNDS planes p * ROUNDS + h
+    struct alignas(8 * (ROUNDS > 1 ? 2 : 1)) Run { float2 v[ROUNDS]; };
+    float2 v[ROUNDS][R1];
+    if (la < PL::NL) {
+        const float2* row = a.src + ((((size_t)img * ZC + la) * nxb + xb) * N + ja) * PLANES + p * ROUNDS;
+        if (!PL::PACK || la) {
+#pragma unroll
+            for (int m = 0; m < R1; ++m) {
+                const Run x = *reinterpret_cast<const Run*>(row + R2 * m * PLANES);
+#pragma unroll
+                for (int h = 0; h < ROUNDS; ++h) v[h][m] = make_float2(x.v[h].x, -x.v[h].y);
+            }
+        } else {                              // line 0 = row 0 + i row N/2, conjugated
+            const float2* rown = row + (size_t)(N / 2) * nxb * N * PLANES;
+#pragma unroll
+            for (int m = 0; m < R1; ++m) {
+                const Run x = *reinterpret_cast<const Run*>(row + R2 * m * PLANES), y = *reinterpret_cast<const Run*>(rown + R2 * m * PLANES);
+#pragma unroll
+                for (int h = 0; h < ROUNDS; ++h) v[h][m] = make_float2(x.v[h].x - y.v[h].y, -(x.v[h].y + y.v[h].x));
+            }
+        }
+    }
+    const size_t pitch = (size_t)d.noy * d.noz;
+    const float bj = a.bias ? a.bias[img % a.fo] : 0.f;
+    const int left = d.nox - PLANES * xb;                     // planes from this block's first on
+#pragma unroll
+    for (int h = 0; h < ROUNDS; ++h) {
+        if (h >= left) break;
+        __syncthreads();                      // twiddles are in LDS; the plane before has been stored
+        inv_plane<R1, R2, PAR>(v[h], tws, lds + N, PL::RS, a.QP, d, a.out + ((size_t)img * d.nox + PLANES * xb + h) * pitch,
+                               ROUNDS * pitch, left, bj, a.relu);
     }
 }
 
@@ -199,66 +296,38 @@ struct FusedFwdArgs {
     float2* dst;           // X2'[img][x][oz][oy]
     const float2* tw;      // [N]
     Dims d;
+    const float* col;      // powers of two of the f input images of a tuple (mac_xd.hip)
+    int f;
 };
 
 // Lines per transform: along z two real rows ride in one complex line, N / 2 lines at most.  Along y the plane has
 // N / 2 + 1 lines (oz = 0 ... N / 2), but the first and the last are real sequences (sums and alternating sums of
 // real rows): with PACK they ride together as real and imaginary part of line 0 and are separated, by the same
 // symmetry, when the rows are stored -- N / 2 lines in both directions.
-template <int R1, int R2>
-__global__ __launch_bounds__((fused_nth_fwd<R1, R2>())) __attribute__((amdgpu_waves_per_eu((fused_waves<R1, R2, true>()))))
-void k_fwd_zy(FusedFwdArgs a)
+// NP raw planes [ny][nz] in R, RS elements apart (behind a barrier), to their transformed lines [NL][P] in R, in natural
+// order, behind a barrier.  Of NP neighbouring threads each works on another plane.
+template <int R1, int R2, int NP>
+__device__ __forceinline__ void fwd_plane(const float2* tws, float2* const R0, int RS, int ny, int nz)
 {
     using TS = TwoStep<R1, R2>;
     constexpr int N = TS::N, P = TS::P, ZC = N / 2 + 1;
     constexpr bool PACK = fused_fwd_packs(N);
     constexpr int NL = PACK ? N / 2 : ZC;
-    extern __shared__ float2 lds[];
-    const int RP = a.d.nz;             // the raw plane keeps its pitch
-    float2* tws = lds;                 // [N]
-    float2* R = lds + N;               // in turn: raw plane [ny][RP] floats, exchange buffer and lines [NL][P]
-    const int t = threadIdx.x, NTH = blockDim.x;
-    const int x = blockIdx.x, img = blockIdx.y;
-    const Dims& d = a.d;
-    const int ny = d.ny, nz = d.nz;
-    const float* plane = a.in + (((size_t)img * d.nx + x) * ny) * nz;
-
-    for (int q = t; q < N; q += NTH) tws[q] = a.tw[q];
-
+    const int t = threadIdx.x / NP;
+    float2* const R = R0 + threadIdx.x % NP * RS;
     const int ja = t % R2, la = t / R2;
     const bool in_a = la < NL;
     const int lb = t % NL, q = t / NL;
+    const float* raw = reinterpret_cast<const float*>(R);
     float2 v[R1];
     float2 u[R2];
-
-    // ---- the (y, z) plane, contiguous in the input tensor, into LDS with fully coalesced loads.  (Reading each
-    // line's samples straight into the registers of the first step, as the separate z pass does, touches every
-    // cache line from four instructions and, for some row lengths, evicts it in between: measured up to 2.8x
-    // slower with a whole plane per workgroup.)
-    float* raw = reinterpret_cast<float*>(R);
-    {
-        // a flat copy, rows at their pitch in memory.  (Padding the rows in LDS so that the lines a wave reads
-        // together spread over all banks costs index arithmetic per element -- these kernels are bound by issuing
-        // instructions, not by LDS -- and was measured 3-8 % slower at almost every length.)
-        const int tot = ny * nz;
-        for (int i0 = 0; i0 < tot; i0 += 8 * NTH) {
-            float r[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) r[k] = plane[min(i0 + k * NTH + t, tot - 1)];
-#pragma unroll
-            for (int k = 0; k < 8; ++k)
-                if (i0 + k * NTH + t < tot) raw[i0 + k * NTH + t] = r[k];
-        }
-    }
-    __syncthreads();
-
     // ---- along z, real to complex: rows 2p and 2p+1 ride as real and imaginary part of line p
     const int np = (ny + 1) >> 1;             // <= N / 2 < ZC lines
     if (in_a) {
         const int ya = 2 * min(la, np - 1);
         const float ma = la < np ? 1.f : 0.f, mb = (la < np && ya + 1 < ny) ? 1.f : 0.f;
-        const float* ra = raw + ya * RP;
-        const float* rb = raw + min(ya + 1, ny - 1) * RP;
+        const float* ra = raw + ya * nz;
+        const float* rb = raw + min(ya + 1, ny - 1) * nz;
         // rows that fill the transform length: constant offsets, no padding in z
         if (nz == N) {
 #pragma unroll
@@ -324,6 +393,48 @@ void k_fwd_zy(FusedFwdArgs a)
         for (int r = 0; r < R2; ++r) R[lb * P + q + R1 * r] = u[r];
     }
     __syncthreads();
+}
+
+template <int R1, int R2>
+__global__ __launch_bounds__((fused_nth_fwd<R1, R2>())) __attribute__((amdgpu_waves_per_eu((fused_waves<R1, R2, true>()))))
+void k_fwd_zy(FusedFwdArgs a)
+{
+    using TS = TwoStep<R1, R2>;
+    constexpr int N = TS::N, P = TS::P, ZC = N / 2 + 1;
+    constexpr bool PACK = fused_fwd_packs(N);
+    extern __shared__ float2 lds[];
+    float2* tws = lds;                 // [N]
+    float2* R = lds + N;               // in turn: raw plane [ny][nz] floats, exchange buffer and lines [NL][P]
+    const int t = threadIdx.x, NTH = blockDim.x;
+    const int x = blockIdx.x, img = blockIdx.y;
+    const Dims& d = a.d;
+    const int ny = d.ny, nz = d.nz;
+    const float* plane = a.in + (((size_t)img * d.nx + x) * ny) * nz;
+
+    for (int q = t; q < N; q += NTH) tws[q] = a.tw[q];
+
+    // ---- the (y, z) plane, contiguous in the input tensor, into LDS with fully coalesced loads.  (Reading each
+    // line's samples straight into the registers of the first step, as the separate z pass does, touches every
+    // cache line from four instructions and, for some row lengths, evicts it in between: measured up to 2.8x
+    // slower with a whole plane per workgroup.)
+    float* raw = reinterpret_cast<float*>(R);
+    {
+        // a flat copy, rows at their pitch in memory.  (Padding the rows in LDS so that the lines a wave reads
+        // together spread over all banks costs index arithmetic per element -- these kernels are bound by issuing
+        // instructions, not by LDS -- and was measured 3-8 % slower at almost every length.)
+        const int tot = ny * nz;
+        for (int i0 = 0; i0 < tot; i0 += 8 * NTH) {
+            float r[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) r[k] = plane[min(i0 + k * NTH + t, tot - 1)];
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (i0 + k * NTH + t < tot) raw[i0 + k * NTH + t] = r[k];
+        }
+    }
+    __syncthreads();
+
+    fwd_plane<R1, R2, 1>(tws, R, 0, ny, nz);
     float2* dst = a.dst + (((size_t)img * d.nx + x) * ZC) * N;
     // a wave per row, or per two or four rows where rows are at most 32 or 16 long; rows 0 and N / 2 come out of
     // line 0 = C: (C[oy] + conj(C[N - oy])) / 2 and -i (C[oy] - conj(C[N - oy])) / 2
@@ -337,6 +448,79 @@ void k_fwd_zy(FusedFwdArgs a)
                 dst[(size_t)l * N + e] = l ? cscale(mul_mi(csub(c, m)), 0.5f) : cscale(cadd(c, m), 0.5f);
             }
         }
+    }
+}
+
+// A value the compiler knows nothing about: what is worked out from it is worked out again, not kept in registers.
+__device__ __forceinline__ int fresh(int v)
+{
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
+// Four neighbouring x at a time (see k_inv_yz_planes): X2 as [img][oz][x / 4][oy][x % 4].
+template <int R1, int R2>
+__global__ __launch_bounds__((Planes<R1, R2, true>::NTH)) __attribute__((amdgpu_waves_per_eu((Planes<R1, R2, true>::WAVES))))
+void k_fwd_zy_planes(FusedFwdArgs a)
+{
+    using PL = Planes<R1, R2, true>;
+    constexpr int N = PL::N, P = N + 2, ZC = N / 2 + 1, NTH = PL::NTH, PAR = PL::PAR, ROUNDS = PL::ROUNDS, RS = PL::RS;
+    constexpr int NV = (PAR * ZC * N + NTH - 1) / NTH, NF = (N * N + NTH - 1) / NTH;    // results and raw values of a plane per thread
+    extern __shared__ float2 lds[];
+    float2* tws = lds;                 // [N]
+    float2* R = lds + N;               // per plane, in turn: raw plane [ny][nz] floats, exchange buffer and lines [NL][P]
+    const int t = threadIdx.x, xb = blockIdx.x, img = blockIdx.y, nxb = gridDim.x;
+    const Dims& d = a.d;
+    const int tot = d.ny * d.nz, left = d.nx - PLANES * xb;      // planes from this block's first on
+    const float* plane = a.in + ((size_t)img * d.nx + PLANES * xb) * tot;
+    const float ps = a.col ? a.col[img % a.f] : 1.f;
+
+    // the planes of a round; the next round's are requested while one is transformed.  (Planes beyond the image repeat its
+    // last one, and are never read.)
+    float raw[PAR][NF];
+    auto request = [&](int h) {
+        const int tp = fresh(t);
+#pragma unroll
+        for (int p = 0; p < PAR; ++p) {
+            const float* src = plane + (size_t)min(p * ROUNDS + h, left - 1) * tot;
+#pragma unroll
+            for (int k = 0; k < NF; ++k) raw[p][k] = src[min(k * NTH + tp, tot - 1)];
+        }
+    };
+    request(0);
+    for (int q = t; q < N; q += NTH) tws[q] = a.tw[q];
+    struct alignas(8 * (ROUNDS > 1 ? 2 : 1)) Run { float2 v[ROUNDS]; } keep[NV];
+#pragma unroll
+    for (int h = 0; h < ROUNDS; ++h) {
+        if (h) __syncthreads();               // the lines have been read: the region takes the next raw plane
+        const int tp = fresh(t);
+#pragma unroll
+        for (int p = 0; p < PAR; ++p)
+#pragma unroll
+            for (int k = 0; k < NF; ++k)
+                if (k * NTH + tp < tot) reinterpret_cast<float*>(R + p * RS)[k * NTH + tp] = raw[p][k];
+        __syncthreads();
+        if (h + 1 < ROUNDS && h + 1 < left) request(h + 1);
+        fwd_plane<R1, R2, PAR>(tws, R, RS, d.ny, d.nz);
+        const float2* Rp = R + tp % PAR * RS;
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+            const int i = min((k * NTH + tp) / PAR, ZC * N - 1), l = i / N, e = i - l * N;
+            if (PL::PACK && (l == 0 || l == N / 2)) {
+                const float2 c = Rp[e], m = cconj(Rp[e ? N - e : 0]);
+                keep[k].v[h] = l ? cscale(mul_mi(csub(c, m)), 0.5f) : cscale(cadd(c, m), 0.5f);
+            } else keep[k].v[h] = Rp[l * P + e];
+        }
+    }
+    // neighbouring threads store neighbouring values: whole runs of a row
+    float2* dst = a.dst + (((size_t)img * ZC) * nxb + xb) * N * PLANES + t % PAR * ROUNDS;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        const int i = (k * NTH + t) / PAR, l = i / N, e = i - l * N;
+        if (i >= ZC * N) break;
+#pragma unroll
+        for (int h = 0; h < ROUNDS; ++h) { keep[k].v[h].x *= ps; keep[k].v[h].y *= ps; }
+        *reinterpret_cast<Run*>(dst + ((size_t)l * nxb * N + e) * PLANES) = keep[k];
     }
 }
 
@@ -445,6 +629,7 @@ znni_status launch_fwd_zy(const LayerPlan& L, const float* in, hipStream_t st)
     const Dims& d = L.d;
     FusedFwdArgs a;
     a.in = in; a.dst = L.buf1; a.tw = L.twy; a.d = d;
+    a.col = nullptr; a.f = 1;
     const dim3 grid(d.nx, L.nimg);
     ZNNI_FUSED_CASES(k_fwd_zy)
 }
@@ -460,6 +645,69 @@ znni_status launch_inv_yz(const LayerPlan& L, const float* bias, float* out, uns
     a.QP = F.QP;
     const dim3 grid(d.nox, L.nimgo);
     ZNNI_FUSED_CASES(k_inv_yz)
+}
+
+// The kernels for four planes: threads and LDS of a workgroup.
+static bool planes_shape(const LayerPlan& L, FusedShape* F, bool forward)
+{
+    if (!fused_shape(L, F, forward)) return false;
+    const int N = L.d.Ny;
+    const bool packs = forward ? fused_fwd_packs(N) : fused_inv_packs(N);
+    const int lines = packs ? N / 2 : L.d.zc, par = planes_together(N, packs);
+    F->nth = planes_nth(lines, std::max(F->R1, F->R2), par);
+    F->lds = sizeof(float2) * (size_t)(N + par * planes_pitch((forward ? lines : L.d.zc) * (N + 2)));
+    return N <= PLANES_MAX && F->nth <= 1024 && F->lds <= 80 * 1024;
+}
+
+bool fused_planes_available(const LayerPlan& L)
+{
+    FusedShape F;
+    return planes_shape(L, &F, true) && planes_shape(L, &F, false);
+}
+
+#define ZNNI_PLANES_CASES(KERNEL)                                                                  \
+    switch (F.R1 * 100 + F.R2) {                                                                   \
+        case 204: return launch_fused(KERNEL<2, 4>, a, F, grid, st);                               \
+        case 502: return launch_fused(KERNEL<5, 2>, a, F, grid, st);                               \
+        case 304: return launch_fused(KERNEL<3, 4>, a, F, grid, st);                               \
+        case 702: return launch_fused(KERNEL<7, 2>, a, F, grid, st);                               \
+        case 404: return launch_fused(KERNEL<4, 4>, a, F, grid, st);                               \
+        case 504: return launch_fused(KERNEL<5, 4>, a, F, grid, st);                               \
+        case 604: return launch_fused(KERNEL<6, 4>, a, F, grid, st);                               \
+        case 704: return launch_fused(KERNEL<7, 4>, a, F, grid, st);                               \
+        case 408: return launch_fused(KERNEL<4, 8>, a, F, grid, st);                               \
+        case 606: return launch_fused(KERNEL<6, 6>, a, F, grid, st);                               \
+        case 508: return launch_fused(KERNEL<5, 8>, a, F, grid, st);                               \
+        case 608: return launch_fused(KERNEL<6, 8>, a, F, grid, st);                               \
+        case 708: return launch_fused(KERNEL<7, 8>, a, F, grid, st);                               \
+        case 808: return launch_fused(KERNEL<8, 8>, a, F, grid, st);                               \
+    }                                                                                              \
+    return ZNNI_ERR_UNSUPPORTED_SIZE;
+
+// in -> X2 in blocks of four x (buf1); Yd in blocks of four xo (Yt) -> out
+znni_status launch_fwd_zy_planes(const LayerPlan& L, const float* in, hipStream_t st)
+{
+    FusedShape F;
+    if (!planes_shape(L, &F, true)) return ZNNI_ERR_UNSUPPORTED_SIZE;
+    const Dims& d = L.d;
+    FusedFwdArgs a;
+    a.in = in; a.dst = L.buf1; a.tw = L.twy; a.d = d;
+    a.col = split_scales(L).col; a.f = L.f;
+    const dim3 grid((d.nx + PLANES - 1) / PLANES, L.nimg);
+    ZNNI_PLANES_CASES(k_fwd_zy_planes)
+}
+
+znni_status launch_inv_yz_planes(const LayerPlan& L, const float* bias, float* out, unsigned flags, hipStream_t st)
+{
+    FusedShape F;
+    if (!planes_shape(L, &F, false)) return ZNNI_ERR_UNSUPPORTED_SIZE;
+    const Dims& d = L.d;
+    FusedArgs a;
+    a.src = L.Yt; a.out = out; a.tw = L.twy; a.bias = bias;
+    a.d = d; a.fo = L.fo; a.relu = (flags & ZNNI_RELU) ? 1 : 0;
+    a.QP = F.QP;
+    const dim3 grid((d.nox + PLANES - 1) / PLANES, L.nimgo);
+    ZNNI_PLANES_CASES(k_inv_yz_planes)
 }
 
 }  // namespace znni

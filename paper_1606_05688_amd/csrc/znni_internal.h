@@ -33,6 +33,9 @@ struct LayerPlan {
     // The x axis is not transformed (mac_xd.hip): in -> X1 -> X2, multiply-accumulate with the kx taps as shifted
     // reads of X2 -> Yd[imgo][oz][oy][xo] (in Yt), inverse y pass reading Yd transposed -> Y1 -> out.
     bool xdirect;
+    // ... and both z and y are transformed by the fused kernels that take four planes, X2 and Yd lying in blocks of four x
+    // (passes_fused.hip).  Implies xdirect.
+    bool planes;
     // ... and the kx taps are applied through length-8 transforms of overlapping blocks of X2 rows (mac_xb.hip)
     // instead of shifted reads; A then holds the length-8 transforms of the taps.  Implies xdirect.
     bool xblock;
@@ -127,6 +130,11 @@ znni_status launch_fast_fwd_xt(const LayerPlan& L, hipStream_t st);
 // Inverse y and z transforms in one kernel when a (oz, oy) plane fits LDS (passes_fused.hip); reads Y2 from buf0.
 bool fused_inv_yz_available(const LayerPlan& L);
 znni_status launch_inv_yz(const LayerPlan& L, const float* bias, float* out, unsigned flags, hipStream_t st);
+
+// The same for layers whose x axis is not transformed (LayerPlan::planes): in -> X2 in buf1, Yd in Yt -> out.
+bool fused_planes_available(const LayerPlan& L);
+znni_status launch_fwd_zy_planes(const LayerPlan& L, const float* in, hipStream_t st);
+znni_status launch_inv_yz_planes(const LayerPlan& L, const float* bias, float* out, unsigned flags, hipStream_t st);
 
 // Two-step in-register passes for selected transform lengths (passes_fast.hip).
 bool fast_pass_available(int N);
