@@ -101,12 +101,18 @@ constexpr unsigned ROUTE_FULL_X = 1u << 30;
 // passes.  Over 140 random batches of 8 to 64 inputs (lengths up to 64, 2 to 96 images, 1 to 9 taps) that go
 // here 1.3 times as fast as on the fully transformed route on average, the worst 4 % behind (25 x 84 -> 8 of 29^3, 8 x 4 x 5
 // kernels); 64 x 80 -> 80 of 51^3, 5^3 7.1 against 9.7 ms; 8 x 32 -> 32 of 64^3, 7^3
-// 0.51 against 0.67.  From eight inputs on; for fewer the two routes of before are as they were.
+// 0.51 against 0.67.
+// Fewer inputs go here where their transformed images are at most PLANES_SMALL together: what counts there are launches, and
+// this route has two fewer than either other.  Over 300 random layers of 1 to 7 inputs (lengths up to 64, 1 to 96 images, 1
+// to 9 taps) 1.15 times as fast up to 32 MB as the faster of the two picks, the worst 5 % behind (2 x 80 -> 16 of 16 x 13 x 13,
+// 7^3 kernels); 1.06 times from there to 100 MB, where the rules of before stay.
+constexpr double PLANES_SMALL = 32e6;
 static bool pick_planes(const LayerPlan& L, unsigned flags)
 {
     if (flags & (ROUTE_FULL_X | ZNNI_MAC_REFERENCE | ZNNI_MAC_SINGLE | ZNNI_MAC_BATCH | ZNNI_MAC_XDIRECT | ZNNI_MAC_XBLOCK)) return false;
-    if (L.S < 8 || !mac_xd_available(L) || !fused_planes_available(L)) return false;
+    if (!mac_xd_available(L) || !fused_planes_available(L)) return false;
     const Dims& d = L.d;
+    if (L.S < 8) return 8.0 * (L.nimg + (double)L.nimgo) * d.nx * d.zc * d.Ny <= PLANES_SMALL;
     const double pairs = (double)L.fp * L.Mp;
     const double products = 24.0 * d.kx * ((d.nox + 15) & ~15) * pairs * L.S / 0.7e15;
     const double batch = 1.7e-12 * pairs * d.Nx * ((L.S + 15) / 16);
@@ -436,6 +442,7 @@ static unsigned one_route(int S, int f, int fi, int fo, const int n[3], const in
     if (shape_plan(S, fi, fo, n, k, flags, &full) || shape_plan(S, f % fi, fo, n, k, flags, &rest)) return flags;
     if (full.xblock != rest.xblock) return (flags & ~(unsigned)ZNNI_MAC_XBLOCK) | ROUTE_FULL_X;
     if (full.xdirect != rest.xdirect) return flags | (full.xdirect ? (unsigned)ZNNI_MAC_XDIRECT : ROUTE_FULL_X);
+    if (full.planes != rest.planes) return flags | (unsigned)ZNNI_MAC_XDIRECT;
     return flags;
 }
 

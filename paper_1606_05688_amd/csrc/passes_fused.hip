@@ -226,27 +226,29 @@ void k_inv_yz(FusedArgs a)
 // waves leave a CU to two of them that wait at the same barriers.  Measured, together against one by one, us: forward at
 // 64 (8 x 32 images) 108, 141; 56 (64 x 80 of 51^3) 1851, 1521; 48 238, 258; 40 103, 90; 32 58, 65; 20 60, 55; 14 49, 67.
 // Inverse at 64 107, 122; 56 1795, 1564; 48 311, 250; 40 115, 88; 32 239, 224; 20 49, 48; 14 33, 40.
-constexpr int planes_together(int N, bool packs) { return packs || N <= 14 ? 4 : 1; }
+// Where there are too few workgroups to fill the chip four planes one by one are four times the latency: always together.
+constexpr bool planes_wide(int N, bool packs) { return packs || N <= 14; }
+constexpr long long PLANES_FEW = 1024;
 constexpr int planes_nth(int lines, int T, int par) { return (par * lines * T + 63) / 64 * 64; }
 // elements from one plane's region to the next: whole rows of the 64 banks and a quarter
 constexpr int planes_pitch(int region) { return (region + 31) / 32 * 32 + 8; }
-template <int R1, int R2, bool FWD>
+template <int R1, int R2, int PAR_, bool FWD>
 struct Planes {
     static constexpr int N = R1 * R2;
     static constexpr bool PACK = FWD ? fused_fwd_packs(N) : fused_inv_packs(N);
     static constexpr int NL = N / 2 + (PACK ? 0 : 1);                   // lines per transform
-    static constexpr int PAR = planes_together(N, PACK), ROUNDS = PLANES / PAR;
+    static constexpr int PAR = PAR_, ROUNDS = PLANES / PAR;
     static constexpr int NTH = planes_nth(NL, R1 > R2 ? R1 : R2, PAR);
     static constexpr int RS = planes_pitch((FWD ? NL : N / 2 + 1) * (N + 2));
     // registers: one by one, three (forward) or four waves per SIMD
     static constexpr int WAVES = PAR > 1 ? 4 : FWD ? 3 : 4;
 };
 
-template <int R1, int R2>
-__global__ __launch_bounds__((Planes<R1, R2, false>::NTH)) __attribute__((amdgpu_waves_per_eu((Planes<R1, R2, false>::WAVES))))
+template <int R1, int R2, int PAR_>
+__global__ __launch_bounds__((Planes<R1, R2, PAR_, false>::NTH)) __attribute__((amdgpu_waves_per_eu((Planes<R1, R2, PAR_, false>::WAVES))))
 void k_inv_yz_planes(FusedArgs a)
 {
-    using PL = Planes<R1, R2, false>;
+    using PL = Planes<R1, R2, PAR_, false>;
     constexpr int N = PL::N, ZC = N / 2 + 1, PAR = PL::PAR, ROUNDS = PL::ROUNDS;
     extern __shared__ float2 lds[];
     float2* tws = lds;
@@ -459,11 +461,11 @@ __device__ __forceinline__ int fresh(int v)
 }
 
 // Four neighbouring x at a time (see k_inv_yz_planes): X2 as [img][oz][x / 4][oy][x % 4].
-template <int R1, int R2>
-__global__ __launch_bounds__((Planes<R1, R2, true>::NTH)) __attribute__((amdgpu_waves_per_eu((Planes<R1, R2, true>::WAVES))))
+template <int R1, int R2, int PAR_>
+__global__ __launch_bounds__((Planes<R1, R2, PAR_, true>::NTH)) __attribute__((amdgpu_waves_per_eu((Planes<R1, R2, PAR_, true>::WAVES))))
 void k_fwd_zy_planes(FusedFwdArgs a)
 {
-    using PL = Planes<R1, R2, true>;
+    using PL = Planes<R1, R2, PAR_, true>;
     constexpr int N = PL::N, P = N + 2, ZC = N / 2 + 1, NTH = PL::NTH, PAR = PL::PAR, ROUNDS = PL::ROUNDS, RS = PL::RS;
     constexpr int NV = (PAR * ZC * N + NTH - 1) / NTH, NF = (N * N + NTH - 1) / NTH;    // results and raw values of a plane per thread
     extern __shared__ float2 lds[];
@@ -648,12 +650,14 @@ znni_status launch_inv_yz(const LayerPlan& L, const float* bias, float* out, uns
 }
 
 // The kernels for four planes: threads and LDS of a workgroup.
-static bool planes_shape(const LayerPlan& L, FusedShape* F, bool forward)
+static bool planes_shape(const LayerPlan& L, FusedShape* F, bool forward, int* together = nullptr)
 {
     if (!fused_shape(L, F, forward)) return false;
     const int N = L.d.Ny;
     const bool packs = forward ? fused_fwd_packs(N) : fused_inv_packs(N);
-    const int lines = packs ? N / 2 : L.d.zc, par = planes_together(N, packs);
+    const long long groups = ((forward ? L.d.nx : L.d.nox) + PLANES - 1) / PLANES * (long long)(forward ? L.nimg : L.nimgo);
+    const int lines = packs ? N / 2 : L.d.zc, par = planes_wide(N, packs) || groups < PLANES_FEW ? PLANES : 1;
+    if (together) *together = par;
     F->nth = planes_nth(lines, std::max(F->R1, F->R2), par);
     F->lds = sizeof(float2) * (size_t)(N + par * planes_pitch((forward ? lines : L.d.zc) * (N + 2)));
     return N <= PLANES_MAX && F->nth <= 1024 && F->lds <= 80 * 1024;
@@ -665,49 +669,68 @@ bool fused_planes_available(const LayerPlan& L)
     return planes_shape(L, &F, true) && planes_shape(L, &F, false);
 }
 
-#define ZNNI_PLANES_CASES(KERNEL)                                                                  \
-    switch (F.R1 * 100 + F.R2) {                                                                   \
-        case 204: return launch_fused(KERNEL<2, 4>, a, F, grid, st);                               \
-        case 502: return launch_fused(KERNEL<5, 2>, a, F, grid, st);                               \
-        case 304: return launch_fused(KERNEL<3, 4>, a, F, grid, st);                               \
-        case 702: return launch_fused(KERNEL<7, 2>, a, F, grid, st);                               \
-        case 404: return launch_fused(KERNEL<4, 4>, a, F, grid, st);                               \
-        case 504: return launch_fused(KERNEL<5, 4>, a, F, grid, st);                               \
-        case 604: return launch_fused(KERNEL<6, 4>, a, F, grid, st);                               \
-        case 704: return launch_fused(KERNEL<7, 4>, a, F, grid, st);                               \
-        case 408: return launch_fused(KERNEL<4, 8>, a, F, grid, st);                               \
-        case 606: return launch_fused(KERNEL<6, 6>, a, F, grid, st);                               \
-        case 508: return launch_fused(KERNEL<5, 8>, a, F, grid, st);                               \
-        case 608: return launch_fused(KERNEL<6, 8>, a, F, grid, st);                               \
-        case 708: return launch_fused(KERNEL<7, 8>, a, F, grid, st);                               \
-        case 808: return launch_fused(KERNEL<8, 8>, a, F, grid, st);                               \
-    }                                                                                              \
+template <int R1, int R2>
+static znni_status launch_planes(const FusedFwdArgs& a, const FusedShape& F, int par, dim3 grid, hipStream_t st)
+{
+    if constexpr (!planes_wide(R1 * R2, fused_fwd_packs(R1 * R2)))
+        if (par == 1) return launch_fused(k_fwd_zy_planes<R1, R2, 1>, a, F, grid, st);
+    return launch_fused(k_fwd_zy_planes<R1, R2, PLANES>, a, F, grid, st);
+}
+template <int R1, int R2>
+static znni_status launch_planes(const FusedArgs& a, const FusedShape& F, int par, dim3 grid, hipStream_t st)
+{
+    if constexpr (!planes_wide(R1 * R2, fused_inv_packs(R1 * R2)))
+        if (par == 1) return launch_fused(k_inv_yz_planes<R1, R2, 1>, a, F, grid, st);
+    return launch_fused(k_inv_yz_planes<R1, R2, PLANES>, a, F, grid, st);
+}
+template <typename Args>
+static znni_status launch_planes(const Args& a, const FusedShape& F, int par, dim3 grid, hipStream_t st)
+{
+    switch (F.R1 * 100 + F.R2) {
+        case 204: return launch_planes<2, 4>(a, F, par, grid, st);
+        case 502: return launch_planes<5, 2>(a, F, par, grid, st);
+        case 304: return launch_planes<3, 4>(a, F, par, grid, st);
+        case 702: return launch_planes<7, 2>(a, F, par, grid, st);
+        case 404: return launch_planes<4, 4>(a, F, par, grid, st);
+        case 504: return launch_planes<5, 4>(a, F, par, grid, st);
+        case 604: return launch_planes<6, 4>(a, F, par, grid, st);
+        case 704: return launch_planes<7, 4>(a, F, par, grid, st);
+        case 408: return launch_planes<4, 8>(a, F, par, grid, st);
+        case 606: return launch_planes<6, 6>(a, F, par, grid, st);
+        case 508: return launch_planes<5, 8>(a, F, par, grid, st);
+        case 608: return launch_planes<6, 8>(a, F, par, grid, st);
+        case 708: return launch_planes<7, 8>(a, F, par, grid, st);
+        case 808: return launch_planes<8, 8>(a, F, par, grid, st);
+    }
     return ZNNI_ERR_UNSUPPORTED_SIZE;
+}
 
 // in -> X2 in blocks of four x (buf1); Yd in blocks of four xo (Yt) -> out
 znni_status launch_fwd_zy_planes(const LayerPlan& L, const float* in, hipStream_t st)
 {
     FusedShape F;
-    if (!planes_shape(L, &F, true)) return ZNNI_ERR_UNSUPPORTED_SIZE;
+    int par = 1;
+    if (!planes_shape(L, &F, true, &par)) return ZNNI_ERR_UNSUPPORTED_SIZE;
     const Dims& d = L.d;
     FusedFwdArgs a;
     a.in = in; a.dst = L.buf1; a.tw = L.twy; a.d = d;
     a.col = split_scales(L).col; a.f = L.f;
     const dim3 grid((d.nx + PLANES - 1) / PLANES, L.nimg);
-    ZNNI_PLANES_CASES(k_fwd_zy_planes)
+    return launch_planes(a, F, par, grid, st);
 }
 
 znni_status launch_inv_yz_planes(const LayerPlan& L, const float* bias, float* out, unsigned flags, hipStream_t st)
 {
     FusedShape F;
-    if (!planes_shape(L, &F, false)) return ZNNI_ERR_UNSUPPORTED_SIZE;
+    int par = 1;
+    if (!planes_shape(L, &F, false, &par)) return ZNNI_ERR_UNSUPPORTED_SIZE;
     const Dims& d = L.d;
     FusedArgs a;
     a.src = L.Yt; a.out = out; a.tw = L.twy; a.bias = bias;
     a.d = d; a.fo = L.fo; a.relu = (flags & ZNNI_RELU) ? 1 : 0;
     a.QP = F.QP;
     const dim3 grid((d.nox + PLANES - 1) / PLANES, L.nimgo);
-    ZNNI_PLANES_CASES(k_inv_yz_planes)
+    return launch_planes(a, F, par, grid, st);
 }
 
 }  // namespace znni

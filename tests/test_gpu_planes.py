@@ -1,5 +1,5 @@
-"""Batches of small images that go untransformed along x, four planes at a time (no flag names this route: it is taken for
-eight inputs and more of lengths up to 64), against the oracle, and divided against whole."""
+"""Small images that go untransformed along x, four planes at a time (no flag names this route: it is taken for batches of
+lengths up to 64 and for small layers), against the oracle, and divided against whole."""
 import numpy as np
 import pytest
 import torch
@@ -27,6 +27,10 @@ CASES = [(8, 2, 3, (8, 8, 7), (2, 3, 2)), (9, 3, 17, (13, 10, 9), (3, 2, 4)), (8
          (10, 17, 5, (15, 13, 14), (4, 3, 3)), (8, 4, 33, (18, 16, 16), (1, 5, 2)), (17, 3, 4, (20, 19, 20), (3, 1, 3)),
          (8, 33, 6, (25, 24, 23), (2, 3, 5)), (11, 2, 5, (27, 28, 26), (4, 4, 4)), (8, 6, 49, (34, 32, 31), (5, 3, 2)),
          (8, 1, 2, (9, 33, 36), (2, 2, 2)), (12, 4, 3, (41, 40, 39), (3, 6, 3)), (8, 20, 20, (22, 47, 48), (5, 5, 5)),
+         # the same lengths where workgroups are few, and where they are many
+         (1, 3, 2, (35, 36, 35), (3, 2, 2)), (1, 1, 1, (19, 39, 40), (9, 1, 2)), (2, 5, 3, (51, 56, 53), (4, 4, 4)),
+         (16, 16, 4, (20, 18, 20), (2, 3, 2)), (40, 8, 40, (17, 24, 22), (3, 3, 3)), (40, 8, 8, (28, 35, 36), (3, 2, 5)),
+         (1, 1, 1, (7, 8, 8), (1, 1, 1)), (1, 2, 3, (16, 16, 16), (3, 3, 3)), (1, 70, 90, (9, 9, 10), (9, 9, 9)),
          (8, 3, 8, (51, 51, 51), (5, 5, 5)), (9, 5, 4, (30, 64, 63), (6, 7, 7)), (8, 3, 2, (66, 61, 64), (4, 3, 9))]
 
 
