@@ -90,11 +90,19 @@ struct XdArgs {
 };
 
 constexpr int XD_MAX_K = 9;     // taps along x at most: the halo of a staged row
-template <int RT, int CT>
-constexpr size_t xd_lds_bytes() { return (size_t)16 * (4 * 8 * (16 * CT + 16) + 4 * 128 * RT + 4 * RT); }
+// One row tile: the four waves take neighbouring strips of one input and stage them together.  There is little to multiply and
+// the image rows are what counts: together a wave reads whole rows of four images, and the columns two strips share are read
+// once (19 -> 5 of 295^3, 5^3 kernels 935 us, every wave its own strip 1210; 14 -> 12 of 111 x 88 x 87, 6 x 2 x 4 43 against 45).
+// Narrow tiles have more waves for it: without the early requests below, held to 96 registers, they have five per SIMD.
+template <int RT, bool PLANES> constexpr bool xd_shared() { return RT == 1 && !PLANES; }
+template <int RT, int CT, bool PLANES>
+constexpr size_t xd_lds_bytes()
+{
+    return (size_t)16 * ((xd_shared<RT, PLANES>() ? 8 * (64 * CT + 16) : 4 * 8 * (16 * CT + 16)) + 4 * 128 * RT + 4 * RT + 5);
+}
 // Three workgroups per CU where LDS and registers (168 a lane) allow, two otherwise.
-template <int RT, int CT>
-constexpr int xd_blocks() { return xd_lds_bytes<RT, CT>() <= 53 * 1024 && RT * CT <= 6 ? 3 : 2; }
+template <int RT, int CT, bool PLANES>
+constexpr int xd_blocks() { return xd_shared<RT, PLANES>() && CT <= 2 ? 5 : xd_lds_bytes<RT, CT, PLANES>() <= 53 * 1024 && RT * CT <= 6 ? 3 : 2; }
 
 // Slot of a pencil's stored kernel transforms -> image quad and tap: the order the contraction walks them in, chunks of four
 // quads, inside a chunk tap by tap, quads fastest.
@@ -110,17 +118,20 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
 {
     // staged columns of a strip (its outputs and their halo) and the pitch of an image quad (rows start on the same bank:
     // the sixteen-lane groups of a 16-byte LDS read then share no bank in any phase)
-    constexpr int XN = 16 * CT + 8, XW = 16 * CT + 16;
+    constexpr bool SHARED = xd_shared<RT, PLANES>();
+    constexpr int XN = 16 * CT + 8, XW = (SHARED ? 64 : 16) * CT + 16;
     // Rounds of a wave over a strip's units: strips of three column tiles and more take a quad per round (its image rows are
     // then scalar addresses) and the columns beyond 64 of all quads in further ones.
-    constexpr int XH = CT >= 3 ? (XN > 64 ? XN - 64 : 0) : XN, NQ = CT >= 3 ? 4 : 0, NR = NQ + (4 * XH + 63) / 64;
+    // Staged together, wave w takes quad w, 64 columns a round and the halo in a last one.
+    constexpr int XH = CT >= 3 ? (XN > 64 ? XN - 64 : 0) : XN, NQ = CT >= 3 ? 4 : 0, NR = SHARED ? CT + 1 : NQ + (4 * XH + 63) / 64;
     // Whether the four sums of an accumulator are neighbouring outputs of one image, stored as 32 bytes a lane, or outputs
     // of four images, stored as 128 bytes of an image by sixteen lanes.  The latter takes 2 to 3 % less from three row tiles
     // on and in planes (8 x 32 -> 32 of 64^3, 7^3 0.26 against 0.30 ms), the former below (7 -> 9 of 150 x 142 x 95 57 against 60 us).
     constexpr bool XROWS = RT <= 2 && !PLANES;
     // Where registers allow, the first chunk's rows are requested before anything is waited for, and the rows of the next
     // chunk while one is multiplied.
-    constexpr bool EARLY = RT * CT <= 10, AHEAD = RT <= 2 && RT * CT <= 8;
+    constexpr bool MORE = !SHARED || CT >= 3;                // (elsewhere another wave per SIMD is worth more)
+    constexpr bool EARLY = MORE && RT * CT <= 10, AHEAD = MORE && RT <= 2 && RT * CT <= 8;
     static_assert(XD_MAX_K - 1 <= 8, "the halo is eight columns");
     half8* const As = lds;                                   // [two pairs of steps][slot kk][row tile][hi, lo][16]
 
@@ -133,14 +144,16 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
     const int mblk = (int)g.d_nwg.div(sub);
     const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
     const int l16 = lane & 15, kk = lane >> 4;
-    const int strip = ((int)sub - mblk * (int)g.d_nwg.d) * 4 + wave;
+    const int strip = SHARED ? (int)sub - mblk * (int)g.d_nwg.d : ((int)sub - mblk * (int)g.d_nwg.d) * 4 + wave;
     const bool live = strip < g.nstrips;                     // (waves without a strip only carry kernel operands)
     const int sI = (int)g.d_spr.div((unsigned)min(strip, g.nstrips - 1));
-    const int col0 = (min(strip, g.nstrips - 1) - sI * (int)g.d_spr.d) * 16 * CT;
+    const int row0 = (min(strip, g.nstrips - 1) - sI * (int)g.d_spr.d) * (SHARED ? 64 : 16) * CT;       // first staged column
+    const int wcol = SHARED ? wave * 16 * CT : 0, col0 = row0 + wcol;                                   // ... and this wave's first
     const int K = g.K, f = g.f;
     const int poz = (int)g.d_Ny.div((unsigned)pencil), poy = pencil - poz * g.Ny;
-    half8* const Xs = lds + 4 * RT * 128 + wave * 8 * XW;    // this wave's own: [hi, lo][quad][XW]
-    float* const rjs = reinterpret_cast<float*>(lds + 4 * RT * 128 + 32 * XW);          // [RT * 16]
+    half8* const Xs = lds + 4 * RT * 128 + (SHARED ? 0 : wave * 8 * XW);      // this wave's own, or all waves': [hi, lo][quad][XW]
+    float* const rjs = reinterpret_cast<float*>(lds + 4 * RT * 128 + (SHARED ? 8 : 32) * XW);           // [RT * 16]
+    unsigned* const wred = reinterpret_cast<unsigned*>(rjs + RT * 16);        // [turn][largest, smallest][wave], [wave]
 
     // ---- kernel operands: this thread's share of a step, NU units of 16 bytes (surplus units repeat the last one).
     // Slots past the last one are read from it.
@@ -198,17 +211,17 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
     load_a();
 
     const float2* xrow = g.X2 + (size_t)(unsigned)(sI * f) * g.ximg + (size_t)poz * g.xpen + (size_t)poy * g.xrow;
-    const int xlast = min(g.nx, col0 + 16 * CT + K - 1) - 1;     // last column any of the strip's outputs needs
+    const int xlast = min(g.nx, row0 + (SHARED ? 64 : 16) * CT + K - 1) - 1;     // last column any of the strip's outputs needs
     auto xoff = [&](int x) { x = min(x, xlast); return (x >> 2) * g.xblk + (x & 3); };
     int QC = 4;                                              // image quads of the chunk
-    auto unit_q = [&](int n) { return n < NQ ? n : min(lane + 64 * (n - NQ), 4 * XH - 1) / max(XH, 1); };
-    auto unit_x = [&](int n) { return n < NQ ? min(lane, XN - 1) : (NQ ? 64 : 0) + min(lane + 64 * (n - NQ), 4 * XH - 1) % max(XH, 1); };
+    auto unit_q = [&](int n) { return SHARED ? wave : n < NQ ? n : min(lane + 64 * (n - NQ), 4 * XH - 1) / max(XH, 1); };
+    auto unit_x = [&](int n) { return SHARED ? (n < CT ? 64 * n + lane : 64 * CT + (lane & 7)) : n < NQ ? min(lane, XN - 1) : (NQ ? 64 : 0) + min(lane + 64 * (n - NQ), 4 * XH - 1) % max(XH, 1); };
     int sexp = 126;                                          // exponent of the scale the image values carry
     int chunk = 0;
     bool apart = false;                                      // magnitudes along x too far apart for halves
     // One chunk of sixteen images of the strip to LDS, a (quad, x) unit per lane and round.  Values beyond a row are read
     // from its end, images beyond the last from the last: neither reaches a stored output (the images count as zeros).
-    auto round = [&](int n, int qc) { return n < NQ ? n < qc : 64 * (n - NQ) < qc * XH; };
+    auto round = [&](int n, int qc) { return SHARED ? wave < qc : n < NQ ? n < qc : 64 * (n - NQ) < qc * XH; };
     float2 raw[NR][4];
     auto request = [&]() {
         const int i0 = chunk * 16, qc = min(4, ((f + 3) >> 2) - 4 * chunk);
@@ -221,7 +234,7 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
                 continue;
             }
             const int uq = unit_q(n);
-            const unsigned off = 8u * (unsigned)xoff(col0 + unit_x(n));
+            const unsigned off = 8u * (unsigned)xoff(row0 + unit_x(n));
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 raw[n][q] = *reinterpret_cast<const float2*>(
@@ -242,8 +255,14 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
             m = fmaxf(m, u);
             mn = min(mn, small_code(u));
         }
-        unsigned mb = wave_max(m);
-        const unsigned sm = wave_min(mn);
+        unsigned mb = wave_max(m), sm = wave_min(mn);
+        if constexpr (SHARED) {
+            unsigned* const red = wred + (chunk & 1) * 8;
+            if (lane == 0) { red[wave] = mb; red[4 + wave] = sm; }
+            __syncthreads();                                 // (also: all waves are through with the chunk before)
+            mb = (unsigned)__builtin_amdgcn_readfirstlane((int)max(max(red[0], red[1]), max(red[2], red[3])));
+            sm = (unsigned)__builtin_amdgcn_readfirstlane((int)min(min(red[4], red[5]), min(red[6], red[7])));
+        }
         if (mb >= 0x7f800000u) {                             // infinities or NaNs: the scale is that of the finite values
             m = 0.f;
 #pragma unroll
@@ -256,6 +275,12 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
                     max3_abs(m, ax < INFINITY ? ax : 0.f, ay < INFINITY ? ay : 0.f);
                 }
             mb = wave_max(m);
+            if constexpr (SHARED) {
+                if (lane == 0) wred[16 + wave] = mb;
+                __syncthreads();
+                mb = (unsigned)__builtin_amdgcn_readfirstlane((int)max(max(wred[16], wred[17]), max(wred[18], wred[19])));
+                __syncthreads();
+            }
         }
         apart |= split_too_wide(mb, sm);
         const int sn = min(sexp, split_exp(__uint_as_float(mb)));
@@ -287,7 +312,8 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
             d[0] = __builtin_bit_cast(half8, h);
             d[4 * XW] = __builtin_bit_cast(half8, l);
         }
-        __builtin_amdgcn_wave_barrier();
+        if constexpr (SHARED) __syncthreads();
+        else __builtin_amdgcn_wave_barrier();
         ++chunk;
     };
 
@@ -305,7 +331,7 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
             if (AHEAD && 16 * chunk < f) request();
         }
         --left;
-        const half8* xs = Xs + l16 + qx + max(K - 1 - a, 0);
+        const half8* xs = Xs + wcol + l16 + qx + max(K - 1 - a, 0);
         if (QC == 4) ++a;
         else {
             quad += QC == 3; a += QC == 3 ? 1 : QC == 2 ? 2 : 4;
@@ -362,7 +388,8 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
     if (nsteps > 2) load_a();
     const half8* const as0 = As + kk * RT * 32 + l16;
     for (int gs = 0, buf = 0; gs < nsteps; gs += 2, buf ^= 1) {
-        __syncthreads();                                     // this pair's operands are in place, the last one's are free
+        // this pair's operands are in place, the last one's are free (staged together, the first chunk's barriers say so)
+        if (!SHARED || gs) __syncthreads();
         if (live) step(as0 + buf * RT * 256);
         if (gs + 2 < nsteps) {
             park_a(gs + 2, buf ^ 1);
@@ -464,7 +491,7 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
 
 // Rows of X2 and Yd along x.
 template <int RT, int CT, bool SUM>
-__global__ __launch_bounds__(256, (xd_blocks<RT, CT>())) void k_mac_xd(XdArgs g)
+__global__ __launch_bounds__(256, (xd_blocks<RT, CT, false>())) void k_mac_xd(XdArgs g)
 {
     extern __shared__ half8 lds[];
     xd_body<RT, CT, SUM, false>(g, lds);
@@ -472,7 +499,7 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT>())) void k_mac_xd(XdArgs g)
 // Rows in blocks of four x, a block of every oy after the other, as the kernels of passes_fused.hip that take four planes
 // leave and read them.  Four neighbouring pencils share every cache line: they are neighbours on one XCD.
 template <int RT, int CT>
-__global__ __launch_bounds__(256, (xd_blocks<RT, CT>())) void k_mac_planes(XdArgs g)
+__global__ __launch_bounds__(256, (xd_blocks<RT, CT, true>())) void k_mac_planes(XdArgs g)
 {
     extern __shared__ half8 lds[];
     xd_body<RT, CT, true, true>(g, lds);
@@ -621,15 +648,16 @@ static znni_status launch_xd(const LayerPlan& L, int accumulate, hipStream_t st)
     }
     g.f = L.f; g.fo = L.fo; g.Mp = L.Mp; g.K = d.kx;
     g.nx = d.nx; g.nox = d.nox; g.Ny = d.Ny;
-    const int spr = ((d.nox + 15) / 16 + CT - 1) / CT, pg = PLANES ? 4 : 1;
+    constexpr int PER = xd_shared<RT, PLANES>() ? 4 : 1;        // strips that are staged together and count as one here
+    const int spr = ((d.nox + 15) / 16 + CT * PER - 1) / (CT * PER), pg = PLANES ? 4 : 1;
     g.nstrips = L.S * spr; g.npencils = L.ozn * d.Ny; g.accumulate = accumulate;
-    const int nwg = (g.nstrips + 3) / 4, nsub = nwg * L.mac_nmblk;
+    const int nwg = (g.nstrips * PER + 3) / 4, nsub = nwg * L.mac_nmblk;
     g.d_sub.set((unsigned)(nsub * pg)); g.d_pg.set((unsigned)pg); g.d_spr.set((unsigned)spr); g.d_nwg.set((unsigned)nwg);
     g.d_Ny.set((unsigned)d.Ny);
     g.X2 = L.buf1 + (size_t)L.oz0 * g.xpen; g.Yd = L.Yt + (size_t)L.oz0 * g.ypen;
     const long long blocks = (long long)((g.npencils + 8 * pg - 1) / (8 * pg)) * nsub * pg * 8;
     if (blocks > 0x7fffffffll) return ZNNI_ERR_SHAPE;
-    constexpr size_t lds = xd_lds_bytes<RT, CT>();
+    constexpr size_t lds = xd_lds_bytes<RT, CT, PLANES>();
     void (*kernel)(XdArgs);
     if constexpr (PLANES) kernel = k_mac_planes<RT, CT>;
     else kernel = k_mac_xd<RT, CT, SUM>;
@@ -646,12 +674,12 @@ static znni_status launch_xd(const LayerPlan& L, int accumulate, hipStream_t st)
 template <int RT, bool SUM, bool PLANES>
 static znni_status launch_xd_cols_s(const LayerPlan& L, int accumulate, hipStream_t st)
 {
-    constexpr int MAXCT = xd_max_ct<RT>();
+    constexpr int MAXCT = xd_max_ct<RT>(), PER = xd_shared<RT, PLANES>() ? 4 : 1;
     const int tiles = (L.d.nox + 15) / 16;
     int CT = 1;
     long long best = -1;
     for (int c = 1; c <= MAXCT; ++c) {
-        const long long waves = ((long long)L.S * ((tiles + c - 1) / c) + 3) / 4 * 4;
+        const long long waves = ((long long)L.S * ((tiles + c * PER - 1) / (c * PER)) * PER + 3) / 4 * 4;
         const int rounds = (4 * (16 * c + 8) + 63) / 64;
         const long long n = waves * (96 * L.d.kx * RT * c + 200 * rounds + 800);
         if (best < 0 || n <= best) { best = n; CT = c; }
