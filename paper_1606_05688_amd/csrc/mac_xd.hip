@@ -90,19 +90,21 @@ struct XdArgs {
 };
 
 constexpr int XD_MAX_K = 9;     // taps along x at most: the halo of a staged row
-// One row tile: the four waves take neighbouring strips of one input and stage them together.  There is little to multiply and
-// the image rows are what counts: together a wave reads whole rows of four images, and the columns two strips share are read
-// once (19 -> 5 of 295^3, 5^3 kernels 935 us, every wave its own strip 1210; 14 -> 12 of 111 x 88 x 87, 6 x 2 x 4 43 against 45).
+// One row tile, and narrow strips: the four waves take neighbouring strips of one input and stage them together.  There is
+// little to multiply and the image rows are what counts, or the columns that two strips share are as many as their own: together a wave reads whole rows of four images, and the columns two strips share are read
+// once (19 -> 5 of 295^3, 5^3 kernels 935 us, every wave its own strip 1210; 14 -> 12 of 111 x 88 x 87, 6 x 2 x 4 43 against 45;
+// 28 -> 75 of 62^3, 7^3 107 against 117).  Where neither holds, as with five row tiles of two column tiles, it is the slower way (80 -> 80
+// of 200^3, 5^3 4.15 against 3.91 ms).
 // Narrow tiles have more waves for it: without the early requests below, held to 96 registers, they have five per SIMD.
-template <int RT, bool PLANES> constexpr bool xd_shared() { return RT == 1 && !PLANES; }
+constexpr bool xd_shared(int RT, int CT, bool planes) { return (RT == 1 || CT == 1 || (RT == 2 && CT == 2)) && !planes; }
 template <int RT, int CT, bool PLANES>
 constexpr size_t xd_lds_bytes()
 {
-    return (size_t)16 * ((xd_shared<RT, PLANES>() ? 8 * (64 * CT + 16) : 4 * 8 * (16 * CT + 16)) + 4 * 128 * RT + 4 * RT + 5);
+    return (size_t)16 * ((xd_shared(RT, CT, PLANES) ? 8 * (64 * CT + 16) : 4 * 8 * (16 * CT + 16)) + 4 * 128 * RT + 4 * RT + 5);
 }
 // Three workgroups per CU where LDS and registers (168 a lane) allow, two otherwise.
 template <int RT, int CT, bool PLANES>
-constexpr int xd_blocks() { return xd_shared<RT, PLANES>() && CT <= 2 ? 5 : xd_lds_bytes<RT, CT, PLANES>() <= 53 * 1024 && RT * CT <= 6 ? 3 : 2; }
+constexpr int xd_blocks() { return xd_shared(RT, CT, PLANES) && RT == 1 && CT <= 2 ? 5 : xd_lds_bytes<RT, CT, PLANES>() <= 53 * 1024 && RT * CT <= 6 ? 3 : 2; }
 
 // Slot of a pencil's stored kernel transforms -> image quad and tap: the order the contraction walks them in, chunks of four
 // quads, inside a chunk tap by tap, quads fastest.
@@ -118,7 +120,7 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
 {
     // staged columns of a strip (its outputs and their halo) and the pitch of an image quad (rows start on the same bank:
     // the sixteen-lane groups of a 16-byte LDS read then share no bank in any phase)
-    constexpr bool SHARED = xd_shared<RT, PLANES>();
+    constexpr bool SHARED = xd_shared(RT, CT, PLANES);
     constexpr int XN = 16 * CT + 8, XW = (SHARED ? 64 : 16) * CT + 16;
     // Rounds of a wave over a strip's units: strips of three column tiles and more take a quad per round (its image rows are
     // then scalar addresses) and the columns beyond 64 of all quads in further ones.
@@ -130,7 +132,7 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
     constexpr bool XROWS = RT <= 2 && !PLANES;
     // Where registers allow, the first chunk's rows are requested before anything is waited for, and the rows of the next
     // chunk while one is multiplied.
-    constexpr bool MORE = !SHARED || CT >= 3;                // (elsewhere another wave per SIMD is worth more)
+    constexpr bool MORE = RT > 1 || CT >= 3;                // (elsewhere another wave per SIMD is worth more)
     constexpr bool EARLY = MORE && RT * CT <= 10, AHEAD = MORE && RT <= 2 && RT * CT <= 8;
     static_assert(XD_MAX_K - 1 <= 8, "the halo is eight columns");
     half8* const As = lds;                                   // [two pairs of steps][slot kk][row tile][hi, lo][16]
@@ -648,7 +650,7 @@ static znni_status launch_xd(const LayerPlan& L, int accumulate, hipStream_t st)
     }
     g.f = L.f; g.fo = L.fo; g.Mp = L.Mp; g.K = d.kx;
     g.nx = d.nx; g.nox = d.nox; g.Ny = d.Ny;
-    constexpr int PER = xd_shared<RT, PLANES>() ? 4 : 1;        // strips that are staged together and count as one here
+    constexpr int PER = xd_shared(RT, CT, PLANES) ? 4 : 1;        // strips that are staged together and count as one here
     const int spr = ((d.nox + 15) / 16 + CT * PER - 1) / (CT * PER), pg = PLANES ? 4 : 1;
     g.nstrips = L.S * spr; g.npencils = L.ozn * d.Ny; g.accumulate = accumulate;
     const int nwg = (g.nstrips * PER + 3) / 4, nsub = nwg * L.mac_nmblk;
@@ -674,11 +676,12 @@ static znni_status launch_xd(const LayerPlan& L, int accumulate, hipStream_t st)
 template <int RT, bool SUM, bool PLANES>
 static znni_status launch_xd_cols_s(const LayerPlan& L, int accumulate, hipStream_t st)
 {
-    constexpr int MAXCT = xd_max_ct<RT>(), PER = xd_shared<RT, PLANES>() ? 4 : 1;
+    constexpr int MAXCT = xd_max_ct<RT>();
     const int tiles = (L.d.nox + 15) / 16;
     int CT = 1;
     long long best = -1;
     for (int c = 1; c <= MAXCT; ++c) {
+        const int PER = xd_shared(RT, c, PLANES) ? 4 : 1;
         const long long waves = ((long long)L.S * ((tiles + c * PER - 1) / (c * PER)) * PER + 3) / 4 * 4;
         const int rounds = (4 * (16 * c + 8) + 63) / 64;
         const long long n = waves * (96 * L.d.kx * RT * c + 200 * rounds + 800);
