@@ -12,7 +12,7 @@
  * pruned as in Section III-A (k^2, then k*n~, then n~^2 one-dimensional transforms) and their last stage is
  * evaluated inside the multiply-accumulate kernel, so no full-size kernel spectrum is ever stored.  Along x
  * (the slowest axis, transformed last) the common transform size of images and kernels is the library's choice
- * per layer shape: the full n~ for batches of small images; elsewhere no transform at all (the kx-tap sum written
+ * per layer shape: the full n~ for small images with many products per image; elsewhere no transform at all (the kx-tap sum written
  * out; or, where a call asks for it, blocks of eight).  The valid outputs are the same numbers up to fp32 rounding
  * whichever is taken.  Bias and transfer function are applied where the inverse transform
  * finishes an output image (Section IV-A-3).
@@ -81,7 +81,7 @@ enum {
                                     /* more than 12 kernel taps, or up to 8 inputs with an odd transform       */
                                     /* length along x)                                                          */
     ZNNI_MAC_XDIRECT = 16u,         /* force the route that does not transform the x axis at all: transforms    */
-                                    /* along z and y only, and the kernel's taps along x applied as a short     */
+                                    /* along z and y only, one pass each, and the taps along x applied as a short */
                                     /* valid convolution inside the multiply-accumulate (same contraction       */
                                     /* length as ZNNI_MAC_SINGLE, no x passes; ignored where it does not exist: */
                                     /* more than 9 taps along x, or a y transform length without an in-register */

@@ -48,7 +48,7 @@ static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // Whether a layer runs without transforming its x axis (mac_xd.hip).  A flag that names a multiply-accumulate form
 // decides; otherwise that route is taken, provided the y transform has an in-register kernel (only those read the
-// transposed layout), except for small images with many inputs or many images: with fused z+y kernels on both sides the
+// transposed layout), except for small images with many inputs or many images that do not go four planes at a time (pick_planes): with fused z+y kernels on both sides the
 // fully transformed route has as many passes, and a kernel-spectrum value generated once per bin serves all inputs.
 // Measured, whole layer, untransformed against fully transformed: 80 -> 80 images of 100^3, 5^3 kernels 1.57 against
 // 2.02 ms; 32 -> 32 of 64^3, 7^3 0.137 against 0.171; 8 x 32 -> 32 of 130^3, 5^3 (no fused kernels) 6.2 against 8.9;

@@ -14,12 +14,12 @@
 // transform on either side and no twiddle products.  So when every kernel-spectrum value would be used once
 // (few inputs per batch) the x axis is never transformed: the forward x pass, the inverse x pass and the tensors
 // between them disappear, and the right operand of the matrix product is the image row itself, read at kx
-// shifted offsets.  (With many inputs per batch a kernel-spectrum value generated once per bin serves them all,
-// and the fully transformed route of mac_batch.hip does less work.)
+// shifted offsets.  (With many inputs per batch a kernel-spectrum value generated once per bin serves them all, as in
+// mac_batch.hip, but on fp32 products and behind two more passes: batches of small images come here as well.)
 //
-// Layouts: X2[img][oz][oy][x < ldx] as the forward y pass leaves it, A[oz][oy][i/4][a][i%4][j<Mp] scaled by
-// 1/(Ny Nz), Yd[imgo][oz][oy][xo < ldxo], which the inverse y pass reads with a transposing load.
-//
+// Layouts: X2[img][oz][oy][x < ldx] as the forward y pass leaves it, Yd[imgo][oz][oy][xo < ldxo], which the inverse y pass
+// reads with a transposing load; or, next to the fused z+y kernels that take four planes (passes_fused.hip), X2[img][oz]
+// [x/4][oy][x%4] and Yd likewise (k_mac_planes).  A: see k_kprep_xd.
 //
 // The products run on the fp16 matrix instructions (v_mfma_f32_16x16x32_f16, sixteen times the rate of the fp32 ones)
 // with every fp32 value carried as two halves, v = hi + lo (two halves together hold 22 bits and a sign, an error of
@@ -61,7 +61,8 @@
 // is staged, the second is made of it with one packed instruction per register.
 //
 // A wave owns a strip of 16*CT outputs along x of one pencil (oz, oy) of one input and RT row tiles of 16 output images; the
-// four waves of a workgroup own four strips of a pencil, of one input or of several, and share its kernel operands.  Strips
+// four waves of a workgroup own four strips of a pencil, of one input or of several, and share its kernel operands (and, with
+// one row tile or narrow strips of one input, the staged rows: xd_shared).  Strips
 // are as wide as the row divides best into (launch_xd_cols_s): rows of 316 outputs are four strips of 80 where four waves
 // of one 192-wide tile and the next left a sixth of the products to padding.  Input images go through in chunks of sixteen.  A wave
 // reads its own rows into registers, splits them and leaves them in its own part of LDS as [image quad][x] units of 16

@@ -22,6 +22,9 @@
 // registers across the barrier that hands the region over.  That is 42 KB at N = 100 -- three workgroups per CU,
 // where separate regions (83 KB) left room for one, and a workgroup's life is a chain of memory round trips and
 // barriers that only other workgroups can fill.  The forward kernel exists up to length 128, the inverse up to 120.
+//
+// Both also exist for four neighbouring x of layers whose x axis is not transformed (k_fwd_zy_planes, k_inv_yz_planes, up to
+// length 64).
 #include "two_step.h"
 #include <algorithm>
 #include "znni_internal.h"
