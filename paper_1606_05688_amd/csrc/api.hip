@@ -104,9 +104,9 @@ constexpr unsigned ROUTE_FULL_X = 1u << 30;
 // 0.51 against 0.67.
 // Fewer inputs go here where their transformed images are at most PLANES_SMALL together: what counts there are launches, and
 // this route has two fewer than either other.  Over 300 random layers of 1 to 7 inputs (lengths up to 64, 1 to 96 images, 1
-// to 9 taps) 1.15 times as fast up to 32 MB as the faster of the two picks, the worst 5 % behind (2 x 80 -> 16 of 16 x 13 x 13,
-// 7^3 kernels); 1.06 times from there to 100 MB, where the rules of before stay.
-constexpr double PLANES_SMALL = 32e6;
+// to 9 taps) 1.15 times as fast up to 40 MB as the route they took before, the worst 5 % behind (2 x 80 -> 16 of 16 x 13 x 13,
+// 7^3 kernels); 1.05 to 1.1 times, and more often behind, from there to 100 MB, where the rules of before stay.
+constexpr double PLANES_SMALL = 40e6;
 static bool pick_planes(const LayerPlan& L, unsigned flags)
 {
     if (flags & (ROUTE_FULL_X | ZNNI_MAC_REFERENCE | ZNNI_MAC_SINGLE | ZNNI_MAC_BATCH | ZNNI_MAC_XDIRECT | ZNNI_MAC_XBLOCK)) return false;
