@@ -101,7 +101,7 @@ constexpr bool xd_shared(int RT, int CT, bool planes) { return (RT == 1 || CT ==
 template <int RT, int CT, bool PLANES>
 constexpr size_t xd_lds_bytes()
 {
-    return (size_t)16 * ((xd_shared(RT, CT, PLANES) ? 8 * (64 * CT + 16) : 4 * 8 * (16 * CT + 16)) + 4 * 128 * RT + 4 * RT + 5);
+    return (size_t)16 * ((xd_shared(RT, CT, PLANES) ? 8 * (64 * CT + 16) : 4 * 8 * (16 * CT + 16)) + 4 * 128 * RT + 4 * RT + 7);
 }
 // Three workgroups per CU where LDS and registers (168 a lane) allow, two otherwise.
 template <int RT, int CT, bool PLANES>
@@ -156,7 +156,7 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
     const int poz = (int)g.d_Ny.div((unsigned)pencil), poy = pencil - poz * g.Ny;
     half8* const Xs = lds + 4 * RT * 128 + (SHARED ? 0 : wave * 8 * XW);      // this wave's own, or all waves': [hi, lo][quad][XW]
     float* const rjs = reinterpret_cast<float*>(lds + 4 * RT * 128 + (SHARED ? 8 : 32) * XW);           // [RT * 16]
-    unsigned* const wred = reinterpret_cast<unsigned*>(rjs + RT * 16);        // [turn][largest, smallest][wave], [wave]
+    unsigned* const wred = reinterpret_cast<unsigned*>(rjs + RT * 16);        // [turn][largest, smallest, zeros][wave], [wave]
 
     // ---- kernel operands: this thread's share of a step, NU units of 16 bytes (surplus units repeat the last one).
     // Slots past the last one are read from it.
@@ -222,6 +222,8 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
     int sexp = 126;                                          // exponent of the scale the image values carry
     int chunk = 0;
     bool apart = false;                                      // magnitudes along x too far apart for halves
+    unsigned most = 0;                                       // largest finite magnitude (its bits) of the chunks so far
+    bool zeros = false;                                      // whether one of them is zero somewhere along the strip
     // One chunk of sixteen images of the strip to LDS, a (quad, x) unit per lane and round.  Values beyond a row are read
     // from its end, images beyond the last from the last: neither reaches a stored output (the images count as zeros).
     auto round = [&](int n, int qc) { return SHARED ? wave < qc : n < NQ ? n < qc : 64 * (n - NQ) < qc * XH; };
@@ -250,6 +252,7 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
         // are added up (an image far below the others, say of rounding errors only, is no reason to leave halves)
         float m = 0.f;
         unsigned mn = ~0u;
+        bool zero = false;
 #pragma unroll
         for (int n = 0; n < NR; ++n) {
             float u = 0.f;
@@ -257,14 +260,16 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
             for (int q = 0; q < 4; ++q) max3_abs(u, raw[n][q].x, raw[n][q].y);
             m = fmaxf(m, u);
             mn = min(mn, small_code(u));
+            zero |= round(n, QC) && u == 0.f;
         }
-        unsigned mb = wave_max(m), sm = wave_min(mn);
+        unsigned mb = wave_max(m), sm = wave_min(mn), zb = __any(zero);
         if constexpr (SHARED) {
-            unsigned* const red = wred + (chunk & 1) * 8;
-            if (lane == 0) { red[wave] = mb; red[4 + wave] = sm; }
+            unsigned* const red = wred + (chunk & 1) * 12;
+            if (lane == 0) { red[wave] = mb; red[4 + wave] = sm; red[8 + wave] = zb; }
             __syncthreads();                                 // (also: all waves are through with the chunk before)
             mb = (unsigned)__builtin_amdgcn_readfirstlane((int)max(max(red[0], red[1]), max(red[2], red[3])));
             sm = (unsigned)__builtin_amdgcn_readfirstlane((int)min(min(red[4], red[5]), min(red[6], red[7])));
+            zb = (unsigned)__builtin_amdgcn_readfirstlane((int)(red[8] | red[9] | red[10] | red[11]));
         }
         if (mb >= 0x7f800000u) {                             // infinities or NaNs: the scale is that of the finite values
             m = 0.f;
@@ -279,13 +284,17 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
                 }
             mb = wave_max(m);
             if constexpr (SHARED) {
-                if (lane == 0) wred[16 + wave] = mb;
+                if (lane == 0) wred[24 + wave] = mb;
                 __syncthreads();
-                mb = (unsigned)__builtin_amdgcn_readfirstlane((int)max(max(wred[16], wred[17]), max(wred[18], wred[19])));
+                mb = (unsigned)__builtin_amdgcn_readfirstlane((int)max(max(wred[24], wred[25]), max(wred[26], wred[27])));
                 __syncthreads();
             }
         }
-        apart |= split_too_wide(mb, sm);
+        // Next to the largest value of its own chunk; next to that of all chunks so far, whose scale it carries, where an earlier
+        // one is zero somewhere (elsewhere that one's values, of which every column then has some, outweigh it).
+        most = max(most, mb);
+        apart |= split_too_wide(zeros ? most : mb, sm);
+        zeros |= zb != 0;
         const int sn = min(sexp, split_exp(__uint_as_float(mb)));
         if (sn < sexp && chunk) {                            // a larger chunk: the sums follow its scale
 #pragma unroll
