@@ -46,8 +46,9 @@
  *     multiplied in fp32, and so are kernels where all taps of an input image, or one tap of all of them, are that far
  *     below the largest of their output image; the bound stands for single kernel values.
  *     Transform route without x transform: fp32 as well where magnitudes lie that far apart along x, and input images
- *     whose kernels are far smaller than those of others have scales of their own; the bound stands for the spectra of
- *     the input images at one frequency, and for the kernels of an output image after those scales.
+ *     whose kernels are far smaller than those of others have scales of their own.  Where, after those scales, the kernels
+ *     of an output image are more than 2^14 apart or zero, fp32 too if the spectra of the input images at one frequency
+ *     lie more than 2^19 apart, or some are zero; the bound stands for single taps along x.
  */
 #ifndef ZNNI_H
 #define ZNNI_H

@@ -58,7 +58,10 @@ constexpr int KPREP_OZ = 16;
 //
 // Of an output image: no value of a kernel's transform exceeds the sum of its magnitudes, so the factor that brings the
 // largest such sum over the input images (times the transform's own scale) to 2^14 keeps every value in range.  A wave per
-// input image, lanes along its taps.
+// input image, lanes along its taps.  Whether such sums of an output image lie more than 2^UNEVEN apart goes into bits that
+// the inverse of its power of two does not need: the sign where one is zero or that small, the lowest where one is that small
+// and not zero (what either means to the multiply-accumulate: mac_xd.hip).
+constexpr int UNEVEN = 14;
 __device__ __forceinline__ int kprep_col_exp(float cmax, float most)
 {
     const int t = (int)(__float_as_uint(cmax) >> 23) - (int)(__float_as_uint(most) >> 23);
@@ -68,6 +71,7 @@ __device__ __forceinline__ void kprep_row_scale(const float* __restrict__ w, con
                                                 int fo, int fp, int taps, size_t wj_stride, float scale)
 {
     __shared__ float best[4];
+    __shared__ uint2 least[4];
     __shared__ signed char exps[2048];                       // of the first images; beyond, they are worked out again
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     auto cmax = [&](int i) {
@@ -107,6 +111,7 @@ __device__ __forceinline__ void kprep_row_scale(const float* __restrict__ w, con
             S.cinv[i] = __uint_as_float((unsigned)(127 - e) << 23);
         }
     m = 0.f;
+    unsigned lo = ~0u, lo1 = ~0u;                            // smallest sum (its bits); smallest that is not zero, less one
     if (j < fo)
         for (int i0 = wave; i0 < f; i0 += 4 * U) {
             float s[U] = {};
@@ -124,15 +129,21 @@ __device__ __forceinline__ void kprep_row_scale(const float* __restrict__ w, con
             for (int u = 0; u < U; ++u) {
                 const float e = ldexpf(s[u] * scale, -col_exp(min(i0 + 4 * u, f - 1)));
                 m = fmaxf(m, e < INFINITY ? e : 0.f);
+                lo = min(lo, __float_as_uint(e));
+                lo1 = min(lo1, __float_as_uint(e) - 1u);
             }
         }
-    if (lane == 0) best[wave] = m;
+    if (lane == 0) { best[wave] = m; least[wave] = make_uint2(lo, lo1); }
     __syncthreads();
     if (threadIdx.x == 0) {
         m = fmaxf(fmaxf(best[0], best[1]), fmaxf(best[2], best[3]));
+        lo = min(min(least[0].x, least[1].x), min(least[2].x, least[3].x));
+        lo1 = min(min(least[0].y, least[1].y), min(least[2].y, least[3].y));
+        const bool small = (int)lo1 < (int)__float_as_uint(m) - (UNEVEN << 23) && lo1 != ~0u;
+        const unsigned bits = (small || lo == 0 ? 0x80000000u : 0u) | (small ? 1u : 0u);
         const int e = max(min(14 - ((int)((__float_as_uint(m) >> 23) & 255u) - 127), 120), -120);
         S.row[j] = m > 0.f ? __uint_as_float((unsigned)(127 + e) << 23) : 1.f;
-        S.rinv[j] = m > 0.f ? __uint_as_float((unsigned)(127 - e) << 23) : 1.f;
+        S.rinv[j] = m > 0.f ? __uint_as_float((unsigned)(127 - e) << 23 | bits) : 1.f;
     }
 }
 __global__ __launch_bounds__(256) void k_kprep_z(const float* __restrict__ w, float2* __restrict__ A1,

@@ -41,8 +41,13 @@
 //    wave whose largest values at one x and another are more than 2^SPLIT_SPAN apart sums all over again in fp32, from
 //    global memory.  (A voxel of 1e9 in every 100 000: 40 -> 40 of 128^3, 3^3 kernels 0.84 -> 1.34 ms for the layer, 80 -> 80
 //    with 7^3 2.9 -> 6.8; on fp32 products alone 0.95 and 4.2.)
-//  * What is left: input images far apart whose kernels do not make up for it, each the only one that some output image is
-//    made of, and kernels of an output image far apart both ways: an absolute error of 2^-40 of the largest.
+//  * Kernels of an output image of uneven size (the sums of their magnitudes more than 2^14 apart, or zero: kprep_row_scale
+//    leaves two bits behind).  Elsewhere the largest input images have a part in every output image, and what is lost of the
+//    others is small next to it.  Here an output image may be made of the small ones alone: every image then counts by
+//    itself when a wave looks at how far its values lie apart, and the fp32 sums take kernel transforms made again from A1.
+//    (8 x 40 -> 20 of 40 x 24 x 22, groups of images 2^30 apart that no output image shares: 2.9e-3 off without it, 3e-7
+//    with it.  Where kernels are even it costs 0.3 us.)
+//  * What is left: single taps along x far below the others of their output image (an absolute error of 2^-40 of the largest).
 //
 // Whole layers come out 0.6 to 1.0 times as far from their 64-bit values as with fp32 matrix
 // instructions (80 -> 80 of 128^3, 7^3 kernels: 3.7e-7 against 5.4e-7), and the kernel is (multiply-accumulate alone,
@@ -80,7 +85,13 @@ struct XdArgs {
     FastDiv d_sub, d_pg, d_spr, d_nwg, d_Ny;
     const float2* X2;
     const half8* A;             // [pencil][slot][row tile][hi, lo][16 output images], 4 complex images each
-    const float* rinv;          // [Mp] inverse of the power of two the kernel transforms of an output image carry
+    const float* rinv;          // [Mp] inverse of the power of two the kernel transforms of an output image carry, and two bits
+    // what the kernel transforms are made of (k_kprep_xd): after the z stage, scales, twiddles along y
+    const float2* A1;
+    const float *row, *cinv;
+    const float2* tw;
+    float scale;
+    int ky, fp;
     float2* Yd;
     unsigned ximg, yimg;        // elements between the rows of consecutive images in X2 / Yd
     size_t xpen, ypen;          // elements between the rows of pencils (oz, oy) and (oz + 1, oy)
@@ -224,6 +235,9 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
     bool apart = false;                                      // magnitudes along x too far apart for halves
     unsigned most = 0;                                       // largest finite magnitude (its bits) of the chunks so far
     bool zeros = false;                                      // whether one of them is zero somewhere along the strip
+    // Kernels of an output image of uneven size: every image counts by itself, in all chunks
+    unsigned uneven = 0;
+    unsigned least = ~0u;                                    // smallest code of the chunks so far
     // One chunk of sixteen images of the strip to LDS, a (quad, x) unit per lane and round.  Values beyond a row are read
     // from its end, images beyond the last from the last: neither reaches a stored output (the images count as zeros).
     auto round = [&](int n, int qc) { return SHARED ? wave < qc : n < NQ ? n < qc : 64 * (n - NQ) < qc * XH; };
@@ -253,6 +267,8 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
         float m = 0.f;
         unsigned mn = ~0u;
         bool zero = false;
+        unsigned bits = __float_as_uint(rjs[min(lane, RT * 16 - 1)]);
+        if (RT > 4) bits |= __float_as_uint(rjs[64 + l16]);
 #pragma unroll
         for (int n = 0; n < NR; ++n) {
             float u = 0.f;
@@ -261,6 +277,24 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
             m = fmaxf(m, u);
             mn = min(mn, small_code(u));
             zero |= round(n, QC) && u == 0.f;
+        }
+        uneven = __ballot((int)bits < 0) != 0;
+        if (uneven) {
+            // (where some are far below the largest and not zero, halves hold those badly, and an image that is zero is as good
+            // as one that is far below the others)
+            const unsigned tiny = __ballot(bits & 1u) != 0;
+            mn = ~0u;
+#pragma unroll
+            for (int n = 0; n < NR; ++n)
+                if (round(n, QC))
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        float v = 0.f;
+                        float2 p = raw[n][q];
+                        asm volatile("" : "+v"(p.x), "+v"(p.y));     // (for the same reason as below)
+                        max3_abs(v, p.x, p.y);
+                        mn = min(mn, (__float_as_uint(v) << 1) - 1u + tiny);
+                    }
         }
         unsigned mb = wave_max(m), sm = wave_min(mn), zb = __any(zero);
         if constexpr (SHARED) {
@@ -293,7 +327,8 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
         // Next to the largest value of its own chunk; next to that of all chunks so far, whose scale it carries, where an earlier
         // one is zero somewhere (elsewhere that one's values, of which every column then has some, outweigh it).
         most = max(most, mb);
-        apart |= split_too_wide(zeros ? most : mb, sm);
+        least = min(least, sm);
+        apart |= split_too_wide(zeros || uneven ? most : mb, uneven ? least : sm);
         zeros |= zb != 0;
         const int sn = min(sexp, split_exp(__uint_as_float(mb)));
         if (sn < sexp && chunk) {                            // a larger chunk: the sums follow its scale
@@ -400,8 +435,7 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
     if (nsteps > 2) load_a();
     const half8* const as0 = As + kk * RT * 32 + l16;
     for (int gs = 0, buf = 0; gs < nsteps; gs += 2, buf ^= 1) {
-        // this pair's operands are in place, the last one's are free (staged together, the first chunk's barriers say so)
-        if (!SHARED || gs) __syncthreads();
+        __syncthreads();                                     // this pair's operands are in place, the last one's are free
         if (live) step(as0 + buf * RT * 256);
         if (gs + 2 < nsteps) {
             park_a(gs + 2, buf ^ 1);
@@ -413,8 +447,20 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
 
     if (apart) {
         // All over again in fp32, from global memory, four slots of one complex image each per pair of matrix instructions
-        // (kernels: their two halves added up).
+        // (kernels: their two halves added up, or, where an output image's are uneven, the sum along y again).
         const float sx = pow2f(sexp);
+        const size_t per = (size_t)K * g.fp * g.Mp;
+        const float2* const a1 = g.A1 + (size_t)poz * g.ky * per + mblk * RT * 16 + l16;
+        auto again = [&](int r, int i, int tap) {
+            float2 s = make_float2(0.f, 0.f);
+            for (int b = 0, t = 0; b < g.ky; ++b) {          // t = (poy * b) mod Ny
+                s = cfma(s, a1[b * per + ((size_t)tap * g.fp + i) * g.Mp + r * 16], g.tw[t]);
+                t += poy;
+                if (t >= g.Ny) t -= g.Ny;
+            }
+            const float cr = g.row[(mblk * RT + r) * 16 + l16] * g.scale, ci = g.cinv[i];
+            return make_float2(s.x * cr * ci, s.y * cr * ci);
+        };
 #pragma unroll
         for (int r = 0; r < RT; ++r)
 #pragma unroll
@@ -438,7 +484,8 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
 #pragma unroll
                 for (int r = 0; r < RT; ++r) {
                     const half2 ah = reinterpret_cast<const half2*>(ap + r * 32)[q], al = reinterpret_cast<const half2*>(ap + r * 32 + 16)[q];
-                    const float ar = (float)ah[0] + (float)al[0], ai = (float)ah[1] + (float)al[1];
+                    float ar = (float)ah[0] + (float)al[0], ai = (float)ah[1] + (float)al[1];
+                    if (uneven) { const float2 e = again(r, 4 * qd + q, tap); ar = e.x; ai = e.y; }
 #pragma unroll
                     for (int c = 0; c < CT; ++c) {
                         auto mm = [](float p, float v, floatx4& d) {
@@ -457,13 +504,14 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
     // ---- results.  The smaller factor first: either alone may be out of range where the result is not.  Rows of Yd are
     // padded to whole fours.
     const float inv = pow2f(-sexp);
+    auto scale_of = [&](int row) { return __uint_as_float(__float_as_uint(rjs[row]) & 0x7f800000u); };
     float2* const ypen = g.Yd + (size_t)poz * g.ypen + (size_t)poy * g.yrow;
 #pragma unroll
     for (int r = 0; r < RT; ++r) {
         const int j0 = (mblk * RT + r) * 16;
         if constexpr (XROWS) {                               // element e of lane (kk, l16): image l16, output 4 kk + e
             if (j0 + l16 >= g.fo) continue;
-            const float s = rjs[r * 16 + l16], f0 = fminf(inv, s), f1 = fmaxf(inv, s);
+            const float s = scale_of(r * 16 + l16), f0 = fminf(inv, s), f1 = fmaxf(inv, s);
             float2* y = ypen + (size_t)(unsigned)(sI * g.fo + j0 + l16) * g.yimg;
 #pragma unroll
             for (int c = 0; c < CT; ++c) {
@@ -485,7 +533,7 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
             for (int e = 0; e < 4; ++e) {
                 const int j = j0 + 4 * kk + e;
                 if (j >= g.fo) break;
-                const float s = rjs[r * 16 + 4 * kk + e], f0 = fminf(inv, s), f1 = fmaxf(inv, s);
+                const float s = scale_of(r * 16 + 4 * kk + e), f0 = fminf(inv, s), f1 = fmaxf(inv, s);
                 float2* y = ypen + (size_t)(unsigned)(sI * g.fo + j) * g.yimg;
 #pragma unroll
                 for (int c = 0; c < CT; ++c) {
@@ -607,17 +655,18 @@ __global__ __launch_bounds__(256) void k_kprep_xd(const float2* __restrict__ A1,
     }
 }
 
+// The factor of the two unnormalised transforms, no power of two.
+static float xd_scale(const Dims& d) { return (float)(1.0 / ((double)d.Ny * d.Nz)); }
 template <int KY>
 static znni_status launch_kprep_xd_k(const LayerPlan& L, hipStream_t st)
 {
     const Dims& d = L.d;
     const int items = d.kx * (L.fp >> 2) * L.Mp;
-    const float scale = (float)(1.0 / ((double)d.Ny * d.Nz));
     const int nb = (items + 255) / 256;
     int noy = KX_OY;
     while (noy > 4 && (long long)nb * ((d.Ny + noy - 1) / noy) * L.ozn < 1024) noy >>= 1;
     k_kprep_xd<KY><<<dim3(nb, (d.Ny + noy - 1) / noy, L.ozn), dim3(256), 0, st>>>(
-        L.A1 + (size_t)L.oz0 * d.ky * d.kx * L.fp * L.Mp, reinterpret_cast<half8*>(L.A), L.twy, split_scales(L).row, split_scales(L).cinv, d.Ny, d.ky, d.kx, L.fp, L.Mp, scale, noy);
+        L.A1 + (size_t)L.oz0 * d.ky * d.kx * L.fp * L.Mp, reinterpret_cast<half8*>(L.A), L.twy, split_scales(L).row, split_scales(L).cinv, d.Ny, d.ky, d.kx, L.fp, L.Mp, xd_scale(d), noy);
     if (hipGetLastError() != hipSuccess) return ZNNI_ERR_HIP;
     return ZNNI_OK;
 }
@@ -650,6 +699,8 @@ static znni_status launch_xd(const LayerPlan& L, int accumulate, hipStream_t st)
     const Dims& d = L.d;
     XdArgs g;
     g.A = reinterpret_cast<const half8*>(L.A); g.rinv = split_scales(L).rinv;
+    g.A1 = L.A1 + (size_t)L.oz0 * d.ky * d.kx * L.fp * L.Mp; g.row = split_scales(L).row; g.cinv = split_scales(L).cinv;
+    g.tw = L.twy; g.scale = xd_scale(d); g.ky = d.ky; g.fp = L.fp;
     if (PLANES) {
         const unsigned nb = (unsigned)(d.nx + 3) / 4, nbo = (unsigned)(d.nox + 3) / 4;
         g.xpen = (size_t)nb * d.Ny * 4; g.ximg = d.zc * (unsigned)g.xpen; g.xrow = 4; g.xblk = d.Ny * 4;

@@ -77,7 +77,8 @@ znni_status make_plan(int S, int f, int fo, const int n[3], const int k[3], unsi
 
 int lines_per_tile(int N);
 
-// The scales behind LayerPlan::rs, powers of two: of the kernel transforms of an output image, with its inverse; of an
+// The scales behind LayerPlan::rs, powers of two: of the kernel transforms of an output image, with its inverse (whose sign and
+// lowest bit say whether its kernels are of uneven size, kprep_row_scale in mac.hip); of an
 // input image's values, with the inverse that its kernel transforms carry; and, in up to sixteen parts, the largest kernel
 // magnitudes of the input images that the latter come from.
 struct SplitScales {

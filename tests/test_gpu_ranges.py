@@ -47,3 +47,62 @@ def test_images_that_are_zero_beyond_large_values(oracle, layer, which):
     got, exp = _run(inp, w, route), oracle.conv3d(inp, w, None, relu=False)
     for x in range(n[0] - k[0] + 1):
         assert np.linalg.norm(got[:, :, x] - exp[:, :, x]) <= 1e-6 * np.linalg.norm(exp[:, :, x]), x
+
+
+def _uneven(seed, layer, far, kind):
+    """Images in two groups 2^far apart, and banks under which some output images are made of the small ones alone."""
+    _, S, f, fo, n, k = layer
+    inp, w = _rand(seed, S, f, fo, n, k)
+    if kind == "groups":            # output images of either group, the other's kernels zero
+        inp[:, 1::2] = np.ldexp(inp[:, 1::2], -far)
+        w[::2, 1::2] = w[1::2, ::2] = 0
+    elif kind == "one":             # one output image in which the large images have no part
+        inp[:, 1::2] = np.ldexp(inp[:, 1::2], -far)
+        w[fo // 2, ::2] = 0
+    elif kind == "crossed":         # the other group's kernels as much smaller as its images are larger
+        inp[:, 1::2] = np.ldexp(inp[:, 1::2], far)
+        w[::2, 1::2], w[1::2, ::2] = np.ldexp(w[::2, 1::2], -far), np.ldexp(w[1::2, ::2], -far)
+    else:                           # "silent": the images whose kernels are the large ones are zero
+        inp[:, ::2] = 0
+        w[fo // 3, 1::2] = np.ldexp(w[fo // 3, 1::2], -far)
+    return inp, w
+
+
+def _each_output_image(got, exp):
+    for s in range(got.shape[0]):
+        for j in range(got.shape[1]):
+            assert np.linalg.norm(got[s, j] - exp[s, j]) <= 1e-6 * np.linalg.norm(exp[s, j]), (s, j)
+
+
+@pytest.mark.parametrize("layer", LAYERS + [(False, 9, 32, 33, (19, 16, 15), (3, 3, 3)), ("xdirect", 1, 8, 5, (70, 12, 20), (2, 11, 2))],
+                         ids=lambda c: "%s_S%d_f%dx%d" % ((c[0] or "planes",) + c[1:4]))
+@pytest.mark.parametrize("kind", ["groups", "one", "crossed", "silent"])
+@pytest.mark.parametrize("far", [13, 20, 30])
+def test_uneven_kernels_keep_every_output_image(oracle, layer, kind, far):
+    """What fp32 products give: an output image is as good as the images it is made of, however large the others are."""
+    inp, w = _uneven(40, layer, far, kind)
+    _each_output_image(_run(inp, w, layer[0]), oracle.conv3d(inp, w, None, relu=False))
+
+
+@pytest.mark.parametrize("share,S,f,fo,n,k", [(0.6, 20, 6, 5, (30, 32, 32), (3, 3, 3)), (0.9, 8, 96, 64, (20, 48, 48), (3, 3, 3)),
+                                              (0.3, 1, 70, 50, (24, 24, 24), (3, 3, 3))])
+@pytest.mark.parametrize("kind", ["crossed", "silent"])
+def test_uneven_kernels_under_a_budget(oracle, share, S, f, fo, n, k, kind):
+    """Sub-batches, slabs and blocks of images: kernel transforms made again belong to their rows and images."""
+    inp, w = _uneven(41, (False, S, f, fo, n, k), 24, kind)
+    d = torch.device("cuda:0")
+    ws = torch.full((int(share * B.znni_conv3d_fft_workspace(S, f, fo, n, k)),), 0xFF, dtype=torch.uint8, device=d)
+    print(f"[ranges] {kind}, divided {B.znni_conv3d_fft_sublayers(S, f, fo, n, k, ws.numel())[0]}", flush=True)
+    got = B.znni_conv3d_fft_budget(torch.from_numpy(inp).to(d), torch.from_numpy(w).to(d), None, workspace=ws)
+    _each_output_image(got.cpu().numpy().astype(np.float64), oracle.conv3d(inp, w, None, relu=False))
+
+
+@pytest.mark.parametrize("layer", LAYERS[:4], ids=lambda c: "%s_S%d_f%dx%d" % ((c[0] or "planes",) + c[1:4]))
+def test_uneven_kernels_that_were_kept(oracle, layer):
+    route, S, f, fo, n, k = layer
+    inp, w = _uneven(42, layer, 24, "crossed")
+    d = torch.device("cuda:0")
+    tw, ws = torch.from_numpy(w).to(d), B.alloc_workspace(S, f, fo, n, k)
+    B.znni_conv3d_fft(torch.from_numpy(_rand(43, S, f, fo, n, k)[0]).to(d), tw, None, workspace=ws, mac_reference=route)
+    got = B.znni_conv3d_fft(torch.from_numpy(inp).to(d), tw, None, workspace=ws, mac_reference=route, keep_kernels=True)
+    _each_output_image(got.cpu().numpy().astype(np.float64), oracle.conv3d(inp, w, None, relu=False))
