@@ -127,6 +127,15 @@ __device__ __forceinline__ void xd_slot(int slot, int K, int fq, int& quad, int&
     quad = 4 * c + s - a * QC;
 }
 
+// What lanes of a wave have written to LDS is there for its other lanes: the wave's LDS operations complete in order, so that
+// nothing has to be waited for, and the fences keep the compiler from moving any across.
+__device__ __forceinline__ void wave_handover()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 template <int RT, int CT, bool SUM, bool PLANES>
 __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
 {
@@ -344,6 +353,7 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
         }
         sexp = sn;
         const float sx = pow2f(sn);
+        if constexpr (!SHARED) wave_handover();              // (all lanes are through with the chunk before)
 #pragma unroll
         for (int n = 0; n < NR; ++n) {
             if (!round(n, QC)) continue;
@@ -360,7 +370,7 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
             d[4 * XW] = __builtin_bit_cast(half8, l);
         }
         if constexpr (SHARED) __syncthreads();
-        else __builtin_amdgcn_wave_barrier();
+        else wave_handover();
         ++chunk;
     };
 
