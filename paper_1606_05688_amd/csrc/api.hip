@@ -103,21 +103,32 @@ constexpr unsigned ROUTE_FULL_X = 1u << 30;
 // kernels); 64 x 80 -> 80 of 51^3, 5^3 7.1 against 9.7 ms; 8 x 32 -> 32 of 64^3, 7^3
 // 0.51 against 0.67.
 // Fewer inputs go here where their transformed images are at most PLANES_SMALL together: what counts there are launches, and
-// this route has two fewer than either other.  Over 300 random layers of 1 to 7 inputs (lengths up to 64, 1 to 96 images, 1
-// to 9 taps) 1.15 times as fast up to 40 MB as the route they took before, the worst 5 % behind (2 x 80 -> 16 of 16 x 13 x 13,
-// 7^3 kernels); 1.05 to 1.1 times, and more often behind, from there to 100 MB, where the rules of before stay.
+// this route has two fewer than either other.  Against the other untransformed one that is all: over 1179 random layers 1.18
+// times as fast, five more than 3 % behind (29 -> 3 of 70 x 49 x 51, 3^3 kernels 68 against 61 us), where a transform's
+// workgroups are a few more than a multiple of the chip's 256 units.  The fully transformed one multiplies sixteen bins of a
+// pencil at a time in workgroups of their own, where a wave here walks through the whole sum: a chunk of sixteen images costs
+// it 0.39 us more and a step of four (quad, tap) slots 0.25, which two launches (9.9 us) and the quicker products of the second
+// tap and the next ones (2.8 ps a value of the kernel bank) make up for or not; where the batch form would serve all inputs, its
+// products count as above.  Over 1344 random layers of 1 to 7 inputs (lengths up to 64, 1 to 1500 images, 1 to 9 taps) 1.154
+// times as fast as on that route, the better of the two 1.165 times, 23 more than 3 % behind (7 x 227 -> 1460 of 8^3, 2^3
+// kernels 350 against 262 us); always this one 1.109, with as little as half the speed (1104 -> 2 of 8^3, 7^3 386 against 202).
 constexpr double PLANES_SMALL = 40e6;
 static bool pick_planes(const LayerPlan& L, unsigned flags)
 {
     if (flags & (ROUTE_FULL_X | ZNNI_MAC_REFERENCE | ZNNI_MAC_SINGLE | ZNNI_MAC_BATCH | ZNNI_MAC_XDIRECT | ZNNI_MAC_XBLOCK)) return false;
     if (!mac_xd_available(L) || !fused_planes_available(L)) return false;
     const Dims& d = L.d;
-    if (L.S < 8) return 8.0 * (L.nimg + (double)L.nimgo) * d.nx * d.zc * d.Ny <= PLANES_SMALL;
-    const double pairs = (double)L.fp * L.Mp;
+    const double pairs = (double)L.fp * L.Mp, pencils = (double)d.zc * d.Ny;
+    // seconds of a pencil
     const double products = 24.0 * d.kx * ((d.nox + 15) & ~15) * pairs * L.S / 0.7e15;
     const double batch = 1.7e-12 * pairs * d.Nx * ((L.S + 15) / 16);
     const double passes = 8.0 * ((double)L.nimg * (d.nx + d.Nx) + (double)L.nimgo * (d.Nx + d.nox)) / 5e12;
-    return products < batch + passes;
+    if (L.S >= 8) return products < batch + passes;
+    if (8.0 * (L.nimg + (double)L.nimgo) * d.nx * pencils > PLANES_SMALL) return false;
+    if (pick_untransformed_x(L, flags)) return true;
+    double gain = 9.9e-6 - 0.39e-6 / 16 * L.f - 0.25e-6 / 16 * d.kx * L.fp + 2.8e-12 * (d.kx - 1) * pairs * pencils;
+    if (mac_batch_preferred(L) && products > batch + passes) gain -= 2.1 * (products - batch - passes) * pencils;
+    return gain > 0;
 }
 
 static bool pick_xdirect(const LayerPlan& L, unsigned flags)
