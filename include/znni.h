@@ -196,8 +196,7 @@ znni_status znni_conv3d_fft_profile(int S, int f, int fo, int n, int k,
  * and output tensors, unpadded); flops[s] = floating-point operations of the contraction in the
  * multiply-accumulate stage, counting 8 per complex multiply-add: (8 S + 8 (kx - 1)) f f' per bin of the transformed
  * image when the x axis is transformed (the per-bin product of Algorithm 3 plus the kx-term sum that stands in for a
- * stored kernel spectrum), 8 kx S f f' per bin of the image transformed along y and z only when it is not (outputs
- * along x in whole fours for batches of small images, whose rows lie in blocks of four), 64 S f f'
+ * stored kernel spectrum), 8 kx S f f' per bin of the image transformed along y and z only when it is not, 64 S f f'
  * per block of 9 - kx outputs where x is transformed in blocks of eight.  Stages a
  * call does not run (the y or z stage where one kernel does both, the x stages where the x axis is not transformed)
  * get 0.  Both arrays have ZNNI_NUM_STAGES elements, indexed like stage_ms above.

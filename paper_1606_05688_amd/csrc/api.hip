@@ -668,8 +668,6 @@ znni_status znni_conv3d_fft_stage_work_v(int S, int f, int fo, const int n[3], c
         const double bins = zc * d.Ny * d.nox;
         hbm_bytes[ZNNI_STAGE_MAC] = ni * x2 + a + no * y2;
         flops[ZNNI_STAGE_MAC] = 8.0 * d.kx * S * (double)f * fo * bins;
-        // rows in blocks of four: the products of whole blocks
-        if (L.planes) flops[ZNNI_STAGE_MAC] = 8.0 * d.kx * S * (double)f * fo * zc * d.Ny * ((d.nox + 3) / 4 * 4);
         if (L.xblock) {
             // one length-8 product per block of V = 9 - kx outputs
             const int V = 9 - d.kx;

@@ -16,6 +16,8 @@ def i3(v):
 
 def family(name):
     """Which layout of output spectra a multiply-accumulate kernel writes; None for other kernels."""
+    if "k_mac_planes" in name:
+        return "four planes"
     if "k_mac_xd" in name or "k_mac_xb" in name:
         return "x not transformed"
     return "x transformed" if re.search(r"k_mac", name) else None
@@ -41,6 +43,7 @@ def main(path, recorder, count):
     sz, vp = ctypes.c_size_t, ctypes.c_void_p
     rng = np.random.default_rng(11)
     ran = divided = ragged = 0
+    seen = set()
     layers = [(1, 91, 38, (18, 18, 18), (6, 6, 6), 0.8), (1, 88, 14, (23, 23, 23), (6, 6, 6), 0.8),
               (1, 77, 83, (17, 17, 17), (7, 7, 7), 0.8), (1, 115, 27, (17, 28, 27), (6, 3, 5), 0.6),
               (1, 40, 20, (100, 100, 100), (5, 5, 5), 0.5), (1, 24, 40, (24, 20, 16), (5, 5, 2), 0.25)]
@@ -71,9 +74,11 @@ def main(path, recorder, count):
                 assert len(set(macs)) == 1, f"{S} x {f} -> {fo} of {n}, kernels {k}, flags {flags}: {macs}"
                 # and the inverse reads what they wrote (pass 7: rows of x as they are)
                 assert (macs[0] == "x not transformed") == bool(re.search(r"k_pass(_long)?ILi\d+ELi\d+ELi7E", inverse)), inverse
+                assert (macs[0] == "four planes") == ("k_inv_yz_planes" in inverse), inverse
+                seen.add(macs[0])
             ran += 1
     print(f"{ran} calls, {divided} layers in blocks of input images, {ragged} with a smaller last block: one route each")
-    assert divided > 20 and ragged > 10
+    assert divided > 20 and ragged > 10 and len(seen) == 3
 
 
 if __name__ == "__main__":

@@ -27,17 +27,22 @@ def test_blocks_of_one_output_block_take_one_route(recorder):
     assert "one route each" in r.stdout
 
 
-# (S, f, fo, n, k, x axis transformed): measured on both routes, the faster one named
-@pytest.mark.parametrize("layer", [(1, 10, 44, 59, 3, False), (1, 8, 8, 64, 5, False), (1, 7, 1, 65, 7, False), (1, 80, 80, 100, 5, False),
-                                   (1, 50, 8, 19, 7, True), (7, 88, 1, 37, 2, True), (4, 4, 118, 19, 3, True),
-                                   (7, 103, 7, 54, 3, True), (1, 45, 30, 16, 7, True), (1, 18, 122, 41, 6, False),
-                                   (3, 83, 6, 41, 5, False), (64, 80, 80, 51, 5, True)],
+# (S, f, fo, n, k, route): measured on the routes that take the layer, the fastest one named, or one that is level with it
+# (10 -> 44 and 18 -> 122 untransformed either way; 50 -> 8 of 19^3 47 us on both routes but the third)
+@pytest.mark.parametrize("layer", [(1, 10, 44, 59, 3, "xdirect"), (1, 8, 8, 64, 5, "planes"), (1, 7, 1, 65, 7, "xdirect"),
+                                   (1, 80, 80, 100, 5, "xdirect"), (1, 50, 8, 19, 7, "planes"), (7, 88, 1, 37, 2, "full x"),
+                                   (4, 4, 118, 19, 3, "planes"), (7, 103, 7, 54, 3, "full x"), (1, 45, 30, 16, 7, "planes"),
+                                   (1, 18, 122, 41, 6, "xdirect"), (3, 83, 6, 41, 5, "xdirect"), (64, 80, 80, 51, 5, "planes"),
+                                   (8, 32, 32, 64, 7, "planes"), (1, 9, 121, 14, 7, "planes"), (1, 32, 32, 64, 7, "xdirect")],
                          ids=lambda c: "S%d_f%dx%d_n%d_k%d_%s" % c)
 def test_small_images_take_the_faster_route(layer):
-    S, f, fo, n, k, transformed = layer
-    _, flops = B.znni_conv3d_fft_stage_work(S, f, fo, n, k)
-    _, untransformed = B.znni_conv3d_fft_stage_work(S, f, fo, n, k, mac_reference="xdirect")
-    assert (flops != untransformed) == transformed
+    S, f, fo, n, k, route = layer
+    nbytes, flops = B.znni_conv3d_fft_stage_work(S, f, fo, n, k)
+    fused = nbytes["fwd_y"] == 0 and nbytes["inv_z"] == 0
+    assert ("full x" if nbytes["fwd_x"] else "planes" if fused else "xdirect") == route
+    # the products are the method's, however the rows lie
+    untransformed = B.znni_conv3d_fft_stage_work(S, f, fo, n, k, mac_reference="xdirect")[1]
+    assert (flops == untransformed) == (route != "full x")
 
 
 # few pencils and long sums: a wave of the untransformed route would walk through the whole sum alone (us there and transformed:
