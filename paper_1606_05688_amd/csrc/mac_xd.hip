@@ -398,12 +398,12 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
         half8 ah[RT], al[RT];
 #pragma unroll
         for (int r = 0; r < RT; ++r) { ah[r] = as[r * 32]; al[r] = as[r * 32 + 16]; }
-        // (r, -i) -> (i, r), one packed instruction per register
-        auto swp = [](half8 v) {
+        // (r, -i) -> (i, r), or of the kernel operand (r, i) -> (i, -r): one packed instruction per register
+        auto swp = [](half8 v, float a, float b) {
             half8 o;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const half2 p = half2{v[2 * e + 1], v[2 * e]} * half2{(_Float16)-1.f, (_Float16)1.f};
+                const half2 p = half2{v[2 * e + 1], v[2 * e]} * half2{(_Float16)a, (_Float16)b};
                 o[2 * e] = p[0]; o[2 * e + 1] = p[1];
             }
             return o;
@@ -413,26 +413,53 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
         // 45 of them in a row (48 images, five taps) that is 2.1e-7 of the result, 0.6e-7 this way, for 8 % more time.
         const floatx4 zero = floatx4{0.f, 0.f, 0.f, 0.f};
 #define ZNNI_XD_MFMA(D, A, X, C) D = XROWS ? __builtin_amdgcn_mfma_f32_16x16x32_f16(X, A, C, 0, 0, 0) : __builtin_amdgcn_mfma_f32_16x16x32_f16(A, X, C, 0, 0, 0)
+        if constexpr (2 * RT > CT) {
 #pragma unroll
-        for (int c = 0; c < CT; ++c) {
-            const half8 hr = xs[16 * c], lr = xs[4 * XW + 16 * c];
-            const half8 hi = swp(hr), li = swp(lr);
-            constexpr int RG = RT == 4 ? 2 : 3;              // row tiles at a time: enough products that do not wait for each other
+            for (int c = 0; c < CT; ++c) {
+                const half8 hr = xs[16 * c], lr = xs[4 * XW + 16 * c];
+                const half8 hi = swp(hr, -1.f, 1.f), li = swp(lr, -1.f, 1.f);
+                constexpr int RG = RT == 4 ? 2 : 3;              // row tiles at a time: enough products that do not wait for each other
 #pragma unroll
-            for (int r0 = 0; r0 < RT; r0 += RG) {
-                floatx4 tr[RG], ti[RG];
+                for (int r0 = 0; r0 < RT; r0 += RG) {
+                    floatx4 tr[RG], ti[RG];
 #pragma unroll
-                for (int r = r0; r < RT && r < r0 + RG; ++r) { tr[r - r0] = SUM ? zero : re[r][c]; ti[r - r0] = SUM ? zero : im[r][c]; }
+                    for (int r = r0; r < RT && r < r0 + RG; ++r) { tr[r - r0] = SUM ? zero : re[r][c]; ti[r - r0] = SUM ? zero : im[r][c]; }
 #pragma unroll
-                for (int r = r0; r < RT && r < r0 + RG; ++r) { ZNNI_XD_MFMA(tr[r - r0], ah[r], lr, tr[r - r0]); ZNNI_XD_MFMA(ti[r - r0], ah[r], li, ti[r - r0]); }
+                    for (int r = r0; r < RT && r < r0 + RG; ++r) { ZNNI_XD_MFMA(tr[r - r0], ah[r], lr, tr[r - r0]); ZNNI_XD_MFMA(ti[r - r0], ah[r], li, ti[r - r0]); }
 #pragma unroll
-                for (int r = r0; r < RT && r < r0 + RG; ++r) { ZNNI_XD_MFMA(tr[r - r0], al[r], hr, tr[r - r0]); ZNNI_XD_MFMA(ti[r - r0], al[r], hi, ti[r - r0]); }
+                    for (int r = r0; r < RT && r < r0 + RG; ++r) { ZNNI_XD_MFMA(tr[r - r0], al[r], hr, tr[r - r0]); ZNNI_XD_MFMA(ti[r - r0], al[r], hi, ti[r - r0]); }
 #pragma unroll
-                for (int r = r0; r < RT && r < r0 + RG; ++r) { ZNNI_XD_MFMA(tr[r - r0], ah[r], hr, tr[r - r0]); ZNNI_XD_MFMA(ti[r - r0], ah[r], hi, ti[r - r0]); }
+                    for (int r = r0; r < RT && r < r0 + RG; ++r) { ZNNI_XD_MFMA(tr[r - r0], ah[r], hr, tr[r - r0]); ZNNI_XD_MFMA(ti[r - r0], ah[r], hi, ti[r - r0]); }
 #pragma unroll
-                for (int r = r0; r < RT && r < r0 + RG; ++r) {
-                    re[r][c] = SUM ? re[r][c] + tr[r - r0] : tr[r - r0];
-                    im[r][c] = SUM ? im[r][c] + ti[r - r0] : ti[r - r0];
+                    for (int r = r0; r < RT && r < r0 + RG; ++r) {
+                        re[r][c] = SUM ? re[r][c] + tr[r - r0] : tr[r - r0];
+                        im[r][c] = SUM ? im[r][c] + ti[r - r0] : ti[r - r0];
+                    }
+                }
+            }
+        } else {
+            // Few row tiles for many column tiles: the second form of an operand from the kernels' side, once a step (1 x 2 to
+            // 1 x 4 tiles and 2 x 4 tiles take 1 to 2 % less of the layer, 2 -> 2 of 220 x 110 x 129, 6^3 kernels 126.6 -> 123.4 us;
+            // 2 x 3 tiles took 2 % more).
+            half8 bh[RT], bl[RT];
+#pragma unroll
+            for (int r = 0; r < RT; ++r) { bh[r] = swp(ah[r], 1.f, -1.f); bl[r] = swp(al[r], 1.f, -1.f); }
+#pragma unroll
+            for (int c = 0; c < CT; ++c) {
+                const half8 hr = xs[16 * c], lr = xs[4 * XW + 16 * c];
+                floatx4 tr[RT], ti[RT];
+#pragma unroll
+                for (int r = 0; r < RT; ++r) { tr[r] = SUM ? zero : re[r][c]; ti[r] = SUM ? zero : im[r][c]; }
+#pragma unroll
+                for (int r = 0; r < RT; ++r) { ZNNI_XD_MFMA(tr[r], ah[r], lr, tr[r]); ZNNI_XD_MFMA(ti[r], bh[r], lr, ti[r]); }
+#pragma unroll
+                for (int r = 0; r < RT; ++r) { ZNNI_XD_MFMA(tr[r], al[r], hr, tr[r]); ZNNI_XD_MFMA(ti[r], bl[r], hr, ti[r]); }
+#pragma unroll
+                for (int r = 0; r < RT; ++r) { ZNNI_XD_MFMA(tr[r], ah[r], hr, tr[r]); ZNNI_XD_MFMA(ti[r], bh[r], hr, ti[r]); }
+#pragma unroll
+                for (int r = 0; r < RT; ++r) {
+                    re[r][c] = SUM ? re[r][c] + tr[r] : tr[r];
+                    im[r][c] = SUM ? im[r][c] + ti[r] : ti[r];
                 }
             }
         }
