@@ -76,6 +76,7 @@
 // or, in a last chunk of fewer images, several taps of fewer quads.  Kernel operands travel global memory -> registers -> LDS,
 // requested two pairs of steps and parked one pair ahead, one quarter per wave (every wave reading all of them for itself
 // asks more of the vector L1 than it delivers: 85 / CT bytes per clock of 64); one barrier per pair of steps.
+#include <algorithm>
 #include "mac_common.h"
 #include "split.h"
 
@@ -770,11 +771,14 @@ static znni_status launch_xd(const LayerPlan& L, int accumulate, hipStream_t st)
 
 // Columns: the strip width whose waves, dealt four to a workgroup, are through a chunk first: its products, its rounds of
 // staging and what a wave waits for in any case (in cycles of a SIMD; products 16 per matrix instruction, 200 per round, 800).
-// Of two that tie the wider one.
+// Of two that tie the wider one.  Fewer waves than the chip has SIMDs all run at once, so that only the time of one counts (without
+// that: 5 x 613 -> 26 of 7 x 7 x 10, 2^3 kernels 164 us for the layer, 141 with it; 2 x 306 -> 80 of 15 x 9 x 13,
+// 5^3 219 and 200).
 template <int RT, bool SUM, bool PLANES>
 static znni_status launch_xd_cols_s(const LayerPlan& L, int accumulate, hipStream_t st)
 {
     constexpr int MAXCT = xd_max_ct<RT>();
+    constexpr long long FULL = 1024;
     const int tiles = (L.d.nox + 15) / 16;
     int CT = 1;
     long long best = -1;
@@ -782,7 +786,7 @@ static znni_status launch_xd_cols_s(const LayerPlan& L, int accumulate, hipStrea
         const int PER = xd_shared(RT, c, PLANES) ? 4 : 1;
         const long long waves = ((long long)L.S * ((tiles + c * PER - 1) / (c * PER)) * PER + 3) / 4 * 4;
         const int rounds = (4 * (16 * c + 8) + 63) / 64;
-        const long long n = waves * (96 * L.d.kx * RT * c + 200 * rounds + 800);
+        const long long n = std::max(waves * L.ozn * L.d.Ny * L.mac_nmblk, FULL) * (96 * L.d.kx * RT * c + 200 * rounds + 800);
         if (best < 0 || n <= best) { best = n; CT = c; }
     }
     switch (CT) {
