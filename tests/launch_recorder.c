@@ -64,3 +64,19 @@ const char* recorded_launches(void)
     log_len = 0;
     return out;
 }
+
+/* Every kernel that was registered, one name a line. */
+const char* registered_kernels(void)
+{
+    static char out[1 << 20];
+    size_t n = 0;
+    for (int i = 0; i < ntable; ++i) {
+        const size_t l = strlen(table[i].name);
+        if (n + l + 2 >= sizeof(out)) break;
+        memcpy(out + n, table[i].name, l);
+        n += l;
+        out[n++] = '\n';
+    }
+    out[n] = 0;
+    return out;
+}

@@ -22,16 +22,22 @@ def _is_planes(S, f, fo, n, k):
     return nb["fwd_x"] == 0 and nb["fwd_y"] == 0 and nb["inv_z"] == 0
 
 
-# Every length up to 64, at it and below it; last blocks of one to four planes on both sides; y and z of different extents
+# Every length up to 64, at it and below it (planes together); last blocks of one to four planes on both sides; y and z of different extents
 CASES = [(8, 2, 3, (8, 8, 7), (2, 3, 2)), (9, 3, 17, (13, 10, 9), (3, 2, 4)), (8, 5, 2, (12, 12, 11), (2, 2, 1)),
          (10, 17, 5, (15, 13, 14), (4, 3, 3)), (8, 4, 33, (18, 16, 16), (1, 5, 2)), (17, 3, 4, (20, 19, 20), (3, 1, 3)),
          (8, 33, 6, (25, 24, 23), (2, 3, 5)), (11, 2, 5, (27, 28, 26), (4, 4, 4)), (8, 6, 49, (34, 32, 31), (5, 3, 2)),
          (8, 1, 2, (9, 33, 36), (2, 2, 2)), (12, 4, 3, (41, 40, 39), (3, 6, 3)), (8, 20, 20, (22, 47, 48), (5, 5, 5)),
-         # the same lengths where workgroups are few, and where they are many
+         # y lengths from 8 to 64 as single inputs and as batches
          (1, 3, 2, (35, 36, 35), (3, 2, 2)), (1, 1, 1, (19, 39, 40), (9, 1, 2)), (2, 5, 3, (51, 56, 53), (4, 4, 4)),
          (16, 16, 4, (20, 18, 20), (2, 3, 2)), (40, 8, 40, (17, 24, 22), (3, 3, 3)), (40, 8, 8, (28, 35, 36), (3, 2, 5)),
          (1, 1, 1, (7, 8, 8), (1, 1, 1)), (1, 2, 3, (16, 16, 16), (3, 3, 3)), (1, 70, 90, (9, 9, 10), (9, 9, 9)),
          (8, 3, 8, (51, 51, 51), (5, 5, 5)), (9, 5, 4, (30, 64, 63), (6, 7, 7)), (8, 3, 2, (66, 61, 64), (4, 3, 9))]
+# Four planes one after the other (where they are many) at every length that has it, forward and inverse, and every pair of
+# row and column tiles of the multiply-accumulate: with CASES all kernels of the route (tests/test_planes_host.py counts them)
+CASES += [(5, 17, 13, (66, 27, 27), (2, 2, 2)), (9, 17, 17, (43, 40, 40), (2, 2, 2)), (9, 9, 17, (50, 56, 56), (2, 2, 2)),
+          (1, 20, 66, (7, 23, 23), (7, 2, 2)), (5, 17, 17, (70, 16, 16), (2, 2, 2)), (3, 17, 79, (18, 20, 19), (2, 2, 2)),
+          (12, 20, 49, (7, 47, 47), (2, 2, 2)), (17, 17, 33, (41, 7, 7), (2, 2, 2)), (12, 17, 49, (39, 10, 9), (2, 2, 2)),
+          (24, 17, 33, (53, 7, 7), (2, 2, 2)), (3, 17, 33, (67, 19, 19), (2, 2, 2)), (12, 17, 66, (35, 9, 10), (2, 2, 2))]
 
 
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "S%d_f%dx%d_n%s_k%s" % (c[0], c[1], c[2], "x".join(map(str, c[3])), "x".join(map(str, c[4]))))

@@ -106,3 +106,58 @@ def test_uneven_kernels_that_were_kept(oracle, layer):
     B.znni_conv3d_fft(torch.from_numpy(_rand(43, S, f, fo, n, k)[0]).to(d), tw, None, workspace=ws, mac_reference=route)
     got = B.znni_conv3d_fft(torch.from_numpy(inp).to(d), tw, None, workspace=ws, mac_reference=route, keep_kernels=True)
     _each_output_image(got.cpu().numpy().astype(np.float64), oracle.conv3d(inp, w, None, relu=False))
+
+
+# rows along x of 1 to 3 planes in the last block of four, one to five row tiles, one input and a batch, planes one by one too
+PLANE_LAYERS = [(1, 18, 20, (41, 16, 15), (4, 2, 3)), (8, 40, 66, (30, 20, 20), (5, 3, 2)), (9, 3, 5, (39, 14, 14), (1, 2, 2)),
+                (2, 20, 40, (47, 24, 23), (7, 3, 3)), (24, 12, 12, (18, 28, 28), (3, 2, 3)), (1, 70, 90, (33, 12, 12), (9, 2, 2))]
+
+
+@pytest.mark.parametrize("layer", PLANE_LAYERS, ids=lambda c: "S%d_f%dx%d" % c[:3])
+@pytest.mark.parametrize("big", [1e6, 1e9, 1e13])
+def test_a_large_value_stays_near_its_x(oracle, layer, big):
+    """The x axis is not transformed: outputs whose taps do not meet the x of a large value keep 32-bit accuracy."""
+    S, f, fo, n, k = layer
+    inp, w = _rand(50, S, f, fo, n, k)
+    inp[S - 1, f // 2, n[0] // 2, 4, 5] = big
+    got, exp = _run(inp, w, False), oracle.conv3d(inp, w, None, relu=False)
+    for s in range(S):
+        for x in range(n[0] - k[0] + 1):
+            assert np.linalg.norm(got[s, :, x] - exp[s, :, x]) <= 1e-6 * np.linalg.norm(exp[s, :, x]), (s, x)
+
+
+@pytest.mark.parametrize("layer", PLANE_LAYERS, ids=lambda c: "S%d_f%dx%d" % c[:3])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), -float("inf")])
+def test_values_that_are_not_finite_stay_in_their_windows(layer, bad):
+    """A value that is not finite reaches the outputs of its input whose taps meet its x, no others."""
+    S, f, fo, n, k = layer
+    inp, w = _rand(51, S, f, fo, n, k)
+    clean = _run(inp, w, False)
+    x = n[0] // 2
+    inp[S - 1, f - 1, x, 4, 5] = bad
+    got = _run(inp, w, False)
+    hit = range(max(0, x - k[0] + 1), min(x + 1, n[0] - k[0] + 1))
+    assert not np.isfinite(got[S - 1][:, hit.start:hit.stop]).any()
+    keep = [q for q in range(n[0] - k[0] + 1) if q not in hit]
+    tol = 1e-6 * np.abs(clean).max()
+    assert np.allclose(got[S - 1][:, keep], clean[S - 1][:, keep], rtol=0, atol=tol)
+    assert np.allclose(got[:S - 1], clean[:S - 1], rtol=0, atol=tol)
+
+
+@pytest.mark.parametrize("share,S,f,fo,n,k", [(0.6, 20, 6, 5, (30, 32, 32), (3, 3, 3)), (0.9, 8, 96, 64, (20, 48, 48), (3, 3, 3)),
+                                              (0.3, 1, 70, 50, (26, 24, 24), (3, 3, 3))])
+def test_a_large_value_under_a_budget(oracle, share, S, f, fo, n, k):
+    """Sub-batches, slabs, and blocks of images whose products are added up: waves that sum again in fp32 write where the
+    others do."""
+    inp, w = _rand(52, S, f, fo, n, k)
+    inp[S - 1, f // 2, 14, 4, 5] = 1e10
+    d = torch.device("cuda:0")
+    ws = torch.full((int(share * B.znni_conv3d_fft_workspace(S, f, fo, n, k)),), 0xFF, dtype=torch.uint8, device=d)
+    sub = B.znni_conv3d_fft_sublayers(S, f, fo, n, k, ws.numel())[0]
+    print(f"[ranges] large value, divided {sub}", flush=True)
+    assert sub != (S, f, fo)
+    got = B.znni_conv3d_fft_budget(torch.from_numpy(inp).to(d), torch.from_numpy(w).to(d), None, workspace=ws).cpu().numpy().astype(np.float64)
+    exp = oracle.conv3d(inp, w, None, relu=False)
+    for s in range(S):
+        for x in range(n[0] - k[0] + 1):
+            assert np.linalg.norm(got[s, :, x] - exp[s, :, x]) <= 1e-6 * np.linalg.norm(exp[s, :, x]), (s, x)
