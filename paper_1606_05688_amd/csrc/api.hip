@@ -46,34 +46,32 @@ static void make_fft_plan(int N, FftPlan* P)
 
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-// Whether a layer runs without transforming its x axis (mac_xd.hip).  A flag that names a multiply-accumulate form
-// decides; otherwise that route is taken, provided the y transform has an in-register kernel (only those read the
-// transposed layout), except for small images with many inputs or many images that do not go four planes at a time (pick_planes): with fused z+y kernels on both sides the
-// fully transformed route has as many passes, and a kernel-spectrum value generated once per bin serves all inputs.
-// Measured, whole layer, untransformed against fully transformed: 80 -> 80 images of 100^3, 5^3 kernels 1.57 against
-// 2.02 ms; 32 -> 32 of 64^3, 7^3 0.137 against 0.171; 8 x 32 -> 32 of 130^3, 5^3 (no fused kernels) 6.2 against 8.9;
-// 32 x 20 -> 20 of 40 x 128 x 100, 3^3 3.39 against 4.06.  With fused kernels and more than 8 inputs: 64 x 80 -> 80 of
-// 51^3, 5^3 12.2 against 9.8; 16 x 80 -> 80 of 80^3, 5^3 8.5 against 7.2; 13 x 64 -> 23 of 39^3, 2^3 0.44 against 0.37; with
-// at most 8 inputs and k * S >= 32 it is level or ahead above length 64 (8 x 80 -> 80 of 99^3, 5^3 8.5 against 10.2,
-// 8 x 48 -> 48 of 72^3, 4^3 1.67 against 1.66, 8 x 16 -> 16 of 120^3, 5^3 2.05 against 2.04).
+// Whether a layer that does not go four planes at a time (pick_planes) runs without transforming its x axis (mac_xd.hip).  A flag
+// that names a multiply-accumulate form decides; otherwise that route is taken, provided the y transform has an in-register
+// kernel (only those read the transposed layout), except for small images with many inputs or many images: with fused z+y
+// kernels on both sides the fully transformed route has as many passes, and a kernel-spectrum value generated once per bin
+// serves all inputs.  Measured, whole layer, untransformed against fully transformed: 80 -> 80 images of 100^3, 5^3 kernels
+// 1.34 against 1.96 ms; 32 -> 32 of 64^3, 7^3 0.137 against 0.174; 8 x 32 -> 32 of 130^3, 5^3 (no fused kernels) 5.9 against 8.9;
+// 32 x 20 -> 20 of 40 x 128 x 100, 3^3 2.92 against 4.06.  With fused kernels and more than 8 inputs: 16 x 80 -> 80 of 80^3, 5^3
+// 7.5 against 7.0; with at most 8 inputs and k * S >= 32 it is ahead or level above length 64 (8 x 80 -> 80 of 99^3, 5^3 7.6
+// against 10.1, 8 x 48 -> 48 of 72^3, 4^3 1.48 against 1.63, 8 x 16 -> 16 of 120^3, 5^3 2.04 against 2.01).
 static bool pick_untransformed_x(const LayerPlan& L, unsigned flags)
 {
     if (flags & (ZNNI_MAC_REFERENCE | ZNNI_MAC_SINGLE | ZNNI_MAC_BATCH)) return false;
     const bool batch = mac_batch_preferred(L);
-    // (rows of the output shorter than half a column block leave most of it idle: 15 x 93 -> 44 of 27 x 21 x 30, 7 x 5 x 2
-    // kernels 0.44 against 0.38 ms)
+    // (batches with rows of the output shorter than that leave most of a column tile idle; around the line the two are level: 15 x
+    // 93 -> 44 of 27 x 21 x 30, 7 x 5 x 2 kernels 0.371 against 0.382 ms)
     if (!(fused_fwd_zy_available(L) && fused_inv_yz_available(L))) return !batch || L.d.nox >= 32;
     if (batch) return L.S <= 8 && L.d.Ny > 64;
-    if (L.S >= 8) return false;          // (8 x 20 -> 34 of 51^3, 3^3 kernels 0.40 against 0.37 ms)
-    // Above length 64 four passes without any along x are faster than two fused ones with two along x.  Up to there the
-    // fused kernels gain with every image, the untransformed route with every product per image (its multiply-accumulate
-    // is the faster one), and where there are few pencils for long sums nothing hides a workgroup's walk.  Over 537
-    // random layers of up to 7 inputs this is 1.1 % off the faster route on average; never transforming x is 5.0 % off,
-    // always doing so 6.9 %.  Untransformed against transformed, us: 10 -> 44 images of 59^3, 3^3 kernels 83 against 89;
-    // 18 -> 122 of 41^3, 6^3 155 against 178; 3 x 83 -> 6 of 41^3, 5^3 189 against 232; 7 -> 1 of 65^3, 7^3 55 against 75;
-    // 50 -> 8 of 19^3, 7^3 65 against 47; 7 x 88 -> 1 of 37^3, 2^3 258 against 197; 4 x 4 -> 118 of 19^3, 3^3 62 against 49;
-    // 7 x 103 -> 7 of 54^3, 3^3 792 against 665.  The largest losses: 9 -> 121 of 14^3, 7^3 64 against 46; 3 x 27 -> 9 of
-    // 49^3, 5^3 110 against 137.
+    if (L.S >= 8) return false;
+    // Above length 64 four passes without any along x are faster than two fused ones with two along x: over 245 random layers of
+    // up to 7 inputs 0.5 % off the faster route on average.  Up to there the fused kernels gain with every image, the untransformed route with every product per image (its multiply-accumulate is the faster
+    // one), and where there are few pencils for long sums nothing hides a workgroup's walk.  Over 204 random layers too large for
+    // four planes this is 3.3 % off the faster route on average, never transforming x 2.8 %, always doing so 13.6 %.  (It is kept for
+    // the many small layers below, where it says which route four planes stand against.)  Untransformed against transformed, us:
+    // 10 -> 44 images of 59^3, 3^3 kernels 80 against 88; 18 -> 122 of 41^3, 6^3 138 against 177; 3 x 83 -> 6 of 41^3, 5^3 192 against
+    // 230; 7 -> 1 of 65^3, 7^3 55 against 74; 7 x 88 -> 1 of 37^3, 2^3 250 against 197; 7 x 103 -> 7 of 54^3, 3^3 777 against 647.
+    // The largest loss: 7 x 4 -> 65 of 37^3, 9 x 6 x 3 115 against 180.
     const int pencils = L.d.zc * L.d.Ny;
     if (L.d.Ny > 64) return true;
     if (L.S * L.f <= 80) return L.S * L.fo <= 300 && 2 * L.f * L.d.kx <= 3 * pencils;
@@ -120,8 +118,8 @@ static bool pick_planes(const LayerPlan& L, unsigned flags)
     const Dims& d = L.d;
     const double pairs = (double)L.fp * L.Mp, pencils = (double)d.zc * d.Ny;
     // seconds of a pencil
-    const double products = 24.0 * d.kx * ((d.nox + 15) & ~15) * pairs * L.S / 0.7e15;
-    const double batch = 1.7e-12 * pairs * d.Nx * ((L.S + 15) / 16);
+    const double products = 24.0 * d.kx * ((d.nox + 15) & ~15) * pairs * L.S / MAC_SPLIT_FLOPS;
+    const double batch = MAC_BATCH_SEC_PER_VALUE * pairs * d.Nx * ((L.S + 15) / 16);
     const double passes = 8.0 * ((double)L.nimg * (d.nx + d.Nx) + (double)L.nimgo * (d.Nx + d.nox)) / 5e12;
     if (L.S >= 8) return products < batch + passes;
     if (8.0 * (L.nimg + (double)L.nimgo) * d.nx * pencils > PLANES_SMALL) return false;

@@ -13,8 +13,10 @@
 //                     two launches; layers that run on split halves (direct_split.hip): the larger of tensors moved
 //                     and products over what that kernel reaches.
 //
-// The model only has to rank the two; it is not used for anything else.  Over 446 random layers that both take, the pick is
-// 1.7 % slower than the faster one on average.
+// The model only has to rank the two; it is not used for anything else.  (Both estimates are low, by a quarter for layers of a
+// fraction of a millisecond, where launches follow each other.)  Over 600 random layers that both take, the pick is 1.0 % slower
+// than the faster one on average (242 of them four planes at a time: 1.3 %), 27 by more than 5 %; always the transform route
+// would be 37 %, always the direct one 82 %.
 #include "direct_split.h"
 #include "mac_common.h"
 
@@ -25,8 +27,6 @@ constexpr double kPassBytesPerSecFast = 5.3e12;     // in-register pass kernels
 constexpr double kPassBytesPerSecGeneric = 2.0e12;  // generic LDS pass kernels
 constexpr double kPrepBytesPerSec = 4.5e12;         // kernel preparation (write-bound)
 constexpr double kMacFlopsPerSec = 110e12;          // issued matrix-core flops of the multiply-accumulate (S = 1 form)
-constexpr double kMacSplitFlopsPerSec = 0.7e15;     // ... of the form on split halves (no x transform)
-constexpr double kMacBatchSecPerValue = 2.1e-12;    // batch form: per kernel-spectrum value and 16 inputs
 constexpr double kDirectFlopsPerSec = 80e12;        // direct convolution, windows of 27 taps and more
 constexpr double kDirectFlopsPerSecSmall = 60e12;   // ... of fewer taps
 constexpr double kDirectWriteBytesPerSec = 3.6e12;  // direct convolution, output write
@@ -54,9 +54,9 @@ static double fft_seconds(int S, int f, int fo, const int n[3], const int k[3])
         // bound by its split products or by the spectra it reads and writes
         const double by = 8.0 * bins * ((double)L.nimg * d.nx + (double)L.nimgo * d.nox) + bank;
         const double ops = 24.0 * d.kx * L.fp * (double)L.Mp * S * d.nox * bins;
-        t += by / kPassBytesPerSecFast > ops / kMacSplitFlopsPerSec ? by / kPassBytesPerSecFast : ops / kMacSplitFlopsPerSec;
+        t += by / kPassBytesPerSecFast > ops / MAC_SPLIT_FLOPS ? by / kPassBytesPerSecFast : ops / MAC_SPLIT_FLOPS;
     } else if (mac_batch_preferred(L)) {
-        t += kMacBatchSecPerValue * L.fp * (double)L.Mp * d.Nx * bins * ((S + 15) / 16);
+        t += MAC_BATCH_SEC_PER_VALUE * L.fp * (double)L.Mp * d.Nx * bins * ((S + 15) / 16);
     } else {
         // three real matrix products per complex one, contraction over (input image, x tap), every column
         t += 6.0 * d.kx * L.fp * (double)L.Mp * S * d.Nx * bins / kMacFlopsPerSec;

@@ -124,6 +124,9 @@ __device__ __forceinline__ void mac_store(const MacWork& w, const floatx4 (&p1)[
 
 // mac_batch.hip: the form for batches, kernel-spectrum values generated once per bin and shared by the S inputs.
 bool mac_batch_available(const LayerPlan& L);      // up to 12 taps along x
+// Rates the choice of a route goes by (api.hip, choose.hip): the batch form per kernel-spectrum value and 16 inputs, the form on
+// split halves (no x transform) in issued operations a second.
+constexpr double MAC_BATCH_SEC_PER_VALUE = 1.7e-12, MAC_SPLIT_FLOPS = 0.7e15;
 bool mac_batch_preferred(const LayerPlan& L);
 znni_status launch_mac_batch(const LayerPlan& L, int accumulate, hipStream_t st);
 

@@ -46,7 +46,7 @@
 //    others is small next to it.  Here an output image may be made of the small ones alone: every image then counts by
 //    itself when a wave looks at how far its values lie apart, and the fp32 sums take kernel transforms made again from A1.
 //    (8 x 40 -> 20 of 40 x 24 x 22, groups of images 2^30 apart that no output image shares: 2.9e-3 off without it, 3e-7
-//    with it.  Where kernels are even it costs 0.3 us.)
+//    with it.  Where kernels are even it costs the smaller layers 0.3 to 0.5 us.)
 //  * What is left: single taps along x far below the others of their output image (an absolute error of 2^-40 of the largest).
 //
 // Whole layers come out 0.6 to 1.0 times as far from their 64-bit values as with fp32 matrix
@@ -103,21 +103,25 @@ struct XdArgs {
 };
 
 constexpr int XD_MAX_K = 9;     // taps along x at most: the halo of a staged row
-// One row tile, and narrow strips: the four waves take neighbouring strips of one input and stage them together.  There is
-// little to multiply and the image rows are what counts, or the columns that two strips share are as many as their own: together a wave reads whole rows of four images, and the columns two strips share are read
-// once (19 -> 5 of 295^3, 5^3 kernels 935 us, every wave its own strip 1210; 14 -> 12 of 111 x 88 x 87, 6 x 2 x 4 43 against 45;
-// 28 -> 75 of 62^3, 7^3 107 against 117).  Where neither holds, as with five row tiles of two column tiles, it is the slower way (80 -> 80
-// of 200^3, 5^3 4.15 against 3.91 ms).
-// Narrow tiles have more waves for it: without the early requests below, held to 96 registers, they have five per SIMD.
+// One row tile, and narrow strips: the four waves take neighbouring strips of one input and stage them together.  With one row
+// tile there is little to multiply and the image rows are what counts; in narrow strips the columns that two of them share are as
+// many as their own.  Together a wave reads whole rows of four images, and shared columns are read once (19 -> 5 of 295^3, 5^3
+// kernels 935 us, every wave its own strip 1210; 14 -> 12 of 111 x 88 x 87, 6 x 2 x 4 43 against 45; 28 -> 75 of 62^3, 7^3 107
+// against 117).  Three to five row tiles of two column tiles are slower that way (277 layers: level, 1.2 and 1.2 % of the layer).
 constexpr bool xd_shared(int RT, int CT, bool planes) { return (RT == 1 || CT == 1 || (RT == 2 && CT == 2)) && !planes; }
 template <int RT, int CT, bool PLANES>
 constexpr size_t xd_lds_bytes()
 {
     return (size_t)16 * ((xd_shared(RT, CT, PLANES) ? 8 * (64 * CT + 16) : 4 * 8 * (16 * CT + 16)) + 4 * 128 * RT + 4 * RT + 7);
 }
-// Three workgroups per CU where LDS and registers (168 a lane) allow, two otherwise.
+// Workgroups per CU: five of the smallest tiles (held to 96 registers a lane), three where LDS and registers (168) allow, two
+// otherwise.
 template <int RT, int CT, bool PLANES>
-constexpr int xd_blocks() { return xd_shared(RT, CT, PLANES) && RT == 1 && CT <= 2 ? 5 : xd_lds_bytes<RT, CT, PLANES>() <= 53 * 1024 && RT * CT <= 6 ? 3 : 2; }
+constexpr int xd_blocks()
+{
+    if (xd_shared(RT, CT, PLANES) && RT == 1 && CT <= 2) return 5;
+    return xd_lds_bytes<RT, CT, PLANES>() <= 53 * 1024 && RT * CT <= 6 ? 3 : 2;
+}
 
 // Slot of a pencil's stored kernel transforms -> image quad and tap: the order the contraction walks them in, chunks of four
 // quads, inside a chunk tap by tap, quads fastest.
@@ -238,8 +242,16 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
     const int xlast = min(g.nx, row0 + (SHARED ? 64 : 16) * CT + K - 1) - 1;     // last column any of the strip's outputs needs
     auto xoff = [&](int x) { x = min(x, xlast); return (x >> 2) * g.xblk + (x & 3); };
     int QC = 4;                                              // image quads of the chunk
-    auto unit_q = [&](int n) { return SHARED ? wave : n < NQ ? n : min(lane + 64 * (n - NQ), 4 * XH - 1) / max(XH, 1); };
-    auto unit_x = [&](int n) { return SHARED ? (n < CT ? 64 * n + lane : 64 * CT + (lane & 7)) : n < NQ ? min(lane, XN - 1) : (NQ ? 64 : 0) + min(lane + 64 * (n - NQ), 4 * XH - 1) % max(XH, 1); };
+    // image quad and column of this lane's unit in round n (surplus lanes repeat the last one)
+    auto rest = [&](int n) { return min(lane + 64 * (n - NQ), 4 * XH - 1); };
+    auto unit_q = [&](int n) {
+        if (SHARED) return wave;
+        return n < NQ ? n : rest(n) / max(XH, 1);
+    };
+    auto unit_x = [&](int n) {
+        if (SHARED) return n < CT ? 64 * n + lane : 64 * CT + (lane & 7);
+        return n < NQ ? min(lane, XN - 1) : (NQ ? 64 : 0) + rest(n) % max(XH, 1);
+    };
     int sexp = 126;                                          // exponent of the scale the image values carry
     int chunk = 0;
     bool apart = false;                                      // magnitudes along x too far apart for halves
@@ -250,7 +262,11 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
     unsigned least = ~0u;                                    // smallest code of the chunks so far
     // One chunk of sixteen images of the strip to LDS, a (quad, x) unit per lane and round.  Values beyond a row are read
     // from its end, images beyond the last from the last: neither reaches a stored output (the images count as zeros).
-    auto round = [&](int n, int qc) { return SHARED ? wave < qc : n < NQ ? n < qc : 64 * (n - NQ) < qc * XH; };
+    // whether round n holds any of the chunk's qc image quads
+    auto round = [&](int n, int qc) {
+        if (SHARED) return wave < qc;
+        return n < NQ ? n < qc : 64 * (n - NQ) < qc * XH;
+    };
     float2 raw[NR][4];
     auto request = [&]() {
         const int i0 = chunk * 16, qc = min(4, ((f + 3) >> 2) - 4 * chunk);
