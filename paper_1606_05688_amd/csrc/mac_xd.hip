@@ -46,7 +46,7 @@
 //    others is small next to it.  Here an output image may be made of the small ones alone: every image then counts by
 //    itself when a wave looks at how far its values lie apart, and the fp32 sums take kernel transforms made again from A1.
 //    (8 x 40 -> 20 of 40 x 24 x 22, groups of images 2^30 apart that no output image shares: 2.9e-3 off without it, 3e-7
-//    with it.  Where kernels are even it costs the smaller layers 0.3 to 0.5 us.)
+//    with it.  Where kernels are even it costs at most 1 % of the layer.)
 //  * What is left: single taps along x far below the others of their output image (an absolute error of 2^-40 of the largest).
 //
 // Whole layers come out 0.6 to 1.0 times as far from their 64-bit values as with fp32 matrix
@@ -112,7 +112,7 @@ constexpr bool xd_shared(int RT, int CT, bool planes) { return (RT == 1 || CT ==
 template <int RT, int CT, bool PLANES>
 constexpr size_t xd_lds_bytes()
 {
-    return (size_t)16 * ((xd_shared(RT, CT, PLANES) ? 8 * (64 * CT + 16) : 4 * 8 * (16 * CT + 16)) + 4 * 128 * RT + 4 * RT + 7);
+    return (size_t)16 * ((xd_shared(RT, CT, PLANES) ? 8 * (64 * CT + 16) : 4 * 8 * (16 * CT + 16)) + 4 * 128 * RT + 4 * RT + 5);
 }
 // Workgroups per CU: five of the smallest tiles (held to 96 registers a lane), three where LDS and registers (168) allow, two
 // otherwise.
@@ -181,7 +181,7 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
     const int poz = (int)g.d_Ny.div((unsigned)pencil), poy = pencil - poz * g.Ny;
     half8* const Xs = lds + 4 * RT * 128 + (SHARED ? 0 : wave * 8 * XW);      // this wave's own, or all waves': [hi, lo][quad][XW]
     float* const rjs = reinterpret_cast<float*>(lds + 4 * RT * 128 + (SHARED ? 8 : 32) * XW);           // [RT * 16]
-    unsigned* const wred = reinterpret_cast<unsigned*>(rjs + RT * 16);        // [turn][largest, smallest, zeros][wave], [wave]
+    unsigned* const wred = reinterpret_cast<unsigned*>(rjs + RT * 16);        // [turn][largest, smallest][wave], [wave]
 
     // ---- kernel operands: this thread's share of a step, NU units of 16 bytes (surplus units repeat the last one).
     // Slots past the last one are read from it.
@@ -256,10 +256,6 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
     int chunk = 0;
     bool apart = false;                                      // magnitudes along x too far apart for halves
     unsigned most = 0;                                       // largest finite magnitude (its bits) of the chunks so far
-    bool zeros = false;                                      // whether one of them is zero somewhere along the strip
-    // Kernels of an output image of uneven size: every image counts by itself, in all chunks
-    unsigned uneven = 0;
-    unsigned least = ~0u;                                    // smallest code of the chunks so far
     // One chunk of sixteen images of the strip to LDS, a (quad, x) unit per lane and round.  Values beyond a row are read
     // from its end, images beyond the last from the last: neither reaches a stored output (the images count as zeros).
     // whether round n holds any of the chunk's qc image quads
@@ -292,9 +288,6 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
         // are added up (an image far below the others, say of rounding errors only, is no reason to leave halves)
         float m = 0.f;
         unsigned mn = ~0u;
-        bool zero = false;
-        unsigned bits = __float_as_uint(rjs[min(lane, RT * 16 - 1)]);
-        if (RT > 4) bits |= __float_as_uint(rjs[64 + l16]);
 #pragma unroll
         for (int n = 0; n < NR; ++n) {
             float u = 0.f;
@@ -302,34 +295,14 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
             for (int q = 0; q < 4; ++q) max3_abs(u, raw[n][q].x, raw[n][q].y);
             m = fmaxf(m, u);
             mn = min(mn, small_code(u));
-            zero |= round(n, QC) && u == 0.f;
         }
-        uneven = __ballot((int)bits < 0) != 0;
-        if (uneven) {
-            // (where some are far below the largest and not zero, halves hold those badly, and an image that is zero is as good
-            // as one that is far below the others)
-            const unsigned tiny = __ballot(bits & 1u) != 0;
-            mn = ~0u;
-#pragma unroll
-            for (int n = 0; n < NR; ++n)
-                if (round(n, QC))
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        float v = 0.f;
-                        float2 p = raw[n][q];
-                        asm volatile("" : "+v"(p.x), "+v"(p.y));     // (for the same reason as below)
-                        max3_abs(v, p.x, p.y);
-                        mn = min(mn, (__float_as_uint(v) << 1) - 1u + tiny);
-                    }
-        }
-        unsigned mb = wave_max(m), sm = wave_min(mn), zb = __any(zero);
+        unsigned mb = wave_max(m), sm = wave_min(mn);
         if constexpr (SHARED) {
-            unsigned* const red = wred + (chunk & 1) * 12;
-            if (lane == 0) { red[wave] = mb; red[4 + wave] = sm; red[8 + wave] = zb; }
+            unsigned* const red = wred + (chunk & 1) * 8;
+            if (lane == 0) { red[wave] = mb; red[4 + wave] = sm; }
             __syncthreads();                                 // (also: all waves are through with the chunk before)
             mb = (unsigned)__builtin_amdgcn_readfirstlane((int)max(max(red[0], red[1]), max(red[2], red[3])));
             sm = (unsigned)__builtin_amdgcn_readfirstlane((int)min(min(red[4], red[5]), min(red[6], red[7])));
-            zb = (unsigned)__builtin_amdgcn_readfirstlane((int)(red[8] | red[9] | red[10] | red[11]));
         }
         if (mb >= 0x7f800000u) {                             // infinities or NaNs: the scale is that of the finite values
             m = 0.f;
@@ -344,18 +317,15 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
                 }
             mb = wave_max(m);
             if constexpr (SHARED) {
-                if (lane == 0) wred[24 + wave] = mb;
+                if (lane == 0) wred[16 + wave] = mb;
                 __syncthreads();
-                mb = (unsigned)__builtin_amdgcn_readfirstlane((int)max(max(wred[24], wred[25]), max(wred[26], wred[27])));
+                mb = (unsigned)__builtin_amdgcn_readfirstlane((int)max(max(wred[16], wred[17]), max(wred[18], wred[19])));
                 __syncthreads();
             }
         }
-        // Next to the largest value of its own chunk; next to that of all chunks so far, whose scale it carries, where an earlier
-        // one is zero somewhere (elsewhere that one's values, of which every column then has some, outweigh it).
+        // next to the largest value of all chunks so far, whose scale it carries
         most = max(most, mb);
-        least = min(least, sm);
-        apart |= split_too_wide(zeros || uneven ? most : mb, uneven ? least : sm);
-        zeros |= zb != 0;
+        apart |= split_too_wide(most, sm);
         const int sn = min(sexp, split_exp(__uint_as_float(mb)));
         if (sn < sexp && chunk) {                            // a larger chunk: the sums follow its scale
 #pragma unroll
@@ -489,7 +459,8 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
     if (nsteps > 2) load_a();
     const half8* const as0 = As + kk * RT * 32 + l16;
     for (int gs = 0, buf = 0; gs < nsteps; gs += 2, buf ^= 1) {
-        __syncthreads();                                     // this pair's operands are in place, the last one's are free
+        // this pair's operands are in place, the last one's are free (staged together, the first chunk's barriers say so)
+        if (!SHARED || gs) __syncthreads();
         if (live) step(as0 + buf * RT * 256);
         if (gs + 2 < nsteps) {
             park_a(gs + 2, buf ^ 1);
@@ -498,6 +469,29 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
         if (live && gs + 1 < nsteps) step(as0 + buf * RT * 256 + RT * 128);
     }
     if (!live) return;
+
+    // Kernels of an output image of uneven size: every image counts by itself, next to the largest value of all.  (Read again for
+    // it: looking at them one by one as they are staged took 6 to 11 % of the kernel where images are few, with even kernels too:
+    // 2 x 3 -> 1 of 142 x 178 x 255, 3^3 206 us, 186 this way, 185 without any check.)
+    unsigned bits = __float_as_uint(rjs[min(lane, RT * 16 - 1)]);
+    if (RT > 4) bits |= __float_as_uint(rjs[64 + l16]);
+    const bool uneven = __ballot((int)bits < 0) != 0;
+    if (uneven && !apart) {
+        // (where some kernels are far below the largest and not zero, halves hold those badly, and an image that is zero is as
+        // good as one that is far below the others)
+        const unsigned tiny = __ballot(bits & 1u) != 0;
+        unsigned mn = ~0u;
+        for (int i = 0; i < f; ++i) {
+            const float2* row = xrow + (size_t)(unsigned)i * g.ximg;
+            for (int x = lane; x < 16 * CT + K - 1; x += 64) {
+                const float2 v = row[xoff(col0 + x)];
+                float m = 0.f;
+                max3_abs(m, v.x, v.y);
+                mn = min(mn, (__float_as_uint(m) << 1) - 1u + tiny);
+            }
+        }
+        apart = split_too_wide(most, wave_min(mn));
+    }
 
     if (apart) {
         // All over again in fp32, from global memory, four slots of one complex image each per pair of matrix instructions
