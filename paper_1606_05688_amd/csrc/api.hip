@@ -96,10 +96,9 @@ constexpr unsigned ROUTE_FULL_X = 1u << 30;
 // kernels around the multiply-accumulate where the fully transformed route has four, products on split halves instead of
 // fp32.  Against that stand kx products per output column (of whole column tiles) instead of about one per bin.  So its
 // products, at the rate its multiply-accumulate reaches, are held against the other form's spectrum values and the two x
-// passes.  Over 140 random batches of 8 to 64 inputs (lengths up to 64, 2 to 96 images, 1 to 9 taps) that go
-// here 1.3 times as fast as on the fully transformed route on average, the worst 4 % behind (25 x 84 -> 8 of 29^3, 8 x 4 x 5
-// kernels); 64 x 80 -> 80 of 51^3, 5^3 7.1 against 9.7 ms; 8 x 32 -> 32 of 64^3, 7^3
-// 0.51 against 0.67.
+// passes.  Over 452 random batches of 8 to 64 inputs that go here (lengths up to 64, up to 800 images, 1 to 9 taps) 1.38 times as
+// fast as on the fully transformed route on average, the worst 5 % behind (22 x 198 -> 485 of 16 x 18 x 18, 5^3 kernels);
+// 64 x 80 -> 80 of 51^3, 5^3 7.1 against 9.7 ms; 8 x 32 -> 32 of 64^3, 7^3 0.51 against 0.67.
 // Fewer inputs go here where their transformed images are at most PLANES_SMALL together: what counts there are launches, and
 // this route has two fewer than either other.  Against the other untransformed one that is all: over 1179 random layers 1.18
 // times as fast, five more than 3 % behind (29 -> 3 of 70 x 49 x 51, 3^3 kernels 68 against 61 us), where a transform's
@@ -108,12 +107,12 @@ constexpr unsigned ROUTE_FULL_X = 1u << 30;
 // costs it 0.34 us more with no row tiles to multiply and 0.11 less with each (the other form takes four steps for it), a
 // chunk of sixteen images 0.59, 0.085 less with each input (x passes).  Two launches (8.4 us) and the quicker products of the
 // second tap and the next ones (2.2 ps a value of the kernel bank) make up for it or not; where the batch form would serve all
-// inputs, its products count as above.  Up to 128 images that is never much (1187 layers: 17 more than 5 % behind, the worst
-// 17 %), and the sums here are the closer ones (stepwise): always this route.  Over 2094 random layers of 1 to 7 inputs (lengths up
-// to 64, 1 to 1500 images, 1 to 9 taps) 1.159 times as fast as on that route and 1.045 times as on this one, the better of the
-// two 1.165 and 1.050; 70 more than 5 % off the better (7 x 227 -> 1460 of 8^3, 2^3 kernels 353 us here, 262 there).  Always this
-// route is as little as half as fast (1104 -> 2 of 8^3, 7^3 386 against 202), never as well (1061 -> 69 of 7^3, 5 x 4 x 4 402
-// against 659).
+// inputs, its products count as above.  Up to 96 images that is never much (1061 layers: 7 more than 5 % behind, the worst 17 %;
+// 4 x 121 -> 3 of 11^3, 9 x 9 x 8 kernels 88 us here, 67 there), and the sums here are the closer ones (stepwise): always this
+// route.  Over 2090 random layers of 1 to 7 inputs (lengths up to 64, 1 to 1500 images, 1 to 9 taps) 1.159 times as fast as on that
+// route and 1.044 times as on this one, the better of the two 1.165 and 1.049; 62 more than 5 % off the better (7 x 227 -> 1460
+// of 8^3, 2^3 kernels 353 us here, 262 there).  Always this route is as little as half as fast (1104 -> 2 of 8^3, 7^3 386 against
+// 202), never as well (1061 -> 69 of 7^3, 5 x 4 x 4 402 against 659).
 constexpr double PLANES_SMALL = 40e6;
 static bool pick_planes(const LayerPlan& L, unsigned flags)
 {
@@ -128,7 +127,7 @@ static bool pick_planes(const LayerPlan& L, unsigned flags)
     if (L.S >= 8) return products < batch + passes;
     if (8.0 * (L.nimg + (double)L.nimgo) * d.nx * pencils > PLANES_SMALL) return false;
     if (pick_untransformed_x(L, flags)) return true;
-    if (L.f <= 128) return true;
+    if (L.f <= 96) return true;
     double gain = 8.4e-6 - (0.59e-6 - 0.085e-6 * L.S) / 16 * L.f - (0.34e-6 - 0.11e-6 * L.mac_RTW) / 16 * d.kx * L.fp +
                   2.2e-12 * (d.kx - 1) * pairs * pencils;
     if (mac_batch_preferred(L) && products > batch + passes) gain -= 3.5 * (products - batch - passes) * pencils;

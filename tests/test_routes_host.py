@@ -49,7 +49,8 @@ def test_small_images_take_the_faster_route(layer):
 # 386 and 202, 397 and 225, 285 and 175, 225 and 132); wide banks make up for it (1855 and 2382, 610 and 901)
 @pytest.mark.parametrize("layer,transformed", [((1, 1104, 2, 8, 7), True), ((1, 1343, 5, 9, 6), True), ((1, 1225, 6, 8, 5), True),
                                                ((1, 1232, 4, 7, 5), True), ((1, 991, 237, 13, 7), False), ((1, 873, 334, 9, 4), False),
-                                               ((1, 1061, 69, 7, 4), False), ((1, 27, 8, 9, 7), False), ((1, 128, 3, 10, 9), False)], ids=str)
+                                               ((1, 1061, 69, 7, 4), False), ((1, 27, 8, 9, 7), False), ((1, 96, 3, 10, 9), False),
+                                               ((4, 121, 3, 11, 9), True)], ids=str)
 def test_long_sums_of_few_pencils(layer, transformed):
     nbytes, _ = B.znni_conv3d_fft_stage_work(*layer)
     assert (nbytes["fwd_x"] > 0) == transformed
