@@ -473,7 +473,9 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
     // Kernels of an output image of uneven size: every image counts by itself, next to the largest value of all.  (Read again for
     // it: looking at them one by one as they are staged took 6 to 11 % of the kernel where images are few, with even kernels too:
     // 2 x 3 -> 1 of 142 x 178 x 255, 3^3 206 us, 186 this way, 185 without any check.)
-    unsigned bits = __float_as_uint(rjs[min(lane, RT * 16 - 1)]);
+    // (the lane's number anew: kept from the start, it takes a register that three by two tiles have to spill)
+    const int ln = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    unsigned bits = __float_as_uint(rjs[min(ln, RT * 16 - 1)]);
     if (RT > 4) bits |= __float_as_uint(rjs[64 + l16]);
     const bool uneven = __ballot((int)bits < 0) != 0;
     if (uneven && !apart) {
@@ -483,7 +485,7 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
         unsigned mn = ~0u;
         for (int i = 0; i < f; ++i) {
             const float2* row = xrow + (size_t)(unsigned)i * g.ximg;
-            for (int x = lane; x < 16 * CT + K - 1; x += 64) {
+            for (int x = ln; x < 16 * CT + K - 1; x += 64) {
                 const float2 v = row[xoff(col0 + x)];
                 float m = 0.f;
                 max3_abs(m, v.x, v.y);
