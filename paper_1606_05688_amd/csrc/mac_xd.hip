@@ -38,8 +38,8 @@
 //    against 39.5 us for the layer, 3 x 5 -> 13 of 56 x 50 x 68, 5 x 5 x 1 86.3 against 84.1; 8 -> 8 of 64^3, 5^3 55.9
 //    against 57.0).
 //  * Values along x: the x axis is not transformed, so a row next to one large value has outputs that never meet it.  A
-//    wave whose largest values at one x and another are more than 2^SPLIT_SPAN apart sums all over again in fp32, from
-//    global memory.  (A voxel of 1e9 in every 100 000: 40 -> 40 of 128^3, 3^3 kernels 0.84 -> 1.34 ms for the layer, 80 -> 80
+//    wave whose largest values at some x lie more than 2^SPLIT_SPAN below the largest of its strip so far sums all over again
+//    in fp32, from global memory.  (A voxel of 1e9 in every 100 000: 40 -> 40 of 128^3, 3^3 kernels 0.84 -> 1.34 ms for the layer, 80 -> 80
 //    with 7^3 2.9 -> 6.8; on fp32 products alone 0.95 and 4.2.)
 //  * Kernels of an output image of uneven size (the sums of their magnitudes more than 2^14 apart, or zero: kprep_row_scale
 //    leaves two bits behind).  Elsewhere the largest input images have a part in every output image, and what is lost of the
@@ -790,7 +790,7 @@ template <int RT, bool SUM, bool PLANES>
 static znni_status launch_xd_cols_s(const LayerPlan& L, int accumulate, hipStream_t st)
 {
     constexpr int MAXCT = xd_max_ct<RT>();
-    constexpr long long FULL = 1024;
+    constexpr long long FULL = 1024;                         // (of the whole layer: its slabs take the same width)
     const int tiles = (L.d.nox + 15) / 16;
     int CT = 1;
     long long best = -1;
@@ -798,7 +798,7 @@ static znni_status launch_xd_cols_s(const LayerPlan& L, int accumulate, hipStrea
         const int PER = xd_shared(RT, c, PLANES) ? 4 : 1;
         const long long waves = ((long long)L.S * ((tiles + c * PER - 1) / (c * PER)) * PER + 3) / 4 * 4;
         const int rounds = (4 * (16 * c + 8) + 63) / 64;
-        const long long n = std::max(waves * L.ozn * L.d.Ny * L.mac_nmblk, FULL) * (96 * L.d.kx * RT * c + 200 * rounds + 800);
+        const long long n = std::max(waves * L.d.zc * L.d.Ny * L.mac_nmblk, FULL) * (96 * L.d.kx * RT * c + 200 * rounds + 800);
         if (best < 0 || n <= best) { best = n; CT = c; }
     }
     switch (CT) {

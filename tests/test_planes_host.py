@@ -74,6 +74,37 @@ def walk(path, recorder, count):
     assert planes > 100 and mixed > 10
 
 
+def slabs(path, recorder, count):
+    """Slabs along the halved axis give the whole layer's result bit for bit: every one runs the whole layer's kernel (a strip's
+    width decides which values share a scale)."""
+    rec, L = ctypes.CDLL(recorder), ctypes.CDLL(path)
+    rec.recorded_launches.restype = ctypes.c_char_p
+    sz, vp = ctypes.c_size_t, ctypes.c_void_p
+    rng = np.random.default_rng(6)
+    found = 0
+    for _ in range(count):
+        S, f, fo = int(rng.choice((1, 1, 2, 9))), int(rng.integers(8, 128)), int(rng.integers(8, 128))
+        base = int(np.exp(rng.uniform(np.log(16), np.log(160))))
+        n, k = (int(base * rng.uniform(0.2, 1.0)) + 9, base, base), [int(v) for v in rng.integers(1, 10, 3)]
+        full = sz(0)
+        if L.znni_conv3d_fft_workspace_v(S, f, fo, _i3(n), _i3(k), ctypes.byref(full)):
+            continue
+        names = []
+        for share in (1.0, rng.uniform(0.4, 1.0)):
+            rec.recorded_launches()
+            rc = L.znni_conv3d_fft_budget_v(S, f, fo, _i3(n), _i3(k), vp(1 << 12), vp(1 << 12), None, vp(1 << 12), 0, vp(1 << 20),
+                                            sz(int(full.value * share)), None)
+            if rc == 0:
+                names.append(rec.recorded_launches().decode().split())
+        if len(names) < 2 or sum("k_kprep_z" in v for v in names[1]) != 1:
+            continue
+        whole, parts = ([v for v in w if "k_mac" in v] for w in names)
+        found += len(parts) > 1
+        assert set(parts) == set(whole), (S, f, fo, n, k, whole, parts)
+    print(f"{found} layers in slabs")
+    assert found > 20
+
+
 def reach(path, recorder, layers):
     """Prints the kernels of the two families that none of the layers launches."""
     rec, L = ctypes.CDLL(recorder), ctypes.CDLL(path)
@@ -104,6 +135,10 @@ def test_blocks_of_one_output_block_share_a_layout(tmp_path):
     _driven(tmp_path, "walk")
 
 
+def test_slabs_run_the_whole_layers_kernel(tmp_path):
+    _driven(tmp_path, "slabs")
+
+
 def test_gpu_layers_reach_every_kernel(tmp_path):
     import test_gpu_planes as P
     import test_gpu_strips as T
@@ -114,5 +149,7 @@ def test_gpu_layers_reach_every_kernel(tmp_path):
 if __name__ == "__main__":
     if sys.argv[3] == "walk":
         walk(sys.argv[1], sys.argv[2], 1200)
+    elif sys.argv[3] == "slabs":
+        slabs(sys.argv[1], sys.argv[2], 4000)
     else:
         reach(sys.argv[1], sys.argv[2], sys.argv[4])
