@@ -232,6 +232,13 @@ def main():
     # transform runs on fp16 matrix instructions with split values, three partial products per product
     nbytes, nflops = B.znni_conv3d_fft_stage_work(S, f, fo, n, k, relu=layer.relu, mac_reference=route)
     split = nbytes["fwd_x"] == 0 and route != "xblock"
+    # planes cut into tiles: z and y are one kernel a side, timed under the first of the two stages that the whole planes have
+    for s_, into in (("fwd_y", "fwd_z"), ("inv_z", "inv_y")):
+        if nbytes[s_] > 2 * HBM_PEAK_GBS * 1e6 * stage_ms[s_]:
+            # one pass over what goes in and one over what comes out, without the tensor between the two
+            between = (nbytes["fwd_z"] - 4 * S * f * n ** 3) if into == "fwd_z" else (nbytes["inv_z"] - 4 * layer.out_voxels)
+            nbytes[into] += nbytes[s_] - 2 * between
+            nbytes[s_] = 0
     mac_peak = MFMA_FP16_PEAK_TFLOPS / 3 if split else MFMA_FP32_PEAK_TFLOPS
     stages = {}
     for s_ in B.STAGES:

@@ -199,7 +199,9 @@ znni_status znni_conv3d_fft_profile(int S, int f, int fo, int n, int k,
  * stored kernel spectrum), 8 kx S f f' per bin of the image transformed along y and z only when it is not, 64 S f f'
  * per block of 9 - kx outputs where x is transformed in blocks of eight.  Stages a
  * call does not run (the y or z stage where one kernel does both, the x stages where the x axis is not transformed)
- * get 0.  Both arrays have ZNNI_NUM_STAGES elements, indexed like stage_ms above.
+ * get 0.  A call that cuts its (y, z) planes into overlapping tiles is counted by the whole planes they are cut from: what tiles
+ * repeat is no work of the method (such a call's z and y transforms are one kernel a side, timed under ZNNI_STAGE_FWD_Z and
+ * ZNNI_STAGE_INV_Y).  Both arrays have ZNNI_NUM_STAGES elements, indexed like stage_ms above.
  */
 znni_status znni_conv3d_fft_stage_work_v(int S, int f, int fo, const int n[3], const int k[3], unsigned flags,
                                          double hbm_bytes[ZNNI_NUM_STAGES], double flops[ZNNI_NUM_STAGES]);

@@ -177,6 +177,7 @@ static znni_status shape_plan(int S, int f, int fo, const int n[3], const int k[
     L->nimgo = S * fo;
     L->fp = (f + 3) & ~3;
     plan_mac(L);        // also sets Mp
+    L->tiles = false;
     L->generic_passes = (flags & ZNNI_PASSES_REFERENCE) != 0;
     L->xblock = pick_xblock(*L, flags);
     L->planes = pick_planes(*L, flags);
@@ -238,12 +239,27 @@ static void place_plan(LayerPlan* L, void* base, const size_t sz[5], bool own_yt
     L->bytes = off;
 }
 
-znni_status make_plan(int S, int f, int fo, const int n[3], const int k[3], unsigned flags, void* base,
-                      LayerPlan* L)
+// The plan that goes through whole planes.
+static znni_status make_whole_plan(int S, int f, int fo, const int n[3], const int k[3], unsigned flags, void* base,
+                                   LayerPlan* L)
 {
     znni_status rc = shape_plan(S, f, fo, n, k, flags, L);
     if (rc) return rc;
     place_plan(L, base, L->sz, false);
+    return ZNNI_OK;
+}
+
+// Tiles are for calls that name no form and no passes.
+static bool may_tile(unsigned flags) { return !(flags & ~(unsigned)(ZNNI_RELU | ZNNI_KEEP_KERNELS)); }
+
+znni_status make_plan(int S, int f, int fo, const int n[3], const int k[3], unsigned flags, void* base,
+                      LayerPlan* L)
+{
+    znni_status rc = make_whole_plan(S, f, fo, n, k, flags, base, L);
+    if (rc) return rc;
+    // (the workspace stays what a shape needs on any route)
+    if (may_tile(flags))
+        if (const int N = pick_tiles(*L, L->bytes, false)) tiles_plan(*L, N, base, L->bytes, false, L);
     return ZNNI_OK;
 }
 
@@ -403,6 +419,22 @@ static znni_status run(const LayerPlan& L, const float* in, const float* w, cons
     ZNNI_MARK(ZNNI_STAGE_KERNEL_PREP);
     // the stored kernel transforms of an earlier call on this workspace may be kept (same w, shape and form)
     if (!(flags & ZNNI_KEEP_KERNELS)) ZNNI_DO(launch_kernel_prep(L, w, bank, st));
+    if (L.tiles && (L.cut.sn < L.cut.S || L.cut.pn < L.cut.pairs)) {
+        // tile pairs take turns (under a budget only)
+        if (ev) return ZNNI_ERR_WORKSPACE;
+        LayerPlan T = L;
+        auto& c = T.cut;
+        for (c.s0 = 0; c.s0 < c.S; c.s0 += L.cut.sn)
+            for (c.p0 = 0; c.p0 < c.pairs; c.p0 += L.cut.pn) {
+                c.sn = c.S - c.s0 < L.cut.sn ? c.S - c.s0 : L.cut.sn;
+                c.pn = c.pairs - c.p0 < L.cut.pn ? c.pairs - c.p0 : L.cut.pn;
+                T.S = c.sn * c.pn; T.nimg = T.S * T.f; T.nimgo = T.S * T.fo;
+                ZNNI_DO(launch_fwd_zy_planes(T, in, st));
+                ZNNI_DO(launch_mac_xd(T, 0, st));
+                ZNNI_DO(launch_inv_yz_planes(T, bias, out, flags, st));
+            }
+        return ZNNI_OK;
+    }
     if (L.xdirect) {
         // x axis not transformed: the x stages do nothing and read about zero
         ZNNI_MARK(ZNNI_STAGE_FWD_Z);
@@ -562,7 +594,47 @@ static znni_status run_slabs(LayerPlan L, int rows, const float* in, const float
     }
     return inv_untransformed_x(L, bias, out, flags, st);
 }
-#undef ZNNI_DO
+// Bytes and flops of every stage of a plan (znni_conv3d_fft_stage_work_v).
+void plan_work(const LayerPlan& L, unsigned flags, double hbm_bytes[ZNNI_NUM_STAGES], double flops[ZNNI_NUM_STAGES])
+{
+    const Dims& d = L.d;
+    const double c = sizeof(float2), ni = L.nimg, no = L.nimgo, zc = d.zc;
+    const double vox = (double)d.nx * d.ny * d.nz, ovox = (double)d.nox * d.noy * d.noz;
+    const double x1 = c * d.nx * d.ny * zc, x2 = c * d.nx * d.Ny * zc, xt = c * (double)d.Nx * d.Ny * zc;
+    const double y2 = c * zc * d.nox * d.Ny, y1 = c * (double)d.nox * d.noy * zc;
+    // stored kernel transforms, unpadded: kx values per kernel column along x, or 8 where x goes in blocks of eight
+    const double a = c * zc * d.Ny * (double)L.f * L.fo * (L.xblock ? 8 : d.kx);
+    for (int q = 0; q < ZNNI_NUM_STAGES; ++q) hbm_bytes[q] = flops[q] = 0.0;
+    if (!(flags & ZNNI_KEEP_KERNELS)) hbm_bytes[ZNNI_STAGE_KERNEL_PREP] = 4.0 * L.f * L.fo * d.kx * d.ky * d.kz + a;
+    const bool fused_zy = L.planes || (!L.xdirect && fused_fwd_zy_available(L)), fused_yz = L.planes || (!L.xdirect && fused_inv_yz_available(L));
+    if (fused_zy) hbm_bytes[ZNNI_STAGE_FWD_Z] = ni * (4.0 * vox + x2);
+    else {
+        hbm_bytes[ZNNI_STAGE_FWD_Z] = ni * (4.0 * vox + x1);
+        hbm_bytes[ZNNI_STAGE_FWD_Y] = ni * (x1 + x2);
+    }
+    if (fused_yz) hbm_bytes[ZNNI_STAGE_INV_Y] = no * (y2 + 4.0 * ovox);
+    else {
+        hbm_bytes[ZNNI_STAGE_INV_Y] = no * (y2 + y1);
+        hbm_bytes[ZNNI_STAGE_INV_Z] = no * (y1 + 4.0 * ovox);
+    }
+    if (L.xdirect) {
+        // the spectra between the y passes and the multiply-accumulate keep the x axis as it is
+        const double bins = zc * d.Ny * d.nox;
+        hbm_bytes[ZNNI_STAGE_MAC] = ni * x2 + a + no * y2;
+        flops[ZNNI_STAGE_MAC] = 8.0 * d.kx * L.S * (double)L.f * L.fo * bins;
+        if (L.xblock) {
+            // one length-8 product per block of V = 9 - kx outputs
+            const int V = 9 - d.kx;
+            flops[ZNNI_STAGE_MAC] = 8.0 * 8 * L.S * (double)L.f * L.fo * zc * d.Ny * ((d.nox + V - 1) / V);
+        }
+    } else {
+        const double bins = zc * d.Ny * d.Nx;
+        hbm_bytes[ZNNI_STAGE_FWD_X] = ni * (x2 + xt);
+        hbm_bytes[ZNNI_STAGE_INV_X] = no * (xt + y2);
+        hbm_bytes[ZNNI_STAGE_MAC] = ni * xt + a + no * xt;
+        flops[ZNNI_STAGE_MAC] = (8.0 * L.S + 8.0 * (d.kx - 1)) * (double)L.f * L.fo * bins;
+    }
+}
 
 // Device address of `scratch` on the current GPU, looked up once per GPU (each GPU holds its own copy of the
 // array at its own address).
@@ -644,45 +716,9 @@ znni_status znni_conv3d_fft_stage_work_v(int S, int f, int fo, const int n[3], c
     if (!hbm_bytes || !flops) return ZNNI_ERR_NULL;
     if (!flags_ok(flags)) return ZNNI_ERR_FLAGS;
     LayerPlan L;
-    znni_status rc = make_plan(S, f, fo, n, k, flags, nullptr, &L);
+    znni_status rc = make_whole_plan(S, f, fo, n, k, flags, nullptr, &L);      // (tiles count as the whole planes they are cut from)
     if (rc) return rc;
-    const Dims& d = L.d;
-    const double c = sizeof(float2), ni = L.nimg, no = L.nimgo, zc = d.zc;
-    const double vox = (double)d.nx * d.ny * d.nz, ovox = (double)d.nox * d.noy * d.noz;
-    const double x1 = c * d.nx * d.ny * zc, x2 = c * d.nx * d.Ny * zc, xt = c * (double)d.Nx * d.Ny * zc;
-    const double y2 = c * zc * d.nox * d.Ny, y1 = c * (double)d.nox * d.noy * zc;
-    // stored kernel transforms, unpadded: kx values per kernel column along x, or 8 where x goes in blocks of eight
-    const double a = c * zc * d.Ny * (double)f * fo * (L.xblock ? 8 : d.kx);
-    for (int q = 0; q < ZNNI_NUM_STAGES; ++q) hbm_bytes[q] = flops[q] = 0.0;
-    if (!(flags & ZNNI_KEEP_KERNELS)) hbm_bytes[ZNNI_STAGE_KERNEL_PREP] = 4.0 * f * fo * d.kx * d.ky * d.kz + a;
-    const bool fused_zy = L.planes || (!L.xdirect && fused_fwd_zy_available(L)), fused_yz = L.planes || (!L.xdirect && fused_inv_yz_available(L));
-    if (fused_zy) hbm_bytes[ZNNI_STAGE_FWD_Z] = ni * (4.0 * vox + x2);
-    else {
-        hbm_bytes[ZNNI_STAGE_FWD_Z] = ni * (4.0 * vox + x1);
-        hbm_bytes[ZNNI_STAGE_FWD_Y] = ni * (x1 + x2);
-    }
-    if (fused_yz) hbm_bytes[ZNNI_STAGE_INV_Y] = no * (y2 + 4.0 * ovox);
-    else {
-        hbm_bytes[ZNNI_STAGE_INV_Y] = no * (y2 + y1);
-        hbm_bytes[ZNNI_STAGE_INV_Z] = no * (y1 + 4.0 * ovox);
-    }
-    if (L.xdirect) {
-        // the spectra between the y passes and the multiply-accumulate keep the x axis as it is
-        const double bins = zc * d.Ny * d.nox;
-        hbm_bytes[ZNNI_STAGE_MAC] = ni * x2 + a + no * y2;
-        flops[ZNNI_STAGE_MAC] = 8.0 * d.kx * S * (double)f * fo * bins;
-        if (L.xblock) {
-            // one length-8 product per block of V = 9 - kx outputs
-            const int V = 9 - d.kx;
-            flops[ZNNI_STAGE_MAC] = 8.0 * 8 * S * (double)f * fo * zc * d.Ny * ((d.nox + V - 1) / V);
-        }
-    } else {
-        const double bins = zc * d.Ny * d.Nx;
-        hbm_bytes[ZNNI_STAGE_FWD_X] = ni * (x2 + xt);
-        hbm_bytes[ZNNI_STAGE_INV_X] = no * (xt + y2);
-        hbm_bytes[ZNNI_STAGE_MAC] = ni * xt + a + no * xt;
-        flops[ZNNI_STAGE_MAC] = (8.0 * S + 8.0 * (d.kx - 1)) * (double)f * fo * bins;
-    }
+    plan_work(L, flags, hbm_bytes, flops);
     return ZNNI_OK;
 }
 
@@ -777,8 +813,20 @@ znni_status znni_conv3d_fft_budget_v(int S, int f, int fo, const int n[3], const
     if (rc) return rc;
     if (((uintptr_t)in | (uintptr_t)w | (uintptr_t)out) & 15u) return ZNNI_ERR_ALIGN;
     if ((uintptr_t)workspace & 255u) return ZNNI_ERR_ALIGN;
+    LayerPlan L;
+    if (may_tile(flags)) {
+        // Where the whole layer goes in tiles: they take less room, and their pairs can take turns in it.  The whole layer's
+        // length, and so its result, where that fits.
+        rc = make_whole_plan(S, f, fo, n, k, flags, nullptr, &L);
+        if (rc) return rc;
+        LayerPlan T;
+        const int N = pick_tiles(L, L.bytes, false);
+        L.bytes = workspace_bytes;
+        if (N && (tiles_plan(L, N, workspace, workspace_bytes, true, &T) ||
+                  tiles_plan(L, pick_tiles(L, workspace_bytes, true), workspace, workspace_bytes, true, &T)))
+            return run(T, in, w, bias, out, flags, (hipStream_t)stream, nullptr);
+    }
     if (D.Si < S || D.fi < f || D.foi < fo) {
-        LayerPlan L;
         int rows = 0;
         if (plan_slabs(S, f, fo, n, k, flags, workspace, workspace_bytes, &L, &rows))
             return run_slabs(L, rows, in, w, bias, out, flags, (hipStream_t)stream);

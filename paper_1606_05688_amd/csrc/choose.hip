@@ -35,12 +35,13 @@ constexpr double kSplitFlopsPerSec = 75e12;         // ... and products of whole
 constexpr double kLaunchSec = 3.5e-6;
 
 // The route and its passes as the planner has them: bytes of every stage of the call that would run.
-static double fft_seconds(int S, int f, int fo, const int n[3], const int k[3])
+double route_seconds(const LayerPlan& L)
 {
-    LayerPlan L;
+    if (L.tiles) return tiles_seconds(L);
     double hb[ZNNI_NUM_STAGES], fl[ZNNI_NUM_STAGES];
-    if (make_plan(S, f, fo, n, k, 0, nullptr, &L) || znni_conv3d_fft_stage_work_v(S, f, fo, n, k, 0, hb, fl)) return -1.0;
+    plan_work(L, 0, hb, fl);
     const Dims& d = L.d;
+    const int S = L.S;
     const double bins = (double)d.zc * d.Ny, bank = 8.0 * bins * d.kx * L.fp * L.Mp;
     double t = bank / kPrepBytesPerSec;
     int launches = 3;                                        // kernels (behind the tables), multiply-accumulate
@@ -62,6 +63,12 @@ static double fft_seconds(int S, int f, int fo, const int n[3], const int k[3])
         t += 6.0 * d.kx * L.fp * (double)L.Mp * S * d.Nx * bins / kMacFlopsPerSec;
     }
     return t + launches * kLaunchSec;
+}
+
+static double fft_seconds(int S, int f, int fo, const int n[3], const int k[3])
+{
+    LayerPlan L;
+    return make_plan(S, f, fo, n, k, 0, nullptr, &L) ? -1.0 : route_seconds(L);
 }
 
 static double direct_seconds(int S, int f, int fo, const int n[3], const int k[3])

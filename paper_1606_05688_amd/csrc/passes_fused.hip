@@ -711,6 +711,7 @@ static znni_status launch_planes(const Args& a, const FusedShape& F, int par, di
 // in -> X2 in blocks of four x (buf1); Yd in blocks of four xo (Yt) -> out
 znni_status launch_fwd_zy_planes(const LayerPlan& L, const float* in, hipStream_t st)
 {
+    if (L.tiles) return launch_fwd_tiles(L, in, st);
     FusedShape F;
     int par = 1;
     if (!planes_shape(L, &F, true, &par)) return ZNNI_ERR_UNSUPPORTED_SIZE;
@@ -724,6 +725,7 @@ znni_status launch_fwd_zy_planes(const LayerPlan& L, const float* in, hipStream_
 
 znni_status launch_inv_yz_planes(const LayerPlan& L, const float* bias, float* out, unsigned flags, hipStream_t st)
 {
+    if (L.tiles) return launch_inv_tiles(L, bias, out, flags, st);
     FusedShape F;
     int par = 1;
     if (!planes_shape(L, &F, false, &par)) return ZNNI_ERR_UNSUPPORTED_SIZE;

@@ -36,6 +36,15 @@ struct LayerPlan {
     // ... and both z and y are transformed by the fused kernels that take four planes, X2 and Yd lying in blocks of four x
     // (passes_fused.hip).  Implies xdirect.
     bool planes;
+    // ... and the (y, z) planes are cut into overlapping tiles, two of which ride as real and imaginary part of one complex
+    // plane (passes_tiles.hip).  Implies planes; S counts tile pairs, d.ny .. d.noz are those of a tile.
+    bool tiles;
+    struct TileCut {
+        int S, ny, nz, noy, noz;      // inputs and the whole images
+        int nty, ntz, pairs;          // tiles along y and z, pairs of them in an image
+        int s0, p0;                   // first input and pair of this launch ...
+        int sn, pn;                   // ... and their numbers: S = sn * pn
+    } cut;
     // ... and the kx taps are applied through length-8 transforms of overlapping blocks of X2 rows (mac_xb.hip)
     // instead of shifted reads; A then holds the length-8 transforms of the taps.  Implies xdirect.
     bool xblock;
@@ -136,6 +145,18 @@ znni_status launch_inv_yz(const LayerPlan& L, const float* bias, float* out, uns
 bool fused_planes_available(const LayerPlan& L);
 znni_status launch_fwd_zy_planes(const LayerPlan& L, const float* in, hipStream_t st);
 znni_status launch_inv_yz_planes(const LayerPlan& L, const float* bias, float* out, unsigned flags, hipStream_t st);
+
+// Tiles (LayerPlan::tiles, passes_tiles.hip).  tiles_plan: the plan `whole` with its planes cut into tiles of transform length N,
+// arrays placed at `base` in `room` bytes, or false where they do not fit; with `chunks`, inputs or tile pairs may take
+// turns.  pick_tiles: the length to take, 0 for the route that `whole` has.
+bool tiles_plan(const LayerPlan& whole, int N, void* base, size_t room, bool chunks, LayerPlan* L);
+double tiles_seconds(const LayerPlan& L);
+int pick_tiles(const LayerPlan& whole, size_t room, bool chunks);
+// Estimated time of a plan (choose.hip); bytes and flops of its stages (api.hip).
+double route_seconds(const LayerPlan& L);
+void plan_work(const LayerPlan& L, unsigned flags, double hbm_bytes[ZNNI_NUM_STAGES], double flops[ZNNI_NUM_STAGES]);
+znni_status launch_fwd_tiles(const LayerPlan& L, const float* in, hipStream_t st);
+znni_status launch_inv_tiles(const LayerPlan& L, const float* bias, float* out, unsigned flags, hipStream_t st);
 
 // Two-step in-register passes for selected transform lengths (passes_fast.hip).
 bool fast_pass_available(int N);
