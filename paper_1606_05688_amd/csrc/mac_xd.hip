@@ -77,33 +77,11 @@
 // requested two pairs of steps and parked one pair ahead, one quarter per wave (every wave reading all of them for itself
 // asks more of the vector L1 than it delivers: 85 / CT bytes per clock of 64); one barrier per pair of steps.
 #include <algorithm>
-#include "mac_common.h"
-#include "split.h"
+#include "mac_xd.h"
 
 namespace znni {
 
-struct XdArgs {
-    FastDiv d_sub, d_pg, d_spr, d_nwg, d_Ny;
-    const float2* X2;
-    const half8* A;             // [pencil][slot][row tile][hi, lo][16 output images], 4 complex images each
-    const float* rinv;          // [Mp] inverse of the power of two the kernel transforms of an output image carry, and two bits
-    // what the kernel transforms are made of (k_kprep_xd): after the z stage, scales, twiddles along y
-    const float2* A1;
-    const float *row, *cinv;
-    const float2* tw;
-    float scale;
-    int ky, fp;
-    float2* Yd;
-    unsigned ximg, yimg;        // elements between the rows of consecutive images in X2 / Yd
-    size_t xpen, ypen;          // elements between the rows of pencils (oz, oy) and (oz + 1, oy)
-    int xrow, yrow;             // ... of pencils (oz, oy) and (oz, oy + 1)
-    int xblk, yblk;             // ... of four neighbouring x (xo) and the next four
-    int f, fo, Mp, K, nx, nox, Ny;
-    int nstrips, npencils, accumulate;
-    int zc, Nz;                 // tiles: rows oz of stored kernel transforms, and of spectra
-};
 
-constexpr int XD_MAX_K = 9;     // taps along x at most: the halo of a staged row
 // One row tile, and narrow strips: the four waves take neighbouring strips of one input and stage them together.  With one row
 // tile there is little to multiply and the image rows are what counts; in narrow strips the columns that two of them share are as
 // many as their own.  Together a wave reads whole rows of four images, and shared columns are read once (19 -> 5 of 295^3, 5^3
@@ -124,15 +102,6 @@ constexpr int xd_blocks()
     return xd_lds_bytes<RT, CT, PLANES>() <= 53 * 1024 && RT * CT <= 6 ? 3 : 2;
 }
 
-// Slot of a pencil's stored kernel transforms -> image quad and tap: the order the contraction walks them in, chunks of four
-// quads, inside a chunk tap by tap, quads fastest.
-__device__ __forceinline__ void xd_slot(int slot, int K, int fq, int& quad, int& a)
-{
-    const int c = slot / (4 * K), s = slot - c * 4 * K, QC = min(4, fq - 4 * c);
-    a = s / QC;
-    quad = 4 * c + s - a * QC;
-}
-
 // What lanes of a wave have written to LDS is there for its other lanes: the wave's LDS operations complete in order, so that
 // nothing has to be waited for, and the fences keep the compiler from moving any across.
 __device__ __forceinline__ void wave_handover()
@@ -142,7 +111,7 @@ __device__ __forceinline__ void wave_handover()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
 }
 
-template <int RT, int CT, bool SUM, bool PLANES, bool TILES = false>
+template <int RT, int CT, bool SUM, bool PLANES>
 __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
 {
     // staged columns of a strip (its outputs and their halo) and the pitch of an image quad (rows start on the same bank:
@@ -189,11 +158,7 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
     const int nslots = K * ((f + 3) >> 2), nsteps = (nslots + 3) >> 2;
     const int sstride = 2 * g.Mp, slast = (nslots - 1) * sstride;       // (32 bits: the layer call's shape limits)
     constexpr int NU = (RT + 1) / 2;
-    // (tiles: spectra of whole complex planes, whose second half of pencils meets the conjugate kernel transforms of the first)
-    const bool mirror = TILES && poz >= g.zc;
-    const int aoz = mirror ? g.Nz - poz : poz, aoy = mirror && poy ? g.Ny - poy : poy;
-    const unsigned flip = mirror ? 0x80000000u : 0u;
-    const half8* Ab = g.A + (size_t)(aoz * g.Ny + aoy) * nslots * sstride + mblk * RT * 32;
+    const half8* Ab = g.A + (size_t)pencil * nslots * sstride + mblk * RT * 32;
     int u_off[NU], u_rest[NU], u_e[NU];                      // offset of the unit's slot in the step requested next
 #pragma unroll
     for (int i = 0; i < NU; ++i) {
@@ -213,13 +178,6 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
                 u_off[i] = min(u_off[i], slast) + 4 * sstride;
             }
     };
-    auto conj_if = [&](half8 v) {
-        if constexpr (!TILES) return v;
-        uintx4 b = __builtin_bit_cast(uintx4, v);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) b[e] ^= flip;
-        return __builtin_bit_cast(half8, b);
-    };
     // The pair's operands to LDS; slots past the last one become zeros (only the last pair can hold any).
     auto park_a = [&](int step, int buf) {
         half8* d = As + buf * RT * 256;
@@ -228,7 +186,7 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
             for (int h = 0; h < 2; ++h)
 #pragma unroll
                 for (int i = 0; i < NU; ++i) {
-                    half8 v = conj_if(ring[h][i]);
+                    half8 v = ring[h][i];
                     if (4 * (step + h) + u_e[i] / (RT * 32) >= nslots)
 #pragma unroll
                         for (int e = 0; e < 8; ++e) v[e] = (_Float16)0;
@@ -238,7 +196,7 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
 #pragma unroll
             for (int h = 0; h < 2; ++h)
 #pragma unroll
-                for (int i = 0; i < NU; ++i) d[h * RT * 128 + u_e[i]] = conj_if(ring[h][i]);
+                for (int i = 0; i < NU; ++i) d[h * RT * 128 + u_e[i]] = ring[h][i];
         }
     };
 
@@ -512,12 +470,12 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
         // (kernels: their two halves added up, or, where an output image's are uneven, the sum along y again).
         const float sx = pow2f(sexp);
         const size_t per = (size_t)K * g.fp * g.Mp;
-        const float2* const a1 = g.A1 + (size_t)aoz * g.ky * per + mblk * RT * 16 + l16;
+        const float2* const a1 = g.A1 + (size_t)poz * g.ky * per + mblk * RT * 16 + l16;
         auto again = [&](int r, int i, int tap) {
             float2 s = make_float2(0.f, 0.f);
             for (int b = 0, t = 0; b < g.ky; ++b) {          // t = (poy * b) mod Ny
                 s = cfma(s, a1[b * per + ((size_t)tap * g.fp + i) * g.Mp + r * 16], g.tw[t]);
-                t += aoy;
+                t += poy;
                 if (t >= g.Ny) t -= g.Ny;
             }
             const float cr = g.row[(mblk * RT + r) * 16 + l16] * g.scale, ci = g.cinv[i];
@@ -548,7 +506,6 @@ __device__ __forceinline__ void xd_body(const XdArgs& g, half8* lds)
                     const half2 ah = reinterpret_cast<const half2*>(ap + r * 32)[q], al = reinterpret_cast<const half2*>(ap + r * 32 + 16)[q];
                     float ar = (float)ah[0] + (float)al[0], ai = (float)ah[1] + (float)al[1];
                     if (uneven) { const float2 e = again(r, 4 * qd + q, tap); ar = e.x; ai = e.y; }
-                    if (TILES) ai = mirror ? -ai : ai;
 #pragma unroll
                     for (int c = 0; c < CT; ++c) {
                         auto mm = [](float p, float v, floatx4& d) {
@@ -626,14 +583,6 @@ __global__ __launch_bounds__(256, (xd_blocks<RT, CT, true>())) void k_mac_planes
 {
     extern __shared__ half8 lds[];
     xd_body<RT, CT, true, true>(g, lds);
-}
-
-// The same rows of tile pairs (passes_tiles.hip), whose spectra are whole complex planes.
-template <int RT, int CT>
-__global__ __launch_bounds__(256, (xd_blocks<RT, CT, true>())) void k_mac_tiles(XdArgs g)
-{
-    extern __shared__ half8 lds[];
-    xd_body<RT, CT, true, true, true>(g, lds);
 }
 
 // ---------------------------------------------------------------------------------------- kernel transform
@@ -726,8 +675,6 @@ __global__ __launch_bounds__(256) void k_kprep_xd(const float2* __restrict__ A1,
     }
 }
 
-// The factor of the two unnormalised transforms, no power of two.
-static float xd_scale(const Dims& d) { return (float)(1.0 / ((double)d.Ny * d.Nz)); }
 template <int KY>
 static znni_status launch_kprep_xd_k(const LayerPlan& L, hipStream_t st)
 {
@@ -764,8 +711,7 @@ znni_status launch_kprep_xd(const LayerPlan& L, hipStream_t st)
 template <int RT> constexpr int xd_max_ct() { return RT >= 4 ? 3 : 5; }
 bool mac_xd_available(const LayerPlan& L) { return L.d.kx >= 1 && L.d.kx <= XD_MAX_K; }
 
-template <int RT, int CT, bool SUM, bool PLANES>
-static znni_status launch_xd(const LayerPlan& L, int accumulate, hipStream_t st)
+static XdArgs xd_args(const LayerPlan& L, int accumulate)
 {
     const Dims& d = L.d;
     XdArgs g;
@@ -774,7 +720,7 @@ static znni_status launch_xd(const LayerPlan& L, int accumulate, hipStream_t st)
     g.tw = L.twy; g.scale = xd_scale(d); g.ky = d.ky; g.fp = L.fp;
     const int rows = L.tiles ? d.Nz : L.ozn;
     g.zc = L.tiles ? d.zc : rows; g.Nz = d.Nz;
-    if (PLANES) {
+    if (L.planes) {
         const unsigned nb = (unsigned)(d.nx + 3) / 4, nbo = (unsigned)(d.nox + 3) / 4, zr = L.tiles ? d.Nz : d.zc;
         g.xpen = (size_t)nb * d.Ny * 4; g.ximg = zr * (unsigned)g.xpen; g.xrow = 4; g.xblk = d.Ny * 4;
         g.ypen = (size_t)nbo * d.Ny * 4; g.yimg = zr * (unsigned)g.ypen; g.yrow = 4; g.yblk = d.Ny * 4;
@@ -784,18 +730,27 @@ static znni_status launch_xd(const LayerPlan& L, int accumulate, hipStream_t st)
     }
     g.f = L.f; g.fo = L.fo; g.Mp = L.Mp; g.K = d.kx;
     g.nx = d.nx; g.nox = d.nox; g.Ny = d.Ny;
+    g.npencils = rows * d.Ny; g.accumulate = accumulate;
+    g.X2 = L.buf1 + (size_t)L.oz0 * g.xpen; g.Yd = L.Yt + (size_t)L.oz0 * g.ypen;
+    return g;
+}
+
+template <int RT, int CT, bool SUM, bool PLANES>
+static znni_status launch_xd(const LayerPlan& L, int accumulate, hipStream_t st)
+{
+    const Dims& d = L.d;
+    XdArgs g = xd_args(L, accumulate);
     constexpr int PER = xd_shared(RT, CT, PLANES) ? 4 : 1;        // strips that are staged together and count as one here
     const int spr = ((d.nox + 15) / 16 + CT * PER - 1) / (CT * PER), pg = PLANES ? 4 : 1;
-    g.nstrips = L.S * spr; g.npencils = rows * d.Ny; g.accumulate = accumulate;
+    g.nstrips = L.S * spr;
     const int nwg = (g.nstrips * PER + 3) / 4, nsub = nwg * L.mac_nmblk;
     g.d_sub.set((unsigned)(nsub * pg)); g.d_pg.set((unsigned)pg); g.d_spr.set((unsigned)spr); g.d_nwg.set((unsigned)nwg);
     g.d_Ny.set((unsigned)d.Ny);
-    g.X2 = L.buf1 + (size_t)L.oz0 * g.xpen; g.Yd = L.Yt + (size_t)L.oz0 * g.ypen;
     const long long blocks = (long long)((g.npencils + 8 * pg - 1) / (8 * pg)) * nsub * pg * 8;
     if (blocks > 0x7fffffffll) return ZNNI_ERR_SHAPE;
     constexpr size_t lds = xd_lds_bytes<RT, CT, PLANES>();
     void (*kernel)(XdArgs);
-    if constexpr (PLANES) kernel = L.tiles ? k_mac_tiles<RT, CT> : k_mac_planes<RT, CT>;
+    if constexpr (PLANES) kernel = k_mac_planes<RT, CT>;
     else kernel = k_mac_xd<RT, CT, SUM>;
     if (lds > 48 * 1024 && hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
         return ZNNI_ERR_HIP;
@@ -815,14 +770,13 @@ static znni_status launch_xd_cols_s(const LayerPlan& L, int accumulate, hipStrea
     constexpr int MAXCT = xd_max_ct<RT>();
     constexpr long long FULL = 1024;                         // (of the whole layer: its slabs take the same width)
     const int tiles = (L.d.nox + 15) / 16;
-    const long long S = L.tiles ? (long long)L.cut.S * L.cut.pairs : L.S;      // (turns take the width of the whole, too)
     int CT = 1;
     long long best = -1;
     for (int c = 1; c <= MAXCT; ++c) {
         const int PER = xd_shared(RT, c, PLANES) ? 4 : 1;
-        const long long waves = (S * ((tiles + c * PER - 1) / (c * PER)) * PER + 3) / 4 * 4;
+        const long long waves = ((long long)L.S * ((tiles + c * PER - 1) / (c * PER)) * PER + 3) / 4 * 4;
         const int rounds = (4 * (16 * c + 8) + 63) / 64;
-        const long long n = std::max(waves * (L.tiles ? L.d.Nz : L.d.zc) * L.d.Ny * L.mac_nmblk, FULL) * (96 * L.d.kx * RT * c + 200 * rounds + 800);
+        const long long n = std::max(waves * L.d.zc * L.d.Ny * L.mac_nmblk, FULL) * (96 * L.d.kx * RT * c + 200 * rounds + 800);
         if (best < 0 || n <= best) { best = n; CT = c; }
     }
     switch (CT) {
@@ -851,6 +805,7 @@ static znni_status launch_xd_cols(const LayerPlan& L, int accumulate, hipStream_
 znni_status launch_mac_xd(const LayerPlan& L, int accumulate, hipStream_t st)
 {
     if (!mac_xd_available(L)) return ZNNI_ERR_UNSUPPORTED_SIZE;
+    if (L.tiles) return launch_mac_quads(L, xd_args(L, accumulate), st);
     switch (L.mac_RTW) {
         case 1: return launch_xd_cols<1>(L, accumulate, st);
         case 2: return launch_xd_cols<2>(L, accumulate, st);

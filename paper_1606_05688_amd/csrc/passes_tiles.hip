@@ -26,7 +26,7 @@
 // fill the SIMDs evenly (60: ten waves) fall to 3.6 and are not offered.
 #include "two_step.h"
 #include <algorithm>
-#include "mac_common.h"
+#include "mac_xd.h"
 
 namespace znni {
 
@@ -339,9 +339,17 @@ bool tiles_plan(const LayerPlan& whole, int N, void* base, size_t room, bool chu
 // and the tail of its last workgroups, and bytes per second behind that.
 struct TileLength { int N; float fwd_us, fwd_tbs, inv_us, inv_tbs; };
 static const TileLength kTileLengths[] = {
-    {24, 8.8f, 5.83f, 8.6f, 5.31f},  {28, 9.5f, 6.14f, 9.0f, 5.25f},   {32, 9.4f, 6.32f, 8.5f, 5.52f},   {36, 9.7f, 6.18f, 9.4f, 5.29f},
-    {40, 9.4f, 5.46f, 8.7f, 4.64f},  {42, 10.1f, 5.45f, 9.7f, 4.51f},  {48, 11.3f, 5.30f, 10.1f, 4.59f}, {56, 12.7f, 5.82f, 10.8f, 4.82f},
-    {64, 11.5f, 5.68f, 9.6f, 5.07f}, {72, 14.5f, 4.53f, 10.2f, 3.70f}, {84, 14.5f, 4.45f, 11.7f, 3.97f}};
+    {24, 8.4f, 5.78f, 8.3f, 5.30f},  {28, 9.2f, 6.14f, 8.6f, 5.23f},  {32, 9.3f, 6.32f, 8.2f, 5.50f},  {36, 9.3f, 6.18f, 8.7f, 5.26f},
+    {40, 8.9f, 5.36f, 8.2f, 4.59f},  {42, 8.8f, 5.30f, 8.2f, 4.49f},  {48, 10.5f, 5.28f, 9.6f, 4.72f}, {56, 11.4f, 5.77f, 9.6f, 4.96f},
+    {64, 11.7f, 5.78f, 9.4f, 5.11f}, {72, 12.9f, 4.46f, 9.7f, 3.76f}, {84, 11.5f, 4.29f, 10.1f, 3.91f}};
+
+// Waves of a multiply-accumulate, what they multiply (column and row tiles times matrix steps) and stage (chunks of images).
+struct MacWaves { double waves, products, chunks; };
+static MacWaves mac_waves(const LayerPlan& L, int CT, double pencils)
+{
+    const double w = pencils * L.mac_nmblk * ((L.d.nox + 16 * CT - 1) / (16 * CT));
+    return MacWaves{w, w * ((L.d.kx * (L.fp >> 2) + 3) / 4) * L.mac_RTW * CT, w * ((L.f + 15) / 16)};
+}
 
 // Estimated times, without the kernel transforms (which a call may keep) and with them.
 struct Seconds { double kept, all; };
@@ -354,18 +362,19 @@ static Seconds tiles_estimate(const LayerPlan& L)
     const double E = (double)c.S * c.pairs, plane = 8.0 * d.Ny * d.Nz, tiles = (double)c.S * c.nty * c.ntz;
     const double xb = (d.nx + 3) / 4 * 4 * plane * E * L.f, yb = (d.nox + 3) / 4 * 4 * plane * E * L.fo;
     const double per = 8.0 * d.zc * d.kx * L.fp * (double)L.Mp, bank = per * d.Ny, a1 = per * d.ky;
-    const double ops = 24.0 * d.kx * L.fp * (double)L.Mp * E * ((d.nox + 15) & ~15) * d.Ny * d.Nz;
+    const MacWaves m = mac_waves(L, quads_strip(L), E * d.Nz * ((d.Ny + 3) & ~3));
     const double turns = (double)((c.S + c.sn - 1) / c.sn) * ((c.pairs + c.pn - 1) / c.pn);
-    double us = turns * (t->fwd_us + t->inv_us + 6.7);
+    double us = turns * (t->fwd_us + t->inv_us + 5.7);
     us += (4.0 * tiles * L.f * d.nx * d.ny * (double)d.nz + xb) / t->fwd_tbs * 1e-6;
     us += (4.0 * tiles * L.fo * d.nox * d.noy * (double)d.noz + yb) / t->inv_tbs * 1e-6;
-    us += ops / 1.87e9 + (xb + yb + bank) / 3.79e6;
-    return Seconds{us * 1e-6, (us + 10.9 + bank / 9.1e6 + a1 / 0.78e6) * 1e-6};
+    static const float product[] = {3.3e-5f, 4.8e-5f, 5.3e-5f, 5.9e-5f, 6.4e-5f};        // by row tiles
+    us += product[L.mac_RTW - 1] * m.products + 2.9e-4 * m.chunks + 7e-4 * m.waves + (xb + yb + bank) / 5.6e6;
+    return Seconds{us * 1e-6, (us + 11 + bank / 9.0e6 + a1 / 0.80e6) * 1e-6};
 }
 double tiles_seconds(const LayerPlan& L) { return tiles_estimate(L).all; }
 
-// The whole planes' route, likewise (1266 random layers whose x axis is not transformed: 0.97 of the time measured, a tenth of
-// them below 0.83 and above 1.11 of it).
+// The whole planes' route, likewise (1015 random layers whose x axis is not transformed: 1.04 of the time measured, a tenth of them
+// below 0.91 and above 1.22 of it; tiles 1.01, 0.89 and 1.12).
 static Seconds whole_estimate(const LayerPlan& L)
 {
     if (!L.xdirect) { const double s = 1.15 * route_seconds(L); return Seconds{s, s}; }
@@ -373,31 +382,33 @@ static Seconds whole_estimate(const LayerPlan& L)
     double hb[ZNNI_NUM_STAGES], fl[ZNNI_NUM_STAGES];
     plan_work(L, 0, hb, fl);
     const double per = 8.0 * d.zc * d.kx * L.fp * (double)L.Mp, bank = per * d.Ny, a1 = per * d.ky;
-    const double ops = 24.0 * d.kx * L.fp * (double)L.Mp * L.S * ((d.nox + 15) & ~15) * d.Ny * d.zc;
-    double us = 33 + hb[ZNNI_STAGE_FWD_Z] / 4.8e6 + hb[ZNNI_STAGE_FWD_Y] / 5.3e6 + hb[ZNNI_STAGE_INV_Y] / 5.7e6 + hb[ZNNI_STAGE_INV_Z] / 5.5e6;
-    us += ops / 1.94e9 + hb[ZNNI_STAGE_MAC] / 4.6e6;
-    return Seconds{us * 1e-6, (us + 11.8 + bank / 6.2e6 + a1 / 1.1e6) * 1e-6};
+    const int tiles = (d.nox + 15) / 16;
+    const MacWaves m = mac_waves(L, std::min(tiles, L.mac_RTW < 4 ? 4 : 2), (double)L.S * d.Ny * d.zc);
+    double us = 32 + hb[ZNNI_STAGE_FWD_Z] / 4.9e6 + hb[ZNNI_STAGE_FWD_Y] / 5.35e6 + hb[ZNNI_STAGE_INV_Y] / 5.8e6 + hb[ZNNI_STAGE_INV_Z] / 5.5e6;
+    // (stepwise sums or not: launch_xd_cols in mac_xd.hip)
+    us += (mac_xb_available(L) || mac_batch_preferred(L) ? 4.3e-5 : 3.55e-5) * m.products + 3.7e-4 * m.chunks + 2.8e-4 * m.waves + hb[ZNNI_STAGE_MAC] / 6.6e6;
+    return Seconds{us * 1e-6, (us + 11.6 + bank / 6.6e6 + a1 / 1.15e6) * 1e-6};
 }
 
-// The length whose estimate is the lowest, if that is below the whole planes'.  Over 1475 random layers of 2 to 100 images of 24 to
-// 320 an edge: 1.24 times as fast on average, 1.30 from 0.3 ms on; the pick is 0.5 % off the best length.  Layers that already go four
-// planes at a time stay there (they have two kernels around the product as well, and lengths that fit).  So do layers below 60 us,
-// and those with many products per value moved (80 -> 80 of 128^3, 7^3: passes 1030 -> 760 us, multiply-accumulate 1020 -> 1400):
-// more products cost more there than fewer passes save.
+// The length whose estimate is the lowest, if that is below the whole planes' by a twelfth, with kernel transforms and without.
+// Over 1015 random layers of 2 to 100 images of 24 to 320 an edge, 834 of which go in tiles: 1.29 times as fast on average (1.26 with
+// kept kernel transforms), two more than 3 % behind whole planes, the worst 6 % (1 x 3 -> 6 of 341 x 227 x 155, 3 x 6 x 9: few images
+// leave chunks of sixteen empty); the pick is 0.5 % off the best length.  Layers that already go four planes at a time stay there
+// (they have two kernels around the product as well, and lengths that fit), and so do layers below 60 us: launches.  With many
+// products per value moved, more products cost more than fewer passes save (80 -> 80 of 128^3, 7^3: passes 1030 -> 700 us,
+// multiply-accumulate 1020 -> 1560).
 int pick_tiles(const LayerPlan& whole, size_t room, bool chunks)
 {
     if (whole.generic_passes || whole.planes || !mac_xd_available(whole)) return 0;
     const Seconds w = whole_estimate(whole);
-    if (w.kept < 60e-6) return 0;                            // (a few launches of a few microseconds: level)
+    if (w.kept < 60e-6) return 0;
     int N = 0;
-    double best = w.all;
+    double best = 0.92 * w.all;
     LayerPlan T;
     for (const TileLength& t : kTileLengths)
         if (tiles_plan(whole, t.N, nullptr, room, chunks, &T)) {
             const Seconds s = tiles_estimate(T);
-            const double bytes = 8.0 * t.N * t.N * T.cut.S * T.cut.pairs * ((double)T.f * T.d.nx + (double)T.fo * T.d.nox);
-            const double ops = 24.0 * T.d.kx * T.fp * (double)T.Mp * T.cut.S * T.cut.pairs * T.d.nox * t.N * t.N;
-            if (s.all < best && s.kept < w.kept && ops < 480 * bytes) { best = s.all; N = t.N; }
+            if (s.all < best && s.kept < 0.92 * w.kept) { best = s.all; N = t.N; }
         }
     return N;
 }

@@ -9,15 +9,18 @@ from paper_1606_05688_amd import binding as B
 pytestmark = pytest.mark.gpu
 
 # With few products each, every kernel of the route (the host test counts them)
-CASES = [(1, 26, 1, (28, 114, 115), (1, 1, 1)), (3, 7, 1, (56, 115, 73), (1, 1, 1)), (3, 7, 2, (79, 51, 59), (1, 1, 1)),
-         (2, 2, 33, (49, 31, 67), (1, 1, 1)), (3, 11, 2, (46, 75, 41), (1, 1, 2)), (1, 2, 47, (74, 65, 52), (1, 1, 2)),
-         (3, 1, 18, (45, 104, 56), (1, 1, 4)), (3, 1, 11, (65, 126, 61), (1, 2, 2)), (2, 1, 33, (46, 81, 48), (1, 4, 2)),
-         (3, 2, 2, (72, 120, 139), (3, 5, 3)), (2, 4, 3, (58, 69, 160), (2, 5, 5)), (1, 2, 72, (37, 42, 58), (1, 1, 1)),
-         (2, 21, 1, (9, 114, 152), (1, 1, 2)), (3, 2, 24, (5, 132, 138), (1, 1, 1)), (1, 1, 17, (23, 158, 128), (1, 1, 2)),
-         (1, 1, 71, (44, 37, 82), (1, 2, 1)), (2, 2, 23, (53, 73, 57), (1, 1, 1)), (2, 1, 56, (18, 38, 146), (1, 2, 1)),
-         (3, 1, 69, (17, 109, 62), (1, 1, 1)), (2, 2, 43, (5, 162, 175), (1, 1, 1)), (1, 1, 61, (9, 153, 160), (1, 1, 2)),
-         (2, 1, 27, (75, 112, 71), (1, 1, 1)), (2, 1, 38, (64, 41, 33), (1, 5, 1)), (1, 1, 36, (35, 109, 60), (1, 2, 2)),
-         (1, 1, 51, (66, 86, 33), (1, 2, 2))]
+CASES = [(1, 33, 1, (5, 159, 121), (5, 1, 1)), (3, 1, 1, (54, 74, 150), (1, 2, 2)),
+         (3, 2, 1, (36, 89, 155), (1, 2, 2)), (2, 2, 33, (49, 31, 67), (1, 1, 1)),
+         (1, 1, 43, (9, 100, 156), (1, 2, 2)), (3, 1, 11, (65, 126, 61), (1, 2, 2)),
+         (3, 1, 3, (48, 138, 88), (1, 3, 1)), (3, 28, 1, (6, 73, 122), (1, 2, 2)),
+         (3, 2, 1, (64, 104, 165), (1, 2, 2)), (3, 2, 2, (72, 120, 139), (3, 5, 3)),
+         (3, 2, 10, (50, 161, 79), (2, 4, 4)), (3, 5, 1, (29, 63, 163), (2, 1, 1)),
+         (1, 2, 72, (37, 42, 58), (1, 1, 1)), (1, 1, 28, (6, 179, 172), (1, 3, 1)),
+         (1, 1, 17, (23, 158, 128), (1, 1, 2)), (1, 2, 41, (29, 124, 61), (1, 1, 1)),
+         (2, 2, 23, (53, 73, 57), (1, 1, 1)), (1, 1, 76, (34, 58, 75), (2, 1, 1)),
+         (2, 1, 56, (18, 38, 146), (1, 2, 1)), (1, 1, 25, (36, 105, 68), (1, 1, 4)),
+         (1, 1, 24, (70, 33, 158), (1, 3, 1)), (1, 1, 61, (9, 153, 160), (1, 1, 2)),
+         (1, 5, 52, (37, 49, 61), (1, 1, 1)), (1, 1, 36, (35, 109, 60), (1, 2, 2))]
 # Long sums, wide kernels, odd numbers of tiles, extents of one tile along y or z, chunks of input images that end short
 CASES += [(1, 21, 19, (40, 97, 97), (3, 3, 3)), (2, 33, 7, (35, 101, 70), (5, 4, 7)), (1, 50, 18, (21, 130, 75), (7, 2, 3)),
           (1, 18, 70, (30, 67, 120), (2, 6, 5)), (1, 17, 17, (11, 200, 201), (4, 9, 8)), (3, 20, 20, (26, 80, 40), (3, 3, 5))]
