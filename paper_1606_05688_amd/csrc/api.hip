@@ -394,7 +394,7 @@ static znni_status validate(int S, int f, int fo, const int n[3], const int k[3]
 // The transforms before and after the multiply-accumulate of a layer whose x axis is not transformed.
 static znni_status fwd_untransformed_x(const LayerPlan& L, const float* in, hipStream_t st)
 {
-    if (L.planes) return launch_fwd_zy_planes(L, in, st);
+    if (L.planes) return launch_fwd_zy_planes(L, in, nullptr, st);
     const znni_status rc = launch_fwd_z(L, in, st);
     return rc ? rc : launch_fwd_y(L, st);
 }
@@ -415,6 +415,13 @@ static znni_status run(const LayerPlan& L, const float* in, const float* w, cons
         if (ev && hipEventRecord(ev[s], st) != hipSuccess) return ZNNI_ERR_HIP; \
     } while (0)
     const size_t bank = (size_t)L.f * L.d.kx * L.d.ky * L.d.kz;
+    if (!ev && !(flags & ZNNI_KEEP_KERNELS) && prep_small_available(L)) {
+        // four launches instead of six (with events between the stages: six, and the same results)
+        ZNNI_DO(launch_fwd_zy_planes(L, in, w, st));
+        ZNNI_DO(launch_kernel_prep_y(L, st));
+        ZNNI_DO(launch_mac_xd(L, 0, st));
+        return launch_inv_yz_planes(L, bias, out, flags, st);
+    }
     ZNNI_DO(launch_twiddles(L, flags & ZNNI_KEEP_KERNELS ? nullptr : w, bank, st));
     ZNNI_MARK(ZNNI_STAGE_KERNEL_PREP);
     // the stored kernel transforms of an earlier call on this workspace may be kept (same w, shape and form)
@@ -429,7 +436,7 @@ static znni_status run(const LayerPlan& L, const float* in, const float* w, cons
                 c.sn = c.S - c.s0 < L.cut.sn ? c.S - c.s0 : L.cut.sn;
                 c.pn = c.pairs - c.p0 < L.cut.pn ? c.pairs - c.p0 : L.cut.pn;
                 T.S = c.sn * c.pn; T.nimg = T.S * T.f; T.nimgo = T.S * T.fo;
-                ZNNI_DO(launch_fwd_zy_planes(T, in, st));
+                ZNNI_DO(launch_fwd_zy_planes(T, in, nullptr, st));
                 ZNNI_DO(launch_mac_xd(T, 0, st));
                 ZNNI_DO(launch_inv_yz_planes(T, bias, out, flags, st));
             }
@@ -438,7 +445,7 @@ static znni_status run(const LayerPlan& L, const float* in, const float* w, cons
     if (L.xdirect) {
         // x axis not transformed: the x stages do nothing and read about zero
         ZNNI_MARK(ZNNI_STAGE_FWD_Z);
-        ZNNI_DO(L.planes ? launch_fwd_zy_planes(L, in, st) : launch_fwd_z(L, in, st));
+        ZNNI_DO(L.planes ? launch_fwd_zy_planes(L, in, nullptr, st) : launch_fwd_z(L, in, st));
         ZNNI_MARK(ZNNI_STAGE_FWD_Y);
         if (!L.planes) ZNNI_DO(launch_fwd_y(L, st));
         ZNNI_MARK(ZNNI_STAGE_FWD_X);

@@ -25,6 +25,7 @@
 //     P1 = Ar Br, P2 = Ai Bi, P3 = (Ar+Ai)(Br+Bi);  Re = P1 - P2, Im = P3 - P1 - P2.
 // A is stored in the order the contraction walks it: [oz][oy][i/4][a][i%4][j<Mp].
 #include <algorithm>
+#include "kprep.h"
 #include "mac_common.h"
 
 namespace znni {
@@ -48,7 +49,6 @@ __device__ __forceinline__ void kprep_gather(float2* tw2, const float2* __restri
 // One thread produces KPREP_OZ consecutive oz for one (b,a,i,j): its kz kernel values -- a short run of w, far
 // from the runs of the neighbouring lanes -- are read once per KPREP_OZ outputs.  (One thread per output re-read w
 // for every oz: 3.2 ms for 80 x 80 kernels of 9^3 at length 100.)
-constexpr int KPREP_OZ = 16;
 
 // Powers of two for the kernel transforms on the route that stores them as split halves (mac_xd.hip).
 //
@@ -61,12 +61,6 @@ constexpr int KPREP_OZ = 16;
 // input image, lanes along its taps.  Whether such sums of an output image lie more than 2^UNEVEN apart goes into bits that
 // the inverse of its power of two does not need: the sign where one is zero or that small, the lowest where one is that small
 // and not zero (what either means to the multiply-accumulate: mac_xd.hip).
-constexpr int UNEVEN = 14;
-__device__ __forceinline__ int kprep_col_exp(float cmax, float most)
-{
-    const int t = (int)(__float_as_uint(cmax) >> 23) - (int)(__float_as_uint(most) >> 23);
-    return cmax == 0.f || t >= -8 ? 0 : (t >= -24 ? t / 2 : max(t + 12, -60));
-}
 __device__ __forceinline__ void kprep_row_scale(const float* __restrict__ w, const SplitScales& S, int parts, int j, int f,
                                                 int fo, int fp, int taps, size_t wj_stride, float scale)
 {
@@ -139,11 +133,7 @@ __device__ __forceinline__ void kprep_row_scale(const float* __restrict__ w, con
         m = fmaxf(fmaxf(best[0], best[1]), fmaxf(best[2], best[3]));
         lo = min(min(least[0].x, least[1].x), min(least[2].x, least[3].x));
         lo1 = min(min(least[0].y, least[1].y), min(least[2].y, least[3].y));
-        const bool small = (int)lo1 < (int)__float_as_uint(m) - (UNEVEN << 23) && lo1 != ~0u;
-        const unsigned bits = (small || lo == 0 ? 0x80000000u : 0u) | (small ? 1u : 0u);
-        const int e = max(min(14 - ((int)((__float_as_uint(m) >> 23) & 255u) - 127), 120), -120);
-        S.row[j] = m > 0.f ? __uint_as_float((unsigned)(127 + e) << 23) : 1.f;
-        S.rinv[j] = m > 0.f ? __uint_as_float((unsigned)(127 - e) << 23 | bits) : 1.f;
+        kprep_row_store(S, j, m, lo, lo1);
     }
 }
 __global__ __launch_bounds__(256) void k_kprep_z(const float* __restrict__ w, float2* __restrict__ A1,

@@ -25,9 +25,9 @@
 //
 // Both also exist for four neighbouring x of layers whose x axis is not transformed (k_fwd_zy_planes, k_inv_yz_planes, up to
 // length 64).
-#include "two_step.h"
 #include <algorithm>
-#include "znni_internal.h"
+#include "kprep.h"
+#include "two_step.h"
 
 namespace znni {
 
@@ -303,6 +303,12 @@ struct FusedFwdArgs {
     Dims d;
     const float* col;      // powers of two of the f input images of a tuple (mac_xd.hip)
     int f;
+    // small layers: the workgroups behind those of the images (prep_small); null: none
+    const float* w;
+    float2 *A1, *twx, *twz;
+    SplitScales S;
+    int nimg, fo, fp, Mp;
+    float scale;
 };
 
 // Lines per transform: along z two real rows ride in one complex line, N / 2 lines at most.  Along y the plane has
@@ -463,10 +469,158 @@ __device__ __forceinline__ int fresh(int v)
     return v;
 }
 
+// The tables of the lengths below (double precision rounded once, as k_twiddles makes them): working them out took every
+// workgroup longer than reading them.
+template <int N> struct TwiddleTable { float2 v[N]; };
+template <int N> constexpr TwiddleTable<N> make_twiddles()
+{
+    TwiddleTable<N> t{};
+    for (int q = 0; q < N; ++q) {
+        // the quadrant, and the place in its first or second half
+        const int quadrant = 4 * q / N, r = 4 * q - quadrant * N;
+        const bool upper = 2 * r > N;
+        const double x = kPi / 2 * (upper ? N - r : r) / N, s0 = ct_sin_series(x), c0 = ct_cos_series(x);
+        const double s = upper ? c0 : s0, c = upper ? s0 : c0;           // of the angle in its quadrant
+        const double sn = quadrant == 0 ? s : quadrant == 1 ? c : quadrant == 2 ? -s : -c;
+        const double cs = quadrant == 0 ? c : quadrant == 1 ? -s : quadrant == 2 ? -c : s;
+        t.v[q].x = (float)cs;
+        t.v[q].y = (float)-sn;
+    }
+    return t;
+}
+template <int N> __device__ const TwiddleTable<N> kTwiddles = make_twiddles<N>();
+
+// exp(-2 pi i q / N), as k_twiddles makes it.
+__device__ __forceinline__ float2 twiddle(int q, int N)
+{
+    double s, c;
+    sincospi(2.0 * (double)q / (double)N, &s, &c);
+    return make_float2((float)c, (float)(-s));
+}
+
+// Small layers of the route below: what launches before the forward kernel would do -- tables, largest kernel magnitudes, the
+// kernel transform's z stage, scales -- is done next to it, by workgroups of their own behind the images'.  Launches follow each
+// other 3.8 us apart, and none of this depends on another launch once whoever needs the largest magnitudes of the kernels looks
+// at the bank itself.  The results are those of the separate kernels (k_twiddles, k_kprep_z, kprep_row_scale), bit for bit.
+// cm: the largest finite kernel magnitude of every input image, a wave per image.  Behind a barrier.
+__device__ __forceinline__ void bank_max(const float* __restrict__ w, float* cm, int f, int fo, int taps)
+{
+    const int lane = threadIdx.x & 63, nw = blockDim.x >> 6, n = fo * taps;
+    for (int i = threadIdx.x >> 6; i < f; i += 2 * nw) {     // two images at a time
+        const int i1 = min(i + nw, f - 1);
+        float m = 0.f, m1 = 0.f;
+        for (int e0 = lane; e0 < n; e0 += 512) {
+            float v[8], v1[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const unsigned e = (unsigned)min(e0 + 64 * u, n - 1), j = e / (unsigned)taps;
+                const float* p = w + (size_t)(j * (unsigned)f * (unsigned)taps + (e - j * taps));
+                v[u] = fabsf(p[i * taps]);
+                v1[u] = fabsf(p[i1 * taps]);
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                m = fmaxf(m, v[u] < INFINITY ? v[u] : 0.f);
+                m1 = fmaxf(m1, v1[u] < INFINITY ? v1[u] : 0.f);
+            }
+        }
+#pragma unroll
+        for (int o = 32; o; o >>= 1) { m = fmaxf(m, __shfl_xor(m, o)); m1 = fmaxf(m1, __shfl_xor(m1, o)); }
+        if (lane == 0) { cm[i] = m; cm[i1] = m1; }
+    }
+    __syncthreads();
+}
+__device__ __forceinline__ float all_max(const float* cm, int f)
+{
+    float m = 0.f;
+    for (int i = threadIdx.x & 63; i < f; i += 64) m = fmaxf(m, cm[i]);
+#pragma unroll
+    for (int o = 32; o; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+    return m;
+}
+
+// Workgroup r of these: output image r's scale (and, first of them, those of the input images); the tables; the z stage.
+template <int N>
+__device__ __forceinline__ void prep_small(const FusedFwdArgs& a, int r, float* lds)
+{
+    const Dims& d = a.d;
+    const int t = threadIdx.x, NT = blockDim.x, wave = t >> 6, lane = t & 63, nw = NT >> 6;
+    const int taps = d.kx * d.ky * d.kz;
+    if (r < a.Mp) {
+        float* cm = lds;
+        float4* part = reinterpret_cast<float4*>(lds + ((a.f + 3) & ~3));       // [wave] largest, smallest, smallest but zero
+        bank_max(a.w, cm, a.f, a.fo, taps);
+        const float most = all_max(cm, a.f);
+        if (r == 0)
+            for (int i = t; i < a.fp; i += NT) {
+                const int e = i < a.f ? kprep_col_exp(cm[i], most) : 0;
+                a.S.col[i] = __uint_as_float((unsigned)(127 + e) << 23);
+                a.S.cinv[i] = __uint_as_float((unsigned)(127 - e) << 23);
+            }
+        float m = 0.f;
+        unsigned lo = ~0u, lo1 = ~0u;
+        if (r < a.fo)
+            for (int i = wave; i < a.f; i += nw) {
+                const float* wi = a.w + ((size_t)r * a.f + i) * taps;
+                float s = 0.f;
+                for (int t0 = 0; t0 < taps; t0 += 64) s += fabsf(wi[min(t0 + lane, taps - 1)]) * (t0 + lane < taps ? 1.f : 0.f);
+#pragma unroll
+                for (int o = 32; o; o >>= 1) s += __shfl_xor(s, o);
+                const float e = ldexpf(s * a.scale, -kprep_col_exp(cm[i], most));
+                m = fmaxf(m, e < INFINITY ? e : 0.f);
+                lo = min(lo, __float_as_uint(e));
+                lo1 = min(lo1, __float_as_uint(e) - 1u);
+            }
+        if (lane == 0) part[wave] = make_float4(m, __uint_as_float(lo), __uint_as_float(lo1), 0.f);
+        __syncthreads();
+        if (t == 0) {
+            for (int q = 0; q < nw; ++q) {
+                const float4 v = part[q];
+                m = fmaxf(m, v.x); lo = min(lo, __float_as_uint(v.y)); lo1 = min(lo1, __float_as_uint(v.z));
+            }
+            kprep_row_store(a.S, r, m, lo, lo1);
+        }
+        return;
+    }
+    if (r == a.Mp) {
+        for (int q = t; q < d.Nx; q += NT) a.twx[q] = twiddle(q, d.Nx);
+        for (int q = t; q < d.Ny; q += NT) {
+            const float2 v = kTwiddles<N>.v[q];              // (Ny = Nz = N here)
+            const_cast<float2*>(a.tw)[q] = v;
+            a.twz[q] = v;
+        }
+        return;
+    }
+    r -= a.Mp + 1;
+    const int per = d.ky * d.kx * a.fp * a.Mp, nb = (per + NT - 1) / NT;
+    const int oz0 = r / nb * KPREP_OZ, idx = (r - r / nb * nb) * NT + t;
+    float2* tw2 = reinterpret_cast<float2*>(lds);            // [taps][KPREP_OZ]
+    for (int e = t; e < d.kz * KPREP_OZ; e += NT) {
+        const int c = e / KPREP_OZ, o = e - c * KPREP_OZ;
+        tw2[e] = kTwiddles<N>.v[(oz0 + o) * c % N];
+    }
+    __syncthreads();
+    if (idx >= per) return;
+    const int j = idx % a.Mp, i = (idx / a.Mp) % a.fp, ba = idx / (a.Mp * a.fp), x = ba % d.kx, y = ba / d.kx;
+    float2 acc[KPREP_OZ];
+#pragma unroll
+    for (int o = 0; o < KPREP_OZ; ++o) acc[o] = make_float2(0.f, 0.f);
+    if (i < a.f && j < a.fo) {
+        const float* wr = a.w + ((((size_t)j * a.f + i) * d.kx + x) * d.ky + y) * d.kz;
+        for (int c = 0; c < d.kz; ++c) {
+            const float v = wr[c];
+#pragma unroll
+            for (int o = 0; o < KPREP_OZ; ++o) acc[o] = caxpy(acc[o], v, tw2[c * KPREP_OZ + o]);
+        }
+    }
+#pragma unroll
+    for (int o = 0; o < KPREP_OZ; ++o)
+        if (oz0 + o < d.zc) a.A1[(size_t)(oz0 + o) * per + idx] = acc[o];
+}
+
 // Four neighbouring x at a time (see k_inv_yz_planes): X2 as [img][oz][x / 4][oy][x % 4].
-template <int R1, int R2, int PAR_>
-__global__ __launch_bounds__((Planes<R1, R2, PAR_, true>::NTH)) __attribute__((amdgpu_waves_per_eu((Planes<R1, R2, PAR_, true>::WAVES))))
-void k_fwd_zy_planes(FusedFwdArgs a)
+template <int R1, int R2, int PAR_, bool SMALL>
+__device__ __forceinline__ void fwd_planes(const FusedFwdArgs& a)
 {
     using PL = Planes<R1, R2, PAR_, true>;
     constexpr int N = PL::N, P = N + 2, ZC = N / 2 + 1, NTH = PL::NTH, PAR = PL::PAR, ROUNDS = PL::ROUNDS, RS = PL::RS;
@@ -476,9 +630,14 @@ void k_fwd_zy_planes(FusedFwdArgs a)
     float2* R = lds + N;               // per plane, in turn: raw plane [ny][nz] floats, exchange buffer and lines [NL][P]
     const int t = threadIdx.x, xb = blockIdx.x, img = blockIdx.y, nxb = gridDim.x;
     const Dims& d = a.d;
+    if (SMALL && img >= a.nimg) {
+        prep_small<N>(a, (img - a.nimg) * nxb + xb, reinterpret_cast<float*>(lds));
+        return;
+    }
     const int tot = d.ny * d.nz, left = d.nx - PLANES * xb;      // planes from this block's first on
     const float* plane = a.in + ((size_t)img * d.nx + PLANES * xb) * tot;
-    const float ps = a.col ? a.col[img % a.f] : 1.f;
+    float ps = 1.f;
+    if (!SMALL && a.col) ps = a.col[img % a.f];
 
     // the planes of a round; the next round's are requested while one is transformed.  (Planes beyond the image repeat its
     // last one, and are never read.)
@@ -493,7 +652,14 @@ void k_fwd_zy_planes(FusedFwdArgs a)
         }
     };
     request(0);
-    for (int q = t; q < N; q += NTH) tws[q] = a.tw[q];
+    if constexpr (!SMALL) {
+        for (int q = t; q < N; q += NTH) tws[q] = a.tw[q];
+    } else {
+        if (t < N) tws[t] = kTwiddles<N>.v[t];               // (N <= 64 < NTH)
+        float* cm = reinterpret_cast<float*>(R + PAR * RS);
+        bank_max(a.w, cm, a.f, a.fo, d.kx * d.ky * d.kz);
+        ps = __uint_as_float((unsigned)(127 + kprep_col_exp(cm[img % a.f], all_max(cm, a.f))) << 23);
+    }
     struct alignas(8 * (ROUNDS > 1 ? 2 : 1)) Run { float2 v[ROUNDS]; } keep[NV];
 #pragma unroll
     for (int h = 0; h < ROUNDS; ++h) {
@@ -527,6 +693,19 @@ void k_fwd_zy_planes(FusedFwdArgs a)
         for (int h = 0; h < ROUNDS; ++h) { keep[k].v[h].x *= ps; keep[k].v[h].y *= ps; }
         *reinterpret_cast<Run*>(dst + ((size_t)l * nxb * N + e) * PLANES) = keep[k];
     }
+}
+
+template <int R1, int R2, int PAR>
+__global__ __launch_bounds__((Planes<R1, R2, PAR, true>::NTH)) __attribute__((amdgpu_waves_per_eu((Planes<R1, R2, PAR, true>::WAVES))))
+void k_fwd_zy_planes(FusedFwdArgs a)
+{
+    fwd_planes<R1, R2, PAR, false>(a);
+}
+// ... with the kernels' first stage beside it (all four planes at once: few workgroups)
+template <int R1, int R2>
+__global__ __launch_bounds__((Planes<R1, R2, PLANES, true>::NTH)) void k_fwd_zy_small(FusedFwdArgs a)
+{
+    fwd_planes<R1, R2, PLANES, true>(a);
 }
 
 // ------------------------------------------------------------------------------------------- host side
@@ -634,7 +813,7 @@ znni_status launch_fwd_zy(const LayerPlan& L, const float* in, hipStream_t st)
     const Dims& d = L.d;
     FusedFwdArgs a;
     a.in = in; a.dst = L.buf1; a.tw = L.twy; a.d = d;
-    a.col = nullptr; a.f = 1;
+    a.col = nullptr; a.f = 1; a.w = nullptr;
     const dim3 grid(d.nx, L.nimg);
     ZNNI_FUSED_CASES(k_fwd_zy)
 }
@@ -675,6 +854,7 @@ bool fused_planes_available(const LayerPlan& L)
 template <int R1, int R2>
 static znni_status launch_planes(const FusedFwdArgs& a, const FusedShape& F, int par, dim3 grid, hipStream_t st)
 {
+    if (a.w) return launch_fused(k_fwd_zy_small<R1, R2>, a, F, grid, st);
     if constexpr (!planes_wide(R1 * R2, fused_fwd_packs(R1 * R2)))
         if (par == 1) return launch_fused(k_fwd_zy_planes<R1, R2, 1>, a, F, grid, st);
     return launch_fused(k_fwd_zy_planes<R1, R2, PLANES>, a, F, grid, st);
@@ -708,8 +888,29 @@ static znni_status launch_planes(const Args& a, const FusedShape& F, int par, di
     return ZNNI_ERR_UNSUPPORTED_SIZE;
 }
 
-// in -> X2 in blocks of four x (buf1); Yd in blocks of four xo (Yt) -> out
-znni_status launch_fwd_zy_planes(const LayerPlan& L, const float* in, hipStream_t st)
+static size_t prep_small_lds(const LayerPlan& L, int nth)
+{
+    const size_t scale = sizeof(float) * ((L.f + 3) & ~3) + sizeof(float4) * (nth / 64), z = sizeof(float2) * L.d.kz * KPREP_OZ;
+    return std::max(scale, z);
+}
+// Whether a layer is small enough for every workgroup of the forward kernel to look at the kernel bank by itself: turns of a wave
+// over the bank, eight values a lane at a time, against the two launches that it saves.  Over 2200 random layers of up to 7
+// inputs and fewer than PLANES_FEW workgroups, against launches of their own: one turn 1.18 times as fast, 2 or 3 1.16, 4 to 8 1.09, 9 to 16
+// 0.99, more 0.6 to 0.85; with more waves than the chip has SIMDs, all of which look at the bank, each a little less (three times as
+// many: 1.05, 1.04, 0.98).  Batches are left out: their transforms fill the chip.
+bool prep_small_available(const LayerPlan& L)
+{
+    FusedShape F;
+    int par = 0;
+    if (!L.planes || L.tiles || L.S >= 8 || !planes_shape(L, &F, true, &par) || par != PLANES) return false;
+    const int nw = F.nth / 64;
+    const long long turns = (long long)((L.f + nw - 1) / nw) * ((L.fo * L.d.kx * L.d.ky * L.d.kz + 511) / 512);
+    const long long waves = (long long)L.nimg * ((L.d.nx + PLANES - 1) / PLANES) * nw;
+    return turns * std::max(waves, 1024ll) <= 8 * 1024;
+}
+
+// in -> X2 in blocks of four x (buf1); Yd in blocks of four xo (Yt) -> out.  w: with the kernels' z stage, scales and tables.
+znni_status launch_fwd_zy_planes(const LayerPlan& L, const float* in, const float* w, hipStream_t st)
 {
     if (L.tiles) return launch_fwd_tiles(L, in, st);
     FusedShape F;
@@ -719,7 +920,16 @@ znni_status launch_fwd_zy_planes(const LayerPlan& L, const float* in, hipStream_
     FusedFwdArgs a;
     a.in = in; a.dst = L.buf1; a.tw = L.twy; a.d = d;
     a.col = split_scales(L).col; a.f = L.f;
-    const dim3 grid((d.nx + PLANES - 1) / PLANES, L.nimg);
+    a.w = w; a.A1 = L.A1; a.twx = L.twx; a.twz = L.twz; a.S = split_scales(L);
+    a.nimg = L.nimg; a.fo = L.fo; a.fp = L.fp; a.Mp = L.Mp; a.scale = (float)(1.0 / ((double)d.Ny * d.Nz));
+    dim3 grid((d.nx + PLANES - 1) / PLANES, L.nimg);
+    if (w) {
+        F.lds = std::max(F.lds + sizeof(float) * L.f, prep_small_lds(L, F.nth));
+        const int per = d.ky * d.kx * L.fp * L.Mp;
+        const long long more = L.Mp + 1 + (long long)((per + F.nth - 1) / F.nth) * ((d.zc + KPREP_OZ - 1) / KPREP_OZ);
+        if (F.lds > 160 * 1024 || L.nimg + (more + grid.x - 1) / grid.x > 65535) return ZNNI_ERR_SHAPE;
+        grid.y += (unsigned)((more + grid.x - 1) / grid.x);
+    }
     return launch_planes(a, F, par, grid, st);
 }
 

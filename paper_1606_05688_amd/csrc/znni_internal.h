@@ -143,7 +143,9 @@ znni_status launch_inv_yz(const LayerPlan& L, const float* bias, float* out, uns
 
 // The same for layers whose x axis is not transformed (LayerPlan::planes): in -> X2 in buf1, Yd in Yt -> out.
 bool fused_planes_available(const LayerPlan& L);
-znni_status launch_fwd_zy_planes(const LayerPlan& L, const float* in, hipStream_t st);
+// w (not NULL where prep_small_available): tables, scales and the kernels' z stage in the same launch.
+bool prep_small_available(const LayerPlan& L);
+znni_status launch_fwd_zy_planes(const LayerPlan& L, const float* in, const float* w, hipStream_t st);
 znni_status launch_inv_yz_planes(const LayerPlan& L, const float* bias, float* out, unsigned flags, hipStream_t st);
 
 // Tiles (LayerPlan::tiles, passes_tiles.hip).  tiles_plan: the plan `whole` with its planes cut into tiles of transform length N,

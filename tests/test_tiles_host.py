@@ -1,5 +1,5 @@
-"""Host side of the route that cuts planes into tiles (a preloaded recorder stands in for the launches): the layers of its GPU
-tests take it and reach all of its kernels, random layers fit the workspace they ask for, and a budget is kept."""
+"""Host side of the route that cuts planes into tiles, and of small layers in four launches (a preloaded recorder stands in for
+the launches): the layers of their GPU tests take them and reach all of their kernels, and a budget is kept."""
 import ctypes
 import json
 import os
@@ -46,6 +46,18 @@ def reach(path, recorder, layers):
     assert len(every) > 40 and not every - seen, sorted(every - seen)
 
 
+def small(path, recorder, layers):
+    """Four launches, of every kernel that has the first stage beside it."""
+    rec, run = _open(path, recorder)
+    seen = set()
+    for layer in json.loads(layers):
+        names = run(*layer)
+        assert len(names) == 4 and "k_fwd_zy_small" in names[0], (layer, names)
+        seen |= set(names)
+    every = {v for v in rec.registered_kernels().decode().split() if "k_fwd_zy_small" in v}
+    assert len(every) == 14 and not every - seen, sorted(every - seen)
+
+
 def walk(path, recorder, count):
     """Every step of the route belongs to it, a transform on either side of a product, whatever the budget."""
     _, run = _open(path, recorder)
@@ -85,9 +97,14 @@ def test_gpu_layers_reach_every_kernel(tmp_path):
     _driven(tmp_path, "reach", json.dumps(T.CASES))
 
 
+def test_small_layers_take_four_launches(tmp_path):
+    import test_gpu_small as S
+    _driven(tmp_path, "small", json.dumps(S.CASES))
+
+
 def test_steps_belong_together(tmp_path):
     _driven(tmp_path, "walk", "1500")
 
 
 if __name__ == "__main__":
-    {"reach": reach, "walk": walk}[sys.argv[3]](sys.argv[1], sys.argv[2], sys.argv[4])
+    {"reach": reach, "small": small, "walk": walk}[sys.argv[3]](sys.argv[1], sys.argv[2], sys.argv[4])
