@@ -11,7 +11,7 @@
 //   direct route:     its matrix-core work over the rate the kernel reaches (lower for windows of fewer than 27
 //                     taps, where staging the image tiles weighs more per product) plus the output write, plus
 //                     two launches; layers that run on split halves (direct_split.hip): the larger of tensors moved
-//                     and products over what that kernel reaches.
+//                     and products over what that kernel reaches; layers of few taps (direct_first.hip): its own estimate.
 //
 // The model only has to rank the two; it is not used for anything else.  (Both estimates are low, by a quarter for layers of a
 // fraction of a millisecond, where launches follow each other.)  Over 600 random layers that both take, the pick is 1.0 % slower
@@ -88,6 +88,8 @@ static double direct_seconds(int S, int f, int fo, const int n[3], const int k[3
         const double tb = by / kSplitBytesPerSec, tf = fl / kSplitFlopsPerSec;
         return (tb > tf ? tb : tf) + 2 * kLaunchSec;
     }
+    const double first = direct_first_seconds(S, f, fo, n, k);
+    if (first >= 0) return first;
     const double rate = k[0] * k[1] * k[2] >= 27 ? kDirectFlopsPerSec : kDirectFlopsPerSecSmall;
     // one workgroup's walk over its contraction, however few of them there are: a step's matrix instructions (sixteen to
     // twenty tiles of 32 cycles per four waves) and about 450 cycles of operand latency.  60 -> 10 images of 27 x 21 x 32,

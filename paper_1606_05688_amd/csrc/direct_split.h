@@ -1,4 +1,4 @@
-// direct_split.h -- plan and launcher of the split-half direct convolution (direct_split.hip).
+// direct_split.h -- plans and launchers of the direct convolutions on split halves (direct_split.hip, direct_first.hip).
 #pragma once
 #include "znni_internal.h"
 
@@ -17,5 +17,20 @@ struct SplitPlan {
 bool split_plan(int S, int f, int fo, const Dims& d, SplitPlan* P);
 znni_status launch_direct_split(const SplitPlan& P, int S, int f, int fo, const Dims& d, const float* in, const float* w,
                                 const float* bias, float* out, int relu, void* workspace, hipStream_t st);
+
+// Layers of few taps, whose result's writing is the bound (direct_first.hip).
+struct FirstPlan {
+    int RTW, nmblk;               // row tiles (16 output images) of a workgroup, blocks of them
+    int TZ, TY, total, tiles;     // columns and rows of a tile, its staged values, tiles
+    double us;                    // estimated time
+};
+
+// Whether (and how) this kernel takes a layer.
+bool first_plan(int S, int f, int fo, const Dims& d, FirstPlan* P);
+znni_status launch_direct_first(const FirstPlan& P, int f, int fo, const Dims& d, const float* in, const float* w, const float* bias,
+                                float* out, int relu, hipStream_t st);
+
+// Estimated time of a direct convolution that direct_first.hip computes; negative where another kernel does.
+double direct_first_seconds(int S, int f, int fo, const int n[3], const int k[3]);
 
 }  // namespace znni
