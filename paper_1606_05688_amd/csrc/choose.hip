@@ -8,15 +8,11 @@
 //                     preparation over the HBM rate those kernels reach (lower for transform lengths served by the
 //                     generic pass kernel), plus the multiply-accumulate's matrix-core work or, where x is not
 //                     transformed, the spectra it moves if they take longer, plus a fixed cost for every launch;
-//   direct route:     its matrix-core work over the rate the kernel reaches (lower for windows of fewer than 27
-//                     taps, where staging the image tiles weighs more per product) plus the output write, plus
-//                     two launches; layers that run on split halves (direct_split.hip): the larger of tensors moved
-//                     and products over what that kernel reaches; layers of few taps (direct_first.hip): its own estimate.
+//   direct route:     the estimate of the kernel that would run (direct.hip, direct_split.hip, direct_first.hip): its walks over
+//                     tiles, taps and staged values, and the tensors it moves.
 //
-// The model only has to rank the two; it is not used for anything else.  (Both estimates are low, by a quarter for layers of a
-// fraction of a millisecond, where launches follow each other.)  Over 600 random layers that both take, the pick is 1.0 % slower
-// than the faster one on average (242 of them four planes at a time: 1.3 %), 27 by more than 5 %; always the transform route
-// would be 37 %, always the direct one 82 %.
+// The model only has to rank the two; it is not used for anything else.  Over 6136 random layers that both take, the pick is 0.6 %
+// slower than the faster one on average, 216 by more than 5 %.
 #include "direct_split.h"
 #include "mac_common.h"
 
@@ -27,11 +23,6 @@ constexpr double kPassBytesPerSecFast = 5.3e12;     // in-register pass kernels
 constexpr double kPassBytesPerSecGeneric = 2.0e12;  // generic LDS pass kernels
 constexpr double kPrepBytesPerSec = 4.5e12;         // kernel preparation (write-bound)
 constexpr double kMacFlopsPerSec = 110e12;          // issued matrix-core flops of the multiply-accumulate (S = 1 form)
-constexpr double kDirectFlopsPerSec = 80e12;        // direct convolution, windows of 27 taps and more
-constexpr double kDirectFlopsPerSecSmall = 60e12;   // ... of fewer taps
-constexpr double kDirectWriteBytesPerSec = 3.6e12;  // direct convolution, output write
-constexpr double kSplitBytesPerSec = 2.6e12;        // direct convolution on split halves: tensors read and written
-constexpr double kSplitFlopsPerSec = 75e12;         // ... and products of whole octets and steps
 constexpr double kLaunchSec = 3.5e-6;
 
 // The route and its passes as the planner has them: bytes of every stage of the call that would run.
@@ -68,36 +59,9 @@ double route_seconds(const LayerPlan& L)
 static double fft_seconds(int S, int f, int fo, const int n[3], const int k[3])
 {
     LayerPlan L;
-    return make_plan(S, f, fo, n, k, 0, nullptr, &L) ? -1.0 : route_seconds(L);
-}
-
-static double direct_seconds(int S, int f, int fo, const int n[3], const int k[3])
-{
-    const double ovox = (double)(n[0] - k[0] + 1) * (n[1] - k[1] + 1) * (n[2] - k[2] + 1);
-    const double taps4 = (k[0] * k[1] * k[2] + 3) / 4 * 4, Mp = (fo + 15) / 16 * 16;
-    const double flops = 2.0 * S * f * taps4 * Mp * ovox;
-    const double wr = 4.0 * S * fo * ovox;
-    Dims d;
-    d.nx = n[0]; d.ny = n[1]; d.nz = n[2];
-    d.kx = k[0]; d.ky = k[1]; d.kz = k[2];
-    d.nox = n[0] - k[0] + 1; d.noy = n[1] - k[1] + 1; d.noz = n[2] - k[2] + 1;
-    SplitPlan P;
-    if (split_plan(S, f, fo, d, &P)) {
-        const double by = wr + 4.0 * S * f * n[0] * n[1] * n[2];
-        const double fl = 2.0 * S * 32 * P.nsteps * 16.0 * P.RT * P.nmblk * ovox;
-        const double tb = by / kSplitBytesPerSec, tf = fl / kSplitFlopsPerSec;
-        return (tb > tf ? tb : tf) + 2 * kLaunchSec;
-    }
-    const double first = direct_first_seconds(S, f, fo, n, k);
-    if (first >= 0) return first;
-    const double rate = k[0] * k[1] * k[2] >= 27 ? kDirectFlopsPerSec : kDirectFlopsPerSecSmall;
-    // one workgroup's walk over its contraction, however few of them there are: a step's matrix instructions (sixteen to
-    // twenty tiles of 32 cycles per four waves) and about 450 cycles of operand latency.  60 -> 10 images of 27 x 21 x 32,
-    // 7 x 6 x 3 kernels: 0.56 ms, where its products alone would take 0.03
-    const double rows = Mp / 16 < 5 ? Mp / 16 : 5;
-    const double walk = f * taps4 / 4 * (rows * 4 * 32 + 450) / 2.2e9;
-    const double t = flops / rate + wr / kDirectWriteBytesPerSec;
-    return (t > walk ? t : walk) + 2 * kLaunchSec;
+    if (make_plan(S, f, fo, n, k, 0, nullptr, &L)) return -1.0;
+    // (the estimate of tiles is that of a call; that of whole planes, which serves to rank routes, is low by 20 to 35 %)
+    return L.tiles ? route_seconds(L) : 1.25 * route_seconds(L);
 }
 
 }  // namespace znni

@@ -341,15 +341,15 @@ static znni_status direct_plan(int S, int f, int fo, const int n[3], const int k
     P->wp_floats = (size_t)f * P->T4 * P->RT * 16;
     // + one step of padding: the kernel requests its kernel values one step ahead
     P->bytes = ((P->wp_floats + (size_t)P->RT * 64) * 4 + 255) / 256 * 256;
-    // This file's kernel, in microseconds: what a call costs, and for every 512 tiles (two a compute unit) a walk over the taps
-    // and over the staged values; a megabyte written.  Fitted with direct_first.hip's to 1900 random layers (standard deviation
-    // 10 %).  That one takes a layer where it is estimated to be the faster by a tenth: over 1586 layers of 9 to 64 taps that both
-    // run, the pick is 31 % faster than always this one on average and 3 % slower than the faster of them; 28 lose 2 to 13 %.
-    const double rt4 = P->RTW * P->CTW / 4.0;
+    // This file's kernel, in microseconds: what a call costs; for every 512 tiles (two a compute unit) a walk over the taps and over
+    // the staged values; a megabyte written.  Fitted to 3601 random layers (standard deviation 15 %).  direct_first.hip's takes a
+    // layer where it is estimated to be the faster by 15 %: over 1586 layers of 9 to 64 taps that both run, the pick is 31 % faster
+    // than always this one on average and 2 % slower than the faster of them; 39 lose 2 to 15 %.
+    const double rt4 = P->RTW * P->CTW / 4.0, steps = (double)f * P->T4 / 4;
     const double turns = (double)S * ((d.nox + TX - 1) / TX) * ((d.noy + TY - 1) / TY) * ((d.noz + TZ - 1) / TZ) * P->nmblk / 512;
-    P->us = 7.6 + turns * (0.26 + rt4 * (0.59 + 0.133 * f * P->T4 / 4) + 0.079 * f * tilevol / 256) +
-            0.099e-6 * 4 * S * fo * ((double)d.nox * d.noy * d.noz);
-    P->first = first_plan(S, f, fo, d, &P->fp) && P->fp.us < 0.9 * P->us;
+    P->us = 9.3 + (turns > 1 ? turns : 1) * (rt4 * (0.27 + 0.122 * steps) + 0.083 * steps + 0.050 * f * tilevol / 256 + 0.35 * ((f + IC - 1) / IC)) +
+            0.164e-6 * 4 * S * fo * ((double)d.nox * d.noy * d.noz);
+    P->first = first_plan(S, f, fo, d, &P->fp) && P->fp.us < 0.85 * P->us;
     P->split = split_plan(S, f, fo, d, &P->sp);
     if (P->split && P->sp.bytes > P->bytes) P->bytes = (P->sp.bytes + 255) / 256 * 256;
     return ZNNI_OK;
@@ -381,10 +381,11 @@ static znni_status launch_direct_t(const DirectArgs& a, const DirectPlan& P, hip
     return P.longz ? launch_direct_s<RTW, CTW, true>(a, P, st) : launch_direct_s<RTW, CTW, false>(a, P, st);
 }
 
-double direct_first_seconds(int S, int f, int fo, const int n[3], const int k[3])
+double direct_seconds(int S, int f, int fo, const int n[3], const int k[3])
 {
     DirectPlan P;
-    return direct_plan(S, f, fo, n, k, &P) || P.split || !P.first ? -1.0 : P.fp.us * 1e-6;
+    if (direct_plan(S, f, fo, n, k, &P)) return -1.0;
+    return 1e-6 * (P.split ? split_us(P.sp, S, f, fo, P.d) : P.first ? P.fp.us : P.us);
 }
 
 }  // namespace znni

@@ -15,6 +15,7 @@ struct SplitPlan {
 
 // Whether (and how) a layer runs on this kernel; d needs image, kernel and output sizes only.
 bool split_plan(int S, int f, int fo, const Dims& d, SplitPlan* P);
+double split_us(const SplitPlan& P, int S, int f, int fo, const Dims& d);     // its estimated time
 znni_status launch_direct_split(const SplitPlan& P, int S, int f, int fo, const Dims& d, const float* in, const float* w,
                                 const float* bias, float* out, int relu, void* workspace, hipStream_t st);
 
@@ -30,7 +31,7 @@ bool first_plan(int S, int f, int fo, const Dims& d, FirstPlan* P);
 znni_status launch_direct_first(const FirstPlan& P, int f, int fo, const Dims& d, const float* in, const float* w, const float* bias,
                                 float* out, int relu, hipStream_t st);
 
-// Estimated time of a direct convolution that direct_first.hip computes; negative where another kernel does.
-double direct_first_seconds(int S, int f, int fo, const int n[3], const int k[3]);
+// Estimated time of a direct convolution, by the kernel that would compute it (negative where none does).
+double direct_seconds(int S, int f, int fo, const int n[3], const int k[3]);
 
 }  // namespace znni

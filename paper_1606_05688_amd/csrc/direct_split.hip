@@ -402,6 +402,16 @@ bool split_plan(int S, int f, int fo, const Dims& d, SplitPlan* P)
     return true;
 }
 
+// What a call costs; for every 512 tiles (two a compute unit, and a tile at least) the products, the staged values and the steps'
+// latency; the kernels' preparation; megabytes written and read.  Fitted to 1634 random layers (standard deviation 16 %).
+double split_us(const SplitPlan& P, int S, int f, int fo, const Dims& d)
+{
+    const double turns = (P.ntiles > 512 ? P.ntiles / 512.0 : 1.0) * P.nmblk, pairs = P.RT * P.CT;
+    const double out = 4e-6 * S * fo * ((double)d.nox * d.noy * d.noz), in = 4e-6 * S * f * ((double)d.nx * d.ny * d.nz) * P.nmblk;
+    return 10.7 + turns * (pairs * (0.155 + 0.0358 * P.nsteps) + 0.40 * P.noct * P.npos / 256 + 0.30 * P.nsteps) + 0.097 * P.nsteps * P.noct +
+           0.19 * out + 0.064 * in;
+}
+
 template <int RT>
 static znni_status launch_rt(const SplitArgs& a, const SplitPlan& P, hipStream_t st)
 {
