@@ -242,8 +242,9 @@ znni_status znni_conv3d_fft_profile_v(int S, int f, int fo, const int n[3], cons
  *   znni_conv3d_fft_budget_v can run in slabs, see there, has a division too, which is then not used.)  ZNNI_ERR_WORKSPACE if even the smallest division
  *   (S_i = f_i = f'_i = 1) does not fit; *bytes then holds what that division needs.
  * znni_conv3d_fft_budget_v: runs the layer with the division chosen for workspace_bytes; where the spectra of the whole
- *   layer fit and only the kernel transforms do not (and x is not transformed), in slabs along the halved axis instead,
- *   which transforms nothing twice and gives znni_conv3d_fft_v's result bit for bit.  Arguments, ownership,
+ *   layer fit and only the kernel transforms do not (and x is not transformed), in slabs along the halved axis instead, and
+ *   where znni_conv3d_fft_v cuts planes into tiles, in turns of tiles: neither transforms anything twice, and both give
+ *   znni_conv3d_fft_v's result bit for bit.  Arguments, ownership,
  *   alignment and status codes as for znni_conv3d_fft_v; ZNNI_ERR_WORKSPACE if no division fits.
  */
 znni_status znni_conv3d_fft_sublayers_v(int S, int f, int fo, const int n[3], const int k[3],

@@ -17,6 +17,9 @@
 // shifted offsets.  (With many inputs per batch a kernel-spectrum value generated once per bin serves them all, as in
 // mac_batch.hip, but on fp32 products and behind two more passes: batches of small images come here as well.)
 //
+// Layers whose planes are cut into tiles (passes_tiles.hip) go through mac_quads.hip instead, with the same halves, scales and
+// kernel operands; here are the others: whole planes, four at a time or by separate passes.
+//
 // Layouts: X2[img][oz][oy][x < ldx] as the forward y pass leaves it, Yd[imgo][oz][oy][xo < ldxo], which the inverse y pass
 // reads with a transposing load; or, next to the fused z+y kernels that take four planes (passes_fused.hip), X2[img][oz]
 // [x/4][oy][x%4] and Yd likewise (k_mac_planes).  A: see k_kprep_xd.
@@ -54,7 +57,7 @@
 // before and after): 80 -> 80 of 128^3, 7^3 2.53 -> 1.05 ms; 40 -> 40 of 128^3, 3^3 0.37 -> 0.22; 37 -> 45 of 93 x 110 x
 // 131, 3 x 4 x 5 0.33 -> 0.25; 80 -> 80 of 200^3, 5^3 9.1 -> 3.8.  Up to eight images with one or two taps it is level to a
 // fifth behind (7 -> 38 of 126 x 180 x 119, 1 tap: 0.118 -> 0.142): there nothing but reading and writing spectra is left.
-// What bounds it: at 48 -> 48 of 320^3, 5^3 (5.0 ms, 6.3 with workgroup-wide staging and 64-column tiles of four waves) the
+// What bounds it: at 48 -> 48 of 320^3, 5^3 on whole planes (5.0 ms, 6.3 with workgroup-wide staging and 64-column tiles of four waves) the
 // matrix pipes are busy half of the time at 1.75 GHz, where the passes next to it run at 2.1 to 2.2: power, of which the
 // products take most.  Without image reads it took 4.3 ms, without stores 4.4, without any memory access 3.7, with a third
 // of the products 3.7; requesting the next chunk's cache lines ahead, other wave priorities and fewer vector

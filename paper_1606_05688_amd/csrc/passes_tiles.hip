@@ -6,15 +6,15 @@
 //  * a tile's plane fits LDS, so z and y are one kernel a side and the tensors between them are gone: 8 N^2 bytes are written or
 //    read per pair of tiles instead of three tensors of that size;
 //  * kernel transforms are those of a tile, shared by all tiles: 48 -> 48 images of 320^3, 5^3 kernels 0.1 GB instead of 4.75.
-// Against it stand the outputs that tiles share their inputs for: (N / V)^2 more of everything.  At 48 -> 48 of 320^3, 5^3: 15.5 ->
-// 12.9 ms for the layer; 40 -> 40 of 128^3, 3^3 0.845 -> 0.656; 37 -> 45 of 93 x 110 x 131, 3 x 4 x 5 0.676 -> 0.508; the results are
-// 0.7 to 1.0 times as far from 64 bits, since transforms are shorter.
+// Against it stand the outputs that tiles share their inputs for: (N / V)^2 more of everything.  With the products
+// in mac_quads.hip, whole layers: 48 -> 48 of 320^3, 5^3 15.7 -> 12.4 ms; 40 -> 40 of 128^3, 3^3 0.840 -> 0.616; 37 -> 45 of 93 x 110 x
+// 131, 3 x 4 x 5 0.669 -> 0.490; the results are 0.7 to 1.0 times as far from 64 bits, since transforms are shorter.
 //
 // Two tiles of a plane ride as the real and the imaginary part of one complex plane, all the way: the products with the kernel
 // transforms are linear, so nothing is taken apart in between, and both transforms are plain complex ones (a real transform of
 // one tile needs an untangling on either side, and every pass through LDS has to know about it).  The spectra are whole complex
 // planes [oz < N][oy < N] of half as many images, with as many products; pencils of the second half meet the conjugate kernel
-// transforms of the first (mac_xd.hip).  The two tiles belong to one image and one x, so that no value meets another input's, or
+// transforms of the first (mac_quads.hip).  The two tiles belong to one image and one x, so that no value meets another input's, or
 // another x's, that it did not meet in the transforms of the whole plane.
 //
 // One workgroup takes four neighbouring x of one pair, one after the other, and holds their spectra in registers, so that 32
