@@ -343,8 +343,8 @@ static znni_status direct_plan(int S, int f, int fo, const int n[3], const int k
     P->bytes = ((P->wp_floats + (size_t)P->RT * 64) * 4 + 255) / 256 * 256;
     // This file's kernel, in microseconds: what a call costs; for every 512 tiles (two a compute unit) a walk over the taps and over
     // the staged values; a megabyte written.  Fitted to 3601 random layers (standard deviation 15 %).  direct_first.hip's takes a
-    // layer where it is estimated to be the faster by 15 %: over 1586 layers of 9 to 64 taps that both run, the pick is 31 % faster
-    // than always this one on average and 2 % slower than the faster of them; 39 lose 2 to 15 %.
+    // layer of 13 to 64 taps where it is estimated to be the faster by 15 %: 962 of 1167 random layers (up to four images), 1.40 times
+    // as fast on average, 22 of them 2 to 16 % slower.
     const double rt4 = P->RTW * P->CTW / 4.0, steps = (double)f * P->T4 / 4;
     const double turns = (double)S * ((d.nox + TX - 1) / TX) * ((d.noy + TY - 1) / TY) * ((d.noz + TZ - 1) / TZ) * P->nmblk / 512;
     P->us = 9.3 + (turns > 1 ? turns : 1) * (rt4 * (0.27 + 0.122 * steps) + 0.083 * steps + 0.050 * f * tilevol / 256 + 0.35 * ((f + IC - 1) / IC)) +

@@ -49,7 +49,7 @@ def reach(path, recorder, layers):
             continue
         first = "k_direct_first" in names[0]
         count[first] += 1
-        assert not first or (len(names) == 1 and 8 < f * k[0] * k[1] * k[2] <= 64)
+        assert not first or (len(names) == 1 and 12 < f * k[0] * k[1] * k[2] <= 64)
     print(count)
     assert min(count) > 300
 
