@@ -38,13 +38,14 @@
  *   - Work is enqueued on `stream` (a hipStream_t passed as void*; NULL = the default stream) and the call
  *     returns without synchronising, except znni_conv3d_fft_profile, which synchronises the stream.
  *   - Results are deterministic: no floating-point atomics, fixed summation order.
- *   - Tensors are dense, row-major, last index fastest.  All values and sums are fp32; two kernels form products
+ *   - Tensors are dense, row-major, last index fastest.  All values and sums are fp32; some kernels form products
  *     of fp32 values on fp16 matrix instructions, each value split in two scaled halves (22 bits and a sign), with results
  *     as close to the 64-bit ones as fp32 products give for values of ordinary spread: a value down to 2^-17 of the
  *     largest that shares its scale keeps 22 bits, one below it has an absolute error of 2^-40 of that largest value.
  *     Direct primitive: a tile (a few hundred voxels of all input images) that holds image values more than 2^19 apart is
  *     multiplied in fp32, and so are kernels where all taps of an input image, or one tap of all of them, are that far
- *     below the largest of their output image; the bound stands for single kernel values.
+ *     below the largest of their output image; the bound stands for single kernel values.  Layers of 13 to 64 taps over at most four
+ *     images are held in three halves, all 24 bits of a value down to 2^-37 of the largest, and multiplied in fp32 beyond that.
  *     Transform route without x transform: fp32 as well where magnitudes lie that far apart along x, and input images
  *     whose kernels are far smaller than those of others have scales of their own.  Where, after those scales, the kernels
  *     of an output image are more than 2^14 apart or zero, fp32 too if the spectra of the input images at one frequency

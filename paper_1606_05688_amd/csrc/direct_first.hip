@@ -2,10 +2,12 @@
 //
 // The same contraction as direct.hip's over (input image, tap), with the shifted image values read from a tile in LDS, for layers
 // with so few products per output that the result's writing should be the bound.  There, the fp32 matrix instructions take as long as
-// the stores (one image to 48, 128^3, 3^3: 67 us at their rate, next to 62 us of stores), so values are split into two halves: one or two
-// steps of 32 taps on v_mfma_f32_16x16x32_f16 and all four partial products (error against 64 bits 5.8e-8 of the result; the fp32
-// kernel's 8.2e-8).  A tile has one power of two, an output image's kernels another; where magnitudes lie too
-// far apart for that, or are not finite, the tile is multiplied in fp32.
+// the stores (one image to 48, 128^3, 3^3: 67 us at their rate, next to 62 us of stores), so every value is three halves, which hold
+// all 24 bits of it: one or two steps of 32 taps on v_mfma_f32_16x16x32_f16, the six partial products that reach the result
+// (error against 64 bits 0.51 of the fp32 kernel's on average over 188 layers, 0.69 at most).  A tile has one power of two, an output
+// image's kernels another: exact for values down to 2^-37 of the largest.  Where magnitudes lie further apart than that, or are not
+// finite, the tile is multiplied in fp32.  Two halves instead of three are 6 % faster here (10 % over those layers), but
+// drop a bit of every fourth value, and more below 2^-17 of the largest.
 //
 // A workgroup keeps its kernels' operands in registers and walks over tiles of 256 outputs of an image (128, 64 or 32 columns, the
 // others rows): values of the next tile are requested before this one is multiplied.  What decided, on that layer (124 us before):
@@ -13,8 +15,8 @@
 //   went to as many places as there are workgroups times images; one tile a workgroup: 253 us, the kernels' operands made each time.
 // * stores of 256-byte runs (through LDS), 16 bytes a lane, without a branch: the wait for the next tile's values then does not
 //   wait for them.  64-byte runs straight from the accumulators: 121 us.  Nontemporal stores: 214 us (rows end inside lines).
-// * two workgroups a compute unit; three: 102 us.
-// Now 95 us, 4.1 TB/s of the 6.2 that a copy reaches; what is left is waiting at the two barriers of a turn.
+// Now 101 us, 3.9 TB/s of the 6.2 that a copy reaches; what is left is waiting at the two barriers of a turn, and LDS: eight bytes a
+// staged value.  (The figures above are from two halves a value, of 95 us.)
 #include <math.h>
 
 #include <algorithm>
@@ -27,7 +29,10 @@ namespace znni {
 typedef float floatx4_f __attribute__((ext_vector_type(4)));
 
 constexpr int FIRST_NQ = 13;                      // staged values of a thread, at most
+// Workgroups a compute unit: one row tile three (two 4 to 14 % slower over 319 layers), two to five row tiles two (three 3 to 17 % slower).
+constexpr int first_resident(int RTW) { return RTW == 1 ? 3 : 2; }
 constexpr int FIRST_SLOTS = 512;                  // workgroups on the chip at once: two a compute unit
+constexpr int FIRST_SPAN = 37;                    // three halves are exact for values down to 2^-37 of the largest
 constexpr int FIRST_P = 68;                       // pitch of a wave's rows on their way out: no bank conflicts either way
 constexpr unsigned FIRST_NONE = 0xfffffff0u;     // an offset that the range check of loads and stores drops
 
@@ -46,11 +51,11 @@ struct FirstArgs {
 // NQ: staged values per thread; ST: steps of 32 taps; RTW: row tiles of 16 output images.  Bound by the result's writing (where many
 // images are written) or by a turn's latency.
 template <int RTW, int ST, int NQ>
-__global__ __launch_bounds__(256, 2) void k_direct_first(FirstArgs a)
+__global__ __launch_bounds__(256, first_resident(RTW)) void k_direct_first(FirstArgs a)
 {
     extern __shared__ unsigned lds_u[];
-    unsigned* const th = lds_u;                                   // staged values: two halves each, or fp32
-    int* const delta = reinterpret_cast<int*>(lds_u + ((a.total + 3) & ~3));   // [64] offset of a tap inside the tile
+    uint2* const th = reinterpret_cast<uint2*>(lds_u);            // staged values: three halves each, or fp32
+    int* const delta = reinterpret_cast<int*>(lds_u + 2 * ((a.total + 1) & ~1));   // [64] offset of a tap inside the tile
     unsigned* const red = reinterpret_cast<unsigned*>(delta + 64);             // [turn][largest, smallest]
     float* const out = reinterpret_cast<float*>(red + 8);                      // [wave][16][FIRST_P]
     const Dims& d = a.d;
@@ -90,7 +95,7 @@ __global__ __launch_bounds__(256, 2) void k_direct_first(FirstArgs a)
     request(tile0);
 
     // ---- kernels: operands of all steps in registers, a power of two per output image
-    half8 wh[ST][RTW], wl[ST][RTW];
+    half8 wh[ST][RTW], wm[ST][RTW], wl[ST][RTW];
     int we[RTW];
     float bj[RTW];
     bool wide = false;
@@ -134,17 +139,20 @@ __global__ __launch_bounds__(256, 2) void k_direct_first(FirstArgs a)
                 m = max(m, (unsigned)__shfl_xor((int)m, o));
                 mn = min(mn, (unsigned)__shfl_xor((int)mn, o));
             }
-            const bool bad = m >= 0x7f800000u || split_too_wide(m, mn);
+            const bool bad = m >= 0x7f800000u || split_too_wide(m, mn, FIRST_SPAN);
             wide |= __ballot(bad) != 0;
             we[r] = split_exp(bad ? 0.f : __uint_as_float(m));
+        }
+#pragma unroll
+        for (int r = 0; r < RTW; ++r) {
             const float sc = pow2f(we[r]);
 #pragma unroll
             for (int st = 0; st < ST; ++st)
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
-                    _Float16 h, l;
-                    split2(v[r][st][u], sc, h, l);
-                    wh[st][r][u] = h; wl[st][r][u] = l;
+                    _Float16 h, c, l;
+                    split3(v[r][st][u], sc, h, c, l);
+                    wh[st][r][u] = h; wm[st][r][u] = c; wl[st][r][u] = l;
                 }
         }
     }
@@ -160,8 +168,8 @@ __global__ __launch_bounds__(256, 2) void k_direct_first(FirstArgs a)
     // a wave: 64 columns of one output row, or 32 of two
     const bool two = a.TZ == 32;
     const int row = two ? 2 * wave : a.TZ == 64 ? wave : wave >> 1, zb = a.TZ == 128 ? (wave & 1) * 64 : 0;
-    const unsigned* const base = th + row * a.TZI + zb + l16;
-    const unsigned* const base2 = base + (two ? a.TZI : 32);
+    const uint2* const base = th + row * a.TZI + zb + l16;
+    int next = two ? a.TZI : 32;                                  // ... to the other two column tiles
     const int half = two && l16 >= 8, zl = 4 * l16 - 32 * half;             // row and first column of what this lane stores
     for (int tile = tile0, turn = 0; tile < a.tiles; tile += nb, turn = turn == 2 ? 0 : turn + 1) {
         unsigned m = 0, mn = ~0u;
@@ -177,17 +185,18 @@ __global__ __launch_bounds__(256, 2) void k_direct_first(FirstArgs a)
         }
         __syncthreads();                                          // (also: all waves are through with the tile before)
         const unsigned most = __builtin_amdgcn_readfirstlane(red[2 * turn]), least = __builtin_amdgcn_readfirstlane(red[2 * turn + 1]);
-        const bool exact = wide || most >= 0x7f800000u || split_too_wide(most, least);
+        const bool exact = wide || most >= 0x7f800000u || split_too_wide(most, least, FIRST_SPAN);
         const int sx = exact ? 0 : split_exp(__uint_as_float(most));
         const float sc = pow2f(sx);
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
             if (256 * q >= a.total) continue;
-            unsigned v = __float_as_uint(raw[q]);
+            uint2 v = make_uint2(__float_as_uint(raw[q]), 0u);
             if (!exact) {
-                _Float16 h, l;
-                split2(raw[q], sc, h, l);
-                v = (unsigned)__builtin_bit_cast(unsigned short, h) | (unsigned)__builtin_bit_cast(unsigned short, l) << 16;
+                _Float16 h, c, l;
+                split3(raw[q], sc, h, c, l);
+                v.x = (unsigned)__builtin_bit_cast(unsigned short, h) | (unsigned)__builtin_bit_cast(unsigned short, c) << 16;
+                v.y = __builtin_bit_cast(unsigned short, l);
             }
             if (t + 256 * q < a.total) th[t + 256 * q] = v;
         }
@@ -203,29 +212,43 @@ __global__ __launch_bounds__(256, 2) void k_direct_first(FirstArgs a)
         for (int r = 0; r < RTW; ++r)
 #pragma unroll
             for (int c = 0; c < 4; ++c) acc[r][c] = floatx4_f{0.f, 0.f, 0.f, 0.f};
+        asm volatile("" : "+v"(next));                              // (their addresses are made again, not kept)
+        const uint2* const base2 = base + next;
         if (!exact) {
 #pragma unroll
             for (int c = 0; c < 4; ++c)
 #pragma unroll
                 for (int st = 0; st < ST; ++st) {
-                    unsigned p[8];
+                    uint2 p[8];
 #pragma unroll
                     for (int u = 0; u < 8; ++u) p[u] = (c < 2 ? base : base2)[16 * (c & 1) + dl[st][u]];
-                    uintx4 hh, ll;
+                    uintx4 hh, mm, ll;
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
-                        hh[u] = __builtin_amdgcn_perm(p[2 * u + 1], p[2 * u], 0x05040100u);
-                        ll[u] = __builtin_amdgcn_perm(p[2 * u + 1], p[2 * u], 0x07060302u);
+                        hh[u] = __builtin_amdgcn_perm(p[2 * u + 1].x, p[2 * u].x, 0x05040100u);
+                        mm[u] = __builtin_amdgcn_perm(p[2 * u + 1].x, p[2 * u].x, 0x07060302u);
+                        ll[u] = __builtin_amdgcn_perm(p[2 * u + 1].y, p[2 * u].y, 0x05040100u);
                     }
-                    const half8 xh = __builtin_bit_cast(half8, hh), xl = __builtin_bit_cast(half8, ll);
+                    const half8 xh = __builtin_bit_cast(half8, hh), xm = __builtin_bit_cast(half8, mm), xl = __builtin_bit_cast(half8, ll);
+                    // the smallest products first, each group under its power of two
+                    __builtin_amdgcn_s_setprio(1);                // (also keeps the operands of several steps out of the registers)
+                    floatx4_f low[RTW];
+#define ZNNI_FIRST(D, X, W, C)                  \
+    _Pragma("unroll") for (int r = 0; r < RTW; ++r) D = __builtin_amdgcn_mfma_f32_16x16x32_f16(X, W[st][r], C, 0, 0, 0)
+                    ZNNI_FIRST(low[r], xl, wh, (floatx4_f{0.f, 0.f, 0.f, 0.f}));
+                    ZNNI_FIRST(low[r], xm, wm, low[r]);
+                    ZNNI_FIRST(low[r], xh, wl, low[r]);
 #pragma unroll
-                    for (int r = 0; r < RTW; ++r) acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xl, wl[st][r], acc[r][c], 0, 0, 0);
+                    for (int r = 0; r < RTW; ++r) low[r] *= SPLIT3_STEP;
+                    ZNNI_FIRST(low[r], xm, wh, low[r]);
+                    ZNNI_FIRST(low[r], xh, wm, low[r]);
+                    ZNNI_FIRST(acc[r][c], xh, wh, acc[r][c]);
+#undef ZNNI_FIRST
+                    __builtin_amdgcn_s_setprio(0);
 #pragma unroll
-                    for (int r = 0; r < RTW; ++r) acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xl, wh[st][r], acc[r][c], 0, 0, 0);
+                    for (int r = 0; r < RTW; ++r)
 #pragma unroll
-                    for (int r = 0; r < RTW; ++r) acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xh, wl[st][r], acc[r][c], 0, 0, 0);
-#pragma unroll
-                    for (int r = 0; r < RTW; ++r) acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xh, wh[st][r], acc[r][c], 0, 0, 0);
+                        for (int e = 0; e < 4; ++e) acc[r][c][e] = fmaf(low[r][e], SPLIT3_STEP, acc[r][c][e]);
                 }
         } else {
 #pragma unroll 1
@@ -233,7 +256,7 @@ __global__ __launch_bounds__(256, 2) void k_direct_first(FirstArgs a)
                 const int k = k4 + kk, o = delta[min(k, 63)];
                 float x[4];
 #pragma unroll
-                for (int c = 0; c < 4; ++c) x[c] = k < a.K ? __uint_as_float((c < 2 ? base : base2)[16 * (c & 1) + o]) : 0.f;
+                for (int c = 0; c < 4; ++c) x[c] = k < a.K ? __uint_as_float((c < 2 ? base : base2)[16 * (c & 1) + o].x) : 0.f;
 #pragma unroll
                 for (int r = 0; r < RTW; ++r) {
                     const float v = a.w[min((rt0 + r) * 16 + l16, a.fo - 1) * a.K + min(k, a.K - 1)], wv = k < a.K ? v : 0.f;
@@ -294,8 +317,7 @@ static const FirstCost kFirstCost[3] = {
 bool first_plan(int S, int f, int fo, const Dims& d, FirstPlan* P)
 {
     const long long K = (long long)f * d.kx * d.ky * d.kz, vox = (long long)d.nx * d.ny * d.nz, ovox = (long long)d.nox * d.noy * d.noz;
-    // (fewer taps: no closer to 64 bits than fp32 sums, 0.95 to 0.99 of their error on average over 170 layers of 9 to 12 and up to 1.17 of
-    // it, 0.72 and never more than 0.91 over 962 of 13 to 64; and a quarter of the layers of up to 8 are slower)
+    // (fewer taps stay with the fp32 kernel: a quarter of the layers of up to 8 are slower here)
     if (K <= 12 || K > 64 || f * vox >= (1ll << 30) - 64 || ovox >= (1ll << 26) - 64 || fo > 65535) return false;
     const int rt = (fo + 15) / 16, most = K <= 32 ? 5 : 3;
     P->nmblk = (rt + most - 1) / most; P->RTW = (rt + P->nmblk - 1) / P->nmblk;
@@ -317,8 +339,7 @@ bool first_plan(int S, int f, int fo, const Dims& d, FirstPlan* P)
 template <int RTW, int ST, int NQ>
 static znni_status launch_first(FirstArgs a, int nmblk, hipStream_t st)
 {
-    const size_t lds = 4 * ((size_t)((a.total + 3) & ~3) + 64 + 8 + 4 * 16 * FIRST_P);
-    // (one row tile: three a compute unit, 4 to 14 % faster over 319 layers; two to five row tiles: 3 to 17 % slower)
+    const size_t lds = 4 * (2 * (size_t)((a.total + 1) & ~1) + 64 + 8 + 4 * 16 * FIRST_P);
     const int blocks = std::min(a.tiles, RTW == 1 ? FIRST_SLOTS * 3 / 2 : FIRST_SLOTS);
     k_direct_first<RTW, ST, NQ><<<dim3((unsigned)blocks, (unsigned)nmblk), dim3(256), lds, st>>>(a);
     return hipGetLastError() == hipSuccess ? ZNNI_OK : ZNNI_ERR_HIP;

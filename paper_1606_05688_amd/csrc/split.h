@@ -37,6 +37,17 @@ __device__ __forceinline__ void split2(float v, float s, _Float16& hi, _Float16&
     lo = (_Float16)fmaf(v, s, -(float)hi);
 }
 
+// A value as three halves, the second and third 2^11 and 2^22 times what is left to them: exact where v * s lies between 2^-23 and
+// 2^15 (a half's last place is 2^-24 at least, so the third's 2^-46).
+constexpr float SPLIT3_STEP = 1.f / 2048;
+__device__ __forceinline__ void split3(float v, float s, _Float16& hi, _Float16& mid, _Float16& lo)
+{
+    hi = (_Float16)(v * s);
+    const float r = fmaf(v, s, -(float)hi) * 2048.f;
+    mid = (_Float16)r;
+    lo = (_Float16)((r - (float)mid) * 2048.f);
+}
+
 // (x, -y) as two pairs of halves, the same values as split2 gives: every half leaves one mixed-precision instruction where
 // it belongs (a product, its conversion, the difference and the packing of pairs took three a value).
 __device__ __forceinline__ void split_conj(float x, float y, float s, unsigned& hi, unsigned& lo)
@@ -80,9 +91,9 @@ __device__ __forceinline__ unsigned wave_min(unsigned v)
 // A magnitude as an integer that orders like it, except that zero is the largest: twice the bits without the sign, less one.
 __device__ __forceinline__ unsigned small_code(float v) { return (__float_as_uint(v) << 1) - 1u; }
 // Whether the smallest such code of a group is out of the range that halves hold next to its largest magnitude (its bits).
-__device__ __forceinline__ bool split_too_wide(unsigned largest, unsigned code)
+__device__ __forceinline__ bool split_too_wide(unsigned largest, unsigned code, int span = SPLIT_SPAN)
 {
-    const int e = (int)(largest >> 23) - SPLIT_SPAN;
+    const int e = (int)(largest >> 23) - span;
     return e > 0 && code < ((unsigned)e << 24) - 1u;
 }
 

@@ -45,7 +45,8 @@ def test_matches_oracle(oracle, case):
         assert np.all(np.abs(got - exp) <= oracle.tolerance(inp, w)[None, :, None, None, None])
     # magnitudes that halves of one scale do not hold (images or kernels): fp32, at most 64 products rounded once each
     far = np.exp2(np.random.default_rng(5).integers(-40, 1, n)).astype(np.float32)
-    for x, v in ((inp * far, w), (inp, w * np.exp2(-30.0 * (np.arange(k[2]) % 2)).astype(np.float32))):
+    odd = np.arange(k[2]) % 2
+    for x, v in ((inp * far, w), (inp, w * np.exp2(-30.0 * odd).astype(np.float32)), (inp, w * np.exp2(-45.0 * odd).astype(np.float32))):
         got, exp, mag = _run(x, v).cpu().numpy().astype(np.float64), oracle.conv3d(x, v, None, relu=False), oracle.conv3d(np.abs(x), np.abs(v), None, relu=False)
         assert np.all(np.abs(got - exp) <= 64 * 2.0 ** -24 * mag)
 
@@ -71,3 +72,29 @@ def test_values_that_are_not_finite(bad):
     hit[win] = True
     assert torch.allclose(got[~hit], clean[~hit], rtol=0, atol=1e-6 * float(clean.abs().max()))
     assert (torch.isnan(got[win]) if np.isnan(bad) else torch.isinf(got[win])).all()
+
+
+@pytest.mark.parametrize("low", [16, 19, 36, 38])
+@pytest.mark.parametrize("where", ["images", "kernels"])
+def test_values_far_below_others_of_their_scale(oracle, where, low):
+    """Results made of values that share a scale with far larger ones, which they never meet, are as good as any: a rounding of
+    2^-24 for each of K sums whose size grows with the square root of their terms, sqrt(K / 2) 2^-24 together."""
+    S, f, fo, n, k = {"images": CASES[5], "kernels": CASES[4]}[where]
+    r = np.random.default_rng(low)
+    inp, w = (np.where(r.random(s) < 0.5, -1, 1) * r.uniform(1, 2, s) for s in ((S, f) + n, (fo, f) + k))
+    K = f * int(np.prod(k))
+    keep = np.ones([a - b + 1 for a, b in zip(n, k)], dtype=bool)
+    if where == "images":                                    # one column of every 32
+        inp *= 2.0 ** -low
+        inp[..., 5::32] = 1
+        for z in range(k[2]):
+            keep[..., 5 - z::32] = False
+    else:                                                    # the second image has the large kernels, and no values
+        w[:, 0] *= 2.0 ** -low
+        w[:, 1] = 1
+        inp[:, 1] = 0
+        K //= 2
+    inp, w = inp.astype(np.float32), w.astype(np.float32)
+    exp = oracle.conv3d(inp, w, None, relu=False)[:, :, keep]
+    got = _run(inp, w).cpu().numpy().astype(np.float64)[:, :, keep]
+    assert np.linalg.norm(got - exp) <= np.sqrt(K / 2) * 2.0 ** -24 * np.linalg.norm(exp)
