@@ -6,7 +6,8 @@
 // all 24 bits of it: one or two steps of 32 taps on v_mfma_f32_16x16x32_f16, the six partial products that reach the result
 // (error against 64 bits 0.51 of the fp32 kernel's on average over 188 layers, 0.69 at most).  A tile has one power of two, an output
 // image's kernels another: exact for values down to 2^-37 of the largest.  Where magnitudes lie further apart than that, or are not
-// finite, the tile is multiplied in fp32.  Two halves instead of three are 6 % faster here (10 % over those layers), but
+// finite, the tile is multiplied in fp32, from the same registers (that layer 119 us, 124 by the fp32 kernel; over those layers 1.05
+// times as fast as by that kernel, 0.69 at worst).  Two halves instead of three are 6 % faster here (10 % over those layers), but
 // drop a bit of every fourth value, and more below 2^-17 of the largest.
 //
 // A workgroup keeps its kernels' operands in registers and walks over tiles of 256 outputs of an image (128, 64 or 32 columns, the
@@ -108,7 +109,7 @@ __global__ __launch_bounds__(256, first_resident(RTW)) void k_direct_first(First
 #pragma unroll
             for (int st = 0; st < ST; ++st)
 #pragma unroll
-                for (int u = 0; u < 8; ++u) v[r][st][u] = a.w[j * a.K + min(st * 32 + kk * 8 + u, a.K - 1)];
+                for (int u = 0; u < 8; ++u) v[r][st][u] = a.w[j * a.K + min(st * 32 + u * 4 + kk, a.K - 1)];
         }
         // (all requested before the first is looked at: a load behind a branch each took a round trip to memory each)
 #pragma unroll
@@ -129,7 +130,7 @@ __global__ __launch_bounds__(256, first_resident(RTW)) void k_direct_first(First
             for (int st = 0; st < ST; ++st)
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
-                    v[r][st][u] = st * 32 + kk * 8 + u < a.K ? v[r][st][u] : 0.f;
+                    v[r][st][u] = st * 32 + u * 4 + kk < a.K ? v[r][st][u] : 0.f;
                     const float ax = fabsf(v[r][st][u]);
                     m = max(m, __float_as_uint(ax));              // (NaNs are the largest)
                     mn = min(mn, small_code(ax));
@@ -147,13 +148,21 @@ __global__ __launch_bounds__(256, first_resident(RTW)) void k_direct_first(First
         for (int r = 0; r < RTW; ++r) {
             const float sc = pow2f(we[r]);
 #pragma unroll
-            for (int st = 0; st < ST; ++st)
+            for (int st = 0; st < ST; ++st) {
+                if (wide) {                                       // fp32 as it is, in the place of the first two halves
+                    uintx4 a0, a1;
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    _Float16 h, c, l;
-                    split3(v[r][st][u], sc, h, c, l);
-                    wh[st][r][u] = h; wm[st][r][u] = c; wl[st][r][u] = l;
+                    for (int u = 0; u < 4; ++u) { a0[u] = __float_as_uint(v[r][st][u]); a1[u] = __float_as_uint(v[r][st][4 + u]); }
+                    wh[st][r] = __builtin_bit_cast(half8, a0); wm[st][r] = __builtin_bit_cast(half8, a1);
+                } else {
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        _Float16 h, c, l;
+                        split3(v[r][st][u], sc, h, c, l);
+                        wh[st][r][u] = h; wm[st][r][u] = c; wl[st][r][u] = l;
+                    }
                 }
+            }
         }
     }
     __syncthreads();
@@ -161,7 +170,7 @@ __global__ __launch_bounds__(256, first_resident(RTW)) void k_direct_first(First
 #pragma unroll
     for (int st = 0; st < ST; ++st)
 #pragma unroll
-        for (int u = 0; u < 8; ++u) dl[st][u] = delta[st * 32 + kk * 8 + u];
+        for (int u = 0; u < 8; ++u) dl[st][u] = delta[st * 32 + u * 4 + kk];
 
     float* const mine = out + wave * 16 * FIRST_P;
     const unsigned ovox = (unsigned)d.nox * d.noy * d.noz;
@@ -251,19 +260,37 @@ __global__ __launch_bounds__(256, first_resident(RTW)) void k_direct_first(First
                         for (int e = 0; e < 4; ++e) acc[r][c][e] = fmaf(low[r][e], SPLIT3_STEP, acc[r][c][e]);
                 }
         } else {
-#pragma unroll 1
-            for (int k4 = 0; k4 < a.K; k4 += 4) {
-                const int k = k4 + kk, o = delta[min(k, 63)];
-                float x[4];
+            // fp32, with the operands where they are: a matrix step's four taps are the u-th of each lane group.  (Hidden from the compiler,
+            // which would otherwise keep all kernel values in registers over the loop.)
+            auto hide = [](half8& v) {
+                uintx4 b = __builtin_bit_cast(uintx4, v);
+                asm volatile("" : "+v"(b));
+                v = __builtin_bit_cast(half8, b);
+            };
 #pragma unroll
-                for (int c = 0; c < 4; ++c) x[c] = k < a.K ? __uint_as_float((c < 2 ? base : base2)[16 * (c & 1) + o].x) : 0.f;
+            for (int st = 0; st < ST; ++st)
 #pragma unroll
-                for (int r = 0; r < RTW; ++r) {
-                    const float v = a.w[min((rt0 + r) * 16 + l16, a.fo - 1) * a.K + min(k, a.K - 1)], wv = k < a.K ? v : 0.f;
+                for (int r = 0; r < RTW; ++r) { hide(wh[st][r]); hide(wm[st][r]); hide(wl[st][r]); }
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[c], wv, acc[r][c], 0, 0, 0);
+            for (int st = 0; st < ST; ++st)
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    if (st * 32 + u * 4 >= a.K) continue;
+                    float x[4];
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const float xv = __uint_as_float((c < 2 ? base : base2)[16 * (c & 1) + dl[st][u]].x);
+                        x[c] = st * 32 + u * 4 + kk < a.K ? xv : 0.f;
+                    }
+#pragma unroll
+                    for (int r = 0; r < RTW; ++r) {
+                        const float split = fmaf(fmaf((float)wl[st][r][u], SPLIT3_STEP, (float)wm[st][r][u]), SPLIT3_STEP, (float)wh[st][r][u]) * pow2f(-we[r]);
+                        const float plain = __uint_as_float(__builtin_bit_cast(uintx4, u < 4 ? wh[st][r] : wm[st][r])[u & 3]);
+                        const float wv = wide ? plain : split;
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[c], wv, acc[r][c], 0, 0, 0);
+                    }
                 }
-            }
         }
         // ---- results: a lane has four neighbouring columns of one output image; through LDS, so that a store takes whole
         // 256-byte runs of four images
