@@ -342,14 +342,18 @@ static znni_status direct_plan(int S, int f, int fo, const int n[3], const int k
     // + one step of padding: the kernel requests its kernel values one step ahead
     P->bytes = ((P->wp_floats + (size_t)P->RT * 64) * 4 + 255) / 256 * 256;
     // This file's kernel, in microseconds: what a call costs; for every 512 tiles (two a compute unit) a walk over the taps and over
-    // the staged values; a megabyte written.  Fitted to 3601 random layers (standard deviation 15 %).  direct_first.hip's takes a
-    // layer of 13 to 64 taps where it is estimated to be the faster by 15 %: 962 of 1167 random layers (up to four images), 1.40 times
-    // as fast on average, 22 of them 2 to 16 % slower.
+    // the staged values; a megabyte written.  Fitted to 3601 random layers (standard deviation 15 %).
     const double rt4 = P->RTW * P->CTW / 4.0, steps = (double)f * P->T4 / 4;
     const double turns = (double)S * ((d.nox + TX - 1) / TX) * ((d.noy + TY - 1) / TY) * ((d.noz + TZ - 1) / TZ) * P->nmblk / 512;
     P->us = 9.3 + (turns > 1 ? turns : 1) * (rt4 * (0.27 + 0.122 * steps) + 0.083 * steps + 0.050 * f * tilevol / 256 + 0.35 * ((f + IC - 1) / IC)) +
             0.164e-6 * 4 * S * fo * ((double)d.nox * d.noy * d.noz);
-    P->first = first_plan(S, f, fo, d, &P->fp) && P->fp.us < 0.85 * P->us;
+    // direct_first.hip's takes a layer of 13 to 64 taps where it is estimated to be the faster by a tenth: 1118 of 1500 random
+    // layers (up to four images), 1.34 times as fast on average, 23 of them by more than 5 % slower, the worst 18 %.  (Long tiles: an
+    // estimate fitted to these layers, of 8 % standard deviation; the one above is 12 % high for few row tiles and images.)
+    const double here = P->longz ? 7.2 + (turns > 1 ? turns : 1) * (0.06 + rt4 * (0.62 + 0.127 * steps) + 0.105 * f * tilevol / 256) +
+                                       0.082e-6 * 4 * S * fo * ((double)d.nox * d.noy * d.noz)
+                                 : P->us;
+    P->first = first_plan(S, f, fo, d, &P->fp) && P->fp.us < 0.9 * here;
     P->split = split_plan(S, f, fo, d, &P->sp);
     if (P->split && P->sp.bytes > P->bytes) P->bytes = (P->sp.bytes + 255) / 256 * 256;
     return ZNNI_OK;

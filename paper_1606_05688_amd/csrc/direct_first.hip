@@ -32,7 +32,7 @@ typedef float floatx4_f __attribute__((ext_vector_type(4)));
 constexpr int FIRST_NQ = 13;                      // staged values of a thread, at most
 // Workgroups a compute unit: one row tile three (two 4 to 14 % slower over 319 layers), two to five row tiles two (three 3 to 17 % slower).
 constexpr int first_resident(int RTW) { return RTW == 1 ? 3 : 2; }
-constexpr int FIRST_SLOTS = 512;                  // workgroups on the chip at once: two a compute unit
+constexpr int first_slots(int RTW) { return 256 * first_resident(RTW); }
 constexpr int FIRST_SPAN = 37;                    // three halves are exact for values down to 2^-37 of the largest
 constexpr int FIRST_P = 68;                       // pitch of a wave's rows on their way out: no bank conflicts either way
 constexpr unsigned FIRST_NONE = 0xfffffff0u;     // an offset that the range check of loads and stores drops
@@ -331,14 +331,14 @@ __global__ __launch_bounds__(256, first_resident(RTW)) void k_direct_first(First
     }
 }
 
-// A tile length's cost in microseconds, fitted to 1900 random layers of 6 to 64 taps (tiles of each length on all of them;
-// standard deviation 12 to 17 %): what a call costs, a workgroup's turn, ... per row tile, ... and step of 32 taps, ... per
-// 256 staged values, a megabyte written, ... where more than three row tiles leave one workgroup.
-struct FirstCost { int TZ; double call, turn, rows, steps, staged, mb, mb_rows; };
+// A tile length's cost in microseconds, fitted to 1500 random layers of 13 to 64 taps (tiles of each length on all of them that they
+// fit; standard deviation 13 to 15 %): what a call costs; a workgroup's turns, per row tile, ... and step of 32 taps; a compute unit's
+// tiles, ... and 256 staged values of them; a megabyte written.
+struct FirstCost { int TZ; double call, rows, steps, tile, staged, mb; };
 static const FirstCost kFirstCost[3] = {
-    {128, 6.4, 0.57, 0.61, 0.42, 0.13, 0.031, 0.005},
-    {64, 6.1, 0.64, 0.39, 0.52, 0.12, 0.084, 0.022},
-    {32, 5.7, 0.57, 0.32, 0.58, 0.12, 0.111, 0.031},
+    {128, 6.5, 0.58, 0.74, 0.28, 0.074, 0.0},
+    {64, 6.3, 0.60, 0.79, 0.35, 0.070, 0.019},
+    {32, 6.1, 0.52, 0.86, 0.36, 0.067, 0.042},
 };
 
 bool first_plan(int S, int f, int fo, const Dims& d, FirstPlan* P)
@@ -354,9 +354,9 @@ bool first_plan(int S, int f, int fo, const Dims& d, FirstPlan* P)
         const long long total = f * (long long)d.kx * (TY + d.ky - 1) * (c.TZ + d.kz - 1);
         const long long tiles = (long long)S * d.nox * ((d.noy + TY - 1) / TY) * ((d.noz + c.TZ - 1) / c.TZ);
         if (total > 256 * FIRST_NQ || tiles >= 1 << 30 || (c.TZ == 32 && d.noz >= 4096)) continue;
-        const double turns = ceil((double)tiles * P->nmblk / FIRST_SLOTS), mb = 4e-6 * S * fo * ovox;
-        const double us = c.call + turns * (c.turn + P->RTW * (c.rows + c.steps * (K > 32 ? 2 : 1)) + c.staged * ((total + 255) / 256)) +
-                          mb * (c.mb + (P->RTW > 3 ? c.mb_rows : 0.0));
+        const double turns = ceil((double)tiles * P->nmblk / first_slots(P->RTW)), per = (double)tiles * P->nmblk / 256;
+        const double us = c.call + turns * P->RTW * (c.rows + c.steps * (K > 32 ? 2 : 1)) + per * (c.tile + c.staged * ((total + 255) / 256)) +
+                          4e-6 * S * fo * ovox * c.mb;
         if (P->us >= 0 && us >= P->us) continue;
         P->us = us; P->TZ = c.TZ; P->TY = TY; P->total = (int)total; P->tiles = (int)tiles;
     }
@@ -367,7 +367,7 @@ template <int RTW, int ST, int NQ>
 static znni_status launch_first(FirstArgs a, int nmblk, hipStream_t st)
 {
     const size_t lds = 4 * (2 * (size_t)((a.total + 1) & ~1) + 64 + 8 + 4 * 16 * FIRST_P);
-    const int blocks = std::min(a.tiles, RTW == 1 ? FIRST_SLOTS * 3 / 2 : FIRST_SLOTS);
+    const int blocks = std::min(a.tiles, first_slots(RTW));
     k_direct_first<RTW, ST, NQ><<<dim3((unsigned)blocks, (unsigned)nmblk), dim3(256), lds, st>>>(a);
     return hipGetLastError() == hipSuccess ? ZNNI_OK : ZNNI_ERR_HIP;
 }

@@ -66,5 +66,17 @@ def test_gpu_layers_reach_every_kernel(tmp_path):
     assert r.returncode == 0, r.stdout[-1000:] + r.stderr[-3000:]
 
 
+def test_estimate_counts_the_turns_that_are_launched():
+    """One row tile: three workgroups on each of 256 compute units, so that the step to a second turn lies behind 768 tiles."""
+    from paper_1606_05688_amd import binding as B
+
+    def us(tiles):                                           # one tile of 8 x 32 outputs for every x
+        prim, est = ctypes.c_int(), (ctypes.c_float * 2)()
+        assert B.lib().znni_conv3d_choose_v(1, 1, 4, _i3((tiles + 2, 10, 34)), _i3((3, 3, 3)), ctypes.byref(prim), est) == 0
+        return est[1]
+
+    assert us(760) - us(500) < us(780) - us(760)
+
+
 if __name__ == "__main__":
     reach(sys.argv[1], sys.argv[2], sys.argv[3])
