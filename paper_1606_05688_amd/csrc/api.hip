@@ -239,9 +239,7 @@ static void place_plan(LayerPlan* L, void* base, const size_t sz[5], bool own_yt
     L->bytes = off;
 }
 
-// The plan that goes through whole planes.
-static znni_status make_whole_plan(int S, int f, int fo, const int n[3], const int k[3], unsigned flags, void* base,
-                                   LayerPlan* L)
+znni_status make_whole_plan(int S, int f, int fo, const int n[3], const int k[3], unsigned flags, void* base, LayerPlan* L)
 {
     znni_status rc = shape_plan(S, f, fo, n, k, flags, L);
     if (rc) return rc;

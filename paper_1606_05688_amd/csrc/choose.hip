@@ -11,8 +11,9 @@
 //   direct route:     the estimate of the kernel that would run (direct.hip, direct_split.hip, direct_first.hip): its walks over
 //                     tiles, taps and staged values, and the tensors it moves.
 //
-// The model only has to rank the two; it is not used for anything else.  Over 6136 random layers that both take, the pick is 0.6 %
-// slower than the faster one on average, 216 by more than 5 %.
+// The model only has to rank the two; it is not used for anything else.  Over 6136 random layers that both take, the pick by these
+// estimates is 0.6 % slower than the faster one on average, 216 by more than 5 %.  Where direct sums are the closer ones to 64 bits, the
+// transform has to be ahead by bare rates as well (direct_stands).
 #include "direct_split.h"
 #include "mac_common.h"
 
@@ -64,6 +65,36 @@ static double fft_seconds(int S, int f, int fo, const int n[3], const int k[3])
     return L.tiles ? route_seconds(L) : 1.25 * route_seconds(L);
 }
 
+// Whether a layer stays with direct sums though transforms are estimated to be the faster.  Direct sums of K products are 1.8e-8 sqrt(K)
+// of the result off its 64-bit value (1.4e-8 on split halves), transforms 1.9e-7 to 2.2e-7 whatever K (108 layers that the two
+// estimates disagree on): sums of up to 136 products (225) come out closer directly, by up to 1.8 times at 40.  So those leave the direct
+// kernels only where whole planes would be faster by rates alone: 80 % of them are then within a third of the transform's time.
+static bool direct_stands(int S, int f, int fo, const int n[3], const int k[3])
+{
+    constexpr double kDirectFlops = 80e12, kDirectFlopsFew = 60e12;      // windows of 27 taps and more, of fewer
+    constexpr double kDirectWrite = 3.6e12, kSplitBytes = 2.6e12, kSplitFlops = 75e12;
+    LayerPlan L;
+    SplitPlan P;
+    const int taps = k[0] * k[1] * k[2];
+    if ((long long)f * taps > 225 || make_whole_plan(S, f, fo, n, k, 0, nullptr, &L)) return false;
+    const bool split = split_plan(S, f, fo, L.d, &P);
+    if (!split && f * taps > 136) return false;
+    const double ovox = (double)L.d.nox * L.d.noy * L.d.noz, wr = 4.0 * S * fo * ovox;
+    double t;
+    if (split) {
+        const double by = (wr + 4.0 * S * f * n[0] * n[1] * n[2]) / kSplitBytes;
+        const double fl = 2.0 * S * 32 * P.nsteps * 16.0 * P.RT * P.nmblk * ovox / kSplitFlops;
+        t = by > fl ? by : fl;
+    } else {
+        // products and writing, or a workgroup's walk over its steps of four taps: matrix instructions of 32 cycles and 450 of latency
+        const double taps4 = (taps + 3) / 4 * 4, Mp = (fo + 15) / 16 * 16, rows = Mp / 16 < 5 ? Mp / 16 : 5;
+        const double walk = f * taps4 / 4 * (rows * 4 * 32 + 450) / 2.2e9;
+        t = 2.0 * S * f * taps4 * Mp * ovox / (taps >= 27 ? kDirectFlops : kDirectFlopsFew) + wr / kDirectWrite;
+        if (t < walk) t = walk;
+    }
+    return t + 2 * kLaunchSec < route_seconds(L);
+}
+
 }  // namespace znni
 
 using namespace znni;
@@ -83,7 +114,7 @@ znni_status znni_conv3d_choose_v(int S, int f, int fo, const int n[3], const int
     if (est_ms) { est_ms[ZNNI_PRIMITIVE_FFT] = (float)(tf * 1e3); est_ms[ZNNI_PRIMITIVE_DIRECT] = (float)(td * 1e3); }
     if (tf < 0) *primitive = ZNNI_PRIMITIVE_DIRECT;
     else if (td < 0) *primitive = ZNNI_PRIMITIVE_FFT;
-    else *primitive = td < tf ? ZNNI_PRIMITIVE_DIRECT : ZNNI_PRIMITIVE_FFT;
+    else *primitive = td < tf || direct_stands(S, f, fo, n, k) ? ZNNI_PRIMITIVE_DIRECT : ZNNI_PRIMITIVE_FFT;
     return ZNNI_OK;
 }
 

@@ -83,6 +83,8 @@ struct LayerPlan {
 // flags: the call's flags (only the bits that pick a multiply-accumulate form matter: they decide `xdirect`).
 znni_status make_plan(int S, int f, int fo, const int n[3], const int k[3], unsigned flags, void* base,
                       LayerPlan* out);
+// The plan that goes through whole planes.
+znni_status make_whole_plan(int S, int f, int fo, const int n[3], const int k[3], unsigned flags, void* base, LayerPlan* out);
 
 int lines_per_tile(int N);
 

@@ -54,3 +54,15 @@ def test_small_images_take_the_faster_route(layer):
 def test_long_sums_of_few_pencils(layer, transformed):
     nbytes, _ = B.znni_conv3d_fft_stage_work(*layer)
     assert (nbytes["fwd_x"] > 0) == transformed
+
+
+def test_closer_direct_sums_are_not_left_for_little():
+    """Direct sums of few products are closer to 64 bits than transforms (1.8e-8 sqrt(products) of the result, 1.4e-8 on split
+    halves, next to 2e-7): layers that rates alone give to the direct kernels stay there."""
+    direct = [(1, 4, 4, (188, 175, 251), (5, 2, 1)), (1, 2, 50, (181, 198, 159), (3, 3, 4)), (1, 3, 18, (305,) * 3, (3,) * 3),
+              (1, 3, 20, (60,) * 3, (3,) * 3), (1, 11, 5, (112, 105, 104), (4, 2, 1)), (1, 19, 4, (53,) * 3, (2,) * 3)]
+    # sums of more products, and layers that transforms are far ahead at
+    transformed = [(1, 4, 16, (72,) * 3, (4,) * 3), (1, 54, 11, (116,) * 3, (2,) * 3), (1, 40, 40, (128,) * 3, (3,) * 3)]
+    for layers, want in ((direct, "direct"), (transformed, "fft")):
+        for layer in layers:
+            assert B.znni_conv3d_choose(*layer)[0] == want, layer
