@@ -240,12 +240,14 @@ znni_status znni_conv3d_fft_profile_v(int S, int f, int fo, const int n[3], cons
  *
  * znni_conv3d_fft_sublayers_v: host only.  Writes the division for `budget_bytes` to sub[3] = {S_i, f_i, f'_i}
  *   and the workspace it needs (<= budget_bytes) to *bytes: what decides whether a budget is enough.  (A layer that
- *   znni_conv3d_fft_budget_v can run in slabs, see there, has a division too, which is then not used.)  ZNNI_ERR_WORKSPACE if even the smallest division
+ *   znni_conv3d_fft_budget_v can run in tiles or slabs, see there, has a division too, which is then not used.)  ZNNI_ERR_WORKSPACE if even the smallest division
  *   (S_i = f_i = f'_i = 1) does not fit; *bytes then holds what that division needs.
- * znni_conv3d_fft_budget_v: runs the layer with the division chosen for workspace_bytes; where the spectra of the whole
- *   layer fit and only the kernel transforms do not (and x is not transformed), in slabs along the halved axis instead, and
- *   where znni_conv3d_fft_v cuts planes into tiles, in turns of tiles: neither transforms anything twice, and both give
- *   znni_conv3d_fft_v's result bit for bit.  Arguments, ownership,
+ * znni_conv3d_fft_budget_v: runs the layer with the division chosen for workspace_bytes, except where it need not transform
+ *   anything twice: where znni_conv3d_fft_v cuts planes into tiles, in turns of tiles, of another size where those of the whole
+ *   layer leave no room for a pair; and where the spectra of the whole layer fit and only the kernel transforms do not (and x is
+ *   not transformed), in slabs along the halved axis.  Turns of tiles of the whole layer's size, and slabs of a layer that
+ *   znni_conv3d_fft_v takes through whole planes, give its result bit for bit; the other ways equal it up to fp32 rounding, as
+ *   divisions do.  Arguments, ownership,
  *   alignment and status codes as for znni_conv3d_fft_v; ZNNI_ERR_WORKSPACE if no division fits.
  */
 znni_status znni_conv3d_fft_sublayers_v(int S, int f, int fo, const int n[3], const int k[3],

@@ -560,7 +560,7 @@ static znni_status run_divided(const Division& D, int S, int f, int fo, const in
 // kernel transform and the multiply-accumulate go through the rows of the halved axis in slabs that share one piece of
 // memory.  Nothing is transformed twice, so this is taken before any division of the images (48 -> 48 images of 160^3,
 // 5^3 kernels with half the workspace: blocks of images 4.64 ms, slabs 2.7 ms; in turns of tiles, which come first where the whole
-// layer takes tiles, 1.7).  The result is that of the whole-layer call, bit for bit.  Only the routes that do not transform x (their kernel transforms lie row by row), and only slabs of
+// layer takes tiles, 1.7).  The result is that of the whole-layer call through whole planes, bit for bit.  Only the routes that do not transform x (their kernel transforms lie row by row), and only slabs of
 // at least SLAB_PENCILS pencils: smaller ones would leave the chip idle between them.
 constexpr int SLAB_PENCILS = 512;
 static bool plan_slabs(int S, int f, int fo, const int n[3], const int k[3], unsigned flags, void* workspace,

@@ -74,6 +74,27 @@ def test_turns_equal_all_at_once(case, share):
     assert bool((ws[size:] == 0xFF).all())
 
 
+# The whole layer's tiles leave no room for a pair: tiles of another length (tests/test_tiles_host.py says so), other roundings
+OTHER_LENGTH = [((1, 84, 2, (67, 70, 66), (1, 2, 1)), 0.22), ((1, 67, 9, (46, 111, 106), (2, 2, 2)), 0.22),
+                ((1, 16, 14, (70, 157, 82), (1, 5, 3)), 0.75)]
+
+
+@pytest.mark.parametrize("case,share", OTHER_LENGTH, ids=str)
+def test_turns_of_another_length(oracle, case, share):
+    S, f, fo, n, k = case
+    d = torch.device("cuda:0")
+    inp, w, b = rand(8, S, f, fo, n, k)
+    ti, tw, tb = (torch.from_numpy(t).to(d) for t in (inp, w, b))
+    size = int(B.znni_conv3d_fft_workspace(S, f, fo, n, k) * share)
+    ws = torch.full((size + 4096,), 0xFF, dtype=torch.uint8, device=d)
+    got = B.znni_conv3d_fft_budget(ti, tw, tb, relu=True, workspace=ws[:size])
+    torch.cuda.synchronize()
+    assert bool((ws[size:] == 0xFF).all())
+    got, exp = got.cpu().numpy().astype(np.float64), oracle.conv3d(inp, w, b, relu=True)
+    assert np.all(np.abs(got - exp) <= oracle.tolerance(inp, w)[None, :, None, None, None])
+    assert np.linalg.norm(got - exp) <= 1e-6 * np.linalg.norm(exp)
+
+
 def test_kept_kernel_transforms_and_replays():
     S, f, fo, n, k = 2, 20, 18, (30, 96, 90), (3, 4, 2)
     d = torch.device("cuda:0")

@@ -46,6 +46,14 @@ def reach(path, recorder, layers):
     assert len(every) > 40 and not every - seen, sorted(every - seen)
 
 
+def lengths(path, recorder, layers):
+    """Turns of tiles of another length than the whole layer's."""
+    _, run = _open(path, recorder)
+    for layer, share in json.loads(layers):
+        whole, turns = ([v for v in run(*layer, share=q) if "k_fwd_tiles" in v] for q in (1.0, share))
+        assert len(whole) == 1 and turns and whole[0] not in turns, (layer, whole, turns)
+
+
 def small(path, recorder, layers):
     """Four launches, of every kernel that has the first stage beside it."""
     rec, run = _open(path, recorder)
@@ -97,6 +105,11 @@ def test_gpu_layers_reach_every_kernel(tmp_path):
     _driven(tmp_path, "reach", json.dumps(T.CASES))
 
 
+def test_gpu_budgets_take_another_length(tmp_path):
+    import test_gpu_tiles as T
+    _driven(tmp_path, "lengths", json.dumps(T.OTHER_LENGTH))
+
+
 def test_small_layers_take_four_launches(tmp_path):
     import test_gpu_small as S
     _driven(tmp_path, "small", json.dumps(S.CASES))
@@ -107,4 +120,4 @@ def test_steps_belong_together(tmp_path):
 
 
 if __name__ == "__main__":
-    {"reach": reach, "small": small, "walk": walk}[sys.argv[3]](sys.argv[1], sys.argv[2], sys.argv[4])
+    {"reach": reach, "lengths": lengths, "small": small, "walk": walk}[sys.argv[3]](sys.argv[1], sys.argv[2], sys.argv[4])
