@@ -230,15 +230,8 @@ def main():
 
     # the work of the kernels that actually ran (fused kernels and skipped stages priced as such); the form without x
     # transform runs on fp16 matrix instructions with split values, three partial products per product
-    nbytes, nflops = B.znni_conv3d_fft_stage_work(S, f, fo, n, k, relu=layer.relu, mac_reference=route)
+    nbytes, nflops = B.znni_conv3d_fft_call_work(S, f, fo, n, k, relu=layer.relu, mac_reference=route)
     split = nbytes["fwd_x"] == 0 and route != "xblock"
-    # planes cut into tiles: z and y are one kernel a side, timed under the first of the two stages that the whole planes have
-    for s_, into in (("fwd_y", "fwd_z"), ("inv_z", "inv_y")):
-        if nbytes[s_] > 2 * HBM_PEAK_GBS * 1e6 * stage_ms[s_]:
-            # one pass over what goes in and one over what comes out, without the tensor between the two
-            between = (nbytes["fwd_z"] - 4 * S * f * n ** 3) if into == "fwd_z" else (nbytes["inv_z"] - 4 * layer.out_voxels)
-            nbytes[into] += nbytes[s_] - 2 * between
-            nbytes[s_] = 0
     mac_peak = MFMA_FP16_PEAK_TFLOPS / 3 if split else MFMA_FP32_PEAK_TFLOPS
     stages = {}
     for s_ in B.STAGES:
@@ -264,7 +257,7 @@ def main():
     roof["avg_launch_ms"] = stage_ms[dom]
     if dom == "mac":
         # `achieved` counts 8 flops per complex multiply-add of the form of the stage that ran (see
-        # znni_conv3d_fft_stage_work_v).  On fp32 matrix instructions each is issued as three real products (6 flops), so
+        # znni_conv3d_fft_call_work_v).  On fp32 matrix instructions each is issued as three real products (6 flops), so
         # the matrix pipes are busy for 3/4 of that rate; on split halves as four real products of three partial ones
         # (24 flops), which the peak above already divides by three
         issued, form = (3.0, "24 the split form issues (peak: fp16 / 3)") if split else (0.75, "6 the three-product form issues")

@@ -193,7 +193,7 @@ znni_status znni_conv3d_fft_profile(int S, int f, int fo, int n, int k,
 
 /*
  * Measurement aid (host only): the work the method itself has to do in each stage of a layer call with these
- * flags, for the kernels that call would run.  hbm_bytes[s] = bytes stage s must read plus write once (its input
+ * flags, by the route that the call would take through whole planes.  hbm_bytes[s] = bytes stage s must read plus write once (its input
  * and output tensors, unpadded); flops[s] = floating-point operations of the contraction in the
  * multiply-accumulate stage, counting 8 per complex multiply-add: (8 S + 8 (kx - 1)) f f' per bin of the transformed
  * image when the x axis is transformed (the per-bin product of Algorithm 3 plus the kx-term sum that stands in for a
@@ -201,11 +201,17 @@ znni_status znni_conv3d_fft_profile(int S, int f, int fo, int n, int k,
  * per block of 9 - kx outputs where x is transformed in blocks of eight.  Stages a
  * call does not run (the y or z stage where one kernel does both, the x stages where the x axis is not transformed)
  * get 0.  A call that cuts its (y, z) planes into overlapping tiles is counted by the whole planes they are cut from: what tiles
- * repeat is no work of the method (such a call's z and y transforms are one kernel a side, timed under ZNNI_STAGE_FWD_Z and
- * ZNNI_STAGE_INV_Y).  Both arrays have ZNNI_NUM_STAGES elements, indexed like stage_ms above.
+ * repeat is no work of the method.  Both arrays have ZNNI_NUM_STAGES elements, indexed like stage_ms above.
+ *
+ * znni_conv3d_fft_call_work_v: the same for the kernels that the call runs, tiles included: spectra of all pairs of tiles, kernel
+ * transforms and products of their length; the z and y transforms of such a call are one kernel a side, counted and timed under
+ * ZNNI_STAGE_FWD_Z and ZNNI_STAGE_INV_Y.  What the times of znni_conv3d_fft_profile are to be held against.
  */
 znni_status znni_conv3d_fft_stage_work_v(int S, int f, int fo, const int n[3], const int k[3], unsigned flags,
                                          double hbm_bytes[ZNNI_NUM_STAGES], double flops[ZNNI_NUM_STAGES]);
+
+znni_status znni_conv3d_fft_call_work_v(int S, int f, int fo, const int n[3], const int k[3], unsigned flags,
+                                        double hbm_bytes[ZNNI_NUM_STAGES], double flops[ZNNI_NUM_STAGES]);
 
 /*
  * General image and kernel sizes (Section IV: an image has size n = <nx,ny,nz>, a kernel k = <kx,ky,kz>, the

@@ -23,7 +23,7 @@ PASSES_REFERENCE = 128
 STAGES = ("kernel_prep", "fwd_z", "fwd_y", "fwd_x", "mac", "inv_x", "inv_y", "inv_z")
 EXPORTS = ("znni_version", "znni_status_string", "znni_fft_size", "znni_conv3d_fft_workspace",
            "znni_conv3d_fft", "znni_conv3d_fft_profile", "znni_conv3d_fft_workspace_v", "znni_conv3d_fft_v",
-           "znni_conv3d_fft_profile_v", "znni_conv3d_fft_static_v", "znni_conv3d_fft_stage_work_v", "znni_conv3d_fft_sublayers_v", "znni_conv3d_fft_budget_v", "znni_conv3d_direct_workspace_v", "znni_conv3d_direct_v", "znni_conv3d_choose_v", "znni_conv3d_workspace_v", "znni_conv3d_v", "znni_mpf", "znni_maxpool",
+           "znni_conv3d_fft_profile_v", "znni_conv3d_fft_static_v", "znni_conv3d_fft_stage_work_v", "znni_conv3d_fft_call_work_v", "znni_conv3d_fft_sublayers_v", "znni_conv3d_fft_budget_v", "znni_conv3d_direct_workspace_v", "znni_conv3d_direct_v", "znni_conv3d_choose_v", "znni_conv3d_workspace_v", "znni_conv3d_v", "znni_mpf", "znni_maxpool",
            "znni_copy_probe")
 
 _lib = None
@@ -62,9 +62,9 @@ def lib():
         L.znni_conv3d_fft_v.argtypes = [i, i, i, i3, i3, vp, vp, vp, vp, u, vp, sz, vp]
         L.znni_conv3d_fft_static_v.restype = i
         L.znni_conv3d_fft_static_v.argtypes = [i, i, i, i3, i3, vp, vp, vp, vp, u, vp]
-        L.znni_conv3d_fft_stage_work_v.restype = i
-        L.znni_conv3d_fft_stage_work_v.argtypes = [i, i, i, i3, i3, u, ctypes.POINTER(ctypes.c_double),
-                                                   ctypes.POINTER(ctypes.c_double)]
+        for fn in (L.znni_conv3d_fft_stage_work_v, L.znni_conv3d_fft_call_work_v):
+            fn.restype = i
+            fn.argtypes = [i, i, i, i3, i3, u, ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_double)]
         L.znni_conv3d_fft_profile_v.restype = i
         L.znni_conv3d_fft_profile_v.argtypes = [i, i, i, i3, i3, vp, vp, vp, vp, u, vp, sz, vp,
                                                 ctypes.POINTER(ctypes.c_float)]
@@ -210,11 +210,19 @@ def znni_conv3d_fft_profile(inp, w, bias=None, relu=False, out=None, workspace=N
 
 
 def znni_conv3d_fft_stage_work(S, f, fo, n, k, relu=False, mac_reference=False):
-    """({stage: bytes the stage must move}, {stage: flops of its contraction}) for the kernels a call would run."""
+    """({stage: bytes the stage must move}, {stage: flops of its contraction}) by the route a call would take through whole planes."""
+    return _work(lib().znni_conv3d_fft_stage_work_v, S, f, fo, n, k, _flags(relu, mac_reference))
+
+
+def znni_conv3d_fft_call_work(S, f, fo, n, k, relu=False, mac_reference=False, keep_kernels=False):
+    """The same for the kernels the call runs, planes cut into tiles included."""
+    return _work(lib().znni_conv3d_fft_call_work_v, S, f, fo, n, k, _flags(relu, mac_reference, keep_kernels))
+
+
+def _work(fn, S, f, fo, n, k, flags):
     nb = (ctypes.c_double * len(STAGES))()
     fl = (ctypes.c_double * len(STAGES))()
-    _check(lib().znni_conv3d_fft_stage_work_v(int(S), int(f), int(fo), _triple(n), _triple(k),
-                                              _flags(relu, mac_reference), nb, fl))
+    _check(fn(int(S), int(f), int(fo), _triple(n), _triple(k), flags, nb, fl))
     return ({name: float(nb[q]) for q, name in enumerate(STAGES)},
             {name: float(fl[q]) for q, name in enumerate(STAGES)})
 

@@ -599,7 +599,8 @@ static znni_status run_slabs(LayerPlan L, int rows, const float* in, const float
     }
     return inv_untransformed_x(L, bias, out, flags, st);
 }
-// Bytes and flops of every stage of a plan (znni_conv3d_fft_stage_work_v).
+
+// Bytes and flops of every stage of a plan (znni_conv3d_fft_stage_work_v, znni_conv3d_fft_call_work_v).
 void plan_work(const LayerPlan& L, unsigned flags, double hbm_bytes[ZNNI_NUM_STAGES], double flops[ZNNI_NUM_STAGES])
 {
     const Dims& d = L.d;
@@ -610,6 +611,17 @@ void plan_work(const LayerPlan& L, unsigned flags, double hbm_bytes[ZNNI_NUM_STA
     // stored kernel transforms, unpadded: kx values per kernel column along x, or 8 where x goes in blocks of eight
     const double a = c * zc * d.Ny * (double)L.f * L.fo * (L.xblock ? 8 : d.kx);
     for (int q = 0; q < ZNNI_NUM_STAGES; ++q) hbm_bytes[q] = flops[q] = 0.0;
+    if (L.tiles) {
+        // pairs of tiles: whole complex planes [Nz][Ny], whichever take turns
+        const auto& t = L.cut;
+        const double in = (double)t.S * L.f * d.nx, out = (double)t.S * L.fo * d.nox, plane = (double)t.pairs * d.Ny * d.Nz;
+        if (!(flags & ZNNI_KEEP_KERNELS)) hbm_bytes[ZNNI_STAGE_KERNEL_PREP] = 4.0 * L.f * L.fo * d.kx * d.ky * d.kz + a;
+        hbm_bytes[ZNNI_STAGE_FWD_Z] = in * (4.0 * t.ny * t.nz + c * plane);
+        hbm_bytes[ZNNI_STAGE_MAC] = c * plane * (in + out) + a;
+        hbm_bytes[ZNNI_STAGE_INV_Y] = out * (c * plane + 4.0 * t.noy * t.noz);
+        flops[ZNNI_STAGE_MAC] = 8.0 * d.kx * L.f * plane * out;
+        return;
+    }
     if (!(flags & ZNNI_KEEP_KERNELS)) hbm_bytes[ZNNI_STAGE_KERNEL_PREP] = 4.0 * L.f * L.fo * d.kx * d.ky * d.kz + a;
     const bool fused_zy = L.planes || (!L.xdirect && fused_fwd_zy_available(L)), fused_yz = L.planes || (!L.xdirect && fused_inv_yz_available(L));
     if (fused_zy) hbm_bytes[ZNNI_STAGE_FWD_Z] = ni * (4.0 * vox + x2);
@@ -715,16 +727,28 @@ znni_status znni_conv3d_fft_v(int S, int f, int fo, const int n[3], const int k[
     return run(L, in, w, bias, out, flags, (hipStream_t)stream, nullptr);
 }
 
-znni_status znni_conv3d_fft_stage_work_v(int S, int f, int fo, const int n[3], const int k[3], unsigned flags,
-                                         double hbm_bytes[ZNNI_NUM_STAGES], double flops[ZNNI_NUM_STAGES])
+static znni_status plan_and_work(decltype(make_plan)* plan, int S, int f, int fo, const int n[3], const int k[3], unsigned flags,
+                                 double* hbm_bytes, double* flops)
 {
     if (!hbm_bytes || !flops) return ZNNI_ERR_NULL;
     if (!flags_ok(flags)) return ZNNI_ERR_FLAGS;
     LayerPlan L;
-    znni_status rc = make_whole_plan(S, f, fo, n, k, flags, nullptr, &L);      // (tiles count as the whole planes they are cut from)
+    const znni_status rc = plan(S, f, fo, n, k, flags, nullptr, &L);
     if (rc) return rc;
     plan_work(L, flags, hbm_bytes, flops);
     return ZNNI_OK;
+}
+
+znni_status znni_conv3d_fft_stage_work_v(int S, int f, int fo, const int n[3], const int k[3], unsigned flags,
+                                         double hbm_bytes[ZNNI_NUM_STAGES], double flops[ZNNI_NUM_STAGES])
+{
+    return plan_and_work(make_whole_plan, S, f, fo, n, k, flags, hbm_bytes, flops);
+}
+
+znni_status znni_conv3d_fft_call_work_v(int S, int f, int fo, const int n[3], const int k[3], unsigned flags,
+                                        double hbm_bytes[ZNNI_NUM_STAGES], double flops[ZNNI_NUM_STAGES])
+{
+    return plan_and_work(make_plan, S, f, fo, n, k, flags, hbm_bytes, flops);
 }
 
 znni_status znni_conv3d_fft_static_v(int S, int f, int fo, const int n[3], const int k[3], const float* in,

@@ -110,6 +110,22 @@ def test_gpu_budgets_take_another_length(tmp_path):
     _driven(tmp_path, "lengths", json.dumps(T.OTHER_LENGTH))
 
 
+def test_work_of_a_call_in_tiles():
+    """48 -> 48 images of 320^3, 5^3 kernels: 10 x 10 tiles of length 36 (32 outputs of 316 an axis), 50 pairs; by form, whole planes."""
+    from paper_1606_05688_amd import binding as B
+    f = fo = 48
+    n, k, no, N, pairs = 320, 5, 316, 36, 50
+    x, y, bank = 8 * f * n * N * N * pairs, 8 * fo * no * N * N * pairs, 8 * (N // 2 + 1) * N * f * fo * k
+    nb, fl = B.znni_conv3d_fft_call_work(1, f, fo, n, k)
+    assert {q: v for q, v in nb.items() if v} == {"kernel_prep": 4 * f * fo * k ** 3 + bank, "fwd_z": 4 * f * n ** 3 + x,
+                                                  "mac": x + bank + y, "inv_y": y + 4 * fo * no ** 3}
+    assert {q: v for q, v in fl.items() if v} == {"mac": 8 * k * f * fo * no * N * N * pairs}
+    assert B.znni_conv3d_fft_call_work(1, f, fo, n, k, keep_kernels=True)[0]["kernel_prep"] == 0
+    for form in ("xdirect", "single", "generic_passes"):
+        assert B.znni_conv3d_fft_call_work(1, f, fo, n, k, mac_reference=form) == B.znni_conv3d_fft_stage_work(1, f, fo, n, k, mac_reference=form)
+    assert B.znni_conv3d_fft_call_work(8, 32, 32, 64, 7) == B.znni_conv3d_fft_stage_work(8, 32, 32, 64, 7)
+
+
 def test_small_layers_take_four_launches(tmp_path):
     import test_gpu_small as S
     _driven(tmp_path, "small", json.dumps(S.CASES))
