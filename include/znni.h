@@ -184,7 +184,9 @@ znni_status znni_conv3d_fft_static_v(int S, int f, int fo, const int n[3], const
  * returning and writes the elapsed milliseconds of each stage to stage_ms[ZNNI_NUM_STAGES] (HOST pointer).
  * Meant for measurement: creates and destroys its events on every call.  For small images the z and y
  * transforms of each side run as one kernel; its time is then reported under ZNNI_STAGE_FWD_Z (forward) and
- * ZNNI_STAGE_INV_Y (inverse), and ZNNI_STAGE_FWD_Y / ZNNI_STAGE_INV_Z read about zero.
+ * ZNNI_STAGE_INV_Y (inverse), and ZNNI_STAGE_FWD_Y / ZNNI_STAGE_INV_Z read about zero.  The smallest layers, whose kernels' first
+ * stage the plain call runs in the launch of the forward transforms (four launches), are profiled with kernels of its own for every
+ * stage (six; the same result bit for bit): their stages add up to more than the plain call takes.
  */
 znni_status znni_conv3d_fft_profile(int S, int f, int fo, int n, int k,
                                     const float* in, const float* w, const float* bias, float* out,
