@@ -808,7 +808,7 @@ static znni_status launch_xd_cols(const LayerPlan& L, int accumulate, hipStream_
 znni_status launch_mac_xd(const LayerPlan& L, int accumulate, hipStream_t st)
 {
     if (!mac_xd_available(L)) return ZNNI_ERR_UNSUPPORTED_SIZE;
-    if (L.tiles) return launch_mac_quads(L, xd_args(L, accumulate), st);
+    if (L.tiles) return accumulate ? ZNNI_ERR_SHAPE : launch_mac_quads(L, xd_args(L, 0), st);     // (sub-layers go through whole planes)
     switch (L.mac_RTW) {
         case 1: return launch_xd_cols<1>(L, accumulate, st);
         case 2: return launch_xd_cols<2>(L, accumulate, st);

@@ -90,8 +90,8 @@ __device__ __forceinline__ TilePos tile_pos(const TileArgs& a, int t)
 }
 
 // The pairs of a block of four x are neighbours on one XCD: they share the rows they overlap in.
-template <int R1, int R2, int W>
-__global__ __launch_bounds__((Tile<R1, R2>::NTH)) __attribute__((amdgpu_waves_per_eu(W)))
+template <int R1, int R2>
+__global__ __launch_bounds__((Tile<R1, R2>::NTH)) __attribute__((amdgpu_waves_per_eu(4)))
 void k_fwd_tiles(TileArgs a)
 {
     using TL = Tile<R1, R2>;
@@ -191,8 +191,8 @@ void k_fwd_tiles(TileArgs a)
 
 // The mirror image: conj . forward . conj along z, then along y; the real part belongs to the first tile, minus the imaginary part
 // to the second.
-template <int R1, int R2, int W>
-__global__ __launch_bounds__((Tile<R1, R2>::NTH)) __attribute__((amdgpu_waves_per_eu(W)))
+template <int R1, int R2>
+__global__ __launch_bounds__((Tile<R1, R2>::NTH)) __attribute__((amdgpu_waves_per_eu(4)))
 void k_inv_tiles(TileArgs a)
 {
     using TL = Tile<R1, R2>;
@@ -427,7 +427,7 @@ template <int R1, int R2, bool FWD>
 static znni_status launch_tiles(const TileArgs& a, hipStream_t st)
 {
     using TL = Tile<R1, R2>;
-    void (*kernel)(TileArgs) = FWD ? k_fwd_tiles<R1, R2, 4> : k_inv_tiles<R1, R2, 4>;
+    void (*kernel)(TileArgs) = FWD ? k_fwd_tiles<R1, R2> : k_inv_tiles<R1, R2>;
     const long long blocks = (long long)((a.groups + 7) / 8) * 8 * a.pairs;
     if (blocks > 0x7fffffffll) return ZNNI_ERR_SHAPE;
     if (TL::LDS > 48 * 1024 && hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)TL::LDS) != hipSuccess)
