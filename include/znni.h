@@ -284,7 +284,7 @@ znni_status znni_conv3d_direct_v(int S, int f, int fo, const int n[3], const int
  * znni_conv3d_choose_v (host only) ranks the transform route and the direct route with a cost model whose rates
  * were measured on MI355X and writes the pick to *primitive; est_ms, if not NULL, receives the two estimates in
  * milliseconds (index = primitive; negative = that primitive does not take this shape).  The pick is the lower estimate, except that
- * layers of few products per output (about 136), whose direct sums are closer to the 64-bit result than transforms, stay direct
+ * layers of few products per output (about 110), whose direct sums are closer to the 64-bit result than transforms, stay direct
  * where transforms would be ahead by little.
  * znni_conv3d_workspace_v / znni_conv3d_v are the workspace query and the layer call of the picked primitive;
  * arguments as for znni_conv3d_fft_v.  When the direct route is picked, ZNNI_MAC_SINGLE, _BATCH, _XDIRECT and

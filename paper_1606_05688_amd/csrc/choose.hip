@@ -11,9 +11,9 @@
 //   direct route:     the estimate of the kernel that would run (direct.hip, direct_split.hip, direct_first.hip): its walks over
 //                     tiles, taps and staged values, and the tensors it moves.
 //
-// The model only has to rank the two; it is not used for anything else.  Over 6136 random layers that both take, the pick by these
-// estimates is 0.6 % slower than the faster one on average, 216 by more than 5 %.  Where direct sums are the closer ones to 64 bits, the
-// transform has to be ahead by bare rates as well (direct_stands).
+// The model only has to rank the two; it is not used for anything else.  Over 23318 random layers that both take, the pick by these
+// estimates is 0.5 % slower than the faster one on average, 685 by more than 5 %.  Where direct sums are the closer ones to 64 bits, the
+// transform has to be ahead by bare rates as well (direct_stands): 1.0 % and 1083 with that.
 #include "direct_split.h"
 #include "mac_common.h"
 
@@ -67,8 +67,9 @@ static double fft_seconds(int S, int f, int fo, const int n[3], const int k[3])
 
 // Whether a layer stays with direct sums though transforms are estimated to be the faster.  Direct sums of K products are 1.8e-8 sqrt(K)
 // of the result off its 64-bit value (1.4e-8 on split halves), transforms 1.9e-7 to 2.2e-7 whatever K (108 layers that the two
-// estimates disagree on): sums of up to 136 products (225) come out closer directly, by up to 1.8 times at 40.  So those leave the direct
-// kernels only where whole planes would be faster by rates alone: 80 % of them are then within a third of the transform's time.
+// estimates disagree on): sums of up to 110 products come out closer directly, by 1.2 times on average up to 100 and 1.8 at 40 (on split
+// halves up to 190); at 114 to 136 the two are level.  So those leave the direct kernels only where whole planes would be faster by
+// rates alone: 621 of 23318 random layers stay, 1.19 times as long as by transforms on average, 2.6 at most.
 static bool direct_stands(int S, int f, int fo, const int n[3], const int k[3])
 {
     constexpr double kDirectFlops = 80e12, kDirectFlopsFew = 60e12;      // windows of 27 taps and more, of fewer
@@ -76,9 +77,9 @@ static bool direct_stands(int S, int f, int fo, const int n[3], const int k[3])
     LayerPlan L;
     SplitPlan P;
     const int taps = k[0] * k[1] * k[2];
-    if ((long long)f * taps > 225 || make_whole_plan(S, f, fo, n, k, 0, nullptr, &L)) return false;
+    if ((long long)f * taps > 190 || make_whole_plan(S, f, fo, n, k, 0, nullptr, &L)) return false;
     const bool split = split_plan(S, f, fo, L.d, &P);
-    if (!split && f * taps > 136) return false;
+    if (!split && f * taps > 110) return false;
     const double ovox = (double)L.d.nox * L.d.noy * L.d.noz, wr = 4.0 * S * fo * ovox;
     double t;
     if (split) {

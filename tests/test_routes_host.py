@@ -62,7 +62,7 @@ def test_closer_direct_sums_are_not_left_for_little():
     direct = [(1, 4, 4, (188, 175, 251), (5, 2, 1)), (1, 2, 50, (181, 198, 159), (3, 3, 4)), (1, 3, 18, (305,) * 3, (3,) * 3),
               (1, 3, 20, (60,) * 3, (3,) * 3), (1, 11, 5, (112, 105, 104), (4, 2, 1)), (1, 19, 4, (53,) * 3, (2,) * 3)]
     # sums of more products, and layers that transforms are far ahead at
-    transformed = [(1, 4, 16, (72,) * 3, (4,) * 3), (1, 54, 11, (116,) * 3, (2,) * 3), (1, 40, 40, (128,) * 3, (3,) * 3)]
+    transformed = [(1, 4, 16, (72,) * 3, (4,) * 3), (1, 2, 46, (24,) * 3, (4,) * 3), (1, 54, 11, (116,) * 3, (2,) * 3), (1, 40, 40, (128,) * 3, (3,) * 3)]
     for layers, want in ((direct, "direct"), (transformed, "fft")):
         for layer in layers:
             assert B.znni_conv3d_choose(*layer)[0] == want, layer
