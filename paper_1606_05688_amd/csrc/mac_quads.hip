@@ -14,10 +14,18 @@
 // and two multiplications for each, 650 vector instructions of a wave became 150.
 //
 // Against mac_xd.hip's kernel on the same rows: 40 -> 40 of 128^3, 3^3 at length 36 352 -> 315 us; 48 -> 48 of 160^3, 5^3 at 56 929 -> 856;
-// of 320^3 at 84 6300 -> 5870; 37 -> 45 of 93 x 110 x 131, 3 x 4 x 5 at 32 290 -> 255.  What bounds it: of the 5.9 ms 2.3 are
-// products, 1.8 vector instructions, 2.5 memory at copy speed, and with two or three waves a SIMD they hardly overlap.  The next chunk's
-// rows on their way to LDS while one is multiplied (global_load_lds) did not change that (5870 -> 6120: the kernel operands
-// behind them return in order), nor did neighbouring quads on one XCD.
+// of 320^3 at 84 6300 -> 5870; 37 -> 45 of 93 x 110 x 131, 3 x 4 x 5 at 32 290 -> 255.
+//
+// What bounds it, at the lengths that are picked (counters; share of the time that a SIMD's matrix pipe is busy, that it issues other
+// vector instructions, that the bytes would take at copy speed; waves a SIMD):
+//   48 -> 48 of 320^3, 5^3, length 36 (6855 us)                41 %   32 %   38 %   1.8   1.93 GHz
+//   40 -> 40 of 128^3, 3^3, length 28 (317)                    25     26     45     1.9   2.32
+//   37 -> 45 of 93 x 110 x 131, 3 x 4 x 5, length 32 (269)     22     25     41     1.9   2.26
+//   48 -> 48 of 160^3, 5^3, length 56, first turn (541)        35     35            2.9   2.08
+// The three add up to the time: with two or three waves a SIMD they hardly overlap, and where a strip has more than six tiles the
+// next chunk's rows are only requested when the chunk begins.  (With them on their way to LDS while one is multiplied,
+// global_load_lds, the 320^3 layer at length 84 took 6120 instead of 5870 us: the kernel operands behind them return in order.
+// Neighbouring quads on one XCD changed nothing.)
 #include <algorithm>
 #include "mac_xd.h"
 

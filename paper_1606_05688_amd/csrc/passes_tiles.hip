@@ -8,7 +8,9 @@
 //  * kernel transforms are those of a tile, shared by all tiles: 48 -> 48 images of 320^3, 5^3 kernels 0.1 GB instead of 4.75.
 // Against it stand the outputs that tiles share their inputs for: (N / V)^2 more of everything.  With the products
 // in mac_quads.hip, whole layers: 48 -> 48 of 320^3, 5^3 15.7 -> 12.4 ms; 40 -> 40 of 128^3, 3^3 0.840 -> 0.616; 37 -> 45 of 93 x 110 x
-// 131, 3 x 4 x 5 0.669 -> 0.490; the results are 0.7 to 1.0 times as far from 64 bits, since transforms are shorter.
+// 131, 3 x 4 x 5 0.669 -> 0.490.  Since transforms are shorter, the results are 0.86 times as far from 64 bits on average, 0.64 to 1.08
+// over 60 layers whose whole planes were multiplied on split halves as well; 0.74, 0.44 to 0.97 over 130 (0.98 with values spread over
+// 2^12) that were transformed along x and multiplied in fp32: halves there too now, in closer sums.
 //
 // Two tiles of a plane ride as the real and the imaginary part of one complex plane, all the way: the products with the kernel
 // transforms are linear, so nothing is taken apart in between, and both transforms are plain complex ones (a real transform of
@@ -19,8 +21,8 @@
 //
 // One workgroup takes four neighbouring x of one pair, one after the other, and holds their spectra in registers, so that 32
 // bytes of a pencil's row are stored together (blocks of four x, as in passes_fused.hip).  Threads lie along lines: z while y is
-// transformed, oy while z is, so that global loads and stores run along z, LDS is read and written without bank conflicts (odd
-// pitch), and up to 64 lines all twiddles of a wave are one, read as scalars.  Every step of a transform reads and writes the
+// transformed, oy while z is, so that global loads and stores run along z, LDS is read and written with few bank conflicts (odd
+// pitch: none at 32 and from 48 on, a fifth of the LDS cycles where a wave's lanes lie along more than one line), and up to 64 lines all twiddles of a wave are one, read as scalars.  Every step of a transform reads and writes the
 // same LDS places, thread for thread, so that there are four barriers a plane (k_fwd_zy has nine).  Bound by memory: N = 36
 // 5.5 TB/s (a copy reaches 6.2), 56 and 64 5.4; at 84 (one workgroup of sixteen waves per CU) 4.4.  Lengths whose workgroups do not
 // fill the SIMDs evenly (60: ten waves) fall to 3.6 and are not offered.
